@@ -93,8 +93,8 @@ def draw(rng):
     values = rng.random() < 0.7
     if kind == "step":
         if rng.random() < 0.3:
-            return {"kind": kind, "stars": _log_int(rng, 3, 64), "polys": 0,
-                    "eps": _log_int(rng, 24, 600), "points": _log_int(rng, 50_000, 10_000_000),
+            return {"kind": kind, "stars": _log_int(rng, 12, 64), "polys": 0,
+                    "eps": _log_int(rng, 64, 600), "points": _log_int(rng, 50_000, 10_000_000),
                     "values": values}
         return {"kind": kind, "stars": 0, "polys": _log_int(rng, 40, 2000),
                 "eps": _log_int(rng, 100, 12_000), "points": _log_int(rng, 100_000, 60_000_000),
