@@ -50,19 +50,20 @@ int sba_debug_grid16_sets(int mode);
 int sba_debug_grid16_lsub(int mode);
 
 /* Build paths, process-wide, read at build time.  Bits set in `off` turn a
- * path off: 1 = sorting each polygon's events in LDS (fused with the
- * coverage step), so that all events take the global radix sort and scans;
- * 2 = bucketing the toggles by row, so that they take the global radix sort;
- * 4 = collecting the distinct polygon sets through a hash table and numbering
- * them in one workgroup, so that all multi-polygon segments take the global
- * radix sort.  0 (default) takes each path wherever it applies (builds
- * without a clip window, polygons of at most 16,384 events, rows of at most
- * 512 toggles; set keys below 2^31 and at most 8,192 distinct sets).
- * SBA_EINVAL outside 0..7.  For tests of both sides of each choice. */
+ * path off: 1 = counting the pairs of edges and rows per row (with 2 and the
+ * global radix sorts and scans of all events instead); 2 = sweeping each row
+ * in LDS by one workgroup, so that the events take the global sorts; 4 =
+ * collecting the distinct polygon sets through a hash table, so that all
+ * multi-polygon segments take the global radix sort.  0 (default) takes each
+ * path wherever it applies (rows of at most 4,096 pairs and toggles; keys of
+ * a polygon, two columns and a flag below 2^63; as many distinct sets as the
+ * table holds).  SBA_EINVAL outside 0..7.  For tests of both sides of each
+ * choice. */
 int sba_debug_build_paths(int off);
 
-/* The paths the last build in the process took, same bits (1: per-polygon
- * event sort, 2: toggle row buckets, 4: hashed set table).  Test support. */
+/* The paths the last build in the process took, same bits (1: pairs counted
+ * per row, 2: rows swept in LDS, 4: the distinct sets hashed and numbered by
+ * one workgroup, at most 8,192 of them).  Test support. */
 int sba_debug_last_build_paths(void);
 
 /* 1: grid builds store the 32-bit format (directory read from global memory

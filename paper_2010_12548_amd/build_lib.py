@@ -5,7 +5,7 @@ import os
 import subprocess
 
 HERE = os.path.dirname(os.path.abspath(__file__))
-SOURCES = ["alloc.hip", "prims.hip", "build.hip", "hilbert.hip", "probe.hip", "serve.hip", "pindex.hip",
+SOURCES = ["alloc.hip", "prims.hip", "build.hip", "rows.hip", "sets.hip", "hilbert.hip", "probe.hip", "serve.hip", "pindex.hip",
            "join.hip", "partition.hip", "api.hip"]
 OUT = os.path.join(HERE, "libsba.so")
 

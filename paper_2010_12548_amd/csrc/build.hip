@@ -22,6 +22,9 @@
 //      interval adds its polygon to the pieces it spans, and the non-empty
 //      pieces are the maximal row segments of constant polygon set;
 //   5. sets of two or more polygons are deduplicated into a set table;
+// Steps 1 to 4 run row by row in LDS (rows.hip); the kernels here that sort
+// all events and toggles globally take the builds whose rows do not fit.
+// Step 5 is in sets.hip.
 //   6. the segments are written into the chosen layout: a two-level tiled
 //      grid (uniform tiles stored once in a directory, mixed tiles as fine
 //      blocks) or, in hilbert.hip, the runs of the Hilbert order.
@@ -31,6 +34,7 @@
 
 #include "sba_internal.h"
 #include "build_state.h"
+#include "sets.h"
 
 // ---------------------------------------------------------------- kernels
 
@@ -279,458 +283,6 @@ __global__ void k_emit_cross(const int4 *edges, const int32_t *epoly, int64_t n_
     evpay[t] = EV_CROSS;
 }
 
-// ------------------------------------------------ events sorted per polygon
-//
-// The events come out of the emit kernels grouped by polygon (edges are
-// numbered polygon by polygon): the boundary events of polygon p, in edge
-// order, and further on its crossings.  Ordering them by (polygon, row, x)
-// therefore only needs each polygon's events ordered by (row, x), which one
-// workgroup does in LDS when the polygon has at most SEG_CAP events: the
-// (row, x) key, re-based to the polygon's own row and column range, and the
-// 2-bit kind packed in 32 bits, sorted by an LSD radix sort of 7-bit digits
-// over the packed word (the order among events of equal (row, x) is not
-// used: the coverage test reads only whole groups).  The
-// polygon's sorted events land where a sort of all events by (polygon, row,
-// x) puts them: after the events of the polygons before it.  The same
-// workgroup then takes the coverage step for its polygon: the prefix sums of
-// the event values over the polygon (the rows before any event are balanced:
-// matched starts and ends, an even number of crossings, so this gives the
-// same coverage as the prefix over all events), each (row, x) group's toggle
-// flag, and the
-// toggle's index among the polygon's toggles; a scan of the per-polygon
-// toggle counts places every toggle.
-
-#define SEG_BLOCK 1024
-#define SEG_ROUNDS 16
-#define SEG_CAP (SEG_BLOCK * SEG_ROUNDS)
-#define SEG_DBITS 7
-#define SEG_RADIX (1 << SEG_DBITS)
-#define SEG_WAVES (SEG_BLOCK / 64)
-
-struct EventSegs {
-    const int32_t *ring_off;
-    const int64_t *vert_off;
-    const int64_t *boff, *coff;  // exclusive scans of the per-edge boundary items and crossings
-    const int64_t *tot;          // tot[0], tot[1]: their totals
-    int64_t nv;                  // edges
-    int use_b, use_c;            // boundary events / crossings among the sorted events
-    int64_t cbase;               // where the crossings start in the event arrays
-};
-
-// polygon p: its sorted events' first input slot of each kind, their counts,
-// and its first output slot
-__device__ __forceinline__ void event_seg(const EventSegs &S, int p, int64_t *ib, int64_t *nbv,
-                                          int64_t *ic, int64_t *ncv, int64_t *o0)
-{
-    const int64_t e0 = S.vert_off[S.ring_off[p]], e1 = S.vert_off[S.ring_off[p + 1]];
-    const int64_t b0 = e0 < S.nv ? S.boff[e0] : S.tot[0], b1 = e1 < S.nv ? S.boff[e1] : S.tot[0];
-    const int64_t c0 = e0 < S.nv ? S.coff[e0] : S.tot[1], c1 = e1 < S.nv ? S.coff[e1] : S.tot[1];
-    *ib = 2 * b0;
-    *nbv = S.use_b ? 2 * (b1 - b0) : 0;
-    *ic = S.cbase + c0;
-    *ncv = S.use_c ? c1 - c0 : 0;
-    *o0 = (S.use_b ? 2 * b0 : 0) + (S.use_c ? c0 : 0);
-}
-
-// the largest polygon's event count, into *mx (zeroed before); also zeroes
-// the per-row toggle counters rowcnt[0..gh]
-__global__ void k_event_seg_max(EventSegs S, int32_t np, unsigned long long *mx,
-                                unsigned long long *rowcnt, int64_t gh)
-{
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t <= gh) rowcnt[t] = 0;
-    const int p = (int)t;
-    if (t >= np) return;
-    int64_t ib, nbv, ic, ncv, o0;
-    event_seg(S, p, &ib, &nbv, &ic, &ncv, &o0);
-    atomicMax(mx, (unsigned long long)(nbv + ncv));
-}
-
-// exclusive scan across a workgroup of SEG_BLOCK lanes (wsum: SEG_WAVES words)
-__device__ __forceinline__ uint32_t seg_excl_scan(uint32_t v, uint32_t *wsum)
-{
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    uint32_t incl = v;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t u = (uint32_t)__shfl_up((int)incl, o, 64);
-        if (lane >= o) incl += u;
-    }
-    if (lane == 63) wsum[w] = incl;
-    __syncthreads();
-    uint32_t before = 0;
-    for (int k = 0; k < w; k++) before += wsum[k];
-    __syncthreads();
-    return before + incl - v;
-}
-
-// event value in 32 bits: starts and ends add +1 / -1 to the count of open
-// boundary intervals (bits 0-30, at most the polygon's event count), a
-// crossing flips bit 31 (the parity of the crossings so far)
-__device__ __forceinline__ uint32_t ev_word(uint32_t kind)
-{
-    return kind == EV_CROSS ? 0x80000000u : (kind == EV_OPEN ? 1u : 0xffffffffu);
-}
-
-__device__ __forceinline__ uint32_t cov_of(uint32_t P) { return (P & 0x7fffffffu) + (P >> 31); }
-
-// Stable LSD radix sort, by one workgroup of SEG_BLOCK lanes, of n <= SEG_CAP
-// 32-bit words in LDS by their bits [0, kbits): 7-bit digits; wave w ranks
-// its own rpw x 64 consecutive words (rpw = the fewest rounds that spread
-// the words over every wave), 64 at a time, equal digits finding each other
-// with SEG_DBITS ballots.  The words end in *src (the two buffers swap once
-// per pass); wcnt holds SEG_WAVES x SEG_RADIX counters.
-__device__ __forceinline__ void lds_radix_u32(uint32_t *&src, uint32_t *&dst, int n, int kbits,
-                                              uint32_t *wcnt, uint32_t *doff, uint32_t *wtot)
-{
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const uint64_t lt = lane ? (~0ull >> (64 - lane)) : 0ull;
-    const int rpw = (n + SEG_BLOCK - 1) / SEG_BLOCK;  // <= SEG_ROUNDS
-    const int wbase = w * 64 * rpw;
-    for (int shift = 0; shift < kbits; shift += SEG_DBITS) {
-        for (int k = threadIdx.x; k < SEG_WAVES * SEG_RADIX; k += SEG_BLOCK) wcnt[k] = 0;
-        __syncthreads();
-        // wave w ranks its own rpw x 64 consecutive words, 64 at a time:
-        // equal digits find each other with SEG_DBITS ballots, so the order
-        // is stable
-        uint32_t kk[SEG_ROUNDS], loc[SEG_ROUNDS];
-#pragma unroll
-        for (int q = 0; q < SEG_ROUNDS; q++) {
-            // rounds past the wave's share or past the words are skipped
-            // (uniform per wave)
-            if (q >= rpw || wbase + q * 64 >= n) break;
-            const int idx = wbase + q * 64 + lane;
-            const bool valid = idx < n;
-            const uint32_t key = valid ? src[idx] : 0u;
-            kk[q] = key;
-            const uint32_t d = (key >> shift) & (SEG_RADIX - 1);
-            uint64_t peers = __ballot(valid);
-#pragma unroll
-            for (int b = 0; b < SEG_DBITS; b++) {
-                const uint64_t bal = __ballot((d >> b) & 1u);
-                peers &= ((d >> b) & 1u) ? bal : ~bal;
-            }
-            const uint32_t old = wcnt[w * SEG_RADIX + d];
-            loc[q] = old + (uint32_t)__popcll(peers & lt);
-            __builtin_amdgcn_wave_barrier();
-            if (valid && (peers & lt) == 0) wcnt[w * SEG_RADIX + d] = old + (uint32_t)__popcll(peers);
-            __builtin_amdgcn_wave_barrier();
-        }
-        __syncthreads();
-        // digit d = threadIdx.x: offsets of the waves within the digit, then
-        // the digit's first slot
-        uint32_t run = 0, incl = 0;
-        if (threadIdx.x < SEG_RADIX) {
-            const int d = threadIdx.x;
-#pragma unroll
-            for (int k = 0; k < SEG_WAVES; k++) {
-                const uint32_t c = wcnt[k * SEG_RADIX + d];
-                wcnt[k * SEG_RADIX + d] = run;
-                run += c;
-            }
-            incl = run;
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const uint32_t u = (uint32_t)__shfl_up((int)incl, o, 64);
-                if (lane >= o) incl += u;
-            }
-            if (lane == 63) wtot[w] = incl;
-        }
-        __syncthreads();
-        if (threadIdx.x < SEG_RADIX) {
-            uint32_t before = 0;
-            for (int k = 0; k < w; k++) before += wtot[k];
-            doff[threadIdx.x] = before + incl - run;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < SEG_ROUNDS; q++) {
-            const int idx = wbase + q * 64 + lane;
-            if (q < rpw && idx < n) {
-                const uint32_t d = (kk[q] >> shift) & (SEG_RADIX - 1);
-                dst[doff[d] + wcnt[w * SEG_RADIX + d] + loc[q]] = kk[q];
-            }
-        }
-        __syncthreads();
-        uint32_t *t = src;
-        src = dst;
-        dst = t;
-    }
-}
-
-// one workgroup per polygon; dynamic LDS: two buffers of `cap` words (the
-// largest polygon's event count rounded up to whole waves' rounds, at most
-// SEG_CAP) and the per-wave digit counts.  Out: the sorted events (kind in
-// bits 0-1 of opay, bit 2 set on a toggle), each event's index among the
-// polygon's toggles before it (otl), the polygon's toggle count (ptot[p]),
-// and error bit 2 when a row ends inside the polygon
-__global__ __launch_bounds__(SEG_BLOCK) void k_event_seg_sort(EventSegs S, const uint64_t *evkey,
-                                                              const uint32_t *evpay, int rxbits,
-                                                              int xbits, int cap, uint64_t *okey,
-                                                              uint32_t *opay, int32_t *otl,
-                                                              int64_t *ptot, int *err,
-                                                              unsigned long long *rowcnt)
-{
-    extern __shared__ uint32_t seg_lds[];
-    uint32_t *src = seg_lds, *dst = seg_lds + cap;
-    uint32_t *wcnt = seg_lds + 2 * cap;  // [SEG_WAVES][SEG_RADIX]
-    __shared__ uint32_t doff[SEG_RADIX];
-    __shared__ uint32_t wtot[SEG_RADIX / 64];
-    __shared__ uint32_t wsum[SEG_WAVES];
-    const int p = blockIdx.x;
-    int64_t ib, nbv, ic, ncv, o0;
-    event_seg(S, p, &ib, &nbv, &ic, &ncv, &o0);
-    const int n = (int)(nbv + ncv);  // <= cap (checked by the host)
-    const uint64_t rxm = (1ull << rxbits) - 1;
-    {
-        // every load of the lane issued before the first LDS store (a
-        // load-store loop would wait for each load in turn)
-        uint64_t kq[SEG_ROUNDS];
-        uint32_t pq[SEG_ROUNDS];
-#pragma unroll
-        for (int q = 0; q < SEG_ROUNDS; q++) {
-            const int i = q * SEG_BLOCK + threadIdx.x;
-            if (i < n) {
-                const int64_t at = i < nbv ? ib + i : ic + (i - nbv);
-                kq[q] = evkey[at];
-                pq[q] = evpay[at];
-            }
-        }
-#pragma unroll
-        for (int q = 0; q < SEG_ROUNDS; q++) {
-            const int i = q * SEG_BLOCK + threadIdx.x;
-            if (i < n) src[i] = (uint32_t)(((kq[q] & rxm) << 2) | pq[q]);
-        }
-    }
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    // the polygon's own row and column range: keys re-based to it need fewer
-    // bits, so fewer passes (a polygon spans a few hundred rows and columns)
-    __shared__ uint32_t rng[4];
-    if (threadIdx.x < 4) rng[threadIdx.x] = (threadIdx.x & 1) ? 0u : 0xffffffffu;
-    __syncthreads();
-    const uint32_t xmask = (1u << xbits) - 1;
-    {
-        uint32_t r0 = 0xffffffffu, r1 = 0, x0 = 0xffffffffu, x1 = 0;
-        for (int i = threadIdx.x; i < n; i += SEG_BLOCK) {
-            const uint32_t rx = src[i] >> 2, r = rx >> xbits, x = rx & xmask;
-            r0 = min(r0, r);
-            r1 = max(r1, r);
-            x0 = min(x0, x);
-            x1 = max(x1, x);
-        }
-        for (int o = 32; o > 0; o >>= 1) {
-            r0 = min(r0, (uint32_t)__shfl_xor((int)r0, o, 64));
-            r1 = max(r1, (uint32_t)__shfl_xor((int)r1, o, 64));
-            x0 = min(x0, (uint32_t)__shfl_xor((int)x0, o, 64));
-            x1 = max(x1, (uint32_t)__shfl_xor((int)x1, o, 64));
-        }
-        if (lane == 0) {
-            atomicMin(&rng[0], r0);
-            atomicMax(&rng[1], r1);
-            atomicMin(&rng[2], x0);
-            atomicMax(&rng[3], x1);
-        }
-    }
-    __syncthreads();
-    const uint32_t rmin = rng[0], xmin = rng[2];
-    const int xw = n ? 32 - __clz((int)(rng[3] - xmin)) : 0;
-    const int rw = n ? 32 - __clz((int)(rng[1] - rmin)) : 0;
-    for (int i = threadIdx.x; i < n; i += SEG_BLOCK) {
-        const uint32_t v = src[i], rx = v >> 2;
-        src[i] = ((((rx >> xbits) - rmin) << xw | ((rx & xmask) - xmin)) << 2) | (v & 3u);
-    }
-    __syncthreads();
-    const int kbits = n ? rw + xw + 2 : 0;
-    lds_radix_u32(src, dst, n, kbits, wcnt, doff, wtot);
-    // coverage: each lane takes `per` consecutive sorted events; dst gets
-    // the inclusive prefix words
-    const int per = (n + SEG_BLOCK - 1) / SEG_BLOCK;
-    const int i0 = threadIdx.x * per, i1 = min(i0 + per, n);
-    uint32_t sum = 0;
-    for (int i = i0; i < i1; i++) sum += ev_word(src[i] & 3u);
-    uint32_t run = seg_excl_scan(sum, wsum);
-    for (int i = i0; i < i1; i++) {
-        run += ev_word(src[i] & 3u);
-        dst[i] = run;
-    }
-    __syncthreads();
-    // toggles: the last event of a (row, x) group where membership changes
-    // from just before the group to just after it
-    uint32_t fbits = 0, cnt = 0;
-    for (int k = 0; k < per; k++) {
-        const int i = i0 + k;
-        if (i >= n) break;
-        const uint32_t key = src[i] >> 2;  // re-based (row, x): row above bit xw
-        if (i + 1 < n && (src[i + 1] >> 2) == key) continue;
-        int a = i;
-        while (a > 0 && (src[a - 1] >> 2) == key) a--;
-        const uint32_t row = key >> xw;
-        const uint32_t before =
-            (a > 0 && ((src[a - 1] >> 2) >> xw) == row) ? cov_of(dst[a - 1]) : 0u;
-        const uint32_t after = cov_of(dst[i]);
-        if ((before > 0) != (after > 0)) {
-            fbits |= 1u << k;
-            cnt++;
-            if (rowcnt) atomicAdd(rowcnt + rmin + row, 1ull);
-        }
-        if ((i + 1 == n || ((src[i + 1] >> 2) >> xw) != row) && after != 0) atomicOr(err, 2);
-    }
-    const uint32_t tex = seg_excl_scan(cnt, wsum);
-    if (threadIdx.x == SEG_BLOCK - 1) ptot[p] = tex + cnt;
-    // dst (the prefix words, no longer needed) takes each event's toggle
-    // index and flag, so the outputs below leave in coalesced stores
-    uint32_t t = tex;
-    for (int k = 0; k < per; k++) {
-        const int i = i0 + k;
-        if (i >= n) break;
-        const uint32_t f = (fbits >> k) & 1u;
-        dst[i] = t | (f << 31);
-        t += f;
-    }
-    __syncthreads();
-    const uint64_t pk = (uint64_t)p << rxbits;
-    const uint32_t lxm = (1u << xw) - 1;
-    for (int i = threadIdx.x; i < n; i += SEG_BLOCK) {
-        const uint32_t v = src[i], tl = dst[i], key = v >> 2;
-        const uint32_t rx = (((key >> xw) + rmin) << xbits) | ((key & lxm) + xmin);
-        okey[o0 + i] = pk | (uint64_t)rx;
-        opay[o0 + i] = (v & 3u) | ((tl >> 31) << 2);
-        otl[o0 + i] = (int32_t)(tl & 0x7fffffffu);
-    }
-}
-
-// toggles of the per-polygon path: event t with its toggle bit set goes to
-// slot o = ptoff[polygon] + otl[t] (polygon, then row and x order); with row
-// buckets, (x << 32 | o) also goes to the bucket of its row, in no order
-// (rowcnt: fill counters, zero on entry)
-__global__ void k_toggle_emit_seg(const uint64_t *key, const uint32_t *pay, const int32_t *otl,
-                                  const int64_t *ptoff, int64_t n, int rxbits, int xbits,
-                                  uint64_t *tkey, int32_t *tpoly, const int64_t *rowoff,
-                                  unsigned long long *rowcnt, uint64_t *rb)
-{
-    int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= n || !(pay[t] & 4u)) return;
-    const uint64_t k = key[t];
-    const int32_t p = (int32_t)(k >> rxbits);
-    const int64_t o = ptoff[p] + otl[t];
-    const uint64_t rx = k & ((1ull << rxbits) - 1);
-    if (tkey) tkey[o] = rx;
-    tpoly[o] = p;
-    if (rb) {
-        const uint64_t row = rx >> xbits, x = rx & ((1ull << xbits) - 1);
-        const int64_t at = rowoff[row] + (int64_t)atomicAdd(rowcnt + row, 1ull);
-        rb[at] = (x << 32) | (uint64_t)o;
-    }
-}
-
-// One workgroup: row offsets of the toggle buckets (exclusive scan of
-// rowcnt[0..gh) into rowoff[0..gh], total at rowoff[gh]), the largest row's
-// count into *mx, and rowcnt zeroed again for use as fill counters.  The
-// rows go by in chunks of one count per lane, the next chunk's counts loaded
-// while the current one is scanned.
-__global__ __launch_bounds__(SEG_BLOCK) void k_row_scan_max(unsigned long long *rowcnt, int64_t gh,
-                                                            int64_t *rowoff,
-                                                            unsigned long long *mx)
-{
-    __shared__ uint32_t wsum[SEG_WAVES];
-    __shared__ uint32_t chunk_tot, smax;
-    if (threadIdx.x == 0) smax = 0;
-    __syncthreads();
-    uint32_t carry = 0, m = 0;
-    uint32_t next = threadIdx.x < gh ? (uint32_t)rowcnt[threadIdx.x] : 0u;
-    for (int64_t c0 = 0; c0 < gh; c0 += SEG_BLOCK) {
-        const int64_t r = c0 + threadIdx.x;
-        const uint32_t cur = next;  // 0 past the last row
-        next = r + SEG_BLOCK < gh ? (uint32_t)rowcnt[r + SEG_BLOCK] : 0u;
-        m = max(m, cur);
-        const uint32_t ex = seg_excl_scan(cur, wsum);
-        if (r < gh) {
-            rowoff[r] = carry + ex;
-            rowcnt[r] = 0;
-        }
-        if (threadIdx.x == SEG_BLOCK - 1) chunk_tot = ex + cur;
-        __syncthreads();
-        carry += chunk_tot;
-        __syncthreads();
-    }
-    for (int o = 32; o > 0; o >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, o, 64));
-    if ((threadIdx.x & 63) == 0) atomicMax(&smax, m);
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        rowoff[gh] = carry;
-        *mx = smax;
-    }
-}
-
-// Rows of at most ROW_CAP toggles: one wavefront per row ranks the row's
-// (x, slot) words in LDS (a word's rank is the number of smaller words:
-// slots are distinct), then walks them in order.  The distinct positions of
-// row r take indices rowoff[r] + 0, 1, ... (a row's toggle count bounds its
-// distinct positions; the indices left over up to rowoff[r + 1] stay holes
-// of depth 0, which no piece reads), and each toggle learns its index.
-#define ROW_CAP 512
-#define ROW_WAVES 4
-__global__ __launch_bounds__(64 * ROW_WAVES) void k_row_pieces(const uint64_t *rb,
-                                                                const int64_t *rowoff, int64_t gh,
-                                                                int xbits, int64_t nt, uint64_t *E,
-                                                                int64_t *rank, int64_t *diff)
-{
-    __shared__ uint64_t raw[ROW_WAVES][ROW_CAP];
-    __shared__ uint64_t sorted[ROW_WAVES][ROW_CAP];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int64_t r = (int64_t)blockIdx.x * ROW_WAVES + wv;
-    if (r >= gh) return;  // whole wavefronts leave; no workgroup barrier below
-    const int64_t base = rowoff[r];
-    const int c = (int)(rowoff[r + 1] - base);  // <= ROW_CAP (checked by the host)
-    uint64_t *w = raw[wv], *s = sorted[wv];
-    {
-        uint64_t v[ROW_CAP / 64];
-#pragma unroll
-        for (int q = 0; q < ROW_CAP / 64; q++)
-            if (q * 64 + lane < c) v[q] = rb[base + q * 64 + lane];
-#pragma unroll
-        for (int q = 0; q < ROW_CAP / 64; q++)
-            if (q * 64 + lane < c) w[q * 64 + lane] = v[q];
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    for (int i = lane; i < c; i += 64) {
-        const uint64_t v = w[i];
-        int rk = 0;
-        for (int j = 0; j < c; j++) rk += w[j] < v ? 1 : 0;
-        s[rk] = v;
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    int64_t nd = 0;  // distinct positions so far
-    for (int q0 = 0; q0 < c; q0 += 64) {
-        const int q = q0 + lane;
-        const bool valid = q < c;
-        const uint64_t v = valid ? s[q] : 0ull;
-        const uint32_t x = (uint32_t)(v >> 32);
-        const bool first = valid && (q == 0 || (uint32_t)(s[q - 1] >> 32) != x);
-        const uint64_t fb = __ballot(first);
-        const uint64_t le = fb & ((2ull << lane) - 1);
-        const int64_t idx = base + nd + __popcll(le) - 1;
-        if (valid) {
-            const uint32_t slot = (uint32_t)v;
-            rank[slot] = idx;
-            if (first) {
-                E[idx] = ((uint64_t)r << xbits) | x;
-                int64_t d = 0;
-                for (int u = q; u < c && (uint32_t)(s[u] >> 32) == x; u++)
-                    d += ((uint32_t)s[u] & 1u) ? -1 : 1;
-                diff[idx] = d;
-            }
-        }
-        nd += __popcll(fb);
-    }
-    for (int64_t q = nd + lane; q < c; q += 64) diff[base + q] = 0;
-    if (r == gh - 1 && lane == 0) diff[nt] = 0;
-}
-
 // ------------------------------------------------ coverage of each row
 //
 // Events carry the key (polygon, row, x) and one of three kinds: the start
@@ -945,24 +497,27 @@ __global__ void k_seg_row_off(const uint32_t *seg_row, int64_t ns, int64_t gh, i
     row_off[r] = lo;
 }
 
-// ------------------------------------------------ multi-polygon set dedup
+// ------------------------------------------------ multi-polygon segments
 
-// Sets of 2 or 3 polygons are packed exactly into fb-bit fields (fb bits hold
-// id+1); larger sets get a key of their own above that range (not shared).
-__global__ void k_multi_keys(const int64_t *multi_mem, int64_t n_multi, int64_t n_mem,
-                             const int32_t *mem_ids, int fb, uint64_t *key, uint32_t *val)
+// set key of multi segment m (sets.h); members of larger sets stay where
+// k_piece_emit sorted them
+__global__ void k_multi_keys(const int64_t *multi_mem, const int64_t *multi_seg, int64_t n_multi,
+                             int64_t n_mem, const int32_t *mem_ids, int fb, uint64_t *key,
+                             uint32_t *val, uint64_t *memloc)
 {
     int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (m >= n_multi) return;
     int64_t a = multi_mem[m], b = (m + 1 < n_multi) ? multi_mem[m + 1] : n_mem;
+    const int64_t o = multi_seg[m];
     uint64_t k = 0;
     if (b - a <= 3) {
         for (int64_t t = a; t < b; t++) k |= (uint64_t)(mem_ids[t] + 1) << (fb * (t - a));
     } else {
-        k = (1ull << (3 * fb)) | (uint64_t)m;
+        k = (1ull << (3 * fb)) + (uint64_t)o;
+        memloc[o] = ((uint64_t)a << 6) | (uint64_t)(b - a);
     }
     key[m] = k;
-    val[m] = (uint32_t)m;
+    val[m] = (uint32_t)o;
 }
 
 __global__ void k_flag_new(const uint64_t *key, int64_t n, int64_t *flag)
@@ -970,195 +525,6 @@ __global__ void k_flag_new(const uint64_t *key, int64_t n, int64_t *flag)
     int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= n) return;
     flag[t] = (t == 0 || key[t] != key[t - 1]) ? 1 : 0;
-}
-
-__global__ void k_set_sizes(const uint64_t *key, const uint32_t *val, const int64_t *gexcl,
-                            int64_t n, const int64_t *multi_mem, int64_t n_multi, int64_t n_mem,
-                            int64_t *set_sz)
-{
-    int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= n) return;
-    if (t == 0 || key[t] != key[t - 1]) {
-        int64_t m = val[t];
-        int64_t a = multi_mem[m], b = (m + 1 < n_multi) ? multi_mem[m + 1] : n_mem;
-        set_sz[gexcl[t]] = b - a;
-    }
-}
-
-__global__ void k_set_fill(const uint64_t *key, const uint32_t *val, const int64_t *gexcl,
-                           int64_t n, const int64_t *multi_mem, int64_t n_multi, int64_t n_mem,
-                           const int32_t *mem_ids, const int64_t *set_off, int32_t *set_ids,
-                           const int64_t *multi_seg, uint32_t *seg_code)
-{
-    int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= n) return;
-    bool first = (t == 0 || key[t] != key[t - 1]);
-    int64_t g = gexcl[t] + (first ? 1 : 0) - 1;
-    int64_t m = val[t];
-    if (first) {
-        int64_t a = multi_mem[m], b = (m + 1 < n_multi) ? multi_mem[m + 1] : n_mem;
-        int64_t o = set_off[g];
-        for (int64_t q = a; q < b; q++) set_ids[o + (q - a)] = mem_ids[q];
-    }
-    seg_code[multi_seg[m]] = CODE_SET_BASE + (uint32_t)g;
-}
-
-// Sets of at most SET_CAP distinct keys (keys below 2^31) take a shorter
-// path than the global sort of all NM keys: a hash table collects the
-// distinct keys (each first insert appends its key to a list), one workgroup
-// sorts the list in LDS, numbers the sets in key order (the numbering the
-// global sort gives), lays out and fills the set table and records each
-// key's number in a table beside the hash, and one lookup per multi segment
-// writes its code.
-#define SET_CAP 8192
-#define SET_EMPTY 0xffffffffu
-
-__device__ __forceinline__ uint32_t set_slot(uint32_t k, int hb)
-{
-    return (k * 2654435761u) >> (32 - hb);
-}
-
-__global__ void k_set_insert(const uint64_t *key, int64_t n, uint32_t *tab, int hb,
-                             uint32_t *list, unsigned long long *cnt)
-{
-    const int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (m >= n) return;
-    const uint32_t k = (uint32_t)key[m], mask = (1u << hb) - 1u;
-    // neighbouring multi segments mostly share their set: only the first of
-    // a run of equal keys inserts it
-    if (m > 0 && (uint32_t)key[m - 1] == k) return;
-    uint32_t s = set_slot(k, hb);
-    // the table has at least twice as many slots as keys: a free slot is
-    // always ahead; a slot already holding the key is seen without an atomic
-    while (true) {
-        const uint32_t seen = tab[s];
-        if (seen == k) return;
-        if (seen != SET_EMPTY) {
-            s = (s + 1) & mask;
-            continue;
-        }
-        const uint32_t prev = atomicCAS(tab + s, SET_EMPTY, k);
-        if (prev == SET_EMPTY) {
-            const unsigned long long at = atomicAdd(cnt, 1ull);
-            if (at < SET_CAP) list[at] = k;
-            return;
-        }
-        if (prev == k) return;
-        s = (s + 1) & mask;
-    }
-}
-
-__device__ __forceinline__ uint32_t set_find(const uint32_t *tab, uint32_t k, int hb)
-{
-    const uint32_t mask = (1u << hb) - 1u;
-    uint32_t s = set_slot(k, hb);
-    while (tab[s] != k) s = (s + 1) & mask;
-    return s;
-}
-
-// members of the set with key k: fb-bit fields of id + 1 (ascending ids) for
-// sets of 2 or 3, else the members of multi segment k - 2^(3 fb)
-__device__ __forceinline__ int64_t set_members(uint32_t k, int fb, const int64_t *multi_mem,
-                                               int64_t n_multi, int64_t n_mem, int64_t *a)
-{
-    if (k < (1u << (3 * fb))) {
-        const uint32_t fm = (1u << fb) - 1u;
-        *a = -1;
-        return ((k & fm) != 0) + (((k >> fb) & fm) != 0) + (((k >> (2 * fb)) & fm) != 0);
-    }
-    const int64_t m = (int64_t)(k - (1u << (3 * fb)));
-    *a = multi_mem[m];
-    return ((m + 1 < n_multi) ? multi_mem[m + 1] : n_mem) - *a;
-}
-
-// one workgroup; dynamic LDS: two buffers of SET_CAP words and the digit
-// counters.  Leaves at once when the list overflowed (the host then takes
-// the global sort).  Out: set_off[0..nd], set_ids, rank[slot] for every
-// key's slot, *nids = the total member count.
-__global__ __launch_bounds__(SEG_BLOCK) void k_set_table(const uint32_t *list,
-                                                         const unsigned long long *cnt,
-                                                         const uint32_t *tab, int hb, int kbits,
-                                                         int fb, const int64_t *multi_mem,
-                                                         int64_t n_multi, int64_t n_mem,
-                                                         const int32_t *mem_ids, uint32_t *rank,
-                                                         int64_t *set_off, int32_t *set_ids,
-                                                         unsigned long long *nids)
-{
-    extern __shared__ uint32_t set_lds[];
-    uint32_t *src = set_lds, *dst = set_lds + SET_CAP;
-    uint32_t *wcnt = set_lds + 2 * SET_CAP;
-    __shared__ uint32_t doff[SEG_RADIX];
-    __shared__ uint32_t wtot[SEG_RADIX / 64];
-    __shared__ uint32_t wsum[SEG_WAVES];
-    const unsigned long long nd = *cnt;
-    if (nd > SET_CAP) return;
-    const int n = (int)nd;
-    for (int i = threadIdx.x; i < n; i += SEG_BLOCK) src[i] = list[i];
-    __syncthreads();
-    lds_radix_u32(src, dst, n, kbits, wcnt, doff, wtot);
-    // set r = src[r]: sizes, offsets (each lane `per` consecutive sets)
-    const int per = (n + SEG_BLOCK - 1) / SEG_BLOCK;
-    const int i0 = threadIdx.x * per, i1 = min(i0 + per, n);
-    uint32_t sum = 0;
-    int64_t a;
-    for (int i = i0; i < i1; i++) sum += (uint32_t)set_members(src[i], fb, multi_mem, n_multi, n_mem, &a);
-    uint32_t off = seg_excl_scan(sum, wsum);
-    for (int i = i0; i < i1; i++) {
-        const uint32_t k = src[i];
-        const int64_t c = set_members(k, fb, multi_mem, n_multi, n_mem, &a);
-        set_off[i] = off;
-        if (a < 0) {
-            const uint32_t fm = (1u << fb) - 1u;
-            for (int64_t t = 0; t < c; t++) set_ids[off + t] = (int32_t)(((k >> (fb * t)) & fm) - 1);
-        } else {
-            for (int64_t t = 0; t < c; t++) set_ids[off + t] = mem_ids[a + t];
-        }
-        rank[set_find(tab, k, hb)] = (uint32_t)i;
-        off += (uint32_t)c;
-    }
-    if (threadIdx.x == SEG_BLOCK - 1) {
-        set_off[n] = off;
-        *nids = off;
-    }
-}
-
-// code of every multi segment: its key's set number
-__global__ void k_set_codes(const uint64_t *key, int64_t n, const unsigned long long *cnt,
-                            const uint32_t *tab, int hb, const uint32_t *rank,
-                            const int64_t *multi_seg, uint32_t *seg_code)
-{
-    const int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (m >= n || *cnt > SET_CAP) return;
-    const uint32_t g = rank[set_find(tab, (uint32_t)key[m], hb)];
-    seg_code[multi_seg[m]] = CODE_SET_BASE + g;
-}
-
-// ------------------------------------------------ segment lookups
-
-__device__ __forceinline__ uint32_t seg_code_at(const int64_t *seg_row_off, const int32_t *seg_x0,
-                                                const int32_t *seg_x1, const uint32_t *seg_code,
-                                                int64_t r, int32_t x)
-{
-    int64_t lo = seg_row_off[r], hi = seg_row_off[r + 1];
-    int64_t a = lo;
-    while (lo < hi) {
-        int64_t mid = (lo + hi) >> 1;
-        if (seg_x0[mid] <= x) lo = mid + 1; else hi = mid;
-    }
-    if (lo > a && x < seg_x1[lo - 1]) return seg_code[lo - 1];
-    return 0;
-}
-
-__global__ void k_lookup_ij(const int64_t *seg_row_off, const int32_t *seg_x0, const int32_t *seg_x1,
-                            const uint32_t *seg_code, int64_t gi0, int64_t gj0, int64_t gw, int64_t gh,
-                            const int64_t *ij, int64_t n, uint32_t *out)
-{
-    int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= n) return;
-    int64_t i = ij[2 * t] - gi0, j = ij[2 * t + 1] - gj0;
-    out[t] = (i < 0 || j < 0 || i >= gw || j >= gh)
-                 ? 0u
-                 : seg_code_at(seg_row_off, seg_x0, seg_x1, seg_code, j, (int32_t)i);
 }
 
 // ------------------------------------------------ tiled grid
@@ -1194,8 +560,9 @@ __device__ __forceinline__ void square_origin(int64_t u, const int64_t *mt, int 
 // G lanes per square (G = min(side, 64)): uniform code of the square, or
 // 0xffffffff and mixed[u] = 1
 template <int G>
-__global__ void k_square_classify(const int64_t *seg_row_off, const int32_t *seg_x0,
-                                  const int32_t *seg_x1, const uint32_t *seg_code, int64_t gw,
+__global__ void k_square_classify(const int64_t *seg_beg, const int64_t *seg_end,
+                                  const int32_t *seg_x0, const int32_t *seg_x1,
+                                  const uint32_t *seg_code, int64_t gw,
                                   int64_t gh, const int64_t *mt, int tl, int sl, int64_t tw,
                                   int64_t n_sq, uint32_t *code, int64_t *mixed)
 {
@@ -1213,7 +580,7 @@ __global__ void k_square_classify(const int64_t *seg_row_off, const int32_t *seg
         lo_c = hi_c = 0;
     }
     for (int64_t r = r0 + lane; r < r1 && x0 < gw; r += G) {
-        int64_t a = seg_row_off[r], lo = a, hi = seg_row_off[r + 1], e = hi;
+        int64_t a = seg_beg[r], lo = a, hi = seg_end[r], e = hi;
         while (lo < hi) {
             int64_t mid = (lo + hi) >> 1;
             if (seg_x0[mid] <= x0) lo = mid + 1; else hi = mid;
@@ -1255,8 +622,8 @@ __global__ void k_flag_list(const int64_t *pos, int64_t n, int64_t total, int64_
 // squares of k_square_classify).  OUT = uint32_t full codes or uint16_t
 // short codes.
 template <typename OUT>
-__global__ __launch_bounds__(256) void k_block_fill(const int64_t *seg_row_off, const int32_t *seg_x0,
-                             const int32_t *seg_x1, const uint32_t *seg_code, int64_t gw,
+__global__ __launch_bounds__(256) void k_block_fill(const int64_t *seg_beg, const int64_t *seg_end,
+                             const int32_t *seg_x0, const int32_t *seg_x1, const uint32_t *seg_code, int64_t gw,
                              int64_t gh, const int64_t *sq, int64_t nblk, const int64_t *mt,
                              int tl, int sl, int64_t tw, int side_log2, uint32_t np, OUT *blocks)
 {
@@ -1278,7 +645,7 @@ __global__ __launch_bounds__(256) void k_block_fill(const int64_t *seg_row_off, 
         for (int c = 0; c < rlen; c++) out[c] = 0;
         return;
     }
-    const int64_t lo = seg_row_off[r], hi = seg_row_off[r + 1];
+    const int64_t lo = seg_beg[r], hi = seg_end[r];
     int64_t a = lo, e = hi;
     while (a < e) {
         int64_t mid = (a + e) >> 1;
@@ -1453,9 +820,9 @@ int key_grid_launch(const sba_polygons *sets, int32_t n_sets, int64_t eps, hipSt
 }
 
 // paths of the coverage stages: bits set in g_build_paths_off turn a path
-// off (1: the per-polygon event sort, 2: the toggle row buckets, 4: the set
-// table through a hash); the last build's paths taken, same bits (tests of
-// both sides of each choice)
+// off (1: the pairs of edges and rows counted per row, 2: the rows swept in
+// LDS, 4: the set table through a hash); the last build's paths taken, same
+// bits (tests of both sides of each choice)
 static std::atomic<int> g_build_paths_off{0}, g_build_paths_last{0};
 
 extern "C" int sba_debug_build_paths(int off)
@@ -1505,13 +872,6 @@ int build_segments(const sba_polygons *polys, int64_t eps, hipStream_t st, sba_h
     const int32_t nr = (int32_t)hsc[1];
     const int64_t nv = hsc[2];
     if (nv > ((int64_t)1 << 31) - 1) return SBA_ELIMIT;
-    B.n_edges = nv;
-    RC(B.alloc(&B.edges, nv));
-    RC(B.alloc(&B.epoly, nv));
-    hipLaunchKernelGGL(k_edges, dim3(grid_for(nv)), dim3(256), 0, st, polys->ring_off, np,
-                       polys->vert_off, nr, polys->xy, nv, B.edges, B.epoly);
-    HIP_OK(hipGetLastError());
-
     const int64_t s = h->s;
     int64_t gi0 = hsc[3], gj0 = hsc[4], gi1 = hsc[5], gj1 = hsc[6];
     if (B.window) {
@@ -1556,6 +916,22 @@ int build_segments(const sba_polygons *polys, int64_t eps, hipStream_t st, sba_h
     if (B.rbits < 1) B.rbits = 1;
     const int pbits = bits_for((uint64_t)(np - 1)) < 1 ? 1 : bits_for((uint64_t)(np - 1));
 
+    // 1-4 row by row in LDS (rows.hip) unless a row is too large for that
+    const int paths_off = g_build_paths_off.load();
+    g_build_paths_last = 0;
+    if (!(paths_off & 1)) {
+        bool taken = false, one = false;
+        RC(rows_coverage(polys, bbox, nv, st, h, B, paths_off, &taken, &one));
+        g_build_paths_last = 1 | (taken ? 2 : 0) | (one ? 4 : 0);
+        if (taken) return h->n_sets >= (int64_t)(TILE_MIXED - CODE_SET_BASE) ? SBA_ELIMIT : 0;
+    }
+    B.n_edges = nv;
+    RC(B.alloc(&B.edges, nv));
+    RC(B.alloc(&B.epoly, nv));
+    hipLaunchKernelGGL(k_edges, dim3(grid_for(nv)), dim3(256), 0, st, polys->ring_off, np,
+                       polys->vert_off, nr, polys->xy, nv, B.edges, B.epoly);
+    HIP_OK(hipGetLastError());
+
     // 1-2: boundary intervals and crossings per edge
     int64_t *nb = nullptr, *nc = nullptr;
     RC(B.alloc(&nb, nv + 1));
@@ -1568,18 +944,7 @@ int build_segments(const sba_polygons *polys, int64_t eps, hipStream_t st, sba_h
         int64_t *out[2] = {nb, nc}, *sum[2] = {tot, tot + 1};
         RC(scan_exclusive_i64_multi(2, in, out, n, sum, st, &B.ws));
     }
-    // the events of the coverage, polygon by polygon: the largest polygon's
-    // count decides whether they are sorted per polygon in LDS
-    EventSegs S{polys->ring_off, polys->vert_off, nb, nc, tot, nv, B.centre ? 0 : 1,
-                B.boundary_only ? 0 : 1, 0};
-    // per-row toggle counters of the row-bucket path, zeroed by the same launch
-    unsigned long long *rowcnt = nullptr;
-    RC(B.alloc(&rowcnt, gh + 1));
-    hipLaunchKernelGGL(k_event_seg_max, dim3(grid_for(std::max<int64_t>(np, gh + 1))), dim3(256), 0,
-                       st, S, np, (unsigned long long *)(B.sc + SC_SEG_MAX), rowcnt, gh);
-    HIP_OK(hipGetLastError());
     RC(fetch());
-    const int64_t seg_max = hsc[SC_SEG_MAX];
     // boundary-only approximations take no row-line crossings (no interior
     // spans); centre-sampled ones no boundary cells, except as the Hilbert
     // layout's candidate keys (where the cell sets can change along the curve)
@@ -1625,91 +990,30 @@ int build_segments(const sba_polygons *polys, int64_t eps, hipStream_t st, sba_h
     uint64_t *tkey = nullptr, *E = nullptr;
     int32_t *tpoly = nullptr;
     int64_t *tf = nullptr;
-    // row buckets of the toggles (per-polygon path, rows of at most ROW_CAP
-    // toggles): each row's distinct positions are found in one wavefront
-    bool rows = false, seg_path = false;
-    uint64_t *rb = nullptr;
-    int64_t *rowoff = nullptr;
-    const int paths_off = g_build_paths_off.load();
-    // Clip-window builds (viewport queries) keep the global sorts: they run
-    // beside persistent probe kernels that hold most of every compute unit's
-    // wave slots and registers, where the per-polygon workgroups of 1024
-    // lanes would wait for those kernels to end; their event counts are
-    // small, so the global passes cost little there.
-    if (NE > 0 && seg_max <= SEG_CAP && rxbits + 2 <= 32 && !(paths_off & 1) && !B.window) {
-        // per polygon in LDS: sort, coverage and toggle flags in one launch
-        seg_path = true;
-        uint64_t *k2 = nullptr;
-        uint32_t *v2 = nullptr;
-        int32_t *tl = nullptr;
-        int64_t *ptot = nullptr, *ptoff = nullptr;
-        RC(B.alloc(&k2, NE));
-        RC(B.alloc(&v2, NE));
-        RC(B.alloc(&tl, NE));
-        RC(B.alloc(&ptot, np));
-        RC(B.alloc(&ptoff, np));
-        S.cbase = B.centre ? 0 : 2 * NB;
-        const int cap = (int)std::max<int64_t>(64, (seg_max + 63) & ~(int64_t)63);
-        const int lds = (2 * cap + SEG_WAVES * SEG_RADIX) * (int)sizeof(uint32_t);
-        (void)hipFuncSetAttribute((const void *)k_event_seg_sort,
-                                  hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  (2 * SEG_CAP + SEG_WAVES * SEG_RADIX) * (int)sizeof(uint32_t));
-        (void)hipGetLastError();
-        hipLaunchKernelGGL(k_event_seg_sort, dim3((unsigned)np), dim3(SEG_BLOCK), lds, st, S,
-                           B.evkey, B.evpay, rxbits, B.xbits, cap, k2, v2, tl, ptot, err, rowcnt);
-        HIP_OK(hipGetLastError());
-        RC(B.alloc(&rowoff, gh + 1));
-        hipLaunchKernelGGL(k_row_scan_max, dim3(1), dim3(SEG_BLOCK), 0, st, rowcnt, gh, rowoff,
-                           (unsigned long long *)(B.sc + SC_ROW_MAX));
-        HIP_OK(hipGetLastError());
-        B.release(nb);  // the edge offsets: read by the launch above, free after it in stream order
-        B.release(nc);
-        B.release(B.evkey);
-        B.release(B.evpay);
-        B.evkey = k2;
-        B.evpay = v2;
-        RC(scan_exclusive_i64(ptot, ptoff, np, tot, st, &B.ws));
-        RC(fetch());
-        NT = hsc[8];
-        herr = (int)(uint32_t)hsc[0];
-        if (herr || (NT & 1)) return SBA_EDEVICE;
-        rows = hsc[SC_ROW_MAX] <= ROW_CAP && !(paths_off & 2);
-        if (!rows) RC(B.alloc(&tkey, std::max<int64_t>(NT, 1)));
-        if (rows) RC(B.alloc(&rb, std::max<int64_t>(NT, 1)));
-        RC(B.alloc(&tpoly, std::max<int64_t>(NT, 1)));
-        hipLaunchKernelGGL(k_toggle_emit_seg, dim3(grid_for(NE)), dim3(256), 0, st, B.evkey,
-                           B.evpay, tl, ptoff, NE, rxbits, B.xbits, tkey, tpoly,
-                           rows ? rowoff : nullptr, rowcnt, rb);
-        HIP_OK(hipGetLastError());
-        B.release(tl);
-        B.release(ptot);
-        B.release(ptoff);
-    } else {
-        B.release(nb);
-        B.release(nc);
-        RC(radix_sort_u64_ws(&B.evkey, &B.evpay, NE, pbits + rxbits, B.ws));
-        int64_t *cex = nullptr;
-        RC(B.alloc(&cex, NE));
-        RC(B.alloc(&tf, NE));
-        hipLaunchKernelGGL(k_ev_values, dim3(grid_for(NE)), dim3(256), 0, st, B.evpay, NE, cex);
-        HIP_OK(hipGetLastError());
-        RC(scan_exclusive_i64(cex, cex, NE, tot, st, &B.ws));
-        hipLaunchKernelGGL(k_toggle_flags, dim3(grid_for(NE)), dim3(256), 0, st, B.evkey,
-                           B.evpay, cex, NE, B.xbits, tf, err);
-        HIP_OK(hipGetLastError());
-        RC(scan_exclusive_i64(tf, tf, NE, tot, st, &B.ws));
-        RC(fetch());
-        NT = hsc[8];
-        herr = (int)(uint32_t)hsc[0];
-        if (herr || (NT & 1)) return SBA_EDEVICE;
-        B.release(cex);
-        RC(B.alloc(&tkey, std::max<int64_t>(NT, 1)));
-        RC(B.alloc(&tpoly, std::max<int64_t>(NT, 1)));
-        hipLaunchKernelGGL(k_toggle_emit, dim3(grid_for(NE)), dim3(256), 0, st, B.evkey, tf, NE,
-                           NT, rxbits, tkey, tpoly);
-        HIP_OK(hipGetLastError());
-    }
-    if (tf) B.release(tf);
+    B.release(nb);
+    B.release(nc);
+    RC(radix_sort_u64_ws(&B.evkey, &B.evpay, NE, pbits + rxbits, B.ws));
+    int64_t *cex = nullptr;
+    RC(B.alloc(&cex, NE));
+    RC(B.alloc(&tf, NE));
+    hipLaunchKernelGGL(k_ev_values, dim3(grid_for(NE)), dim3(256), 0, st, B.evpay, NE, cex);
+    HIP_OK(hipGetLastError());
+    RC(scan_exclusive_i64(cex, cex, NE, tot, st, &B.ws));
+    hipLaunchKernelGGL(k_toggle_flags, dim3(grid_for(NE)), dim3(256), 0, st, B.evkey,
+                       B.evpay, cex, NE, B.xbits, tf, err);
+    HIP_OK(hipGetLastError());
+    RC(scan_exclusive_i64(tf, tf, NE, tot, st, &B.ws));
+    RC(fetch());
+    NT = hsc[8];
+    herr = (int)(uint32_t)hsc[0];
+    if (herr || (NT & 1)) return SBA_EDEVICE;
+    B.release(cex);
+    RC(B.alloc(&tkey, std::max<int64_t>(NT, 1)));
+    RC(B.alloc(&tpoly, std::max<int64_t>(NT, 1)));
+    hipLaunchKernelGGL(k_toggle_emit, dim3(grid_for(NE)), dim3(256), 0, st, B.evkey, tf, NE,
+                       NT, rxbits, tkey, tpoly);
+    HIP_OK(hipGetLastError());
+    B.release(tf);
     B.release(B.evkey);
     B.evkey = nullptr;
     B.release(B.evpay);
@@ -1730,18 +1034,7 @@ int build_segments(const sba_polygons *polys, int64_t eps, hipStream_t st, sba_h
     RC(B.alloc(&segc, NP));
     RC(B.alloc(&mm, NP));
     if (NT == 0) HIP_OK(hipMemsetAsync(diff, 0, sizeof(int64_t) * (NP + 1), st));
-    if (NT && rows) {
-        int64_t *rank = nullptr;
-        RC(B.alloc(&rank, NT));
-        hipLaunchKernelGGL(k_row_pieces, dim3((unsigned)((gh + ROW_WAVES - 1) / ROW_WAVES)),
-                           dim3(64 * ROW_WAVES), 0, st, rb, rowoff, gh, B.xbits, NT, E, rank,
-                           diff);
-        HIP_OK(hipGetLastError());
-        hipLaunchKernelGGL(k_interval_span, dim3(grid_for(NI)), dim3(256), 0, st, rank, NI, ika,
-                           xoff);
-        HIP_OK(hipGetLastError());
-        B.release(rank);
-    } else if (NT) {
+    if (NT) {
         if (NT >= ((int64_t)1 << 32)) return SBA_ELIMIT;
         // sorted with each toggle's slot as payload, so that every toggle
         // learns its index in E without a search (the toggle keys are not
@@ -1766,10 +1059,6 @@ int build_segments(const sba_polygons *polys, int64_t eps, hipStream_t st, sba_h
         B.release(rank);
     }
     B.release(pos);
-    B.release(rb);
-    B.release(rowoff);
-    B.release(rowcnt);
-    g_build_paths_last = (seg_path ? 1 : 0) | (rows ? 2 : 0);
     RC(scan_exclusive_i64(diff, dex, NP, tot + 2, st, &B.ws));
     hipLaunchKernelGGL(k_piece_classify, dim3(grid_for(NP)), dim3(256), 0, st, dex, diff, NP, segc,
                        mm, err);
@@ -1815,99 +1104,32 @@ int build_segments(const sba_polygons *polys, int64_t eps, hipStream_t st, sba_h
     hipLaunchKernelGGL(k_seg_row_off, dim3(grid_for(gh + 1)), dim3(256), 0, st, seg_row, NS, gh,
                        cs);
     HIP_OK(hipGetLastError());
-    B.seg_row_off = cs;
+    B.seg_beg = cs;
+    B.seg_end = cs + 1;
     for (void *p : {(void *)tkey, (void *)tpoly, (void *)E, (void *)ika, (void *)xoff,
                     (void *)diff, (void *)dex, (void *)segc, (void *)mm, (void *)seg_row,
                     (void *)sid, (void *)fill})
         B.release(p);
 
-    // 5: deduplicate the sets of multi-polygon segments
-    h->n_sets = 0;
-    h->n_set_ids = 0;
-    bool set_path = false;
+    // 5: the sets of multi-polygon segments
     if (NM > 0) {
+        SetStage S{};
         uint64_t *mkey = nullptr;
         uint32_t *mval = nullptr;
         RC(B.alloc(&mkey, NM));
         RC(B.alloc(&mval, NM));
-        const int fb = std::min(pbits + 1, 21);  // ids + 1 < 2^21
-        const int kbits = std::max(3 * fb + 1, bits_for(((uint64_t)1 << (3 * fb)) | (uint64_t)NM));
-        if (kbits > 64) return SBA_ELIMIT;
-        hipLaunchKernelGGL(k_multi_keys, dim3(grid_for(NM)), dim3(256), 0, st, multi_mem, NM, NMEM,
-                           mem_ids, fb, mkey, mval);
+        RC(B.alloc(&S.memloc, NS));
+        S.fb = std::min(pbits + 1, 21);  // ids + 1 < 2^21
+        S.mem_ids = mem_ids;
+        hipLaunchKernelGGL(k_multi_keys, dim3(grid_for(NM)), dim3(256), 0, st, multi_mem, multi_seg,
+                           NM, NMEM, mem_ids, S.fb, mkey, mval, S.memloc);
         HIP_OK(hipGetLastError());
-        // sizes are bounded by the multi segments (NM sets, NMEM ids), so the
-        // set table is laid out before its counts reach the host
-        RC(handle_alloc(h, &h->set_off, NM + 1));
-        RC(handle_alloc(h, &h->set_ids, NMEM));
-        if (kbits <= 31 && !(g_build_paths_off.load() & 4)) {
-            // distinct keys through a hash table, sorted by one workgroup
-            int hb = 1;
-            while (((int64_t)1 << hb) < 2 * NM) hb++;
-            if (hb > 31) return SBA_ELIMIT;
-            uint32_t *tab = nullptr, *rank = nullptr, *list = nullptr;
-            RC(B.alloc(&tab, (int64_t)1 << hb));
-            RC(B.alloc(&rank, (int64_t)1 << hb));
-            RC(B.alloc(&list, SET_CAP));
-            HIP_OK(hipMemsetAsync(tab, 0xff, sizeof(uint32_t) << hb, st));
-            unsigned long long *nd = (unsigned long long *)(B.sc + SC_SET_N);
-            unsigned long long *nids = (unsigned long long *)(B.sc + SC_SET_IDS);
-            hipLaunchKernelGGL(k_set_insert, dim3(grid_for(NM)), dim3(256), 0, st, mkey, NM, tab, hb,
-                               list, nd);
-            HIP_OK(hipGetLastError());
-            constexpr int lds = (2 * SET_CAP + SEG_WAVES * SEG_RADIX) * (int)sizeof(uint32_t);
-            (void)hipFuncSetAttribute((const void *)k_set_table,
-                                      hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-            (void)hipGetLastError();
-            hipLaunchKernelGGL(k_set_table, dim3(1), dim3(SEG_BLOCK), lds, st, list, nd, tab, hb,
-                               kbits, fb, multi_mem, NM, NMEM, mem_ids, rank, h->set_off,
-                               h->set_ids, nids);
-            HIP_OK(hipGetLastError());
-            hipLaunchKernelGGL(k_set_codes, dim3(grid_for(NM)), dim3(256), 0, st, mkey, NM, nd, tab,
-                               hb, rank, multi_seg, B.seg_code);
-            HIP_OK(hipGetLastError());
-            RC(B.ws.read(hsc, B.sc, sizeof(hsc)));
-            RC(B.ws.sync());
-            B.release(tab);
-            B.release(rank);
-            B.release(list);
-            if (hsc[SC_SET_N] <= SET_CAP) {
-                set_path = true;
-                h->n_sets = hsc[SC_SET_N];
-                h->n_set_ids = hsc[SC_SET_IDS];
-            }
-        }
-        if (!set_path) {
-            // all keys through the global radix sort
-            int64_t *g = nullptr, *set_sz = nullptr;
-            RC(B.alloc(&g, NM + 1));
-            RC(radix_sort_u64_ws(&mkey, &mval, NM, kbits, B.ws));
-            hipLaunchKernelGGL(k_flag_new, dim3(grid_for(NM)), dim3(256), 0, st, mkey, NM, g);
-            HIP_OK(hipGetLastError());
-            RC(scan_exclusive_i64(g, g, NM, tot, st, &B.ws));
-            RC(B.alloc(&set_sz, NM + 1));
-            HIP_OK(hipMemsetAsync(set_sz, 0, sizeof(int64_t) * (NM + 1), st));
-            hipLaunchKernelGGL(k_set_sizes, dim3(grid_for(NM)), dim3(256), 0, st, mkey, mval, g, NM,
-                               multi_mem, NM, NMEM, set_sz);
-            HIP_OK(hipGetLastError());
-            RC(scan_exclusive_i64(set_sz, h->set_off, NM, h->set_off + NM, st, &B.ws));
-            hipLaunchKernelGGL(k_set_fill, dim3(grid_for(NM)), dim3(256), 0, st, mkey, mval, g, NM,
-                               multi_mem, NM, NMEM, mem_ids, h->set_off, h->set_ids, multi_seg,
-                               B.seg_code);
-            HIP_OK(hipGetLastError());
-            int64_t nids = 0;
-            RC(B.ws.read(hsc, B.sc, sizeof(hsc)));
-            RC(B.ws.read(&nids, h->set_off + NM, sizeof(int64_t)));
-            RC(B.ws.sync());
-            h->n_sets = hsc[8];
-            h->n_set_ids = nids;
-            B.release(g);
-            B.release(set_sz);
-        }
-        B.release(mkey);
-        B.release(mval);
+        bool done = false;
+        if (!(paths_off & 4)) RC(sets_hash_list(S, B, h, mkey, mval, NM, NMEM, NS, st, &done));
+        if (!done) RC(sets_from_list(S, B, h, mkey, mval, NM, NMEM, NS, st));
+        if (S.one_workgroup) g_build_paths_last = g_build_paths_last.load() | 4;
+        sets_release(S, B);
     }
-    g_build_paths_last = g_build_paths_last.load() | (set_path ? 4 : 0);
     B.release(multi_seg);
     B.release(multi_mem);
     B.release(mem_ids);
@@ -1924,7 +1146,7 @@ static void launch_classify(const BuildState &B, const sba_handle *h, const int6
                             int sl, int64_t n_sq, uint32_t *code, int64_t *mixed, hipStream_t st)
 {
     hipLaunchKernelGGL(k_square_classify<G>, dim3(grid_for(n_sq * G)), dim3(256), 0, st,
-                       B.seg_row_off, B.seg_x0, B.seg_x1, B.seg_code, h->gw, h->gh, mt, tl, sl,
+                       B.seg_beg, B.seg_end, B.seg_x0, B.seg_x1, B.seg_code, h->gw, h->gh, mt, tl, sl,
                        h->tw, n_sq, code, mixed);
 }
 
@@ -2082,25 +1304,15 @@ int build_grid(sba_handle *h, BuildState &B, int tile_log2, int sub_log2, hipStr
         RC(handle_alloc(h, &h->blocks16, std::max<int64_t>(cells, 1)));
         if (nfine)
             hipLaunchKernelGGL(k_block_fill<uint16_t>, dim3(grid_for(threads)), dim3(256), 0, st,
-                               B.seg_row_off, B.seg_x0, B.seg_x1, B.seg_code, h->gw, h->gh, fine_sq,
+                               B.seg_beg, B.seg_end, B.seg_x0, B.seg_x1, B.seg_code, h->gw, h->gh, fine_sq,
                                nfine, fine_mt, tl, sl, h->tw, fine_log2, np, h->blocks16);
     } else {
         RC(handle_alloc(h, &h->blocks, std::max<int64_t>(cells, 1)));
         if (nfine)
             hipLaunchKernelGGL(k_block_fill<uint32_t>, dim3(grid_for(threads)), dim3(256), 0, st,
-                               B.seg_row_off, B.seg_x0, B.seg_x1, B.seg_code, h->gw, h->gh, fine_sq,
+                               B.seg_beg, B.seg_end, B.seg_x0, B.seg_x1, B.seg_code, h->gw, h->gh, fine_sq,
                                nfine, fine_mt, tl, sl, h->tw, fine_log2, np, h->blocks);
     }
-    HIP_OK(hipGetLastError());
-    return 0;
-}
-
-int segments_lookup(const BuildState &B, const sba_handle *h, const int64_t *ij, int64_t n,
-                    uint32_t *out, hipStream_t st)
-{
-    if (n <= 0) return 0;
-    hipLaunchKernelGGL(k_lookup_ij, dim3(grid_for(n)), dim3(256), 0, st, B.seg_row_off, B.seg_x0,
-                       B.seg_x1, B.seg_code, h->gi0, h->gj0, h->gw, h->gh, ij, n, out);
     HIP_OK(hipGetLastError());
     return 0;
 }

@@ -9,11 +9,7 @@
 
 #define SC_SLOTS 32
 #define SC_READ 20
-// slot of the largest polygon's event count (read with the edge totals)
-#define SC_SEG_MAX 14
-// slot of the largest row's toggle count (read with the toggle total)
-#define SC_ROW_MAX 15
-// slots of the set table path: distinct sets, total member ids
+// slots of the set table: distinct sets, total member ids
 #define SC_SET_N 18
 #define SC_SET_IDS 19
 
@@ -51,18 +47,28 @@ struct BuildState {
     int64_t NB = 0;              // boundary intervals (events [0, 2 NB) until sorted)
     uint64_t *evkey = nullptr;
     uint32_t *evpay = nullptr;
-    // row segments of constant polygon set
+    // row segments of constant polygon set: row r's are [seg_beg[r], seg_end[r])
     int64_t NS = 0;
-    int64_t *seg_row_off = nullptr;  // [gh+1]
+    int64_t *seg_beg = nullptr, *seg_end = nullptr;
     int32_t *seg_x0 = nullptr, *seg_x1 = nullptr;
     uint32_t *seg_code = nullptr;
-    // Hilbert layout: unique keys of boundary cells
+    // Hilbert layout: unique keys of boundary cells, ascending (bkeys, or
+    // bkeys32 with each cell's segment in bseg from the row sweep, which
+    // takes 32-bit keys where they fit)
     int (*on_boundary_events)(BuildState &, sba_handle *, hipStream_t) = nullptr;
     uint64_t *bkeys = nullptr;
+    uint32_t *bkeys32 = nullptr, *bseg = nullptr;
     int64_t nbkeys = 0;
 };
 
 int build_segments(const sba_polygons *polys, int64_t eps, hipStream_t st, sba_handle *h,
                    BuildState &B, bool need_boundary_cells);
+// segments and sets row by row in LDS (rows.hip); *taken: done, else the
+// caller takes the global sorts; *one: the sets were numbered by one workgroup
+int rows_coverage(const sba_polygons *polys, const int4 *bbox, int64_t nv,
+                  hipStream_t st, sba_handle *h, BuildState &B, int paths_off, bool *taken,
+                  bool *one);
 int hilbert_prepare(BuildState &B, sba_handle *h);
+// the key grid's level (SBA_ELIMIT above 21)
+int hilbert_level(const BuildState &B, sba_handle *h);
 int hilbert_finish(BuildState &B, sba_handle *h, const sba_build_opts &o, hipStream_t st);

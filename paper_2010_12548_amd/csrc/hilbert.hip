@@ -126,16 +126,22 @@ static int hilbert_boundary_cells(BuildState &B, sba_handle *h, hipStream_t st)
     return 0;
 }
 
+int hilbert_level(const BuildState &B, sba_handle *h)
+{
+    // key grid: the stored cell box, padded to 2^L x 2^L
+    int L = 1;
+    while (((int64_t)1 << L) < std::max(h->gw, h->gh)) L++;
+    if (B.key_level > 0) L = B.key_level;  // the box was cut to fit it
+    if (L > 21) return SBA_ELIMIT;
+    h->level = L;
+    return 0;
+}
+
 int hilbert_prepare(BuildState &B, sba_handle *h)
 {
     (void)h;
     B.on_boundary_events = [](BuildState &b, sba_handle *hh, hipStream_t st) -> int {
-        // key grid: the stored cell box, padded to 2^L x 2^L
-        int L = 1;
-        while (((int64_t)1 << L) < std::max(hh->gw, hh->gh)) L++;
-        if (b.key_level > 0) L = b.key_level;  // the box was cut to fit it
-        if (L > 21) return SBA_ELIMIT;
-        hh->level = L;
+        RC(hilbert_level(b, hh));
         return hilbert_boundary_cells(b, hh, st);
     };
     return 0;
@@ -143,86 +149,184 @@ int hilbert_prepare(BuildState &B, sba_handle *h)
 
 // ---------------------------------------------------------------- runs
 
-__device__ __forceinline__ uint32_t code_of_cell(const int64_t *seg_row_off, const int32_t *seg_x0,
-                                                 const int32_t *seg_x1, const uint32_t *seg_code,
-                                                 int64_t gi0, int64_t gj0, int64_t gw, int64_t gh,
-                                                 int64_t i, int64_t j)
-{
-    int64_t x = i - gi0, r = j - gj0;
-    if (x < 0 || r < 0 || x >= gw || r >= gh) return 0;
-    int64_t lo = seg_row_off[r], hi = seg_row_off[r + 1], a = lo;
-    while (lo < hi) {
-        int64_t mid = (lo + hi) >> 1;
-        if (seg_x0[mid] <= (int32_t)x) lo = mid + 1; else hi = mid;
-    }
-    if (lo > a && (int32_t)x < seg_x1[lo - 1]) return seg_code[lo - 1];
-    return 0;
-}
-
 struct SegView {
-    const int64_t *row_off;
+    const int64_t *beg, *end;
     const int32_t *x0, *x1;
     const uint32_t *code;
-    int64_t gi0, gj0, gw, gh;
+    int64_t gw, gh;
 };
 
+// code of the cell with the key: the last segment of its row that starts at
+// or before it, if it reaches it
 __device__ __forceinline__ uint32_t code_of_key(const SegView &S, int L, uint64_t key)
 {
-    uint32_t i, j;
-    hilbert_cell(L, key, &i, &j);
-    return code_of_cell(S.row_off, S.x0, S.x1, S.code, S.gi0, S.gj0, S.gw, S.gh, S.gi0 + i,
-                        S.gj0 + j);
-}
-
-// candidate run starts: every boundary key, the key after it when a gap
-// follows, and key 0 when the first boundary key is not 0
-__global__ void k_cand_counts(const uint64_t *bk, int64_t nb, uint64_t total, int64_t *cnt)
-{
-    int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= nb) return;
-    uint64_t next = (t + 1 < nb) ? bk[t + 1] : total;
-    cnt[t] = 1 + ((next > bk[t] + 1) ? 1 : 0);
-}
-
-__global__ void k_cand_write(const uint64_t *bk, int64_t nb, uint64_t total, const int64_t *off,
-                             int64_t lead, SegView S, int L, uint64_t *ckey, uint32_t *ccode)
-{
-    int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t == 0 && lead) {
-        ckey[0] = 0;
-        ccode[0] = code_of_key(S, L, 0);
+    uint32_t x, r;
+    hilbert_cell(L, key, &x, &r);
+    if (x >= S.gw || r >= S.gh) return 0;
+    const int64_t a = S.beg[r];
+    int64_t lo = a, hi = S.end[r];
+    while (lo < hi) {
+        const int64_t mid = (lo + hi) >> 1;
+        if (S.x0[mid] <= (int32_t)x) lo = mid + 1; else hi = mid;
     }
-    if (t >= nb) return;
-    int64_t o = lead + off[t];
-    uint64_t k = bk[t];
-    ckey[o] = k;
-    ccode[o] = code_of_key(S, L, k);
-    uint64_t next = (t + 1 < nb) ? bk[t + 1] : total;
-    if (next > k + 1) {
-        ckey[o + 1] = k + 1;
-        ccode[o + 1] = code_of_key(S, L, k + 1);
+    return lo > a && (int32_t)x < S.x1[lo - 1] ? S.code[lo - 1] : 0;
+}
+
+// Candidate run starts: key 0, every boundary key, and the key after one
+// when a gap follows.  A candidate whose code differs from the one before it
+// starts a run.
+#define RUN_BLOCK 256
+#define NO_GAP 0xffffffffu
+
+// codes of boundary key t and of the gap after it
+template <typename K>
+__device__ __forceinline__ uint32_t gap_code(const K *bk, int64_t nb, uint64_t total, int64_t t,
+                                             const SegView &S, int L)
+{
+    const uint64_t next = t + 1 < nb ? (uint64_t)bk[t + 1] : total;
+    return next > (uint64_t)bk[t] + 1 ? code_of_key(S, L, (uint64_t)bk[t] + 1) : NO_GAP;
+}
+
+template <typename K>
+__device__ __forceinline__ uint32_t bkey_code(const K *bk, const uint32_t *bseg, int64_t t,
+                                              const SegView &S, int L)
+{
+    if (!bseg) return code_of_key(S, L, (uint64_t)bk[t]);
+    const uint32_t q = bseg[t];
+    return q == 0xffffffffu ? 0u : S.code[q];
+}
+
+// bit 0: boundary key t starts a run, bit 1: the gap after it does
+__device__ __forceinline__ uint32_t run_bits(uint32_t c, uint32_t g, uint32_t prev)
+{
+    return (c != prev ? 1u : 0u) | (g != NO_GAP && g != c ? 2u : 0u);
+}
+
+// codes, and the workgroup's number of run starts
+template <typename K>
+__global__ __launch_bounds__(RUN_BLOCK) void k_run_count(const K *bk, const uint32_t *bseg,
+                                                         int64_t nb, uint64_t total, SegView S,
+                                                         int L, uint32_t *ccode, uint32_t *gcode,
+                                                         int64_t *cnt)
+{
+    __shared__ uint32_t last[RUN_BLOCK];
+    __shared__ uint32_t sum;
+    const int64_t t = (int64_t)blockIdx.x * RUN_BLOCK + threadIdx.x;
+    uint32_t c = 0, g = NO_GAP;
+    if (threadIdx.x == 0) sum = 0;
+    if (t < nb) {
+        c = bkey_code(bk, bseg, t, S, L);
+        g = gap_code(bk, nb, total, t, S, L);
+        ccode[t] = c;
+        gcode[t] = g;
+        last[threadIdx.x] = g != NO_GAP ? g : c;
+    }
+    __syncthreads();
+    uint32_t m = 0;
+    if (t < nb) {
+        uint32_t prev;
+        if (threadIdx.x) {
+            prev = last[threadIdx.x - 1];
+        } else if (t == 0) {
+            prev = code_of_key(S, L, 0);
+        } else {
+            const uint32_t pg = gap_code(bk, nb, total, t - 1, S, L);
+            prev = pg != NO_GAP ? pg : bkey_code(bk, bseg, t - 1, S, L);
+        }
+        m = (uint32_t)__popc(run_bits(c, g, prev));
+    }
+    for (int o = 32; o > 0; o >>= 1) m += (uint32_t)__shfl_xor((int)m, o, 64);
+    if ((threadIdx.x & 63) == 0) atomicAdd(&sum, m);
+    __syncthreads();
+    if (threadIdx.x == 0) cnt[blockIdx.x] = sum;
+}
+
+// run 0 starts at key 0; off: exclusive scan of k_run_count's numbers
+template <typename K>
+__global__ __launch_bounds__(RUN_BLOCK) void k_run_write(const K *bk, int64_t nb, SegView S, int L,
+                                                         const uint32_t *ccode,
+                                                         const uint32_t *gcode, const int64_t *off,
+                                                         uint64_t *starts, uint32_t *starts32,
+                                                         uint32_t *rcode)
+{
+    __shared__ uint32_t wsum[RUN_BLOCK / 64];
+    const int64_t t = (int64_t)blockIdx.x * RUN_BLOCK + threadIdx.x;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    uint32_t c = 0, g = NO_GAP, bits = 0;
+    if (t < nb) {
+        c = ccode[t];
+        g = gcode[t];
+        uint32_t prev;
+        if (t == 0) {
+            prev = code_of_key(S, L, 0);
+        } else {
+            const uint32_t pg = gcode[t - 1];
+            prev = pg != NO_GAP ? pg : ccode[t - 1];
+        }
+        bits = run_bits(c, g, prev);
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        starts[0] = 0;
+        if (starts32) starts32[0] = 0;
+        rcode[0] = code_of_key(S, L, 0);
+    }
+    const uint32_t m = (uint32_t)__popc(bits);
+    uint32_t incl = m;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t u = (uint32_t)__shfl_up((int)incl, o, 64);
+        if (lane >= o) incl += u;
+    }
+    if (lane == 63) wsum[w] = incl;
+    __syncthreads();
+    if (!bits) return;
+    int64_t o = 1 + off[blockIdx.x] + incl - m;
+    for (int k = 0; k < w; k++) o += wsum[k];
+    if (bits & 1u) {
+        starts[o] = (uint64_t)bk[t];
+        if (starts32) starts32[o] = (uint32_t)bk[t];
+        rcode[o] = c;
+        o++;
+    }
+    if (bits & 2u) {
+        starts[o] = (uint64_t)bk[t] + 1;
+        if (starts32) starts32[o] = (uint32_t)bk[t] + 1u;
+        rcode[o] = g;
     }
 }
 
-__global__ void k_run_flags(const uint32_t *ccode, int64_t n, int64_t *flag)
+template <typename K>
+static int write_runs(BuildState &B, sba_handle *h, const K *bk, hipStream_t st)
 {
-    int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= n) return;
-    flag[t] = (t == 0 || ccode[t] != ccode[t - 1]) ? 1 : 0;
-}
-
-__global__ void k_run_write(const uint64_t *ckey, const uint32_t *ccode, int64_t n,
-                            const int64_t *pos, uint64_t *starts, uint32_t *starts32,
-                            uint32_t *rcode)
-{
-    int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= n) return;
-    if (t == 0 || ccode[t] != ccode[t - 1]) {
-        int64_t g = pos[t];
-        starts[g] = ckey[t];
-        if (starts32) starts32[g] = (uint32_t)ckey[t];
-        rcode[g] = ccode[t];
-    }
+    const int L = h->level;
+    const uint64_t total = (uint64_t)1 << (2 * L);
+    const int64_t nb = B.nbkeys, blocks = std::max<int64_t>((nb + RUN_BLOCK - 1) / RUN_BLOCK, 1);
+    const SegView S{B.seg_beg, B.seg_end, B.seg_x0, B.seg_x1, B.seg_code, h->gw, h->gh};
+    uint32_t *ccode = nullptr, *gcode = nullptr;
+    int64_t *cnt = nullptr;
+    RC(B.alloc(&ccode, nb));
+    RC(B.alloc(&gcode, nb));
+    RC(B.alloc(&cnt, blocks + 1));
+    hipLaunchKernelGGL(k_run_count<K>, dim3((unsigned)blocks), dim3(RUN_BLOCK), 0, st, bk, B.bseg,
+                       nb, total, S, L, ccode, gcode, cnt);
+    HIP_OK(hipGetLastError());
+    RC(scan_exclusive_i64(cnt, cnt, blocks, cnt + blocks, st, &B.ws));
+    int64_t nr = 0;
+    RC(B.ws.read(&nr, cnt + blocks, sizeof(int64_t)));
+    RC(B.ws.sync());
+    nr += 1;  // key 0's run
+    if (nr >= ((int64_t)1 << 31)) return SBA_ELIMIT;
+    h->n_runs = nr;
+    RC(handle_alloc(h, &h->starts, nr));
+    RC(handle_alloc(h, &h->run_code, nr));
+    if (2 * L <= 32) RC(handle_alloc(h, &h->starts32, nr));
+    hipLaunchKernelGGL(k_run_write<K>, dim3((unsigned)blocks), dim3(RUN_BLOCK), 0, st, bk, nb, S, L,
+                       ccode, gcode, cnt, h->starts, h->starts32, h->run_code);
+    HIP_OK(hipGetLastError());
+    B.release(ccode);
+    B.release(gcode);
+    B.release(cnt);
+    return 0;
 }
 
 // ---------------------------------------------------------------- learned index
@@ -381,49 +485,9 @@ int hilbert_finish(BuildState &B, sba_handle *h, const sba_build_opts &o, hipStr
 {
     const int L = h->level;
     const uint64_t total = (uint64_t)1 << (2 * L);
-    const int64_t nb = B.nbkeys;
-    const int64_t lead = 1;  // key 0 always opens a run (a boundary key 0 repeats it)
-    SegView S{B.seg_row_off, B.seg_x0, B.seg_x1, B.seg_code, h->gi0, h->gj0, h->gw, h->gh};
-    int64_t *cnt = nullptr, *tot = nullptr;
-    RC(B.alloc(&cnt, nb + 1));
-    RC(B.alloc(&tot, 1));
-    if (nb)
-        hipLaunchKernelGGL(k_cand_counts, dim3(grid_for(nb)), dim3(256), 0, st, B.bkeys, nb, total,
-                           cnt);
-    HIP_OK(hipGetLastError());
-    RC(scan_exclusive_i64(cnt, cnt, nb, tot, st, &B.ws));
-    int64_t nc = 0;
-    if (nb) {
-        RC(B.ws.read(&nc, tot, sizeof(int64_t)));
-        RC(B.ws.sync());
-    }
-    nc += lead;
-    uint64_t *ckey = nullptr;
-    uint32_t *ccode = nullptr;
-    RC(B.alloc(&ckey, nc));
-    RC(B.alloc(&ccode, nc));
-    // a boundary key equal to 0 writes over the leading candidate with the same values
-    hipLaunchKernelGGL(k_cand_write, dim3(grid_for(nb > 0 ? nb : 1)), dim3(256), 0, st, B.bkeys, nb,
-                       total, cnt, lead, S, L, ckey, ccode);
-    HIP_OK(hipGetLastError());
-    int64_t *flag = nullptr;
-    RC(B.alloc(&flag, nc + 1));
-    hipLaunchKernelGGL(k_run_flags, dim3(grid_for(nc)), dim3(256), 0, st, ccode, nc, flag);
-    HIP_OK(hipGetLastError());
-    RC(scan_exclusive_i64(flag, flag, nc, tot, st, &B.ws));
-    int64_t nr = 0;
-    RC(B.ws.read(&nr, tot, sizeof(int64_t)));
-    RC(B.ws.sync());
-    if (nr >= ((int64_t)1 << 31)) return SBA_ELIMIT;
-    h->n_runs = nr;
-    RC(handle_alloc(h, &h->starts, nr));
-    RC(handle_alloc(h, &h->run_code, nr));
-    if (2 * L <= 32) {
-        RC(handle_alloc(h, &h->starts32, nr));
-    }
-    hipLaunchKernelGGL(k_run_write, dim3(grid_for(nc)), dim3(256), 0, st, ckey, ccode, nc, flag,
-                       h->starts, h->starts32, h->run_code);
-    HIP_OK(hipGetLastError());
+    if (B.bkeys32) RC(write_runs<uint32_t>(B, h, B.bkeys32, st));
+    else RC(write_runs<uint64_t>(B, h, B.bkeys, st));
+    const int64_t nr = h->n_runs;
 
     if (o.search == SBA_SEARCH_LEARNED) {
         if (2 * L > 32) return SBA_ELIMIT;  // leaves store 32-bit key bases

@@ -310,8 +310,8 @@ int scan_exclusive_i64_multi(int m, const int64_t *const *in, int64_t *const *ou
 // here: each row scan below leaves its digit's total, and the scatter adds
 // the totals of the lower digits itself, so the pass needs no device-wide
 // atomics and no zeroed counters.
-template <int ROUNDS, int TPW, int RB>
-__global__ __launch_bounds__(RS_BLOCK) void k_rs_hist(const uint64_t *keys, int64_t n, int shift,
+template <typename K, int ROUNDS, int TPW, int RB>
+__global__ __launch_bounds__(RS_BLOCK) void k_rs_hist(const K *keys, int64_t n, int shift,
                                                       int64_t *hist, int64_t nblocks, int64_t span)
 {
     constexpr int RS_TILE = RS_BLOCK * ROUNDS, RADIX = 1 << RB;
@@ -418,9 +418,9 @@ int rs_offsets_launch(int64_t *hist, int64_t nblocks, const unsigned long long *
     return 0;
 }
 
-template <bool HAS_VALS, int ROUNDS, int RB>
-__global__ __launch_bounds__(RS_BLOCK) void k_rs_scatter(const uint64_t *keys, const uint32_t *vals,
-                                                         uint64_t *okeys, uint32_t *ovals,
+template <typename K, bool HAS_VALS, int ROUNDS, int RB>
+__global__ __launch_bounds__(RS_BLOCK) void k_rs_scatter(const K *keys, const uint32_t *vals,
+                                                         K *okeys, uint32_t *ovals,
                                                          int64_t n, int shift,
                                                          const int64_t *goff, int64_t nblocks,
                                                          const int64_t *rowtot)
@@ -433,7 +433,7 @@ __global__ __launch_bounds__(RS_BLOCK) void k_rs_scatter(const uint64_t *keys, c
     // output position of the block's first key of each digit, less that
     // key's place in the staged tile
     __shared__ int64_t dbase[RADIX];
-    __shared__ uint64_t skeys[RS_TILE];
+    __shared__ K skeys[RS_TILE];
     __shared__ uint32_t svals[HAS_VALS ? RS_TILE : 1];
 
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -461,14 +461,14 @@ __global__ __launch_bounds__(RS_BLOCK) void k_rs_scatter(const uint64_t *keys, c
     const int64_t tbase = (int64_t)blockIdx.x * RS_TILE;
     const int64_t wbase = tbase + (int64_t)w * (64 * RS_ROUNDS);
     const uint64_t lt = (lane == 0) ? 0ull : ((~0ull) >> (64 - lane));
-    uint64_t kk[RS_ROUNDS];
+    K kk[RS_ROUNDS];
     uint32_t vv[RS_ROUNDS];
     uint32_t loc[RS_ROUNDS];
 #pragma unroll
     for (int q = 0; q < RS_ROUNDS; q++) {
         int64_t idx = wbase + q * 64 + lane;
         bool valid = idx < n;
-        uint64_t key = valid ? keys[idx] : 0;
+        const K key = valid ? keys[idx] : (K)0;
         kk[q] = key;
         if (HAS_VALS) vv[q] = valid ? vals[idx] : 0;
         uint32_t d = (uint32_t)(key >> shift) & DMASK;
@@ -525,7 +525,7 @@ __global__ __launch_bounds__(RS_BLOCK) void k_rs_scatter(const uint64_t *keys, c
     int64_t tn = n - tbase;
     if (tn > RS_TILE) tn = RS_TILE;
     for (int i = threadIdx.x; i < tn; i += RS_BLOCK) {
-        uint64_t key = skeys[i];
+        const K key = skeys[i];
         uint32_t d = (uint32_t)(key >> shift) & DMASK;
         int64_t g = dbase[d] + i;
         okeys[g] = key;
@@ -545,43 +545,43 @@ static int rs_digit_bits(int64_t n, int bits)
 }
 
 // one pass over digit (keys >> shift) & (2^RB - 1)
-template <int ROUNDS, int RB>
-static int rs_pass_t(const uint64_t *ka, const uint32_t *va, uint64_t *kb, uint32_t *vb, int64_t n,
-                     int shift, int64_t *goff, int64_t nblocks, int64_t *rowtot, hipStream_t st)
+template <typename K, int ROUNDS, int RB>
+static int rs_pass_t(const K *ka, const uint32_t *va, K *kb, uint32_t *vb, int64_t n, int shift,
+                     int64_t *goff, int64_t nblocks, int64_t *rowtot, hipStream_t st)
 {
     // tiles per counting workgroup: one while there are at most 2048 tiles
     // (every tile its own workgroup), else 16 keys a thread and at most about
     // 2048 workgroups
     if (nblocks <= 2048) {
-        hipLaunchKernelGGL((k_rs_hist<ROUNDS, 1, RB>), dim3((unsigned)nblocks), dim3(RS_BLOCK), 0,
-                           st, ka, n, shift, goff, nblocks, (int64_t)1);
+        hipLaunchKernelGGL((k_rs_hist<K, ROUNDS, 1, RB>), dim3((unsigned)nblocks), dim3(RS_BLOCK),
+                           0, st, ka, n, shift, goff, nblocks, (int64_t)1);
     } else {
         constexpr int TPW = 16 / ROUNDS;
         const int64_t span = TPW * ((nblocks + TPW * 2048 - 1) / (TPW * 2048));
-        hipLaunchKernelGGL((k_rs_hist<ROUNDS, TPW, RB>),
+        hipLaunchKernelGGL((k_rs_hist<K, ROUNDS, TPW, RB>),
                            dim3((unsigned)((nblocks + span - 1) / span)), dim3(RS_BLOCK), 0, st, ka,
                            n, shift, goff, nblocks, span);
     }
     hipLaunchKernelGGL(k_rs_rowscan, dim3(1u << RB), dim3(RS_BLOCK), 0, st, goff, nblocks, rowtot);
     if (va)
-        hipLaunchKernelGGL((k_rs_scatter<true, ROUNDS, RB>), dim3((unsigned)nblocks),
+        hipLaunchKernelGGL((k_rs_scatter<K, true, ROUNDS, RB>), dim3((unsigned)nblocks),
                            dim3(RS_BLOCK), 0, st, ka, va, kb, vb, n, shift, goff, nblocks, rowtot);
     else
-        hipLaunchKernelGGL((k_rs_scatter<false, ROUNDS, RB>), dim3((unsigned)nblocks),
+        hipLaunchKernelGGL((k_rs_scatter<K, false, ROUNDS, RB>), dim3((unsigned)nblocks),
                            dim3(RS_BLOCK), 0, st, ka, va, kb, vb, n, shift, goff, nblocks, rowtot);
     return hipGetLastError() == hipSuccess ? 0 : SBA_EDEVICE;
 }
 
-static int rs_pass(const uint64_t *ka, const uint32_t *va, uint64_t *kb, uint32_t *vb, int64_t n,
-                   int shift, int rb, int64_t *goff, int64_t nblocks, int64_t *rowtot,
-                   hipStream_t st)
+template <typename K>
+static int rs_pass(const K *ka, const uint32_t *va, K *kb, uint32_t *vb, int64_t n, int shift,
+                   int rb, int64_t *goff, int64_t nblocks, int64_t *rowtot, hipStream_t st)
 {
     const int r = rs_rounds(n);
     if (r == 4)
-        return rb == 9 ? rs_pass_t<4, 9>(ka, va, kb, vb, n, shift, goff, nblocks, rowtot, st)
-                       : rs_pass_t<4, 8>(ka, va, kb, vb, n, shift, goff, nblocks, rowtot, st);
-    if (r == 8) return rs_pass_t<8, 8>(ka, va, kb, vb, n, shift, goff, nblocks, rowtot, st);
-    return rs_pass_t<16, 8>(ka, va, kb, vb, n, shift, goff, nblocks, rowtot, st);
+        return rb == 9 ? rs_pass_t<K, 4, 9>(ka, va, kb, vb, n, shift, goff, nblocks, rowtot, st)
+                       : rs_pass_t<K, 4, 8>(ka, va, kb, vb, n, shift, goff, nblocks, rowtot, st);
+    if (r == 8) return rs_pass_t<K, 8, 8>(ka, va, kb, vb, n, shift, goff, nblocks, rowtot, st);
+    return rs_pass_t<K, 16, 8>(ka, va, kb, vb, n, shift, goff, nblocks, rowtot, st);
 }
 
 int radix_sort_u64(uint64_t *keys, uint32_t *vals, int64_t n, int bits, hipStream_t st,
@@ -620,12 +620,13 @@ int radix_sort_u64(uint64_t *keys, uint32_t *vals, int64_t n, int bits, hipStrea
     return rc;
 }
 
-int radix_sort_u64_ws(uint64_t **keys, uint32_t **vals, int64_t n, int bits, Workspace &ws)
+template <typename K>
+static int radix_sort_ws(K **keys, uint32_t **vals, int64_t n, int bits, Workspace &ws)
 {
     if (n <= 1 || bits <= 0) return 0;
     hipStream_t st = ws.stream();
     const int64_t nblocks = rs_blocks(n);
-    uint64_t *k2 = nullptr;
+    K *k2 = nullptr;
     uint32_t *v2 = nullptr;
     int64_t *goff = nullptr, *rowtot = nullptr;
     RC(ws.alloc(&k2, n));
@@ -634,7 +635,7 @@ int radix_sort_u64_ws(uint64_t **keys, uint32_t **vals, int64_t n, int bits, Wor
     RC(ws.alloc(&goff, nblocks << rb));
     RC(ws.alloc(&rowtot, (int64_t)1 << rb));
     const int passes = (bits + rb - 1) / rb;
-    uint64_t *ka = *keys, *kb = k2;
+    K *ka = *keys, *kb = k2;
     uint32_t *va = vals ? *vals : nullptr, *vb = v2;
     for (int p = 0; p < passes; p++) {
         RC(rs_pass(ka, va, kb, vb, n, rb * p, rb, goff, nblocks, rowtot, st));
@@ -650,6 +651,16 @@ int radix_sort_u64_ws(uint64_t **keys, uint32_t **vals, int64_t n, int bits, Wor
     *keys = ka;
     if (vals && *vals) *vals = va;
     return 0;
+}
+
+int radix_sort_u64_ws(uint64_t **keys, uint32_t **vals, int64_t n, int bits, Workspace &ws)
+{
+    return radix_sort_ws(keys, vals, n, bits, ws);
+}
+
+int radix_sort_u32_ws(uint32_t **keys, uint32_t **vals, int64_t n, int bits, Workspace &ws)
+{
+    return radix_sort_ws(keys, vals, n, bits, ws);
 }
 
 extern "C" int sba_debug_radix_sort(uint64_t *keys, uint32_t *vals, int64_t n, int32_t bits,

@@ -369,6 +369,8 @@ int radix_sort_u64(uint64_t *keys, uint32_t *vals, int64_t n, int bits, hipStrea
 // are left in whichever buffer the last pass wrote: *keys / *vals are updated
 // to it and the other buffer goes back to ws (so both must come from ws).
 int radix_sort_u64_ws(uint64_t **keys, uint32_t **vals, int64_t n, int bits, Workspace &ws);
+// 32-bit keys (bits <= 32)
+int radix_sort_u32_ws(uint32_t **keys, uint32_t **vals, int64_t n, int bits, Workspace &ws);
 
 // In place: hist[d * nblocks + b] (per block b the count of digit d, 256
 // digits) becomes the position of block b's first key of digit d in the

@@ -1,0 +1,93 @@
+// sets.h -- the polygon sets of multi-polygon segments (sets.hip), shared by
+// the build's stages.  Not part of the public ABI.
+#pragma once
+
+#include "sba_internal.h"
+#include "build_state.h"
+
+// A multi-polygon segment's code until the sets are numbered: SEG_SLOT | the
+// hash slot of its set key.
+#define SEG_SLOT 0x80000000u
+
+// The key of a set of two or three polygons holds its ids + 1, ascending, in
+// fields of fb bits; a larger set is not shared and has the key 2^(3 fb) + the
+// index of its segment (memloc[index]: where its members are in mem_ids << 6 |
+// their number).
+//
+// Distinct keys: an open-addressing table of 2^hb keys, each first insert
+// appending its key and slot to a list (cap entries) and its size to *nids.
+// More distinct keys than the list takes, or a run of SET_PROBES taken slots,
+// leaves *cnt above cap.
+struct SetTab {
+    uint64_t *tab = nullptr;
+    uint32_t *rank = nullptr;  // [2^hb] number of the slot's set
+    uint64_t *list = nullptr;
+    uint32_t *lslot = nullptr;
+    unsigned long long *cnt = nullptr, *nids = nullptr;
+    int hb = 0;
+    uint32_t cap = 0;
+};
+
+struct SetStage {
+    int fb = 0;
+    uint64_t *memloc = nullptr;
+    const int32_t *mem_ids = nullptr;
+    SetTab tab;
+    bool one_workgroup = false;  // the sets were numbered by one workgroup
+};
+
+#define SET_EMPTY (~(uint64_t)0)
+#define SET_PROBES 64
+// distinct sets that one workgroup sorts in LDS
+#define SET_CAP 8192
+
+__device__ __forceinline__ uint32_t set_hash(uint64_t k, int hb)
+{
+    return (uint32_t)((k * 0x9e3779b97f4a7c15ull) >> (64 - hb));
+}
+
+// the key's slot (d: the size of its set)
+__device__ __forceinline__ uint32_t set_insert(const SetTab &T, uint64_t key, uint32_t d)
+{
+    const uint32_t mask = (1u << T.hb) - 1u;
+    uint32_t s = set_hash(key, T.hb);
+    for (int probe = 0; probe < SET_PROBES; probe++) {
+        // a slot that already holds the key is seen without an atomic
+        const uint64_t seen = *(const volatile uint64_t *)(T.tab + s);
+        if (seen == key) return s;
+        if (seen == SET_EMPTY) {
+            const uint64_t prev = atomicCAS((unsigned long long *)(T.tab + s),
+                                            (unsigned long long)SET_EMPTY, (unsigned long long)key);
+            if (prev == SET_EMPTY) {
+                const unsigned long long at = atomicAdd(T.cnt, 1ull);
+                if (at < T.cap) {
+                    T.list[at] = key;
+                    T.lslot[at] = s;
+                    atomicAdd(T.nids, (unsigned long long)d);
+                }
+                return s;
+            }
+            if (prev == key) return s;
+        }
+        s = (s + 1) & mask;
+    }
+    atomicAdd(T.cnt, (unsigned long long)T.cap + 1);
+    return 0;
+}
+
+// an empty table for the sets of np polygons
+int sets_table(SetStage &S, BuildState &B, int32_t np);
+// number the nset distinct sets (nids members) of the table in key order, lay
+// out h's set table (NM multi segments with NMEM members bound its size) and
+// replace the SEG_SLOT codes of B's segments; slots: segment indices
+int sets_from_table(SetStage &S, BuildState &B, sba_handle *h, int64_t NM, int64_t NMEM,
+                    int64_t nset, int64_t nids, int64_t slots, hipStream_t st);
+// the same from the list of multi segments (key, segment), sorted as a whole;
+// mkey and mval come from B.ws and go back to it
+int sets_from_list(SetStage &S, BuildState &B, sba_handle *h, uint64_t *mkey, uint32_t *mval,
+                   int64_t NM, int64_t NMEM, int64_t slots, hipStream_t st);
+// the list through the table: *done when it held them all
+int sets_hash_list(SetStage &S, BuildState &B, sba_handle *h, const uint64_t *mkey,
+                   const uint32_t *mval, int64_t NM, int64_t NMEM, int64_t slots, hipStream_t st,
+                   bool *done);
+void sets_release(SetStage &S, BuildState &B);
