@@ -9,9 +9,8 @@
 
 #define SC_SLOTS 32
 #define SC_READ 20
-// slots of the set table: distinct sets, total member ids
+// slot of the set table's counter
 #define SC_SET_N 18
-#define SC_SET_IDS 19
 
 struct BuildState {
     explicit BuildState(hipStream_t s) : st(s), ws(s) {}

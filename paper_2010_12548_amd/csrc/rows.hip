@@ -308,13 +308,15 @@ __global__ void k_rows_init(const int32_t *ring_off, const int64_t *vert_off, in
 }
 
 // COUNT: rowdiff[r] += pairs that begin at row r less pairs that end before
-// it (the row's pair count is the prefix sum), stat[2k], stat[2k+1] += the
-// boundary strips and crossings (spread over ROW_STATS pairs of counters).
+// it (the row's pair count is the prefix sum), and the boundary strips and
+// crossings go to one of ROW_STATS pairs of counters, each in a cache line of
+// its own (additions to one line take about 10 ns each, one after another).
 // EMIT: every pair to its row's bucket, rowdiff (zero on entry) counting the
 // pairs placed so far.  A workgroup whose edges lie within EROWS rows, as
 // neighbouring edges of a polygon do, counts in LDS and touches each row's
 // global word once.  epw edges a workgroup (its lanes share their pairs).
-#define ROW_STATS 16
+#define ROW_STATS 64
+#define ROW_STAT_STEP 16  // words between counter pairs: a cache line of their own
 
 template <bool EMIT>
 __global__ __launch_bounds__(EB) void k_edge_rows(PolyView P, RowGeo G, int epw, int32_t *rowdiff,
@@ -368,7 +370,7 @@ __global__ __launch_bounds__(EB) void k_edge_rows(PolyView P, RowGeo G, int epw,
     __syncthreads();
     const int32_t r0 = lo_s, span = hi_s - lo_s + 1;
     if (!EMIT && tid == 0 && (sb[0] | sb[1])) {
-        unsigned long long *st = stat + 2 * (blockIdx.x & (ROW_STATS - 1));
+        unsigned long long *st = stat + ROW_STAT_STEP * (blockIdx.x & (ROW_STATS - 1));
         atomicAdd(&st[0], sb[0]);
         atomicAdd(&st[1], sb[1]);
     }
@@ -444,38 +446,46 @@ __device__ __forceinline__ int row_class(uint32_t n)
 
 // One workgroup: from rowdiff (see k_edge_rows) the rows' pair counts and
 // their exclusive scan rowoff[0..gh] (pairs < 2^31); rowdiff goes back to
-// zero.  Rows of class c go to list[c gh ..], out[2 + c] of them (out[6]: rows
-// past the last class); empty rows get their (empty) segment range at once.
-// out[0]: pairs, out[1]: the most in a row.  Each lane takes 8 consecutive
-// rows a chunk.
+// zero.  out[0]: pairs, out[1]: the most in a row, out[6], out[7]: boundary
+// strips and crossings (the sums over stat).  The rows come and go by threads
+// (a lane of eight consecutive rows would touch a line an access) and are
+// summed eight to a lane, the next chunk loaded meanwhile.
 #define RSCAN 1024
 #define RSCAN_PER 8
+#define RS_PAD(i) ((i) + ((i) >> 3))  // a lane's eight in banks of their own
 __global__ __launch_bounds__(RSCAN) void k_row_scan(int32_t *rowdiff, int64_t gh, int64_t *rowoff,
-                                                    int32_t *list, int64_t *seg_beg,
-                                                    int64_t *seg_end, int32_t *row_multi,
+                                                    const unsigned long long *stat,
                                                     unsigned long long *out)
 {
-    __shared__ uint32_t wd[RSCAN / 64], ws[RSCAN / 64];
-    __shared__ uint32_t smax, cnt[ROW_CLASSES + 1];
+    __shared__ uint32_t wd[RSCAN / 64];
+    __shared__ uint32_t chunk[RS_PAD(RSCAN * RSCAN_PER)];
+    __shared__ uint32_t smax;
+    __shared__ unsigned long long sst[2];
     if (threadIdx.x == 0) smax = 0;
-    if (threadIdx.x <= ROW_CLASSES) cnt[threadIdx.x] = 0;
-    __syncthreads();
-    uint32_t cd = 0, cs = 0, m = 0;
+    if (threadIdx.x < 2) sst[threadIdx.x] = 0;
     uint32_t next[RSCAN_PER];
     auto load = [&](int64_t c0) {
 #pragma unroll
         for (int k = 0; k < RSCAN_PER; k++) {
-            const int64_t r = c0 + (int64_t)threadIdx.x * RSCAN_PER + k;
+            const int64_t r = c0 + k * RSCAN + threadIdx.x;
             next[k] = r <= gh ? (uint32_t)rowdiff[r] : 0u;
         }
     };
     load(0);
+    __syncthreads();
+    if (threadIdx.x < 2 * ROW_STATS)
+        atomicAdd(&sst[threadIdx.x & 1],
+                  stat[ROW_STAT_STEP * (threadIdx.x >> 1) + (threadIdx.x & 1)]);
+    uint32_t cd = 0, cs = 0, m = 0;
     for (int64_t c0 = 0; c0 <= gh; c0 += RSCAN * RSCAN_PER) {
         const int64_t b = c0 + (int64_t)threadIdx.x * RSCAN_PER;
+#pragma unroll
+        for (int k = 0; k < RSCAN_PER; k++) chunk[RS_PAD(k * RSCAN + threadIdx.x)] = next[k];
+        __syncthreads();
         uint32_t d[RSCAN_PER], run = 0;
 #pragma unroll
         for (int k = 0; k < RSCAN_PER; k++) {
-            run += next[k];  // differences may be negative: modulo 2^32
+            run += chunk[RS_PAD(threadIdx.x * RSCAN_PER + k)];  // modulo 2^32
             d[k] = run;
         }
         load(c0 + RSCAN * RSCAN_PER);
@@ -489,36 +499,72 @@ __global__ __launch_bounds__(RSCAN) void k_row_scan(int32_t *rowdiff, int64_t gh
             m = max(m, d[k]);
         }
         uint32_t tots;
-        uint32_t o = cs + wg_scan_incl<RSCAN>(sum, ws, &tots) - sum;
+        uint32_t o = cs + wg_scan_incl<RSCAN>(sum, wd, &tots) - sum;
 #pragma unroll
         for (int k = 0; k < RSCAN_PER; k++) {
-            const int64_t r = b + k;
-            if (r <= gh) {
-                rowoff[r] = o;
-                rowdiff[r] = 0;
-            }
-            if (r < gh) {
-                if (d[k] == 0) {
-                    seg_beg[r] = seg_end[r] = 2 * (int64_t)o;
-                    row_multi[r] = 0;
-                } else {
-                    const int c = row_class(d[k]);
-                    const uint32_t at = atomicAdd(&cnt[c], 1u);
-                    if (c < ROW_CLASSES) list[(int64_t)c * gh + at] = (int32_t)r;
-                }
-            }
+            chunk[RS_PAD(threadIdx.x * RSCAN_PER + k)] = o;
             o += d[k];
         }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < RSCAN_PER; k++) {
+            const int64_t r = c0 + k * RSCAN + threadIdx.x;
+            if (r <= gh) {
+                rowoff[r] = chunk[RS_PAD(k * RSCAN + threadIdx.x)];
+                rowdiff[r] = 0;
+            }
+        }
+        __syncthreads();
         cd += totd;
         cs += tots;
     }
-    atomicMax(&smax, m);
+    for (int o = 32; o > 0; o >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, o, 64));
+    if ((threadIdx.x & 63) == 0) atomicMax(&smax, m);
     __syncthreads();
     if (threadIdx.x == 0) {
         out[0] = cs;
         out[1] = smax;
+        out[6] = sst[0];
+        out[7] = sst[1];
     }
-    if (threadIdx.x <= ROW_CLASSES) out[2 + threadIdx.x] = cnt[threadIdx.x];
+}
+
+// The rows by class: list[c gh ..] holds class c's, cnt[c] of them (zero on
+// entry), one reservation a class and workgroup.  Empty rows get their (empty)
+// segment range and figures at once.
+__global__ __launch_bounds__(256) void k_row_lists(const int64_t *rowoff, int64_t gh, int32_t *list,
+                                                   int64_t *seg_beg, int64_t *seg_end,
+                                                   uint32_t *row_stat, unsigned long long *cnt)
+{
+    __shared__ uint32_t n[ROW_CLASSES], base[ROW_CLASSES];
+    const int tid = threadIdx.x;
+    const int64_t r = (int64_t)blockIdx.x * 256 + tid;
+    if (tid < ROW_CLASSES) n[tid] = 0;
+    __syncthreads();
+    int c = -1;
+    if (r < gh) {
+        const int64_t o = rowoff[r];
+        const uint32_t d = (uint32_t)(rowoff[r + 1] - o);
+        if (d == 0) {
+            seg_beg[r] = seg_end[r] = 2 * o;
+            row_stat[r] = row_stat[gh + r] = 0;
+        } else {
+            c = row_class(d);
+        }
+    }
+    uint32_t at = 0;
+    for (int q = 0; q < ROW_CLASSES; q++) {
+        const uint64_t b = __ballot(c == q);
+        if (c != q) continue;
+        const uint32_t rank = (uint32_t)__popcll(b & ((1ull << (tid & 63)) - 1));
+        uint32_t first = 0;
+        if (rank == 0) first = atomicAdd(&n[q], (uint32_t)__popcll(b));
+        at = (uint32_t)__shfl((int)first, __ffsll((long long)b) - 1, 64) + rank;
+    }
+    __syncthreads();
+    if (tid < ROW_CLASSES && n[tid]) base[tid] = (uint32_t)atomicAdd(&cnt[tid], (unsigned long long)n[tid]);
+    __syncthreads();
+    if (c >= 0 && c < ROW_CLASSES) list[(int64_t)c * gh + base[c] + at] = (int32_t)r;
 }
 
 // ---------------------------------------------------------------- sweep
@@ -605,17 +651,15 @@ struct SweepArgs {
     int32_t *seg_x0, *seg_x1;
     uint32_t *seg_code;
     uint64_t *seg_key;       // set keys of multi-polygon segments (list mode), or NULL
-    int32_t *row_multi;      // multi-polygon segments of each row
+    uint32_t *row_stat;      // [gh] multi-polygon segments, [gh] members of each row
     uint64_t *memloc;        // members of the sets of more than three polygons
     int32_t *mem_ids;
     unsigned long long *memcnt;
     int64_t memcap;
     SetTab tab;              // tab.tab NULL: list mode
-    unsigned long long *stat;  // ROW_STATS x {segments, multi segments, members}
     int *err;
 };
 
-#define SWEEP_STATS 4
 #define ERR_DEPTH 8
 #define ERR_ROW 16   // a row does not fit the workgroup
 
@@ -838,6 +882,7 @@ __global__ __launch_bounds__(BLOCK) void k_row_sweep(const SweepArgs A)
     __shared__ P wmax[BLOCK / 64];
     __shared__ uint32_t s_stat[2];
     __shared__ int s_err;
+    __shared__ unsigned long long s_mem;
     const int tid = threadIdx.x;
     const int row = A.list[blockIdx.x];
     const int64_t i0 = A.rowoff[row];
@@ -896,13 +941,23 @@ __global__ __launch_bounds__(BLOCK) void k_row_sweep(const SweepArgs A)
     // segments: the pieces that hold a polygon
     uint32_t nseg = 0, nm = 0, nmem = 0;
     const bool hash = A.tab.tab != nullptr;
-    const bool full = hash && *(const volatile unsigned long long *)A.tab.cnt > A.tab.cap;
+    const bool full = hash && set_full(A.tab);
     for (int b = 0; b < nd; b += BLOCK) {
         const int k = b + tid;
         const int d = k < nd ? L.D[k] : 0;
+        // segments in bits 0-10 (at most 1024 a step), members of large sets
+        // above them (one reservation a step)
+        const uint32_t need = d > 3 && d <= MAX_DEPTH ? (uint32_t)d : 0u;
         uint32_t tot;
-        const uint32_t o = nseg + wg_scan_incl<BLOCK>(d ? 1u : 0u, wsum, &tot) - 1;
-        nseg += tot;
+        const uint32_t sc = wg_scan_incl<BLOCK>((need << 11) | (d ? 1u : 0u), wsum, &tot);
+        if (tot >> 11) {
+            if (tid == 0) s_mem = atomicAdd(A.memcnt, (unsigned long long)(tot >> 11));
+            __syncthreads();
+        }
+        const uint32_t o = nseg + (sc & 0x7ffu) - 1;
+        const int64_t a = need ? (int64_t)s_mem + (int64_t)((sc >> 11) - need) : 0;
+        if (tot >> 11) __syncthreads();
+        nseg += tot & 0x7ffu;
         if (!d) continue;
         const int64_t at = sbase + o;
         A.seg_x0[at] = (int32_t)L.E[k];
@@ -926,7 +981,6 @@ __global__ __launch_bounds__(BLOCK) void k_row_sweep(const SweepArgs A)
                 continue;
             }
             // intervals are in polygon order: the ids come out ascending
-            const int64_t a = (int64_t)atomicAdd(A.memcnt, (unsigned long long)d);
             if (a + d <= A.memcap) {
                 int q = 0;
                 for (int m = 0; m < ni && q < d; m++)
@@ -951,14 +1005,39 @@ __global__ __launch_bounds__(BLOCK) void k_row_sweep(const SweepArgs A)
     if (tid == 0) {
         A.seg_beg[row] = sbase;
         A.seg_end[row] = sbase + nseg;
-        A.row_multi[row] = (int32_t)s_stat[0];
-        unsigned long long *st = A.stat + SWEEP_STATS * (row & (ROW_STATS - 1));
-        atomicAdd(&st[0], (unsigned long long)nseg);
-        if (s_stat[0]) {
-            atomicAdd(&st[1], (unsigned long long)s_stat[0]);
-            atomicAdd(&st[2], (unsigned long long)s_stat[1]);
-        }
+        A.row_stat[row] = s_stat[0];
+        A.row_stat[A.gh + row] = s_stat[1];
     }
+}
+
+// out[0..2] += segments, multi-polygon segments and their members of all rows
+// (the rows' own figures, added up once: an addition to a shared counter by
+// every row took 10 ns a row)
+__global__ __launch_bounds__(256) void k_row_totals(const int64_t *seg_beg, const int64_t *seg_end,
+                                                    const uint32_t *row_stat, int64_t gh,
+                                                    unsigned long long *out)
+{
+    __shared__ unsigned long long sum[3];
+    if (threadIdx.x < 3) sum[threadIdx.x] = 0;
+    __syncthreads();
+    unsigned long long a = 0, b = 0, c = 0;
+    for (int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x; r < gh; r += (int64_t)gridDim.x * 256) {
+        a += (unsigned long long)(seg_end[r] - seg_beg[r]);
+        b += row_stat[r];
+        c += row_stat[gh + r];
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+        a += __shfl_xor(a, o, 64);
+        b += __shfl_xor(b, o, 64);
+        c += __shfl_xor(c, o, 64);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        atomicAdd(&sum[0], a);
+        atomicAdd(&sum[1], b);
+        atomicAdd(&sum[2], c);
+    }
+    __syncthreads();
+    if (threadIdx.x < 3 && sum[threadIdx.x]) atomicAdd(&out[threadIdx.x], sum[threadIdx.x]);
 }
 
 // list mode: the multi-polygon segments of all rows, in row order
@@ -986,7 +1065,7 @@ __global__ __launch_bounds__(256) void k_multi_list(const int64_t *seg_beg, cons
     }
 }
 
-__global__ void k_widen(const int32_t *a, int64_t n, int64_t *b)
+__global__ void k_widen(const uint32_t *a, int64_t n, int64_t *b)
 {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t < n) b[t] = a[t];
@@ -1194,19 +1273,20 @@ int rows_coverage(const sba_polygons *polys, const int4 *bbox, int64_t nv,
     int32_t *rowdiff = nullptr;
     int64_t *rowoff = nullptr;
     unsigned long long *stat = nullptr;
-    // pair totals, sweep totals, then k_row_scan's figures and the members of
-    // large sets
-    constexpr int NST = ROW_STATS * (2 + SWEEP_STATS) + 8;
+    // the pair counters, then the figures that the host reads: k_row_scan's
+    // and k_row_lists' eight, the sweep's totals (k_row_totals), the members of large sets
+    constexpr int NFIG = 12, NST = ROW_STATS * ROW_STAT_STEP + NFIG;
     RC(B.alloc(&rowdiff, (int64_t)gh + 1));
     RC(B.alloc(&rowoff, (int64_t)gh + 1));
     RC(B.alloc(&stat, NST));
-    int32_t *list = nullptr, *row_multi = nullptr;
+    int32_t *list = nullptr;
+    uint32_t *row_stat = nullptr;
     RC(B.alloc(&list, (int64_t)gh * ROW_CLASSES));
-    RC(B.alloc(&row_multi, gh));
+    RC(B.alloc(&row_stat, (int64_t)gh * 2));
     RC(B.alloc(&B.seg_beg, gh));
     RC(B.alloc(&B.seg_end, gh));
-    unsigned long long *sstat = stat + 2 * ROW_STATS, *one = sstat + SWEEP_STATS * ROW_STATS;
-    hipLaunchKernelGGL(k_rows_init, dim3(grid_for(std::max<int64_t>((int64_t)np * 64, gh + 1))),
+    unsigned long long *fig = stat + ROW_STATS * ROW_STAT_STEP;
+    hipLaunchKernelGGL(k_rows_init, dim3(grid_for(std::max<int64_t>((int64_t)np * 64, std::max<int64_t>(gh + 1, NST)))),
                        dim3(256), 0, st, polys->ring_off, polys->vert_off, np, hint, rowdiff,
                        (int64_t)gh + 1, stat, NST);
     // few edges: fewer a workgroup, so that their pairs (each two 64-bit
@@ -1217,26 +1297,24 @@ int rows_coverage(const sba_polygons *polys, const int4 *bbox, int64_t nv,
     const dim3 egrid((unsigned)((nv + epw - 1) / epw));
     hipLaunchKernelGGL(k_edge_rows<false>, egrid, dim3(EB), 0, st, P, G, epw, rowdiff,
                        (const int64_t *)nullptr, (uint4 *)nullptr, stat);
-    hipLaunchKernelGGL(k_row_scan, dim3(1), dim3(RSCAN), 0, st, rowdiff, (int64_t)gh, rowoff, list,
-                       B.seg_beg, B.seg_end, row_multi, one);
+    hipLaunchKernelGGL(k_row_scan, dim3(1), dim3(RSCAN), 0, st, rowdiff, (int64_t)gh, rowoff, stat,
+                       fig);
+    hipLaunchKernelGGL(k_row_lists, dim3(grid_for(gh)), dim3(256), 0, st, rowoff, (int64_t)gh, list,
+                       B.seg_beg, B.seg_end, row_stat, fig + 2);
     HIP_OK(hipGetLastError());
-    unsigned long long hs[NST];
-    RC(B.ws.read(hs, stat, sizeof(hs)));
+    unsigned long long hs[NFIG];
+    RC(B.ws.read(hs, fig, sizeof(hs)));
     RC(B.ws.sync());
-    int64_t NB = 0, NC = 0;
-    for (int k = 0; k < ROW_STATS; k++) {
-        NB += (int64_t)hs[2 * k];
-        NC += (int64_t)hs[2 * k + 1];
-    }
-    const int64_t items_n = (int64_t)hs[NST - 8], max_n = (int64_t)hs[NST - 7];
+    const int64_t items_n = (int64_t)hs[0], max_n = (int64_t)hs[1];
+    const int64_t NB = (int64_t)hs[6], NC = (int64_t)hs[7];
     int64_t rows[ROW_CLASSES];
-    for (int c = 0; c < ROW_CLASSES; c++) rows[c] = (int64_t)hs[NST - 6 + c];
+    for (int c = 0; c < ROW_CLASSES; c++) rows[c] = (int64_t)hs[2 + c];
     if (NC % 2) return SBA_EDEVICE;
     h->n_boundary = NB;
     if (2 * NB + NC >= ((int64_t)1 << 32)) return SBA_ELIMIT;
     auto leave = [&]() {
         for (void *p : {(void *)rowdiff, (void *)rowoff, (void *)stat, (void *)list, (void *)hint,
-                        (void *)row_multi, (void *)B.seg_beg, (void *)B.seg_end})
+                        (void *)row_stat, (void *)B.seg_beg, (void *)B.seg_end})
             B.release(p);
         B.seg_beg = B.seg_end = nullptr;
         return 0;
@@ -1271,7 +1349,7 @@ int rows_coverage(const sba_polygons *polys, const int4 *bbox, int64_t nv,
     SweepArgs A{};
     SetStage S{};
     S.fb = fb;
-    A.row_multi = row_multi;
+    A.row_stat = row_stat;
     A.list = list;
     A.gw = G.gw;
     RC(B.alloc(&S.memloc, slots));
@@ -1288,8 +1366,7 @@ int rows_coverage(const sba_polygons *polys, const int4 *bbox, int64_t nv,
     A.seg_x1 = B.seg_x1;
     A.seg_code = B.seg_code;
     A.memloc = S.memloc;
-    A.memcnt = one + 7;
-    A.stat = sstat;
+    A.memcnt = fig + 11;
     A.err = (int *)B.sc;
     bool hash = !(paths_off & 4);
     A.memcap = std::max<int64_t>(1 << 16, items_n);
@@ -1297,9 +1374,8 @@ int rows_coverage(const sba_polygons *polys, const int4 *bbox, int64_t nv,
     int64_t NS = 0, NM = 0, NMEM = 0, nset = 0, nids = 0;
     for (int attempt = 0;; attempt++) {
         if (attempt > 0) {
-            HIP_OK(hipMemsetAsync(sstat, 0, sizeof(unsigned long long) * SWEEP_STATS * ROW_STATS, st));
-            HIP_OK(hipMemsetAsync(A.memcnt, 0, sizeof(unsigned long long), st));
-            HIP_OK(hipMemsetAsync(B.sc + SC_SET_N, 0, 2 * sizeof(int64_t), st));
+            HIP_OK(hipMemsetAsync(fig + 8, 0, 4 * sizeof(unsigned long long), st));
+            HIP_OK(hipMemsetAsync(B.sc + SC_SET_N, 0, sizeof(int64_t), st));
         }
         if (hash) {
             if (!S.tab.tab) RC(sets_table(S, B, np));
@@ -1311,8 +1387,11 @@ int rows_coverage(const sba_polygons *polys, const int4 *bbox, int64_t nv,
         if (p32 && t32) RC((sweep_launch<uint32_t, uint32_t>(A, rows, st)));
         else if (t32) RC((sweep_launch<uint64_t, uint32_t>(A, rows, st)));
         else RC((sweep_launch<uint64_t, uint64_t>(A, rows, st)));
+        hipLaunchKernelGGL(k_row_totals, dim3((unsigned)std::min<int64_t>((gh + 255) / 256, 64)),
+                           dim3(256), 0, st, B.seg_beg, B.seg_end, row_stat, (int64_t)gh, fig + 8);
+        HIP_OK(hipGetLastError());
         int64_t hsc[SC_READ];
-        RC(B.ws.read(hs, stat, sizeof(hs)));
+        RC(B.ws.read(hs, fig, sizeof(hs)));
         RC(B.ws.read(hsc, B.sc, sizeof(hsc)));
         RC(B.ws.sync());
         const int herr = (int)(uint32_t)hsc[0];
@@ -1328,16 +1407,12 @@ int rows_coverage(const sba_polygons *polys, const int4 *bbox, int64_t nv,
             B.seg_code = nullptr;
             return leave();
         }
-        NS = NM = NMEM = 0;
-        for (int k = 0; k < ROW_STATS; k++) {
-            const unsigned long long *q = hs + 2 * ROW_STATS + SWEEP_STATS * k;
-            NS += (int64_t)q[0];
-            NM += (int64_t)q[1];
-            NMEM += (int64_t)q[2];
-        }
-        const int64_t mem = (int64_t)hs[NST - 1];
-        nset = hsc[SC_SET_N];
-        nids = hsc[SC_SET_IDS];
+        NS = (int64_t)hs[8];
+        NM = (int64_t)hs[9];
+        NMEM = (int64_t)hs[10];
+        const int64_t mem = (int64_t)hs[11];
+        nset = set_count(hsc[SC_SET_N]);
+        nids = set_ids_count(hsc[SC_SET_N]);
         bool again = false;
         if (mem > A.memcap) {
             B.release(A.mem_ids);
@@ -1368,7 +1443,7 @@ int rows_coverage(const sba_polygons *polys, const int4 *bbox, int64_t nv,
             RC(B.alloc(&mkey, NM));
             RC(B.alloc(&mval, NM));
             RC(B.alloc(&moff, (int64_t)gh));
-            hipLaunchKernelGGL(k_widen, dim3(grid_for(gh)), dim3(256), 0, st, A.row_multi,
+            hipLaunchKernelGGL(k_widen, dim3(grid_for(gh)), dim3(256), 0, st, row_stat,
                                (int64_t)gh, moff);
             HIP_OK(hipGetLastError());
             RC(scan_exclusive_i64(moff, moff, gh, nullptr, st, &B.ws));
@@ -1381,7 +1456,7 @@ int rows_coverage(const sba_polygons *polys, const int4 *bbox, int64_t nv,
     }
     *one_wg = S.one_workgroup;
     B.release(A.seg_key);
-    B.release(row_multi);
+    B.release(row_stat);
     B.release(list);
     B.release(A.mem_ids);
     sets_release(S, B);

@@ -15,15 +15,16 @@
 // their number).
 //
 // Distinct keys: an open-addressing table of 2^hb keys, each first insert
-// appending its key and slot to a list (cap entries) and its size to *nids.
-// More distinct keys than the list takes, or a run of SET_PROBES taken slots,
-// leaves *cnt above cap.
+// appending its key and slot to a list (cap entries).  *cnt holds the number
+// of inserts above bit 32 and the sum of their sets' sizes below it (one
+// addition for both).  More distinct keys than the list takes, or a run of
+// SET_PROBES taken slots, leaves the number above cap.
 struct SetTab {
     uint64_t *tab = nullptr;
     uint32_t *rank = nullptr;  // [2^hb] number of the slot's set
     uint64_t *list = nullptr;
     uint32_t *lslot = nullptr;
-    unsigned long long *cnt = nullptr, *nids = nullptr;
+    unsigned long long *cnt = nullptr;
     int hb = 0;
     uint32_t cap = 0;
 };
@@ -40,6 +41,14 @@ struct SetStage {
 #define SET_PROBES 64
 // distinct sets that one workgroup sorts in LDS
 #define SET_CAP 8192
+
+__host__ __device__ inline int64_t set_count(int64_t cnt) { return (int64_t)((uint64_t)cnt >> 32); }
+__host__ __device__ inline int64_t set_ids_count(int64_t cnt) { return cnt & 0xffffffffll; }
+
+__device__ __forceinline__ bool set_full(const SetTab &T)
+{
+    return (*(const volatile unsigned long long *)T.cnt >> 32) > T.cap;
+}
 
 __device__ __forceinline__ uint32_t set_hash(uint64_t k, int hb)
 {
@@ -59,11 +68,10 @@ __device__ __forceinline__ uint32_t set_insert(const SetTab &T, uint64_t key, ui
             const uint64_t prev = atomicCAS((unsigned long long *)(T.tab + s),
                                             (unsigned long long)SET_EMPTY, (unsigned long long)key);
             if (prev == SET_EMPTY) {
-                const unsigned long long at = atomicAdd(T.cnt, 1ull);
+                const unsigned long long at = atomicAdd(T.cnt, (1ull << 32) | d) >> 32;
                 if (at < T.cap) {
                     T.list[at] = key;
                     T.lslot[at] = s;
-                    atomicAdd(T.nids, (unsigned long long)d);
                 }
                 return s;
             }
@@ -71,7 +79,7 @@ __device__ __forceinline__ uint32_t set_insert(const SetTab &T, uint64_t key, ui
         }
         s = (s + 1) & mask;
     }
-    atomicAdd(T.cnt, (unsigned long long)T.cap + 1);
+    atomicMax(T.cnt, (unsigned long long)(T.cap + 1) << 32);
     return 0;
 }
 

@@ -220,7 +220,7 @@ __global__ void k_set_insert(const uint64_t *key, const uint32_t *val, int64_t n
                              const uint64_t *memloc, SetTab T, uint32_t *seg_code)
 {
     const int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (m >= n || *(const volatile unsigned long long *)T.cnt > T.cap) return;
+    if (m >= n || set_full(T)) return;
     int64_t loc;
     const uint64_t k = key[m];
     seg_code[val[m]] = SEG_SLOT | set_insert(T, k, (uint32_t)set_members(k, fb, memloc, &loc));
@@ -274,7 +274,6 @@ int sets_table(SetStage &S, BuildState &B, int32_t np)
     RC(B.alloc(&T.list, T.cap));
     RC(B.alloc(&T.lslot, T.cap));
     T.cnt = (unsigned long long *)(B.sc + SC_SET_N);
-    T.nids = (unsigned long long *)(B.sc + SC_SET_IDS);
     HIP_OK(hipMemsetAsync(T.tab, 0xff, sizeof(uint64_t) << T.hb, B.st));
     return 0;
 }
@@ -341,8 +340,9 @@ int sets_hash_list(SetStage &S, BuildState &B, sba_handle *h, const uint64_t *mk
     int64_t hsc[SC_READ];
     RC(B.ws.read(hsc, B.sc, sizeof(hsc)));
     RC(B.ws.sync());
-    if (hsc[SC_SET_N] > (int64_t)S.tab.cap) return 0;
-    RC(sets_from_table(S, B, h, NM, NMEM, hsc[SC_SET_N], hsc[SC_SET_IDS], slots, st));
+    const int64_t nset = set_count(hsc[SC_SET_N]);
+    if (nset > (int64_t)S.tab.cap) return 0;
+    RC(sets_from_table(S, B, h, NM, NMEM, nset, set_ids_count(hsc[SC_SET_N]), slots, st));
     *done = true;
     return 0;
 }
