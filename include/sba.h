@@ -52,8 +52,8 @@ extern "C" {
 #define SBA_KIND_HILBERT  1  /* sorted Hilbert-key runs (adaptive quadtree cells)    */
 
 /* Search used by the Hilbert layout's probe. */
-#define SBA_SEARCH_BINARY   0  /* predecessor by binary search over all run starts   */
-#define SBA_SEARCH_LEARNED  1  /* two-level linear model + bounded search (+ fallback) */
+#define SBA_SEARCH_BINARY   0  /* binary search among the runs of the cell's block   */
+#define SBA_SEARCH_LEARNED  1  /* the same from a two-level linear model's estimate  */
 
 typedef struct sba_handle sba_handle;
 

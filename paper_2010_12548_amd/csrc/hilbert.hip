@@ -329,6 +329,118 @@ static int write_runs(BuildState &B, sba_handle *h, const K *bk, hipStream_t st)
     return 0;
 }
 
+// ---------------------------------------------------------------- block directory
+//
+// One entry per aligned square block of cells (a stretch of consecutive keys):
+// the code of the run that holds the whole block, or TILE_MIXED | the run that
+// holds its first key, from which a search reaches any key of the block.  Most
+// blocks of a partition lie in one run (91 % of the 16 x 16 blocks of 40,000
+// polygons at 1 m), so most lookups are one 4-byte read, at an address that
+// takes no Hilbert key, where a search over the runs takes 6 to 9 cache lines.
+// At least four times as many blocks as runs, at most 2^24 (64 MB, which the
+// memory-side cache holds; 2^22 and 2^23 made the probe of 2e7 points in no
+// order 9 and 4 % slower, by their mixed blocks).
+#define DIR_BITS_MAX 24
+#define DIR_LONG 2048   // runs over more blocks are filled by the whole grid
+
+// Run i's entries are the blocks whose first key it holds.  A wavefront shares
+// the entries of its 64 runs; long runs go to a list (cnt, list).
+__global__ __launch_bounds__(256) void k_dir_fill(const uint64_t *starts, const uint32_t *code,
+                                                  int64_t n, uint64_t total, int shift, int dl,
+                                                  uint32_t *dir, uint32_t *list,
+                                                  unsigned long long *cnt)
+{
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int lane = threadIdx.x & 63;
+    uint64_t next = 0, b0 = 0, m = 0;
+    uint32_t c = 0;
+    if (i < n) {
+        next = i + 1 < n ? starts[i + 1] : total;
+        const uint64_t r = ((uint64_t)1 << shift) - 1;
+        b0 = (starts[i] + r) >> shift;
+        m = ((next + r) >> shift) - b0;
+        c = code[i];
+        if (m > DIR_LONG) {
+            list[atomicAdd(cnt, 1ull)] = (uint32_t)i;
+            m = 0;
+        }
+    }
+    uint32_t incl = (uint32_t)m;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t u = (uint32_t)__shfl_up((int)incl, o, 64);
+        if (lane >= o) incl += u;
+    }
+    const uint32_t all = (uint32_t)__shfl((int)incl, 63, 64);
+    for (uint32_t t0 = 0; t0 < all; t0 += 64) {
+        const uint32_t t = t0 + lane;
+        // the lane's run: the first whose inclusive count exceeds t
+        int a = 0;
+#pragma unroll
+        for (int step = 32; step > 0; step >>= 1) {
+            const uint32_t u = (uint32_t)__shfl((int)incl, a + step - 1, 64);
+            a += u <= t ? step : 0;
+        }
+        a = a > 63 ? 63 : a;
+        const uint32_t first = (uint32_t)__shfl((int)(incl - (uint32_t)m), a, 64);
+        const uint64_t bb = __shfl((unsigned long long)b0, a, 64) + (t - first);
+        const uint64_t nx = __shfl((unsigned long long)next, a, 64);
+        const uint32_t cc = (uint32_t)__shfl((int)c, a, 64);
+        if (t < all) {
+            uint32_t ib, jb;
+            hilbert_cell(dl, bb, &ib, &jb);
+            dir[block_index(ib, jb, dl)] =
+                ((bb + 1) << shift) <= nx ? cc : (TILE_MIXED | (uint32_t)(i - lane + a));
+        }
+    }
+}
+
+__global__ __launch_bounds__(256) void k_dir_long(const uint64_t *starts, const uint32_t *code,
+                                                  int64_t n, uint64_t total, int shift, int dl,
+                                                  uint32_t *dir, const uint32_t *list,
+                                                  const unsigned long long *cnt)
+{
+    const int64_t nl = (int64_t)*cnt;
+    const uint64_t r = ((uint64_t)1 << shift) - 1;
+    for (int64_t q = 0; q < nl; q++) {
+        const int64_t i = list[q];
+        const uint64_t next = i + 1 < n ? starts[i + 1] : total;
+        const uint64_t b1 = (next + r) >> shift;
+        const uint32_t c = code[i];
+        for (uint64_t b = ((starts[i] + r) >> shift) + (uint64_t)blockIdx.x * 256 + threadIdx.x;
+             b < b1; b += (uint64_t)gridDim.x * 256) {
+            uint32_t ib, jb;
+            hilbert_cell(dl, b, &ib, &jb);
+            dir[block_index(ib, jb, dl)] =
+                ((b + 1) << shift) <= next ? c : (TILE_MIXED | (uint32_t)i);
+        }
+    }
+}
+
+static int build_directory(BuildState &B, sba_handle *h, hipStream_t st)
+{
+    const int bits = std::min(DIR_BITS_MAX, bits_for((uint64_t)h->n_runs) + 2);
+    const int dl = std::min(h->level, (bits + 1) / 2);
+    const int64_t blocks = (int64_t)1 << (2 * dl);
+    const int shift = 2 * (h->level - dl);
+    h->dir_level = dl;
+    RC(handle_alloc(h, &h->pdir, blocks));
+    uint32_t *list = nullptr;
+    unsigned long long *cnt = nullptr;
+    RC(B.alloc(&list, blocks / DIR_LONG + 1));
+    RC(B.alloc(&cnt, 1));
+    HIP_OK(hipMemsetAsync(cnt, 0, sizeof(unsigned long long), st));
+    const uint64_t total = (uint64_t)1 << (2 * h->level);
+    hipLaunchKernelGGL(k_dir_fill, dim3(grid_for(h->n_runs)), dim3(256), 0, st, h->starts,
+                       h->run_code, h->n_runs, total, shift, dl, h->pdir, list, cnt);
+    hipLaunchKernelGGL(k_dir_long, dim3(512), dim3(256), 0, st, h->starts, h->run_code, h->n_runs,
+                       total, shift, dl, h->pdir, list, cnt);
+    HIP_OK(hipGetLastError());
+    B.release(list);
+    B.release(cnt);
+    return 0;
+}
+
 // ---------------------------------------------------------------- learned index
 //
 // Two-level piecewise-linear model over the sorted run starts (the idea of a
@@ -488,6 +600,7 @@ int hilbert_finish(BuildState &B, sba_handle *h, const sba_build_opts &o, hipStr
     if (B.bkeys32) RC(write_runs<uint32_t>(B, h, B.bkeys32, st));
     else RC(write_runs<uint64_t>(B, h, B.bkeys, st));
     const int64_t nr = h->n_runs;
+    RC(build_directory(B, h, st));
 
     if (o.search == SBA_SEARCH_LEARNED) {
         if (2 * L > 32) return SBA_ELIMIT;  // leaves store 32-bit key bases

@@ -8,20 +8,22 @@
 // and adds the point to a per-workgroup histogram in LDS.  At the end every
 // workgroup adds its non-empty bins to the caller's outputs (zeroed by a
 // small kernel before the probe) with one global atomic per bin; no global
-// atomics per point.  Polygon counts too large for per-polygon bins use a
-// per-workgroup LDS table of the cell codes met in a contiguous item of
-// points instead.  A call allocates nothing.
+// atomics per point.  Polygon counts too large for a bin each, and every
+// Hilbert handle, use LDS lines of consecutive polygons' bins, placed by a
+// hash (k_probe_items).  A call allocates nothing.
 //
 // Cell lookup per layout:
 //   grid     directory entry of the cell's tile (staged in LDS in the
 //            16-bit format), for mixed tiles the sub-tile's entry, for mixed
 //            sub-tiles the cell's code in a fine block;
-//   hilbert  Hilbert key of the cell, then the run holding it: binary search
-//            over the run starts, or the learned index's bounded search.
+//   hilbert  directory entry of the cell's block; for blocks of several runs
+//            the Hilbert key of the cell, then the run holding it among the
+//            block's: binary search, or started at the learned index's estimate.
 #include <stdio.h>
 
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 #include <vector>
 
 #include "sba_internal.h"
@@ -58,16 +60,17 @@ struct HilbView {
     const uint32_t *k32;   // run starts (L <= 16)
     const uint64_t *k64;   // run starts
     const uint32_t *code;  // run codes
+    // block directory (sba_handle::pdir) and cells in 32-bit arithmetic, as in
+    // Grid16: valid when the stored box lies in the int32 coordinates
+    const uint32_t *dir;
+    int32_t dl;
+    uint32_t pre, post;
+    int32_t fits32;
     float a;               // learned root
     uint32_t nl;
     const int4 *leaves;
     const int32_t *leaf_lo;
     const uint16_t *tab;   // Hilbert table in LDS (set by the kernel) or NULL
-    // Region of a partitioned item (set by the kernel, NULL otherwise): runs
-    // sq0 .. sq1 hold every key of the item's points, and samp (in LDS) holds
-    // every sS-th of their starts, sn of them: samp[j] = k32[sq0 + j * sS].
-    const uint32_t *samp;
-    int32_t sq0, sq1, sS, sn;
 };
 
 // the Hilbert key of cell (i, j) of the view's grid
@@ -163,44 +166,6 @@ __device__ __forceinline__ int64_t pred_search(const K *keys, int64_t lo, int64_
     return lo;
 }
 
-template <typename K>
-__device__ __forceinline__ int64_t learned_search(const HilbView &v, const K *keys, K key)
-{
-    uint32_t l = root_leaf((uint64_t)key, v.a, v.nl);
-    int4 lf = v.leaves[l];
-    int64_t llo = v.leaf_lo[l], lhi = v.leaf_lo[l + 1];
-    int64_t p = predict_in_leaf(lf, llo, lhi, (uint64_t)key);
-    int64_t ra, rb;
-    leaf_range(llo, lhi, &ra, &rb);
-    int64_t lo = p - lf.w, hi = p + lf.w;
-    lo = lo < ra ? ra : lo;
-    hi = hi > rb ? rb : hi;
-    if (lo <= hi && keys[lo] <= key) {
-        int64_t q = pred_search<K>(keys, lo, hi - lo + 1, key);
-        if (q == v.n - 1 || keys[q + 1] > key) return q;
-    }
-    return pred_search<K>(keys, 0, v.n, key);  // bracket missed: full search
-}
-
-template <int SEARCH>
-__device__ __forceinline__ uint32_t hilbert_code(const HilbView &v, int32_t x, int32_t y)
-{
-    int64_t dx = (int64_t)x - v.ox, dy = (int64_t)y - v.oy;
-    if ((uint64_t)dx >= v.extx || (uint64_t)dy >= v.exty) return 0;
-    uint32_t i = divmagic((uint32_t)dx, v.mag, v.shift);
-    uint32_t j = divmagic((uint32_t)dy, v.mag, v.shift);
-    uint64_t key = hkey(v, i, j);
-    int64_t q;
-    if (v.k32) {
-        q = SEARCH ? learned_search<uint32_t>(v, v.k32, (uint32_t)key)
-                   : pred_search<uint32_t>(v.k32, 0, v.n, (uint32_t)key);
-    } else {
-        q = pred_search<uint64_t>(v.k64, 0, v.n, key);
-    }
-    return v.code[q];
-}
-
-
 // ---------------------------------------------------------------- batched lookups
 //
 // NP points at a time with no data-dependent branch around a load: all NP
@@ -289,33 +254,6 @@ __device__ __forceinline__ void pred_search_n(const K *keys, int64_t *lo, int64_
 #pragma unroll
         for (int k = 0; k < NP; k++) lo[k] = (v[k] <= key[k]) ? lo[k] + half : lo[k];
         len -= half;
-    }
-}
-
-// As pred_search_n with a window length per point: the wave steps while any
-// of its lanes still has a window longer than one (lanes that are done
-// re-read their current key, which changes nothing).
-template <typename K, int NP>
-__device__ __forceinline__ void pred_search_var(const K *keys, int64_t *lo, int64_t *len,
-                                                const K *key)
-{
-    while (true) {
-        bool more = false;
-#pragma unroll
-        for (int k = 0; k < NP; k++) more |= len[k] > 1;
-        if (!__any(more)) break;
-        K v[NP];
-        int64_t half[NP];
-#pragma unroll
-        for (int k = 0; k < NP; k++) {
-            half[k] = len[k] >> 1;
-            v[k] = keys[lo[k] + half[k]];
-        }
-#pragma unroll
-        for (int k = 0; k < NP; k++) {
-            lo[k] = (v[k] <= key[k]) ? lo[k] + half[k] : lo[k];
-            len[k] -= half[k];
-        }
     }
 }
 
@@ -426,25 +364,118 @@ __device__ __forceinline__ void learned_search_n(const HilbView &v, const uint32
     }
 }
 
-// The same, NP/2 points at a time when NP >= 8 (unless FULL): each lookup
-// holds a leaf, its range and its bracket, and the learned probe runs with
-// more waves (more points in flight on the chip) when half of them are held
-// at once.  FULL keeps all NP in flight per wave: points in no order within
-// their region (the partitioned probe) take this search for nearly every
-// point and gain more from the loads in flight than from the waves.
-template <int NP, bool FULL = false>
-__device__ __forceinline__ void learned_search_halves(const HilbView &v, const uint32_t *kk,
-                                                      const uint64_t *key, int64_t *q)
+// The run of a key inside its mixed block: the last of the runs (at most one a
+// key of the block) from lo on that starts at or before the key (run lo does).  With the learned
+// index the search starts at the model's position (clamped to the block), else
+// at the block's first run.  It reads the starts 1, 2, 4 .. 32 places away at
+// once, then three at a time inside the bracket that they leave: about three
+// rounds of loads in a line or two for the 20 runs of a partition's mixed
+// block, where doubling and halving steps take ten.
+template <bool LEARNED, typename K>
+__device__ __forceinline__ int32_t run_in_block(const HilbView &v, const K *keys, K key, int32_t lo)
 {
-    if constexpr (NP >= 8 && !FULL) {
-        learned_search_n<NP / 2>(v, kk, key, q);
-        learned_search_n<NP / 2>(v, kk + NP / 2, key + NP / 2, q + NP / 2);
-    } else {
-        learned_search_n<NP>(v, kk, key, q);
+    constexpr int W = 6;
+    int32_t hi = (int32_t)min((int64_t)lo + ((int64_t)1 << min(2 * (v.L - v.dl), 30)), v.n);
+    bool up = true;
+    if (LEARNED) {
+        const int4 lf = v.leaves[root_leaf((uint64_t)key, v.a, v.nl)];
+        const int64_t q = predict((uint64_t)(uint32_t)lf.x, __int_as_float(lf.y),
+                                  __int_as_float(lf.z), (uint64_t)key);
+        const int32_t p = (int32_t)(q < lo ? lo : (q > hi - 1 ? hi - 1 : q));
+        up = keys[p] <= key;
+        if (up) lo = p; else hi = p;
     }
+    // the bracket is [lo, hi): keys[lo] <= key < keys[hi]
+    while (hi - lo > 4) {
+        K s[W];
+        int32_t at[W];
+#pragma unroll
+        for (int k = 0; k < W; k++) {
+            at[k] = up ? min(lo + (1 << k), hi - 1) : max(hi - (1 << k), lo + 1);
+            s[k] = keys[at[k]];
+        }
+        const int32_t l0 = lo, h0 = hi;
+        int32_t far = up ? l0 : h0;
+#pragma unroll
+        for (int k = 0; k < W; k++) {
+            // keys ascend: the last place at or before the key, the first after it
+            if (s[k] <= key) lo = max(lo, at[k]); else hi = min(hi, at[k]);
+            far = at[k];
+        }
+        if (up ? lo < far : hi > far) break;  // the bracket lies between two places read
+    }
+    while (hi - lo > 1) {
+        const int32_t len = hi - lo;
+        const int32_t c1 = lo + max(len >> 2, 1), c2 = lo + max(len >> 1, 1),
+                      c3 = lo + max((3 * len) >> 2, 1);
+        const K s1 = keys[c1], s2 = keys[c2], s3 = keys[c3];
+        if (s3 <= key) {
+            lo = c3;
+        } else if (s2 <= key) {
+            lo = c2;
+            hi = c3;
+        } else if (s1 <= key) {
+            lo = c1;
+            hi = c2;
+        } else {
+            hi = c1;
+        }
+    }
+    return lo;
 }
 
-template <int SEARCH, int NP, bool FULL = false>
+// The directory entries of NP points (0 outside the stored box): a code, or
+// TILE_MIXED | a run; cell: i | j << 16 (below level 17).
+template <int NP>
+__device__ __forceinline__ void dir_codes(const HilbView &v, const int32_t *xs, const int32_t *ys,
+                                          uint32_t *c, uint32_t *cell)
+{
+    bool ok[NP];
+    uint32_t b[NP];
+    const int r = v.L - v.dl;
+    if (v.fits32) {
+        // a point and the box both lie in the int32 coordinates, so the
+        // offset modulo 2^32 is below the extent exactly when the point is in
+        // the box
+        const uint32_t ox = (uint32_t)v.ox, oy = (uint32_t)v.oy;
+#pragma unroll
+        for (int k = 0; k < NP; k++) {
+            const uint32_t dx = (uint32_t)xs[k] - ox, dy = (uint32_t)ys[k] - oy;
+            ok[k] = dx < v.extx && dy < v.exty;
+            const uint32_t i = __umulhi((ok[k] ? dx : 0u) << v.pre, v.mag) >> v.post;
+            const uint32_t j = __umulhi((ok[k] ? dy : 0u) << v.pre, v.mag) >> v.post;
+            cell[k] = i | (j << 16);
+            b[k] = block_index(i >> r, j >> r, v.dl);
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < NP; k++) {
+            const int64_t dx = (int64_t)xs[k] - v.ox, dy = (int64_t)ys[k] - v.oy;
+            ok[k] = (uint64_t)dx < v.extx && (uint64_t)dy < v.exty;
+            const uint32_t i = divmagic(ok[k] ? (uint32_t)dx : 0u, v.mag, v.shift);
+            const uint32_t j = divmagic(ok[k] ? (uint32_t)dy : 0u, v.mag, v.shift);
+            cell[k] = i | (j << 16);
+            b[k] = block_index(i >> r, j >> r, v.dl);
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < NP; k++) c[k] = ok[k] ? gld(v.dir + b[k]) : 0u;
+}
+
+// the code of a mixed block's entry e for the point
+template <bool LEARNED>
+__device__ __forceinline__ uint32_t mixed_code(const HilbView &v, int32_t x, int32_t y, uint32_t e)
+{
+    const uint32_t i = divmagic((uint32_t)((int64_t)x - v.ox), v.mag, v.shift);
+    const uint32_t j = divmagic((uint32_t)((int64_t)y - v.oy), v.mag, v.shift);
+    const uint64_t key = hkey(v, i, j);
+    const int32_t lo = (int32_t)(e & ~TILE_MIXED);
+    return gld(v.code + (v.k32 ? run_in_block<LEARNED, uint32_t>(v, v.k32, (uint32_t)key, lo)
+                               : run_in_block<LEARNED, uint64_t>(v, v.k64, key, lo)));
+}
+
+// Codes of NP points
+template <bool LEARNED, int NP>
 __device__ __forceinline__ void hilbert_codes(const HilbView &v, const int32_t *xs, const int32_t *ys,
                                               uint32_t *c)
 {
@@ -453,196 +484,11 @@ __device__ __forceinline__ void hilbert_codes(const HilbView &v, const int32_t *
         for (int k = 0; k < NP; k++) c[k] = 0;
         return;
     }
-    bool ok[NP];
-    uint64_t key[NP];
+    uint32_t cell[NP];
+    dir_codes<NP>(v, xs, ys, c, cell);
 #pragma unroll
-    for (int k = 0; k < NP; k++) {
-        int64_t dx = (int64_t)xs[k] - v.ox, dy = (int64_t)ys[k] - v.oy;
-        ok[k] = (uint64_t)dx < v.extx && (uint64_t)dy < v.exty;
-        uint32_t i = divmagic(ok[k] ? (uint32_t)dx : 0u, v.mag, v.shift);
-        uint32_t j = divmagic(ok[k] ? (uint32_t)dy : 0u, v.mag, v.shift);
-        key[k] = hkey(v, i, j);
-    }
-    int64_t q[NP];
-    if (v.k32) {
-        uint32_t k32[NP];
-#pragma unroll
-        for (int k = 0; k < NP; k++) k32[k] = (uint32_t)key[k];
-        if (SEARCH) {
-            learned_search_halves<NP, FULL>(v, k32, key, q);
-        } else {
-#pragma unroll
-            for (int k = 0; k < NP; k++) q[k] = 0;
-            pred_search_n<uint32_t, NP>(v.k32, q, v.n, k32);
-        }
-    } else {
-#pragma unroll
-        for (int k = 0; k < NP; k++) q[k] = 0;
-        pred_search_n<uint64_t, NP>(v.k64, q, v.n, key);
-    }
-    uint32_t r[NP];
-#pragma unroll
-    for (int k = 0; k < NP; k++) r[k] = v.code[q[k]];
-#pragma unroll
-    for (int k = 0; k < NP; k++) c[k] = ok[k] ? r[k] : 0u;
-}
-
-// Wave-bracketed Hilbert lookups for points in spatial order.  The NP
-// points of every lane of the wave (all lanes take part: the caller keeps
-// the wave together) have keys in [kmin, kmax]; two searches with those
-// wave-uniform keys -- binary search or the learned index, as the handle
-// is searched -- give the runs qlo and qhi that hold them.  When the
-// bracket spans at most 64 runs, the wave reads the bracket's starts and
-// codes once (a lane each) and every point finds its run by a binary search
-// over the lanes' registers: no memory access per point.  A wider bracket
-// (points in no order) takes the per-point search.  Exact either way: the
-// run of every key lies in [qlo, qhi].
-__device__ __forceinline__ uint32_t wave_min_u32(uint32_t v)
-{
-    for (int o = 32; o > 0; o >>= 1) v = min(v, (uint32_t)__shfl_xor((int)v, o, 64));
-    return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
-}
-
-__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v)
-{
-    for (int o = 32; o > 0; o >>= 1) v = max(v, (uint32_t)__shfl_xor((int)v, o, 64));
-    return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
-}
-
-// Binary search through a partitioned item's region: the last sample
-// start <= key in LDS, then the at most sS runs after it in global memory
-// (one or two cache lines) instead of a search over every run.
-template <int NP>
-__device__ __forceinline__ void hilbert_codes_region(const HilbView &v, const uint32_t *key,
-                                                     const bool *ok, uint32_t *c)
-{
-    int32_t j[NP];
-#pragma unroll
-    for (int k = 0; k < NP; k++) j[k] = 0;
-    for (int32_t len = v.sn; len > 1;) {
-        const int32_t half = len >> 1;
-#pragma unroll
-        for (int k = 0; k < NP; k++) j[k] = v.samp[j[k] + half] <= key[k] ? j[k] + half : j[k];
-        len -= half;
-    }
-    int32_t lo[NP], len[NP];
-#pragma unroll
-    for (int k = 0; k < NP; k++) {
-        lo[k] = v.sq0 + j[k] * v.sS;
-        len[k] = min(v.sS, v.sq1 + 1 - lo[k]);
-    }
-    pred_search_var4<NP>(v.k32, lo, len, key);
-    uint32_t r[NP];
-#pragma unroll
-    for (int k = 0; k < NP; k++) r[k] = v.code[lo[k]];
-#pragma unroll
-    for (int k = 0; k < NP; k++) c[k] = ok[k] ? r[k] : 0u;
-}
-
-template <int SEARCH, int NP, bool FULL = false>
-__device__ __forceinline__ void hilbert_codes_wave(const HilbView &v, const int32_t *xs,
-                                                   const int32_t *ys, uint32_t *c)
-{
-    if (v.extx == 0 || !v.k32) {  // empty handle; 64-bit keys take the plain path
-        hilbert_codes<SEARCH, NP, FULL>(v, xs, ys, c);
-        return;
-    }
-    bool ok[NP];
-    uint32_t key[NP];
-    uint32_t kmin = 0xffffffffu, kmax = 0u;
-#pragma unroll
-    for (int k = 0; k < NP; k++) {
-        int64_t dx = (int64_t)xs[k] - v.ox, dy = (int64_t)ys[k] - v.oy;
-        ok[k] = (uint64_t)dx < v.extx && (uint64_t)dy < v.exty;
-        uint32_t i = divmagic(ok[k] ? (uint32_t)dx : 0u, v.mag, v.shift);
-        uint32_t j = divmagic(ok[k] ? (uint32_t)dy : 0u, v.mag, v.shift);
-        key[k] = (uint32_t)hkey(v, i, j);
-        kmin = ok[k] ? min(kmin, key[k]) : kmin;
-        kmax = ok[k] ? max(kmax, key[k]) : kmax;
-    }
-    if constexpr (FULL && !SEARCH) {
-        if (v.samp) {  // a partitioned item's region
-            hilbert_codes_region<NP>(v, key, ok, c);
-            return;
-        }
-    }
-    kmin = wave_min_u32(kmin);
-    kmax = wave_max_u32(kmax);
-    if (kmax < kmin) {  // no point of the wave lies in the stored box
-#pragma unroll
-        for (int k = 0; k < NP; k++) c[k] = 0;
-        return;
-    }
-    // runs expected in [kmin, kmax] if they were spread evenly over the
-    // 4^L keys: far more than a wave holds means points in no spatial order
-    // (or spread over a partition region), where the bracket searches would
-    // only add to the per-point ones
-    if (((uint64_t)(kmax - kmin) * (uint64_t)v.n) >> (2 * v.L) > 1024) {
-        hilbert_codes<SEARCH, NP, FULL>(v, xs, ys, c);
-        return;
-    }
-    const int64_t qlo = SEARCH ? learned_search<uint32_t>(v, v.k32, kmin)
-                               : pred_search<uint32_t>(v.k32, 0, v.n, kmin);
-    const int64_t qhi = SEARCH ? learned_search<uint32_t>(v, v.k32, kmax)
-                               : pred_search<uint32_t>(v.k32, 0, v.n, kmax);
-    const int32_t w = (int32_t)__builtin_amdgcn_readfirstlane((int)(qhi - qlo + 1));
-    if (qhi - qlo + 1 > 64) {
-        // per point, a binary search restricted to the bracket; a learned
-        // index searches a bracket of more than 4096 runs through its own
-        // windows instead
-        int64_t q[NP];
-        if (SEARCH && qhi - qlo + 1 > 4096) {
-            uint64_t k64[NP];
-#pragma unroll
-            for (int k = 0; k < NP; k++) k64[k] = key[k];
-            learned_search_halves<NP, FULL>(v, key, k64, q);
-        } else {
-#pragma unroll
-            for (int k = 0; k < NP; k++) q[k] = qlo;
-            pred_search_n<uint32_t, NP>(v.k32, q, qhi - qlo + 1, key);
-        }
-        uint32_t r[NP];
-#pragma unroll
-        for (int k = 0; k < NP; k++) r[k] = v.code[q[k]];
-#pragma unroll
-        for (int k = 0; k < NP; k++) c[k] = ok[k] ? r[k] : 0u;
-        return;
-    }
-    const int lane = (int)(threadIdx.x & 63);
-    const int64_t mine = qlo + (lane < w ? lane : w - 1);
-    const uint32_t wstart = v.k32[mine];
-    const uint32_t wcode = v.code[mine];
-#pragma unroll
-    for (int k = 0; k < NP; k++) {
-        // last lane l < w with wstart(l) <= key: keys[qlo] <= kmin <= key
-        int lo = 0, len = w;
-        while (len > 1) {
-            const int half = len >> 1;
-            const uint32_t sv = (uint32_t)__shfl((int)wstart, lo + half, 64);
-            lo = sv <= key[k] ? lo + half : lo;
-            len -= half;
-        }
-        const uint32_t cv = (uint32_t)__shfl((int)wcode, lo, 64);
-        c[k] = ok[k] ? cv : 0u;
-    }
-}
-
-template <int LAYOUT, int NP>
-__device__ __forceinline__ void codes_of(const GridView &g, const HilbView &hv, const int32_t *xs,
-                                         const int32_t *ys, uint32_t *c)
-{
-    if (LAYOUT == 0) grid_codes<NP>(g, xs, ys, c);
-    else hilbert_codes<LAYOUT == 2 ? 1 : 0, NP>(hv, xs, ys, c);
-}
-
-// As codes_of, with the wave-bracketed lookups for the Hilbert layouts; every
-// lane of the wave must call it.
-template <int LAYOUT, int NP, bool FULL = false>
-__device__ __forceinline__ void codes_of_wave(const GridView &g, const HilbView &hv,
-                                              const int32_t *xs, const int32_t *ys, uint32_t *c)
-{
-    if (LAYOUT == 0) grid_codes<NP>(g, xs, ys, c);
-    else hilbert_codes_wave<LAYOUT == 2 ? 1 : 0, NP, FULL>(hv, xs, ys, c);
+    for (int k = 0; k < NP; k++)
+        if (c[k] & TILE_MIXED) c[k] = mixed_code<LEARNED>(v, xs[k], ys[k], c[k]);
 }
 
 struct Agg {
@@ -703,7 +549,9 @@ __device__ __forceinline__ uint32_t code_of(const GridView &g, const HilbView &h
                                             int32_t y)
 {
     if (LAYOUT == 0) return grid_code(g, x, y);
-    return hilbert_code<LAYOUT == 2 ? 1 : 0>(hv, x, y);
+    uint32_t c[1];
+    hilbert_codes<LAYOUT == 2, 1>(hv, &x, &y, c);
+    return c[0];
 }
 
 // A workgroup's LDS histogram into the outputs (zeroed before the launch):
@@ -722,28 +570,24 @@ __device__ __forceinline__ void flush_bins(const uint32_t *lcnt, const unsigned 
     }
 }
 
-// LDS-privatised histograms, added to the outputs once per workgroup
-template <int LAYOUT, bool VALS>
+// LDS-privatised histograms, added to the outputs once per workgroup (grids
+// whose directory does not fit LDS)
+template <bool VALS>
 __global__ __launch_bounds__(PROBE_BLOCK) void k_probe_lds(const int4 *__restrict__ xy4,
                                                            const longlong2 *__restrict__ v2,
                                                            const int32_t *__restrict__ xy,
                                                            const int64_t *__restrict__ vals,
-                                                           int64_t n, GridView g, HilbView hv,
+                                                           int64_t n, GridView g,
                                                            Agg A, int32_t np,
                                                            uint64_t *__restrict__ counts,
                                                            int64_t *__restrict__ sums)
 {
     extern __shared__ unsigned long long smem[];
-    __shared__ uint16_t s_htab[LAYOUT ? HILBERT_TAB : 1];
     unsigned long long *lsum = smem;
     uint32_t *lcnt = (uint32_t *)(smem + np);
     for (int p = threadIdx.x; p < np; p += PROBE_BLOCK) {
         lcnt[p] = 0;
         lsum[p] = 0;
-    }
-    if (LAYOUT) {
-        hilbert_tab_fill(s_htab, PROBE_BLOCK);
-        hv.tab = s_htab;
     }
     __syncthreads();
     const int64_t npairs = n >> 1;
@@ -770,7 +614,7 @@ __global__ __launch_bounds__(PROBE_BLOCK) void k_probe_lds(const int4 *__restric
             ys[2 * u + 1] = q[u].w;
         }
         uint32_t c[2 * PROBE_UNROLL];
-        codes_of<LAYOUT, 2 * PROBE_UNROLL>(g, hv, xs, ys, c);
+        grid_codes<2 * PROBE_UNROLL>(g, xs, ys, c);
 #pragma unroll
         for (int u = 0; u < PROBE_UNROLL; u++) {
             add_lds<VALS>(c[2 * u], vv[u].x, A, lcnt, lsum);
@@ -779,7 +623,7 @@ __global__ __launch_bounds__(PROBE_BLOCK) void k_probe_lds(const int4 *__restric
     }
     if ((n & 1) && blockIdx.x == 0 && threadIdx.x == 0) {
         int64_t k = n - 1;
-        uint32_t c = code_of<LAYOUT>(g, hv, xy[2 * k], xy[2 * k + 1]);
+        uint32_t c = grid_code(g, xy[2 * k], xy[2 * k + 1]);
         add_lds<VALS>(c, VALS ? vals[k] : 0, A, lcnt, lsum);
     }
     __syncthreads();
@@ -876,6 +720,13 @@ static void views(const sba_handle *h, GridView *g, HilbView *hv)
         hv->k32 = h->starts32;
         hv->k64 = h->starts;
         hv->code = h->run_code;
+        hv->dir = h->pdir;
+        hv->dl = h->dir_level;
+        hv->pre = h->shift >= 32 ? 0u : 1u;
+        hv->post = h->shift >= 32 ? (uint32_t)(h->shift - 32) : 0u;
+        const int64_t lim = (int64_t)1 << 31;
+        hv->fits32 = hv->ox >= -lim && hv->oy >= -lim && hv->ox + h->gw * h->s <= lim &&
+                     hv->oy + h->gh * h->s <= lim;
         hv->a = h->root_a;
         hv->nl = 1u << h->log2_leaves;
         hv->leaves = h->leaves;
@@ -887,12 +738,10 @@ static void views(const sba_handle *h, GridView *g, HilbView *hv)
 static int g_blocks_per_cu = 8;
 
 static int launch_items(const int32_t *xy, const int64_t *values, int64_t n, const sba_handle *h,
-                        int layout, bool part, uint64_t *counts, int64_t *sums, hipStream_t st,
-                        const PartRegions *regions = nullptr);
+                        int layout, int per_cu, uint64_t *counts, int64_t *sums, hipStream_t st);
 
 
-template <int LAYOUT>
-static int launch_layout(const int32_t *xy, const int64_t *values, int64_t n, const sba_handle *h,
+static int launch_lds(const int32_t *xy, const int64_t *values, int64_t n, const sba_handle *h,
                          uint64_t *counts, int64_t *sums, hipStream_t st)
 {
     GridView g;
@@ -908,20 +757,17 @@ static int launch_layout(const int32_t *xy, const int64_t *values, int64_t n, co
     if (nb < 1) nb = 1;
     const int4 *xy4 = (const int4 *)xy;
     const longlong2 *v2 = (const longlong2 *)values;
-    if (np <= LDS_MAX_POLYS) {
-        hipLaunchKernelGGL(k_zero_out, dim3(grid_for(np)), dim3(256), 0, st, counts,
-                           vals ? sums : nullptr, np);
-        size_t lds = (size_t)np * 12;
-        if (vals)
-            hipLaunchKernelGGL((k_probe_lds<LAYOUT, true>), dim3((unsigned)nb), dim3(PROBE_BLOCK), lds,
-                               st, xy4, v2, xy, values, n, g, hv, A, np, counts, sums);
-        else
-            hipLaunchKernelGGL((k_probe_lds<LAYOUT, false>), dim3((unsigned)nb), dim3(PROBE_BLOCK), lds,
-                               st, xy4, v2, xy, values, n, g, hv, A, np, counts, sums);
-        HIP_OK(hipGetLastError());
-        return 0;
-    }
-    return launch_items(xy, values, n, h, LAYOUT, false, counts, sums, st);
+    hipLaunchKernelGGL(k_zero_out, dim3(grid_for(np)), dim3(256), 0, st, counts,
+                       vals ? sums : nullptr, np);
+    size_t lds = (size_t)np * 12;
+    if (vals)
+        hipLaunchKernelGGL(k_probe_lds<true>, dim3((unsigned)nb), dim3(PROBE_BLOCK), lds, st, xy4,
+                           v2, xy, values, n, g, A, np, counts, sums);
+    else
+        hipLaunchKernelGGL(k_probe_lds<false>, dim3((unsigned)nb), dim3(PROBE_BLOCK), lds, st, xy4,
+                           v2, xy, values, n, g, A, np, counts, sums);
+    HIP_OK(hipGetLastError());
+    return 0;
 }
 
 
@@ -1725,8 +1571,7 @@ int range_launch(const int32_t *xy, const int64_t *values, int64_t n, const sba_
 }
 
 int items_launch(const int32_t *xy, const int64_t *values, int64_t n, const sba_handle *h,
-                 int32_t search, const PartRegions *regions, uint64_t *counts, int64_t *sums,
-                 hipStream_t st)
+                 int32_t search, uint64_t *counts, int64_t *sums, hipStream_t st)
 {
     if (h->n_polys == 0) return 0;
     int layout = 0;
@@ -1734,8 +1579,7 @@ int items_launch(const int32_t *xy, const int64_t *values, int64_t n, const sba_
         if (search == SBA_SEARCH_LEARNED && !h->leaves) return SBA_EINVAL;
         layout = search == SBA_SEARCH_LEARNED ? 2 : 1;
     }
-    return launch_items(xy, values, n, h, layout, true, counts, sums, st,
-                        layout == 1 ? regions : nullptr);
+    return launch_items(xy, values, n, h, layout, 2, counts, sums, st);
 }
 
 // Name of the kernel a range call launches ("" when it takes two passes).
@@ -1764,13 +1608,11 @@ int probe_launch(const int32_t *xy, const int64_t *values, int64_t n, const sba_
     }
     if (h->kind == SBA_KIND_GRID) {
         if (grid16_fits(h)) return launch_grid16(xy, values, n, h, counts, sums, st);
-        return launch_layout<0>(xy, values, n, h, counts, sums, st);
+        if (h->n_polys <= LDS_MAX_POLYS) return launch_lds(xy, values, n, h, counts, sums, st);
+        return launch_items(xy, values, n, h, 0, 1, counts, sums, st);
     }
-    if (search == SBA_SEARCH_LEARNED) {
-        if (!h->leaves) return SBA_EINVAL;
-        return launch_layout<2>(xy, values, n, h, counts, sums, st);
-    }
-    return launch_layout<1>(xy, values, n, h, counts, sums, st);
+    if (search == SBA_SEARCH_LEARNED && !h->leaves) return SBA_EINVAL;
+    return launch_items(xy, values, n, h, search == SBA_SEARCH_LEARNED ? 2 : 1, 1, counts, sums, st);
 }
 
 int lookup_launch(const sba_handle *h, const int64_t *ij, int64_t n, int32_t *ref, hipStream_t st)
@@ -1808,10 +1650,10 @@ extern "C" const char *sba_probe_kernel(const sba_handle *h, int with_values)
         return buf;
     }
     int layout = h->kind == SBA_KIND_GRID ? 0 : (h->search == SBA_SEARCH_LEARNED ? 2 : 1);
-    if (h->n_polys <= LDS_MAX_POLYS)
-        snprintf(buf, sizeof(buf), "k_probe_lds<%d, %s>", layout, v);
+    if (h->kind == SBA_KIND_GRID && h->n_polys <= LDS_MAX_POLYS)
+        snprintf(buf, sizeof(buf), "k_probe_lds<%s>", v);
     else
-        snprintf(buf, sizeof(buf), "k_probe_items<%d, %s, false>", layout, v);
+        snprintf(buf, sizeof(buf), "k_probe_items<%d, %s, 1>", layout, v);
     return buf;
 }
 
@@ -1900,8 +1742,6 @@ extern "C" int sba_debug_set_blocks_per_cu(int k)
 
 #define BATCH_ITEM (1 << 18)
 #define BATCH_PER_CU 4
-#define ITEM_MIN 4096
-#define ITEMS_PER_WG 8
 
 struct TaskDev {
     GridView g;
@@ -1916,7 +1756,6 @@ struct TaskDev {
     int32_t vx0, vy0, vx1, vy1;  // viewport [vx0, vx1] x [vy0, vy1] (inclusive)
     unsigned long long *counts;
     unsigned long long *sums;
-    PartRegions reg;             // the items kernel over partitioned points (bq NULL: none)
 };
 
 struct ItemDev {
@@ -1934,12 +1773,9 @@ __device__ __forceinline__ bool in_view(const TaskDev &T, int32_t x, int32_t y)
 // open addressing in LDS): the serving loop keeps its points bucketed, so the
 // points of one item come from a small area and meet few codes; a code that
 // finds no free slot within BATCH_PROBES steps goes to the outputs directly.
-// The item probe's table has ITEM_SLOTS slots (its items may hold points
-// in no order); the batch's has BATCH_SLOTS (bucketed points), which keeps
-// a batch workgroup's LDS small enough for several per compute unit.
-#define ITEM_SLOTS_LOG2 11
+// BATCH_SLOTS slots keep a batch workgroup's LDS small enough for several
+// per compute unit.
 #define BATCH_SLOTS_LOG2 10
-#define ITEM_SLOTS (1 << ITEM_SLOTS_LOG2)
 #define BATCH_SLOTS (1 << BATCH_SLOTS_LOG2)
 #define BATCH_PROBES 16
 #define BATCH_EMPTY 0xffffffffu
@@ -1977,9 +1813,8 @@ __device__ __forceinline__ void table_add(const CodeTable &H, uint32_t code, int
     add_global<VALS>(code, v, T.A, T.counts, T.sums, n);
 }
 
-// FMT (grid layout): the handle's format, as for grid_codes; FULL: as for
-// the learned search
-template <int LAYOUT, bool VALS, int FMT = 0, bool FULL = false>
+// FMT (grid layout): the handle's format, as for grid_codes
+template <int LAYOUT, bool VALS, int FMT = 0>
 __device__ __forceinline__ void batch_item(const TaskDev &T, int64_t lo, int64_t hi,
                                            const CodeTable &H)
 {
@@ -2032,7 +1867,7 @@ __device__ __forceinline__ void batch_item(const TaskDev &T, int64_t lo, int64_t
         if (LAYOUT == 0)
             grid_codes<2 * PROBE_UNROLL, FMT>(T.g, xs, ys, c);
         else
-            codes_of_wave<LAYOUT, 2 * PROBE_UNROLL, FULL>(T.g, T.hv, xs, ys, c);
+            hilbert_codes<LAYOUT == 2, 2 * PROBE_UNROLL>(T.hv, xs, ys, c);
         // a lane's points of the trip (pairs 64 apart) often share their code
         // when the input is in spatial order: runs of one code take one add
         uint32_t cur = c[0], run = 1;
@@ -2086,107 +1921,310 @@ __device__ __forceinline__ void table_flush(const CodeTable &H, const TaskDev &T
 }
 
 // One aggregate over all points when the polygon count is too large for
-// per-polygon LDS bins: workgroups take contiguous items (round robin, so
-// no counter is needed) and count each in the LDS table of cell codes; points
-// in spatial order (bucketed, Hilbert-sorted) meet few codes per item and
-// almost never reach global memory, points in no order fall back to a global
-// atomic per point once the table is full.
-// Items are dealt to the chip's 8 XCDs in contiguous eighths (workgroup b
-// runs on XCD b mod 8, the dispatcher's round robin), so the points the
-// workgroups of one XCD hold at a time come from one stretch of the input:
-// for spatially ordered or partitioned points, one region whose part of the
-// structure fits that XCD's L2.  The grid size is a multiple of 8.
-// The region of a partitioned item [lo, hi): the buckets of its first and
-// last points, the runs that hold their keys, and every S-th start of those
-// runs in LDS (S the smallest step that fits ITEM_SAMPLES of them).  Every
-// thread of the workgroup calls it; it returns after a barrier.
-#define ITEM_SAMPLES 4096
-__device__ __forceinline__ void stage_region(const TaskDev &T, int64_t lo, int64_t hi,
-                                             uint32_t *samp, int32_t *reg)
+// per-polygon LDS bins: one workgroup of 16 wavefronts per compute unit takes
+// chunks of points and counts them in LDS, in lines of 16 (COUNT: 32)
+// consecutive polygons' bins.  The lines are placed by a hash of their
+// number, first come first served; a point whose line found no place goes to
+// the outputs directly.
+//
+// What bounds it with points in no order is the additions to the outputs: they
+// are made at the memory side, about 16 G a second over the chip, two a point
+// (2e7 points of 40,000 polygons at 1 m: 2.45 ms, of which the lookups are
+// 0.5).  Lines hold the polygons that most of a unit's points meet, whatever
+// their order, and go out as whole cache lines, 16 additions in one.  A hash
+// table of single codes (2,048 slots a workgroup, four on a unit) overflowed
+// within an item of 4,096 such points and sent each slot out by itself.
+//
+// A bin with values is one 64-bit word, points above bit 44 and their values'
+// sum below it: at most FLUSH_POINTS are added before the bins go out.  The
+// points that need more than one directory entry and one addition (in mixed
+// blocks of the Hilbert layout, 9 in 100 at that size; of polygon sets; with
+// values outside [0, 2^24)) wait in a queue of the wavefront until a lane each can take 64 of
+// them: searched in lockstep with the others they made every wavefront step
+// through each search with all of its 512 points.
+//
+// The chunks of the input's k-th eighth go in turn to the workgroups of XCD k
+// (workgroup b runs on XCD b mod 8, the dispatcher's round robin), so the
+// points the workgroups of one XCD hold at a time come from one stretch of the
+// input: for spatially ordered or partitioned points, one region whose part of
+// the structure fits that XCD's L2 (a contiguous share a workgroup spread them
+// over the whole eighth).  The grid size is a multiple of 8.
+#define LINE_BLOCK 1024
+#define LINE_WAVES (LINE_BLOCK / 64)
+#define LINE_PROBES 4
+#define LINE_EMPTY 0xffffffffu
+#define CHUNK (LINE_WAVES * 64 * 2 * PROBE_UNROLL)  // points a workgroup takes at a time
+#define FLUSH_POINTS (1 << 19)  // below 2^20: a bin's count has 20 bits
+#define VAL_BITS 24
+#define SUM_BITS 44
+#define SLOWQ 128   // queued points of a wavefront
+
+template <bool VALS>
+struct LineBins {
+    typedef std::conditional_t<VALS, unsigned long long, uint32_t> Word;
+    static constexpr int LOG2 = VALS ? 4 : 5;
+    Word *bin;         // [lines << LOG2]
+    uint32_t *tag;     // [lines] line number or LINE_EMPTY
+    uint32_t lines;
+    bool direct;       // every line has its own place
+};
+
+// Workgroups per compute unit: one with all of its LDS for points in no known
+// order, two for partitioned points (a region meets few lines, and twice the
+// wavefronts hide twice the latency).
+static __host__ __device__ constexpr int line_count(int per_cu)
 {
-    if (threadIdx.x == 0) {
-        // last bucket b with start <= p: buckets may be empty, so this is
-        // the bucket that holds point p
-        auto bucket_of = [&](int64_t p) {
-            int32_t b = 0, len = 256;
-            while (len > 1) {
-                const int32_t half = len >> 1;
-                b = gld(T.reg.bstart + (int64_t)(b + half) * T.reg.bstride) <= p ? b + half : b;
-                len -= half;
-            }
-            return b;
-        };
-        const int32_t b0 = bucket_of(lo), b1 = bucket_of(hi - 1);
-        const int64_t q0 = gld(T.reg.bq + b0), q1 = gld(T.reg.bq + b1 + 1);
-        const int64_t m = q1 - q0 + 1;
-        const int64_t step = (m + ITEM_SAMPLES - 1) / ITEM_SAMPLES;
-        reg[0] = (int32_t)q0;
-        reg[1] = (int32_t)q1;
-        reg[2] = (int32_t)step;
-        reg[3] = (int32_t)((m + step - 1) / step);
-    }
-    __syncthreads();
-    const int32_t q0 = reg[0], step = reg[2], ns = reg[3];
-    for (int32_t j = threadIdx.x; j < ns; j += PROBE_BLOCK)
-        samp[j] = gld(T.hv.k32 + q0 + (int64_t)j * step);
-    __syncthreads();
+    // LDS less the Hilbert table, the queues and a little more
+    return (PROBE_LDS_BYTES / per_cu - HILBERT_TAB * 2 - LINE_WAVES * SLOWQ * 12 - 512) / (128 + 4);
 }
 
-// PART: the points come partitioned by region but in no order inside one
-// (the partitioned probe): nearly every lookup takes the plain search,
-// which keeps all its loads in flight per wave; otherwise the workgroup is
-// held to 4 waves per SIMD worth of registers, which points in spatial
-// order (bracketed lookups) turn into throughput.
-template <int LAYOUT, bool VALS, bool PART>
-__global__ __launch_bounds__(PROBE_BLOCK, PART ? 1 : 4) void k_probe_items(const TaskDev T0, int64_t item,
-                                                             int64_t n_items)
+// n points of polygon p < np with values' sum v (each value below 2^VAL_BITS)
+template <bool VALS>
+__device__ __forceinline__ void line_add(const LineBins<VALS> &B, uint32_t p, uint32_t n,
+                                         unsigned long long v, const TaskDev &T)
 {
-    __shared__ uint32_t s_key[ITEM_SLOTS];
-    __shared__ uint32_t s_cnt[ITEM_SLOTS];
-    __shared__ unsigned long long s_sum[ITEM_SLOTS];
-    __shared__ int s_full;
-    __shared__ uint16_t s_htab[LAYOUT ? HILBERT_TAB : 1];
-    constexpr bool REGIONS = PART && LAYOUT == 1;
-    __shared__ uint32_t s_samp[REGIONS ? ITEM_SAMPLES : 1];
-    __shared__ int32_t s_reg[4];
-    const CodeTable H{s_key, s_cnt, s_sum, &s_full, ITEM_SLOTS_LOG2};
-    for (int k = threadIdx.x; k < ITEM_SLOTS; k += PROBE_BLOCK) {
-        s_key[k] = BATCH_EMPTY;
-        s_cnt[k] = 0;
-        s_sum[k] = 0;
+    typedef typename LineBins<VALS>::Word Word;
+    constexpr uint32_t mask = (1u << LineBins<VALS>::LOG2) - 1u;
+    const uint32_t line = p >> LineBins<VALS>::LOG2;
+    const Word w = VALS ? (Word)(((unsigned long long)n << SUM_BITS) + v) : (Word)n;
+    uint32_t h = line;
+    if (!B.direct) {
+        h = __umulhi(line * 2654435761u, B.lines);
+        bool found = false;
+        for (int k = 0; k < LINE_PROBES; k++) {
+            uint32_t t = B.tag[h];
+            if (t == LINE_EMPTY) t = atomicCAS(&B.tag[h], LINE_EMPTY, line);
+            if (t == LINE_EMPTY || t == line) {
+                found = true;
+                break;
+            }
+            h = h + 1 == B.lines ? 0 : h + 1;
+        }
+        if (!found) {
+            gadd(&T.counts[p], n);
+            if (VALS) gadd(&T.sums[p], v);
+            return;
+        }
     }
-    if (threadIdx.x == 0) s_full = 0;
+    atomicAdd(&B.bin[(h << LineBins<VALS>::LOG2) | (p & mask)], w);
+}
+
+// the bins to the outputs and back to zero, the lines' places free again (every
+// place is seen: 130 KB take 16 rounds of 1024 lanes)
+template <bool VALS>
+__device__ __forceinline__ void line_flush(const LineBins<VALS> &B, const TaskDev &T)
+{
+    constexpr int LG = LineBins<VALS>::LOG2;
+    for (uint32_t k = threadIdx.x; k < B.lines << LG; k += LINE_BLOCK) {
+        const auto w = B.bin[k];
+        const uint32_t line = B.direct ? k >> LG : B.tag[k >> LG];
+        // the line's last bin frees its place (its 16 or 32 lanes are of one
+        // wavefront and have read the tag)
+        if (!B.direct && (k & ((1u << LG) - 1u)) == (1u << LG) - 1u) B.tag[k >> LG] = LINE_EMPTY;
+        if (w == 0) continue;
+        B.bin[k] = 0;
+        const uint32_t p = (line << LG) | (k & ((1u << LG) - 1u));
+        if (p >= T.A.np) continue;
+        if (VALS) {
+            gadd(&T.counts[p], (unsigned long long)w >> SUM_BITS);
+            gadd(&T.sums[p], (unsigned long long)w & ((1ull << SUM_BITS) - 1));
+        } else {
+            gadd(&T.counts[p], (unsigned long long)w);
+        }
+    }
+}
+
+template <int LAYOUT, bool VALS, int PER_CU>
+__global__ __launch_bounds__(LINE_BLOCK, 4) void k_probe_items(const TaskDev T0, int64_t chunks,
+                                                               int flush_every)
+{
+    extern __shared__ unsigned long long line_lds[];
+    __shared__ uint16_t s_htab[LAYOUT ? HILBERT_TAB : 1];
+    // queued points: their number in the launch, code or directory entry, and
+    // (32-bit keys) cell
+    __shared__ uint32_t s_queue[LINE_WAVES][LAYOUT ? 3 : 2][SLOWQ];
+    typedef typename LineBins<VALS>::Word Word;
+    constexpr int NL = line_count(PER_CU), LG = LineBins<VALS>::LOG2;
     TaskDev T = T0;
+    LineBins<VALS> B;
+    B.bin = (Word *)line_lds;
+    B.tag = (uint32_t *)(B.bin + ((size_t)NL << LG));
+    const uint32_t need = (T.A.np + (1u << LG) - 1u) >> LG;
+    B.direct = need <= (uint32_t)NL;
+    B.lines = B.direct ? need : (uint32_t)NL;
+    for (uint32_t k = threadIdx.x; k < B.lines << LG; k += LINE_BLOCK) B.bin[k] = 0;
+    for (uint32_t k = threadIdx.x; k < B.lines; k += LINE_BLOCK) B.tag[k] = LINE_EMPTY;
     if (LAYOUT) {
-        hilbert_tab_fill(s_htab, PROBE_BLOCK);
+        hilbert_tab_fill(s_htab, LINE_BLOCK);
         T.hv.tab = s_htab;
     }
     __syncthreads();
-    const int64_t nx = gridDim.x >> 3, per = (n_items + 7) >> 3;
-    const int64_t first = (int64_t)(blockIdx.x & 7) * per;
-    const int64_t last = min(first + per, n_items);
-    for (int64_t it = first + (blockIdx.x >> 3); it < last; it += nx) {
-        const int64_t lo = it * item, hi = min(lo + item, T.n);
-        if constexpr (REGIONS) {
-            if (T.reg.bq) {
-                stage_region(T, lo, hi, s_samp, s_reg);
-                T.hv.samp = s_samp;
-                T.hv.sq0 = s_reg[0];
-                T.hv.sq1 = s_reg[1];
-                T.hv.sS = s_reg[2];
-                T.hv.sn = s_reg[3];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    uint32_t *qpoint = s_queue[wave][0], *qcode = s_queue[wave][1],
+             *qcell = s_queue[wave][LAYOUT ? 2 : 0];
+    int queued = 0;  // the same in every lane of the wavefront
+    // n points of polygon code - 1, v their values' sum, each value in range
+    auto add = [&](uint32_t code, uint32_t n, unsigned long long v) {
+        if (code - 1u < T.A.np) line_add<VALS>(B, code - 1u, n, v, T);
+    };
+    auto one = [&](uint32_t p, long long v) {
+        if (p >= T.A.np) return;
+        if (!VALS || ((unsigned long long)v >> VAL_BITS) == 0) {
+            line_add<VALS>(B, p, 1, (unsigned long long)v, T);
+        } else {
+            gadd(&T.counts[p], 1ull);
+            gadd(&T.sums[p], (unsigned long long)v);
+        }
+    };
+    // the newest (up to 64) queued points, a lane each
+    auto drain = [&]() {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        const int m = queued < 64 ? queued : 64;
+        queued -= m;
+        if (lane < m) {
+            const int64_t i = qpoint[queued + lane];
+            const long long v = VALS ? gld(T.vals + i) : 0;
+            uint32_t c = qcode[queued + lane];
+            if (LAYOUT && (c & TILE_MIXED)) {
+                const uint32_t ij = qcell[queued + lane];
+                if (T.hv.k32)
+                    c = gld(T.hv.code +
+                            run_in_block<LAYOUT == 2, uint32_t>(
+                                T.hv, T.hv.k32, (uint32_t)hkey(T.hv, ij & 0xffffu, ij >> 16),
+                                (int32_t)(c & ~TILE_MIXED)));
+                else
+                    c = mixed_code<LAYOUT == 2>(T.hv, gld(T.xy + 2 * i), gld(T.xy + 2 * i + 1), c);
+            }
+            if (c < CODE_SET_BASE) {
+                one(c - 1u, v);
+            } else if (c - CODE_SET_BASE < T.A.n_sets) {
+                const uint32_t k = c - CODE_SET_BASE;
+                for (int64_t t = gld(T.A.set_off + k), e = gld(T.A.set_off + k + 1); t < e; t++)
+                    one((uint32_t)gld(T.A.set_ids + t), v);
             }
         }
-        batch_item<LAYOUT, VALS, 0, PART>(T, lo, hi, H);
-        __syncthreads();
-        table_flush(H, T, VALS);
-        __syncthreads();
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    const int4 *xy4 = (const int4 *)T.xy;
+    const longlong2 *v2 = (const longlong2 *)T.vals;
+    constexpr int NP = 2 * PROBE_UNROLL;
+    constexpr int64_t WB = 64 * PROBE_UNROLL;
+    const int64_t npairs = T.n >> 1;
+    if ((T.n & 1) && blockIdx.x == 0 && threadIdx.x == 0) {
+        const int64_t i = T.n - 1;
+        const uint32_t c = code_of<LAYOUT>(T.g, T.hv, T.xy[2 * i], T.xy[2 * i + 1]);
+        add_global<VALS>(c, VALS ? T.vals[i] : 0, T.A, T.counts, T.sums);
+    }
+    // each wave takes WB consecutive pairs of a chunk, so the points of one
+    // wave's trip are neighbours in the input; lanes past the end take a point
+    // no cell holds.  The chunk after next is loaded while one is counted.
+    int4 qn[PROBE_UNROLL];
+    longlong2 vn[PROBE_UNROLL];
+    const int64_t nx = gridDim.x >> 3, per = (chunks + 7) >> 3;
+    const int64_t first = (int64_t)(blockIdx.x & 7) * per + (blockIdx.x >> 3);
+    const int64_t last = min((int64_t)(blockIdx.x & 7) * per + per, chunks);
+    auto load = [&](int64_t ch) {
+#pragma unroll
+        for (int u = 0; u < PROBE_UNROLL; u++) {
+            const int64_t t = (ch * LINE_WAVES + wave) * WB + (int64_t)u * 64 + lane;
+            const bool in = ch < last && t < npairs;
+            qn[u] = in ? gld(xy4 + t) : make_int4(INT32_MIN, INT32_MIN, INT32_MIN, INT32_MIN);
+            vn[u] = (VALS && in) ? gld(v2 + t) : make_longlong2(0, 0);
+        }
+    };
+    load(first);
+    int done = 0;
+    for (int64_t ch = first; ch < last; ch += nx) {
+        {
+            const int64_t w0 = (ch * LINE_WAVES + wave) * WB;
+            int4 q[PROBE_UNROLL];
+            longlong2 vv[PROBE_UNROLL];
+#pragma unroll
+            for (int u = 0; u < PROBE_UNROLL; u++) {
+                q[u] = qn[u];
+                vv[u] = vn[u];
+            }
+            load(ch + nx);
+            int32_t xs[NP], ys[NP];
+#pragma unroll
+            for (int u = 0; u < PROBE_UNROLL; u++) {
+                xs[2 * u] = q[u].x;
+                ys[2 * u] = q[u].y;
+                xs[2 * u + 1] = q[u].z;
+                ys[2 * u + 1] = q[u].w;
+            }
+            uint32_t c[NP];
+            uint32_t cell[NP];
+            if (LAYOUT == 0) grid_codes<NP>(T.g, xs, ys, c);
+            else dir_codes<NP>(T.hv, xs, ys, c, cell);
+#pragma unroll
+            for (int k = 0; k < NP; k++) {
+                const long long v = (k & 1) ? vv[k >> 1].y : vv[k >> 1].x;
+                // not one polygon's code (sets lie above them, and mixed
+                // blocks' entries above those), or a large value
+                const bool slow = c[k] >= CODE_SET_BASE ||
+                                  (VALS && c[k] != 0 && ((unsigned long long)v >> VAL_BITS) != 0);
+                const uint64_t b = __ballot(slow);
+                if (b) {
+                    if (slow) {
+                        const int at = queued + __popcll(b & ((1ull << lane) - 1));
+                        qpoint[at] =
+                            2u * (uint32_t)(w0 + (int64_t)(k >> 1) * 64 + lane) + (uint32_t)(k & 1);
+                        qcode[at] = c[k];
+                        if (LAYOUT) qcell[at] = cell[k];
+                        c[k] = 0;
+                    }
+                    queued += __popcll(b);
+                    if (queued >= 64) drain();
+                }
+            }
+            // a lane's points of the trip (pairs 64 apart) often share their
+            // code when the input is in spatial order: runs take one add
+            uint32_t cur = c[0], run = 1;
+            unsigned long long rs = (unsigned long long)vv[0].x;
+#pragma unroll
+            for (int k = 1; k < NP; k++) {
+                const unsigned long long v =
+                    (unsigned long long)((k & 1) ? vv[k >> 1].y : vv[k >> 1].x);
+                if (c[k] == cur) {
+                    run++;
+                    rs += v;
+                } else {
+                    add(cur, run, rs);
+                    cur = c[k];
+                    run = 1;
+                    rs = v;
+                }
+            }
+            add(cur, run, rs);
+        }
+        if (++done == flush_every || ch + nx >= last) {  // the same in the whole workgroup
+            done = 0;
+            while (queued > 0) drain();
+            __syncthreads();
+            line_flush<VALS>(B, T);
+            __syncthreads();
+        }
     }
 }
 
+typedef void (*items_fn)(const TaskDev, int64_t, int);
+
+template <int PER_CU>
+static items_fn items_pick(int layout, bool vals)
+{
+    const items_fn kerns[6] = {k_probe_items<0, false, PER_CU>, k_probe_items<0, true, PER_CU>,
+                               k_probe_items<1, false, PER_CU>, k_probe_items<1, true, PER_CU>,
+                               k_probe_items<2, false, PER_CU>, k_probe_items<2, true, PER_CU>};
+    return kerns[layout * 2 + (vals ? 1 : 0)];
+}
+
 static int launch_items(const int32_t *xy, const int64_t *values, int64_t n, const sba_handle *h,
-                        int layout, bool part, uint64_t *counts, int64_t *sums, hipStream_t st,
-                        const PartRegions *regions)
+                        int layout, int per_cu, uint64_t *counts, int64_t *sums, hipStream_t st)
 {
     const bool vals = values != nullptr && sums != nullptr;
     TaskDev T{};
@@ -2199,35 +2237,27 @@ static int launch_items(const int32_t *xy, const int64_t *values, int64_t n, con
     T.vals = vals ? values : nullptr;
     T.counts = (unsigned long long *)counts;
     T.sums = vals ? (unsigned long long *)sums : nullptr;
-    if (regions && layout == 1 && h->starts32) T.reg = *regions;
-    // about ITEMS_PER_WG items per workgroup (even sizes keep the pairs
-    // aligned), so the round robin ends evenly
-    int64_t nb = std::max<int64_t>(
-        1, std::min<int64_t>((n + ITEM_MIN - 1) / ITEM_MIN, (int64_t)cu_count() * g_blocks_per_cu));
-    nb = (nb + 7) & ~(int64_t)7;  // whole rounds of the 8 XCDs
-    int64_t item = (n + nb * ITEMS_PER_WG - 1) / (nb * ITEMS_PER_WG);
-    item = std::max<int64_t>(ITEM_MIN, (item + 1) & ~(int64_t)1);
-    const int64_t n_items = (n + item - 1) / item;
     hipLaunchKernelGGL(k_zero_out, dim3(grid_for(h->n_polys)), dim3(256), 0, st, counts,
                        vals ? sums : nullptr, h->n_polys);
-    const dim3 grid((unsigned)nb);
-#define ITEMS_CASE(L, V, P)                                                                        \
-    hipLaunchKernelGGL((k_probe_items<L, V, P>), grid, dim3(PROBE_BLOCK), 0, st, T, item, n_items)
-    switch (layout * 4 + (vals ? 2 : 0) + (part ? 1 : 0)) {
-    case 0: ITEMS_CASE(0, false, false); break;
-    case 1: ITEMS_CASE(0, false, true); break;
-    case 2: ITEMS_CASE(0, true, false); break;
-    case 3: ITEMS_CASE(0, true, true); break;
-    case 4: ITEMS_CASE(1, false, false); break;
-    case 5: ITEMS_CASE(1, false, true); break;
-    case 6: ITEMS_CASE(1, true, false); break;
-    case 7: ITEMS_CASE(1, true, true); break;
-    case 8: ITEMS_CASE(2, false, false); break;
-    case 9: ITEMS_CASE(2, false, true); break;
-    case 10: ITEMS_CASE(2, true, false); break;
-    default: ITEMS_CASE(2, true, true); break;
+    const int lds = line_count(per_cu) * (128 + 4);
+    const items_fn kern = per_cu == 2 ? items_pick<2>(layout, vals) : items_pick<1>(layout, vals);
+    (void)hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    (void)hipGetLastError();
+    // queued points are numbered in 32 bits: at most 2^31 of them a launch
+    for (int64_t at = 0; at < n; at += (int64_t)1 << 31) {
+        T.n = std::min<int64_t>(n - at, (int64_t)1 << 31);
+        T.xy = xy + 2 * at;
+        if (vals) T.vals = values + at;
+        const int64_t chunks = (T.n + CHUNK - 1) / CHUNK;
+        int64_t nb = std::min<int64_t>(chunks, (int64_t)cu_count() * per_cu);
+        nb = (nb + 7) & ~(int64_t)7;  // whole rounds of the 8 XCDs
+        // a workgroup's bins go out after FLUSH_POINTS points at most; over
+        // partitioned points every few chunks, before lines of regions left
+        // behind fill the places
+        const int flush_every = per_cu == 2 ? 6 : FLUSH_POINTS / CHUNK;
+        hipLaunchKernelGGL(kern, dim3((unsigned)nb), dim3(LINE_BLOCK), lds, st, T, chunks,
+                           flush_every);
     }
-#undef ITEMS_CASE
     HIP_OK(hipGetLastError());
     return 0;
 }

@@ -149,6 +149,11 @@ struct sba_handle {
     uint32_t *starts32;  // [n_runs] same keys when 2*level <= 32 (else NULL)
     uint32_t *run_code;  // [n_runs] cell code of each run
     int64_t n_runs;
+    uint32_t *pdir;      // directory of square blocks of 2^(level - dir_level) cells a
+                         // side, 4^dir_level of them at block_index: the code of the run
+                         // that holds the whole block, else TILE_MIXED | the run that
+                         // holds its first key
+    int32_t dir_level;
     // learned index over starts
     int32_t log2_leaves;
     float root_a;        // leaf = floor((float)(key - root_k0) * root_a)
@@ -284,6 +289,14 @@ __host__ __device__ inline uint32_t hilbert_index_tab(int L, uint32_t i, uint32_
         fr = e >> 8;
     }
     return d;
+}
+
+// Place of block (ib, jb) in a directory of 2^dl x 2^dl blocks: rows of tiles
+// of 8 x 4 blocks, a 128-byte line each.
+__host__ __device__ inline uint32_t block_index(uint32_t ib, uint32_t jb, int dl)
+{
+    if (dl < 3) return (jb << dl) | ib;
+    return ((jb >> 2) << (dl + 2)) | ((ib >> 3) << 5) | ((jb & 3u) << 3) | (ib & 7u);
 }
 
 // Inverse of hilbert_index.
@@ -451,23 +464,9 @@ int probe_launch(const int32_t *xy, const int64_t *values, int64_t n, const sba_
                  int32_t search, uint64_t *counts, int64_t *sums, hipStream_t st);
 int lookup_launch(const sba_handle *h, const int64_t *ij, int64_t n, int32_t *ref, hipStream_t st);
 // the probe over contiguous items of points with an LDS table of cell codes
-// (any layout; for points in spatial order)
-// Points partitioned into 256 buckets by the top 8 bits of their Hilbert
-// keys (2L-bit keys, bucket = key >> bshift): bucket b starts at
-// bstart[b * bstride] of the partitioned array, and runs bq[b] .. bq[b + 1]
-// hold every key of bucket b (bq has 257 entries, on the device).
-struct PartRegions {
-    const int64_t *bq;
-    const int64_t *bstart;
-    int64_t bstride;
-    int32_t bshift;
-};
-
-// The item probe over partitioned points (regions: NULL, or the buckets of a
-// Hilbert handle's points for its binary search).
+// (any layout; for points in spatial order, or partitioned by region)
 int items_launch(const int32_t *xy, const int64_t *values, int64_t n, const sba_handle *h,
-                 int32_t search, const PartRegions *regions, uint64_t *counts, int64_t *sums,
-                 hipStream_t st);
+                 int32_t search, uint64_t *counts, int64_t *sums, hipStream_t st);
 int range_launch(const int32_t *xy, const int64_t *values, int64_t n, const sba_handle *h,
                  const sba_handle *hb, uint64_t *counts, int64_t *sums, uint64_t *bcounts,
                  int64_t *bsums, hipStream_t st);
