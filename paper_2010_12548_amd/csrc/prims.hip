@@ -1,6 +1,7 @@
 // prims.hip -- device-wide exclusive scan and LSD radix sort used by the
 // approximation build.  Written for 64-lane wavefronts.
 #include "sba_internal.h"
+#include "wave.h"
 
 #define SCAN_BLOCK 256
 #define SCAN_ITEMS 8
@@ -286,62 +287,47 @@ int scan_exclusive_i64_multi(int m, const int64_t *const *in, int64_t *const *ou
 // ---------------------------------------------------------------- radix sort
 //
 // One pass per digit of RB = 8 bits (9 bits for sorts under RS_SMALL keys
-// whose key width then needs one pass fewer), least significant first.  A
-// block sorts a tile of RS_TILE keys: each of its 4 waves owns a contiguous
-// quarter and walks it 64 keys at a time; lanes with equal digits find each
-// other with RB ballots, so the rank of a key among equal digits before it is
-// a popcount and the pass is stable.  Keys are staged in LDS in digit order
-// and written out in runs, which keeps the global writes coalesced.
+// whose key width then needs one pass fewer), least significant first.  Each
+// wave of a block owns a contiguous part of the block's tile and walks it 64
+// keys at a time; lanes with equal digits find each other with RB ballots, so
+// the rank of a key among equal digits before it is a popcount and the pass is
+// stable.  Keys are staged in LDS in digit order and written out in runs,
+// which keeps the global writes coalesced.
 
 #define RS_BLOCK 256
 #define RS_WAVES (RS_BLOCK / 64)
-// A block sorts ROUNDS x 256 keys: 4 rounds below RS_SMALL keys, so that a
-// sort of a few hundred thousand keys still spreads over every compute unit;
-// 8 below RS_MID (28 KB of LDS per block, which fits beside a persistent probe
-// holding the rest of a CU); 16 for larger inputs (fewer offsets to scan).
+// Below RS_SMALL keys a block sorts 4 x 256 of them, so that a sort of a few
+// hundred thousand keys still spreads over every compute unit; larger sorts
+// take the tiles of RB_TILE keys further down.
 #define RS_SMALL (4 << 20)
-#define RS_MID (64 << 20)
+#define RS_ROUNDS 4
+#define RS_TILE (RS_BLOCK * RS_ROUNDS)
 #define RS_RADIX 256       // digits of an 8-bit pass (the partition pass uses these offsets)
 
 // per block and digit: count, laid out digit-major (hist[d * nblocks + b]).
-// A workgroup counts `span` consecutive tiles, TPW at a time with every key
-// of the TPW tiles loaded before any is counted (one tile a workgroup for
-// small sorts).  No digit totals are formed
-// here: each row scan below leaves its digit's total, and the scatter adds
-// the totals of the lower digits itself, so the pass needs no device-wide
-// atomics and no zeroed counters.
-template <typename K, int ROUNDS, int TPW, int RB>
+// No digit totals are formed here: each row scan below leaves its digit's
+// total, and the scatter adds the totals of the lower digits itself, so the
+// pass needs no device-wide atomics and no zeroed counters.
+template <typename K, int RB>
 __global__ __launch_bounds__(RS_BLOCK) void k_rs_hist(const K *keys, int64_t n, int shift,
-                                                      int64_t *hist, int64_t nblocks, int64_t span)
+                                                      int64_t *hist, int64_t nblocks)
 {
-    constexpr int RS_TILE = RS_BLOCK * ROUNDS, RADIX = 1 << RB;
-    __shared__ uint32_t h[TPW][RADIX];
-    const int64_t bfirst = (int64_t)blockIdx.x * span;
-    const int64_t blast = min(bfirst + span, nblocks);
-    for (int64_t b0 = bfirst; b0 < blast; b0 += TPW) {
+    constexpr int RADIX = 1 << RB;
+    __shared__ uint32_t h[RADIX];
+    for (int d = threadIdx.x; d < RADIX; d += RS_BLOCK) h[d] = 0;
+    __syncthreads();
+    uint32_t dg[RS_ROUNDS];
 #pragma unroll
-        for (int t = 0; t < TPW; t++)
-            for (int d = threadIdx.x; d < RADIX; d += RS_BLOCK) h[t][d] = 0;
-        __syncthreads();
-        uint32_t dg[TPW * ROUNDS];
-#pragma unroll
-        for (int k = 0; k < TPW * ROUNDS; k++) {
-            const int64_t idx = b0 * RS_TILE + (int64_t)k * RS_BLOCK + threadIdx.x;
-            dg[k] = (idx < n && b0 + k / ROUNDS < blast)
-                        ? (uint32_t)(keys[idx] >> shift) & (uint32_t)(RADIX - 1)
-                        : RADIX;
-        }
-#pragma unroll
-        for (int k = 0; k < TPW * ROUNDS; k++)
-            if (dg[k] < RADIX) atomicAdd(&h[k / ROUNDS][dg[k]], 1u);
-        __syncthreads();
-#pragma unroll
-        for (int t = 0; t < TPW; t++) {
-            if (b0 + t < blast)
-                for (int d = threadIdx.x; d < RADIX; d += RS_BLOCK)
-                    hist[(int64_t)d * nblocks + b0 + t] = h[t][d];
-        }
+    for (int k = 0; k < RS_ROUNDS; k++) {
+        const int64_t idx = (int64_t)blockIdx.x * RS_TILE + (int64_t)k * RS_BLOCK + threadIdx.x;
+        dg[k] = idx < n ? (uint32_t)(keys[idx] >> shift) & (uint32_t)(RADIX - 1) : RADIX;
     }
+#pragma unroll
+    for (int k = 0; k < RS_ROUNDS; k++)
+        if (dg[k] < RADIX) atomicAdd(&h[dg[k]], 1u);
+    __syncthreads();
+    for (int d = threadIdx.x; d < RADIX; d += RS_BLOCK)
+        hist[(int64_t)d * nblocks + blockIdx.x] = h[d];
 }
 
 // In place, one workgroup per digit d: the exclusive scan of digit d's block
@@ -418,14 +404,14 @@ int rs_offsets_launch(int64_t *hist, int64_t nblocks, const unsigned long long *
     return 0;
 }
 
-template <typename K, bool HAS_VALS, int ROUNDS, int RB>
+template <typename K, bool HAS_VALS, int RB>
 __global__ __launch_bounds__(RS_BLOCK) void k_rs_scatter(const K *keys, const uint32_t *vals,
                                                          K *okeys, uint32_t *ovals,
                                                          int64_t n, int shift,
                                                          const int64_t *goff, int64_t nblocks,
                                                          const int64_t *rowtot)
 {
-    constexpr int RS_ROUNDS = ROUNDS, RS_TILE = RS_BLOCK * ROUNDS, RADIX = 1 << RB;
+    constexpr int RADIX = 1 << RB;
     constexpr int DPT = RADIX / RS_BLOCK;  // digits per thread, consecutive
     constexpr uint32_t DMASK = RADIX - 1;
     __shared__ uint32_t wcnt[RS_WAVES][RADIX];
@@ -533,9 +519,247 @@ __global__ __launch_bounds__(RS_BLOCK) void k_rs_scatter(const K *keys, const ui
     }
 }
 
-static int rs_rounds(int64_t n) { return n < RS_SMALL ? 4 : (n < RS_MID ? 8 : 16); }
+// Sorts of RS_SMALL keys and more.  What bounds a pass is the traffic, keys and
+// values read and written once and the keys read once more for the counts, as
+// long as the stores leave in long runs and enough loads are in flight: a
+// block of 512 takes 8192 keys (32 keys of a digit on average, 128 bytes and
+// more), loads all of them before ranking any, and stages keys and values one
+// after the other in the same LDS (64 KB for 8 bytes each, and 11 KB of
+// counters), so two blocks fit a compute unit.
+//
+// Counts: a workgroup counts a span of consecutive tiles and leaves, per tile
+// and digit, the keys of that digit in the span's tiles before it (whole rows
+// of 256 digits; digit-major rows made every count a store and a load of its
+// own line), and the span's totals, which one small kernel scans per digit.
+//
+// 5e7 keys of 8 bytes with 4-byte values, a pass: scatter 496 us with tiles of
+// 2048 keys staged together, 412 with 4096, 352 with 8192 (1.2 GB, 3.4 TB/s);
+// counts and offsets 209, then 120 us.
+#define RB_BLOCK 512
+#define RB_WAVES (RB_BLOCK / 64)
+#define RB_ROUNDS 16
+#define RB_TILE (RB_BLOCK * RB_ROUNDS)
+#define RB_SPANS 1024    // at most
 
-static int64_t rs_blocks(int64_t n) { return (n + RS_BLOCK * rs_rounds(n) - 1) / (RS_BLOCK * rs_rounds(n)); }
+// 16 bytes of keys (a caller's array is aligned to its keys only)
+typedef uint32_t keys16_t __attribute__((ext_vector_type(4), aligned(4)));
+
+template <typename K>
+__global__ __launch_bounds__(256) void k_rb_hist(const K *__restrict__ keys, int64_t n, int shift,
+                                                 uint32_t *__restrict__ hist,
+                                                 int64_t *__restrict__ spans, int64_t nblocks,
+                                                 int64_t span)
+{
+    constexpr int PER = 16 / sizeof(K);        // keys of a load
+    constexpr int LOADS = RB_TILE / 256 / PER;
+    __shared__ uint32_t h[2][256];
+    const int tid = threadIdx.x;
+    h[0][tid] = h[1][tid] = 0;
+    __syncthreads();
+    const int64_t b0 = (int64_t)blockIdx.x * span, b1 = min(b0 + span, nblocks);
+    // the next tile is loaded while one is counted (a partial tile key by key)
+    keys16_t q[LOADS], qn[LOADS];
+    auto load = [&](int64_t b, keys16_t *v) {
+        if (b < b1 && (b + 1) * RB_TILE <= n) {
+#pragma unroll
+            for (int u = 0; u < LOADS; u++)
+                v[u] = ((const keys16_t *)(keys + b * RB_TILE))[u * 256 + tid];
+        }
+    };
+    load(b0, qn);
+    uint32_t run = 0;
+    int ph = 0;
+    for (int64_t b = b0; b < b1; b++, ph ^= 1) {
+#pragma unroll
+        for (int u = 0; u < LOADS; u++) q[u] = qn[u];
+        load(b + 1, qn);
+        if ((b + 1) * RB_TILE <= n) {
+#pragma unroll
+            for (int u = 0; u < LOADS; u++) {
+#pragma unroll
+                for (int e = 0; e < PER; e++) {
+                    const K key = sizeof(K) == 8
+                                      ? (K)(((uint64_t)q[u][(2 * e + 1) & 3] << 32) |
+                                             q[u][(2 * e) & 3])
+                                      : (K)q[u][e];
+                    atomicAdd(&h[ph][(uint32_t)(key >> shift) & 255u], 1u);
+                }
+            }
+        } else {
+            for (int64_t t = b * RB_TILE + tid; t < n; t += 256)
+                atomicAdd(&h[ph][(uint32_t)(keys[t] >> shift) & 255u], 1u);
+        }
+        __syncthreads();
+        // the other set of counters takes the next tile meanwhile; this one is
+        // clear before the tile after it (a barrier lies between)
+        const uint32_t c = h[ph][tid];
+        h[ph][tid] = 0;
+        hist[b * 256 + tid] = run;
+        run += c;
+    }
+    spans[(int64_t)blockIdx.x * 256 + tid] = run;
+}
+
+// spans[s][d] becomes the keys of digit d in the spans before s, rowtot[d] the
+// digit's keys: 16 digits a workgroup, 64 parts of the spans each.
+__global__ __launch_bounds__(1024) void k_rb_spans(int64_t *spans, int nspans, int64_t *rowtot)
+{
+    __shared__ int64_t part[64][16];
+    const int d = blockIdx.x * 16 + (threadIdx.x & 15), p = threadIdx.x >> 4;
+    const int per = (nspans + 63) / 64, s0 = p * per, s1 = min(s0 + per, nspans);
+    int64_t v[RB_SPANS / 64], sum = 0;
+#pragma unroll
+    for (int k = 0; k < RB_SPANS / 64; k++) {
+        v[k] = s0 + k < s1 ? spans[(int64_t)(s0 + k) * 256 + d] : 0;
+        sum += v[k];
+    }
+    part[p][threadIdx.x & 15] = sum;
+    __syncthreads();
+    if (threadIdx.x < 16) {
+        int64_t run = 0;
+        for (int q = 0; q < 64; q++) {
+            const int64_t c = part[q][threadIdx.x];
+            part[q][threadIdx.x] = run;
+            run += c;
+        }
+        rowtot[d] = run;
+    }
+    __syncthreads();
+    int64_t run = part[p][threadIdx.x & 15];
+#pragma unroll
+    for (int k = 0; k < RB_SPANS / 64; k++) {
+        if (s0 + k < s1) spans[(int64_t)(s0 + k) * 256 + d] = run;
+        run += v[k];
+    }
+}
+
+template <typename K, typename V, bool HAS_VALS>
+__global__ __launch_bounds__(RB_BLOCK) void k_rb_scatter(
+    const K *__restrict__ keys, const V *__restrict__ vals, K *__restrict__ okeys,
+    V *__restrict__ ovals, int64_t n, int shift, const uint32_t *__restrict__ hist,
+    const int64_t *__restrict__ spans, int64_t span, const int64_t *__restrict__ rowtot)
+{
+    __shared__ uint32_t wcnt[RB_WAVES][256];
+    __shared__ uint32_t bdoff[256];
+    // output position of the block's first key of each digit, less that
+    // key's place in the staged tile
+    __shared__ int64_t dbase[256];
+    __shared__ uint64_t wsum[4];
+    typedef std::conditional_t<(HAS_VALS && sizeof(V) > sizeof(K)), V, K> Stage;
+    __shared__ Stage stage[RB_TILE];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int64_t tbase = (int64_t)blockIdx.x * RB_TILE;
+    const int tn = (int)min((int64_t)RB_TILE, n - tbase);
+    K kk[RB_ROUNDS];
+    V vv[HAS_VALS ? RB_ROUNDS : 1];
+#pragma unroll
+    for (int q = 0; q < RB_ROUNDS; q++) {
+        const int t = (w * RB_ROUNDS + q) * 64 + lane;
+        kk[q] = t < tn ? keys[tbase + t] : (K)0;
+    }
+    if (HAS_VALS) {
+#pragma unroll
+        for (int q = 0; q < RB_ROUNDS; q++) {
+            const int t = (w * RB_ROUNDS + q) * 64 + lane;
+            vv[q] = t < tn ? vals[tbase + t] : (V)0;
+        }
+    }
+    for (int k = tid; k < RB_WAVES * 256; k += RB_BLOCK) (&wcnt[0][0])[k] = 0;
+    // the keys of lower digits, and of this digit in the tiles before
+    uint64_t rt = 0, incl = 0;
+    if (tid < 256) {
+        rt = (uint64_t)rowtot[tid];
+        incl = wave_scan<OpAdd>(rt);
+        if (lane == 63) wsum[w] = incl;
+    }
+    __syncthreads();
+    if (tid < 256) {
+        uint64_t below = incl - rt;
+        for (int k = 0; k < w; k++) below += wsum[k];
+        dbase[tid] = (int64_t)below + spans[(int64_t)(blockIdx.x / span) * 256 + tid] +
+                     hist[(int64_t)blockIdx.x * 256 + tid];
+    }
+    const uint64_t lt = (lane == 0) ? 0ull : ((~0ull) >> (64 - lane));
+    const uint32_t lt_lo = (uint32_t)lt, lt_hi = (uint32_t)(lt >> 32);
+    uint32_t loc[RB_ROUNDS];
+#pragma unroll
+    for (int q = 0; q < RB_ROUNDS; q++) {
+        const bool valid = (w * RB_ROUNDS + q) * 64 + lane < tn;
+        const uint32_t d = (uint32_t)(kk[q] >> shift) & 255u;
+        const uint64_t vb = __ballot(valid);
+        uint32_t lo = (uint32_t)vb, hi = (uint32_t)(vb >> 32);
+#pragma unroll
+        for (int b = 0; b < 8; b++) {
+            const int32_t s = (int32_t)(d << (31 - b));
+            const uint64_t bal = __ballot(s < 0);
+            const uint32_t m = (uint32_t)(s >> 31);
+            lo &= ~((uint32_t)bal ^ m);
+            hi &= ~((uint32_t)(bal >> 32) ^ m);
+        }
+        const uint32_t before = __popc(lo & lt_lo) + __popc(hi & lt_hi);
+        const uint32_t old = wcnt[w][d];
+        loc[q] = old + before;
+        __builtin_amdgcn_wave_barrier();
+        if (valid && before == 0) wcnt[w][d] = old + __popc(lo) + __popc(hi);
+        __builtin_amdgcn_wave_barrier();
+    }
+    __syncthreads();
+    // the tile's count of each digit, the waves' shares before one another,
+    // and the digits' places in the staged tile
+    uint32_t c = 0, ci = 0;
+    if (tid < 256) {
+#pragma unroll
+        for (int k = 0; k < RB_WAVES; k++) {
+            const uint32_t u = wcnt[k][tid];
+            wcnt[k][tid] = c;
+            c += u;
+        }
+        ci = wave_scan<OpAdd>(c);
+        if (lane == 63) wsum[w] = ci;
+    }
+    __syncthreads();
+    if (tid < 256) {
+        uint32_t excl = ci - c;
+        for (int k = 0; k < w; k++) excl += (uint32_t)wsum[k];
+        bdoff[tid] = excl;
+        dbase[tid] -= (int64_t)excl;
+    }
+    __syncthreads();
+    K *sk = (K *)stage;
+#pragma unroll
+    for (int q = 0; q < RB_ROUNDS; q++) {
+        if ((w * RB_ROUNDS + q) * 64 + lane < tn) {
+            const uint32_t d = (uint32_t)(kk[q] >> shift) & 255u;
+            loc[q] += bdoff[d] + wcnt[w][d];
+            sk[loc[q]] = kk[q];
+        }
+    }
+    __syncthreads();
+    int64_t g[RB_ROUNDS];
+#pragma unroll
+    for (int q = 0; q < RB_ROUNDS; q++) {
+        const int i = q * RB_BLOCK + tid;
+        g[q] = 0;
+        if (i < tn) {
+            const K key = sk[i];
+            g[q] = dbase[(uint32_t)(key >> shift) & 255u] + i;
+            okeys[g[q]] = key;
+        }
+    }
+    if (HAS_VALS) {
+        __syncthreads();
+        V *sv = (V *)stage;
+#pragma unroll
+        for (int q = 0; q < RB_ROUNDS; q++)
+            if ((w * RB_ROUNDS + q) * 64 + lane < tn) sv[loc[q]] = vv[q];
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < RB_ROUNDS; q++) {
+            const int i = q * RB_BLOCK + tid;
+            if (i < tn) ovals[g[q]] = sv[i];
+        }
+    }
+}
 
 // digit width of a sort of n keys of `bits` bits: 9 where that saves a pass
 // for the small sorts (the build's), else 8
@@ -544,64 +768,93 @@ static int rs_digit_bits(int64_t n, int bits)
     return (n < RS_SMALL && (bits + 8) / 9 < (bits + 7) / 8) ? 9 : 8;
 }
 
-// one pass over digit (keys >> shift) & (2^RB - 1)
-template <typename K, int ROUNDS, int RB>
-static int rs_pass_t(const K *ka, const uint32_t *va, K *kb, uint32_t *vb, int64_t n, int shift,
-                     int64_t *goff, int64_t nblocks, int64_t *rowtot, hipStream_t st)
+// a sort's counters
+struct SortWs {
+    int64_t nblocks = 0, span = 1, nspans = 0;
+    int rb = 8;
+    int64_t *goff = nullptr;    // small: [digits][nblocks]; large: [nspans][256]
+    uint32_t *hist = nullptr;   // large: [nblocks][256]
+    int64_t *rowtot = nullptr;  // [digits]
+};
+
+static int sort_ws_get(SortWs &S, int64_t n, int bits, hipStream_t st, Workspace *ws)
 {
-    // tiles per counting workgroup: one while there are at most 2048 tiles
-    // (every tile its own workgroup), else 16 keys a thread and at most about
-    // 2048 workgroups
-    if (nblocks <= 2048) {
-        hipLaunchKernelGGL((k_rs_hist<K, ROUNDS, 1, RB>), dim3((unsigned)nblocks), dim3(RS_BLOCK),
-                           0, st, ka, n, shift, goff, nblocks, (int64_t)1);
+    S.rb = rs_digit_bits(n, bits);
+    if (n < RS_SMALL) {
+        S.nblocks = (n + RS_TILE - 1) / RS_TILE;
+        RC(tmp_get(ws, &S.goff, S.nblocks << S.rb, st));
     } else {
-        constexpr int TPW = 16 / ROUNDS;
-        const int64_t span = TPW * ((nblocks + TPW * 2048 - 1) / (TPW * 2048));
-        hipLaunchKernelGGL((k_rs_hist<K, ROUNDS, TPW, RB>),
-                           dim3((unsigned)((nblocks + span - 1) / span)), dim3(RS_BLOCK), 0, st, ka,
-                           n, shift, goff, nblocks, span);
+        S.nblocks = (n + RB_TILE - 1) / RB_TILE;
+        S.span = (S.nblocks + RB_SPANS - 1) / RB_SPANS;
+        S.nspans = (S.nblocks + S.span - 1) / S.span;
+        RC(tmp_get(ws, &S.goff, S.nspans * 256, st));
+        RC(tmp_get(ws, &S.hist, S.nblocks * 256, st));
     }
-    hipLaunchKernelGGL(k_rs_rowscan, dim3(1u << RB), dim3(RS_BLOCK), 0, st, goff, nblocks, rowtot);
-    if (va)
-        hipLaunchKernelGGL((k_rs_scatter<K, true, ROUNDS, RB>), dim3((unsigned)nblocks),
-                           dim3(RS_BLOCK), 0, st, ka, va, kb, vb, n, shift, goff, nblocks, rowtot);
-    else
-        hipLaunchKernelGGL((k_rs_scatter<K, false, ROUNDS, RB>), dim3((unsigned)nblocks),
-                           dim3(RS_BLOCK), 0, st, ka, va, kb, vb, n, shift, goff, nblocks, rowtot);
-    return hipGetLastError() == hipSuccess ? 0 : SBA_EDEVICE;
+    return tmp_get(ws, &S.rowtot, (int64_t)1 << S.rb, st);
 }
 
-template <typename K>
-static int rs_pass(const K *ka, const uint32_t *va, K *kb, uint32_t *vb, int64_t n, int shift,
-                   int rb, int64_t *goff, int64_t nblocks, int64_t *rowtot, hipStream_t st)
+static void sort_ws_put(SortWs &S, hipStream_t st, Workspace *ws)
 {
-    const int r = rs_rounds(n);
-    if (r == 4)
-        return rb == 9 ? rs_pass_t<K, 4, 9>(ka, va, kb, vb, n, shift, goff, nblocks, rowtot, st)
-                       : rs_pass_t<K, 4, 8>(ka, va, kb, vb, n, shift, goff, nblocks, rowtot, st);
-    if (r == 8) return rs_pass_t<K, 8, 8>(ka, va, kb, vb, n, shift, goff, nblocks, rowtot, st);
-    return rs_pass_t<K, 16, 8>(ka, va, kb, vb, n, shift, goff, nblocks, rowtot, st);
+    tmp_put(ws, S.goff, st);
+    if (S.hist) tmp_put(ws, S.hist, st);
+    tmp_put(ws, S.rowtot, st);
+}
+
+template <typename K, bool HAS, int RB>
+static void rs_small_pass(const K *ka, const uint32_t *va, K *kb, uint32_t *vb, int64_t n,
+                          int shift, const SortWs &S, hipStream_t st)
+{
+    const dim3 nb((unsigned)S.nblocks), blk(RS_BLOCK);
+    hipLaunchKernelGGL((k_rs_hist<K, RB>), nb, blk, 0, st, ka, n, shift, S.goff, S.nblocks);
+    hipLaunchKernelGGL(k_rs_rowscan, dim3(1u << RB), blk, 0, st, S.goff, S.nblocks, S.rowtot);
+    hipLaunchKernelGGL((k_rs_scatter<K, HAS, RB>), nb, blk, 0, st, ka, va, kb, vb, n, shift, S.goff,
+                       S.nblocks, S.rowtot);
+}
+
+// one pass over digit (keys >> shift) & (2^rb - 1)
+template <typename K, typename V>
+static int rs_pass(const K *ka, const V *va, K *kb, V *vb, int64_t n, int shift, const SortWs &S,
+                   hipStream_t st)
+{
+    if (n < RS_SMALL) {
+        if constexpr (sizeof(V) == 4) {
+            if (va && S.rb == 9) rs_small_pass<K, true, 9>(ka, va, kb, vb, n, shift, S, st);
+            else if (va) rs_small_pass<K, true, 8>(ka, va, kb, vb, n, shift, S, st);
+            else if (S.rb == 9) rs_small_pass<K, false, 9>(ka, va, kb, vb, n, shift, S, st);
+            else rs_small_pass<K, false, 8>(ka, va, kb, vb, n, shift, S, st);
+        }
+    } else {
+        hipLaunchKernelGGL(k_rb_hist<K>, dim3((unsigned)S.nspans), dim3(256), 0, st, ka, n, shift,
+                           S.hist, S.goff, S.nblocks, S.span);
+        hipLaunchKernelGGL(k_rb_spans, dim3(16), dim3(1024), 0, st, S.goff, (int)S.nspans,
+                           S.rowtot);
+        if (va)
+            hipLaunchKernelGGL((k_rb_scatter<K, V, true>), dim3((unsigned)S.nblocks),
+                               dim3(RB_BLOCK), 0, st, ka, va, kb, vb, n, shift, S.hist, S.goff,
+                               S.span, S.rowtot);
+        else
+            hipLaunchKernelGGL((k_rb_scatter<K, V, false>), dim3((unsigned)S.nblocks),
+                               dim3(RB_BLOCK), 0, st, ka, va, kb, vb, n, shift, S.hist, S.goff,
+                               S.span, S.rowtot);
+    }
+    return hipGetLastError() == hipSuccess ? 0 : SBA_EDEVICE;
 }
 
 int radix_sort_u64(uint64_t *keys, uint32_t *vals, int64_t n, int bits, hipStream_t st,
                    Workspace *ws)
 {
     if (n <= 1 || bits <= 0) return 0;
-    const int64_t nblocks = rs_blocks(n);
     uint64_t *k2 = nullptr;
     uint32_t *v2 = nullptr;
-    int64_t *goff = nullptr, *rowtot = nullptr;
+    SortWs S;
     int rc = tmp_get(ws, &k2, n, st);
     if (!rc && vals) rc = tmp_get(ws, &v2, n, st);
-    const int rb = rs_digit_bits(n, bits);
-    if (!rc) rc = tmp_get(ws, &goff, nblocks << rb, st);
-    if (!rc) rc = tmp_get(ws, &rowtot, (int64_t)1 << rb, st);
-    const int passes = (bits + rb - 1) / rb;
+    if (!rc) rc = sort_ws_get(S, n, bits, st, ws);
+    const int passes = (bits + S.rb - 1) / S.rb;
     uint64_t *ka = keys, *kb = k2;
     uint32_t *va = vals, *vb = v2;
     for (int p = 0; p < passes && !rc; p++) {
-        rc = rs_pass(ka, va, kb, vb, n, rb * p, rb, goff, nblocks, rowtot, st);
+        rc = rs_pass(ka, va, kb, vb, n, S.rb * p, S, st);
         if (rc) break;
         uint64_t *tk = ka; ka = kb; kb = tk;
         uint32_t *tv = va; va = vb; vb = tv;
@@ -615,8 +868,7 @@ int radix_sort_u64(uint64_t *keys, uint32_t *vals, int64_t n, int bits, hipStrea
     }
     tmp_put(ws, k2, st);
     tmp_put(ws, v2, st);
-    tmp_put(ws, goff, st);
-    tmp_put(ws, rowtot, st);
+    sort_ws_put(S, st, ws);
     return rc;
 }
 
@@ -625,20 +877,17 @@ static int radix_sort_ws(K **keys, uint32_t **vals, int64_t n, int bits, Workspa
 {
     if (n <= 1 || bits <= 0) return 0;
     hipStream_t st = ws.stream();
-    const int64_t nblocks = rs_blocks(n);
     K *k2 = nullptr;
     uint32_t *v2 = nullptr;
-    int64_t *goff = nullptr, *rowtot = nullptr;
+    SortWs S;
     RC(ws.alloc(&k2, n));
     if (vals && *vals) RC(ws.alloc(&v2, n));
-    const int rb = rs_digit_bits(n, bits);
-    RC(ws.alloc(&goff, nblocks << rb));
-    RC(ws.alloc(&rowtot, (int64_t)1 << rb));
-    const int passes = (bits + rb - 1) / rb;
+    RC(sort_ws_get(S, n, bits, st, &ws));
+    const int passes = (bits + S.rb - 1) / S.rb;
     K *ka = *keys, *kb = k2;
     uint32_t *va = vals ? *vals : nullptr, *vb = v2;
     for (int p = 0; p < passes; p++) {
-        RC(rs_pass(ka, va, kb, vb, n, rb * p, rb, goff, nblocks, rowtot, st));
+        RC(rs_pass(ka, va, kb, vb, n, S.rb * p, S, st));
         std::swap(ka, kb);
         std::swap(va, vb);
     }
@@ -646,8 +895,7 @@ static int radix_sort_ws(K **keys, uint32_t **vals, int64_t n, int bits, Workspa
     // go back to the workspace
     ws.put(kb);
     if (vb) ws.put(vb);
-    ws.put(goff);
-    ws.put(rowtot);
+    sort_ws_put(S, st, &ws);
     *keys = ka;
     if (vals && *vals) *vals = va;
     return 0;

@@ -19,6 +19,7 @@
 #include <vector>
 
 #include "sba_internal.h"
+#include "wave.h"
 #include "build_state.h"
 #include "sets.h"
 
@@ -221,50 +222,6 @@ __device__ __forceinline__ uint4 edge_row_item(const Edge &E, int32_t j, bool cr
 
 #define EB 256       // lanes per workgroup, at most one edge each
 #define EROWS 1024   // rows a workgroup's edges may span to share LDS counters
-
-// v from the lane that the DPP control names, 0 where there is none
-template <int CTRL, int ROWS>
-__device__ __forceinline__ uint32_t dpp0(uint32_t v)
-{
-    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, false);
-}
-
-struct OpAdd {
-    template <typename T>
-    __device__ static T f(T a, T b) { return a + b; }
-};
-struct OpMax {
-    template <typename T>
-    __device__ static T f(T a, T b) { return a > b ? a : b; }
-};
-
-// inclusive scan over the wavefront (identity 0; every lane takes part):
-// shifts of 1, 2, 4, 8 inside the rows of 16 lanes, then the rows' last lanes
-// broadcast, all in the vector ALU; a chain of six cross-lane reads through
-// LDS takes ten times as long
-template <typename OP>
-__device__ __forceinline__ uint32_t wave_scan(uint32_t v)
-{
-    v = OP::f(v, dpp0<0x111, 0xf>(v));
-    v = OP::f(v, dpp0<0x112, 0xf>(v));
-    v = OP::f(v, dpp0<0x114, 0xf>(v));
-    v = OP::f(v, dpp0<0x118, 0xf>(v));
-    v = OP::f(v, dpp0<0x142, 0xa>(v));
-    v = OP::f(v, dpp0<0x143, 0xc>(v));
-    return v;
-}
-
-template <typename OP>
-__device__ __forceinline__ uint64_t wave_scan(uint64_t v)
-{
-    const int lane = threadIdx.x & 63;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint64_t u = __shfl_up((unsigned long long)v, o, 64);
-        if (lane >= o) v = OP::f(v, u);
-    }
-    return v;
-}
 
 // inclusive scan over a workgroup of BLOCK lanes; *tot receives the whole.
 // wsum: BLOCK / 64 words of LDS.
