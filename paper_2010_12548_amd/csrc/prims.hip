@@ -404,9 +404,9 @@ int rs_offsets_launch(int64_t *hist, int64_t nblocks, const unsigned long long *
     return 0;
 }
 
-template <typename K, bool HAS_VALS, int RB>
-__global__ __launch_bounds__(RS_BLOCK) void k_rs_scatter(const K *keys, const uint32_t *vals,
-                                                         K *okeys, uint32_t *ovals,
+template <typename K, typename V, bool HAS_VALS, int RB>
+__global__ __launch_bounds__(RS_BLOCK) void k_rs_scatter(const K *keys, const V *vals,
+                                                         K *okeys, V *ovals,
                                                          int64_t n, int shift,
                                                          const int64_t *goff, int64_t nblocks,
                                                          const int64_t *rowtot)
@@ -420,7 +420,7 @@ __global__ __launch_bounds__(RS_BLOCK) void k_rs_scatter(const K *keys, const ui
     // key's place in the staged tile
     __shared__ int64_t dbase[RADIX];
     __shared__ K skeys[RS_TILE];
-    __shared__ uint32_t svals[HAS_VALS ? RS_TILE : 1];
+    __shared__ V svals[HAS_VALS ? RS_TILE : 1];
 
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int d0 = threadIdx.x * DPT;
@@ -448,7 +448,7 @@ __global__ __launch_bounds__(RS_BLOCK) void k_rs_scatter(const K *keys, const ui
     const int64_t wbase = tbase + (int64_t)w * (64 * RS_ROUNDS);
     const uint64_t lt = (lane == 0) ? 0ull : ((~0ull) >> (64 - lane));
     K kk[RS_ROUNDS];
-    uint32_t vv[RS_ROUNDS];
+    V vv[RS_ROUNDS];
     uint32_t loc[RS_ROUNDS];
 #pragma unroll
     for (int q = 0; q < RS_ROUNDS; q++) {
@@ -800,15 +800,15 @@ static void sort_ws_put(SortWs &S, hipStream_t st, Workspace *ws)
     tmp_put(ws, S.rowtot, st);
 }
 
-template <typename K, bool HAS, int RB>
-static void rs_small_pass(const K *ka, const uint32_t *va, K *kb, uint32_t *vb, int64_t n,
-                          int shift, const SortWs &S, hipStream_t st)
+template <typename K, typename V, bool HAS, int RB>
+static void rs_small_pass(const K *ka, const V *va, K *kb, V *vb, int64_t n, int shift,
+                          const SortWs &S, hipStream_t st)
 {
     const dim3 nb((unsigned)S.nblocks), blk(RS_BLOCK);
     hipLaunchKernelGGL((k_rs_hist<K, RB>), nb, blk, 0, st, ka, n, shift, S.goff, S.nblocks);
     hipLaunchKernelGGL(k_rs_rowscan, dim3(1u << RB), blk, 0, st, S.goff, S.nblocks, S.rowtot);
-    hipLaunchKernelGGL((k_rs_scatter<K, HAS, RB>), nb, blk, 0, st, ka, va, kb, vb, n, shift, S.goff,
-                       S.nblocks, S.rowtot);
+    hipLaunchKernelGGL((k_rs_scatter<K, V, HAS, RB>), nb, blk, 0, st, ka, va, kb, vb, n, shift,
+                       S.goff, S.nblocks, S.rowtot);
 }
 
 // one pass over digit (keys >> shift) & (2^rb - 1)
@@ -817,12 +817,10 @@ static int rs_pass(const K *ka, const V *va, K *kb, V *vb, int64_t n, int shift,
                    hipStream_t st)
 {
     if (n < RS_SMALL) {
-        if constexpr (sizeof(V) == 4) {
-            if (va && S.rb == 9) rs_small_pass<K, true, 9>(ka, va, kb, vb, n, shift, S, st);
-            else if (va) rs_small_pass<K, true, 8>(ka, va, kb, vb, n, shift, S, st);
-            else if (S.rb == 9) rs_small_pass<K, false, 9>(ka, va, kb, vb, n, shift, S, st);
-            else rs_small_pass<K, false, 8>(ka, va, kb, vb, n, shift, S, st);
-        }
+        if (va && S.rb == 9) rs_small_pass<K, V, true, 9>(ka, va, kb, vb, n, shift, S, st);
+        else if (va) rs_small_pass<K, V, true, 8>(ka, va, kb, vb, n, shift, S, st);
+        else if (S.rb == 9) rs_small_pass<K, V, false, 9>(ka, va, kb, vb, n, shift, S, st);
+        else rs_small_pass<K, V, false, 8>(ka, va, kb, vb, n, shift, S, st);
     } else {
         hipLaunchKernelGGL(k_rb_hist<K>, dim3((unsigned)S.nspans), dim3(256), 0, st, ka, n, shift,
                            S.hist, S.goff, S.nblocks, S.span);
@@ -909,6 +907,65 @@ int radix_sort_u64_ws(uint64_t **keys, uint32_t **vals, int64_t n, int bits, Wor
 int radix_sort_u32_ws(uint32_t **keys, uint32_t **vals, int64_t n, int bits, Workspace &ws)
 {
     return radix_sort_ws(keys, vals, n, bits, ws);
+}
+
+// keys with 64-bit values that stay where they are: the first pass reads vals,
+// the sorted ones are left in a buffer of ws
+template <typename K>
+static int radix_sort_vals_ws(K **keys, const int64_t *vals, int64_t **out, int64_t n, int bits,
+                              Workspace &ws)
+{
+    hipStream_t st = ws.stream();
+    int64_t *v1 = nullptr, *v2 = nullptr;
+    RC(ws.alloc(&v1, n));
+    if (n <= 1 || bits <= 0) {
+        HIP_OK(hipMemcpyAsync(v1, vals, sizeof(int64_t) * n, hipMemcpyDeviceToDevice, st));
+        *out = v1;
+        return 0;
+    }
+    K *k2 = nullptr;
+    SortWs S;
+    RC(ws.alloc(&k2, n));
+    RC(sort_ws_get(S, n, bits, st, &ws));
+    const int passes = (bits + S.rb - 1) / S.rb;
+    if (passes > 1) RC(ws.alloc(&v2, n));
+    K *ka = *keys, *kb = k2;
+    const int64_t *va = vals;
+    int64_t *vb = v1, *spare = v2;
+    for (int p = 0; p < passes; p++) {
+        RC(rs_pass(ka, va, kb, vb, n, S.rb * p, S, st));
+        std::swap(ka, kb);
+        va = vb;
+        std::swap(vb, spare);
+    }
+    ws.put(kb);
+    if (vb) ws.put(vb);
+    sort_ws_put(S, st, &ws);
+    *keys = ka;
+    *out = const_cast<int64_t *>(va);
+    return 0;
+}
+
+int radix_sort_vals_ws(uint64_t **keys, const int64_t *vals, int64_t **out, int64_t n, int bits,
+                       Workspace &ws)
+{
+    return radix_sort_vals_ws<uint64_t>(keys, vals, out, n, bits, ws);
+}
+
+int radix_sort_vals_ws(uint32_t **keys, const int64_t *vals, int64_t **out, int64_t n, int bits,
+                       Workspace &ws)
+{
+    return radix_sort_vals_ws<uint32_t>(keys, vals, out, n, bits, ws);
+}
+
+int radix_sort_keys_ws(uint64_t **keys, int64_t n, int bits, Workspace &ws)
+{
+    return radix_sort_ws(keys, (uint32_t **)nullptr, n, bits, ws);
+}
+
+int radix_sort_keys_ws(uint32_t **keys, int64_t n, int bits, Workspace &ws)
+{
+    return radix_sort_ws(keys, (uint32_t **)nullptr, n, bits, ws);
 }
 
 extern "C" int sba_debug_radix_sort(uint64_t *keys, uint32_t *vals, int64_t n, int32_t bits,

@@ -384,6 +384,14 @@ int radix_sort_u64(uint64_t *keys, uint32_t *vals, int64_t n, int bits, hipStrea
 int radix_sort_u64_ws(uint64_t **keys, uint32_t **vals, int64_t n, int bits, Workspace &ws);
 // 32-bit keys (bits <= 32)
 int radix_sort_u32_ws(uint32_t **keys, uint32_t **vals, int64_t n, int bits, Workspace &ws);
+// keys alone, or with 64-bit values that are read only: the sorted values go
+// to a new buffer of ws, *out
+int radix_sort_keys_ws(uint64_t **keys, int64_t n, int bits, Workspace &ws);
+int radix_sort_keys_ws(uint32_t **keys, int64_t n, int bits, Workspace &ws);
+int radix_sort_vals_ws(uint64_t **keys, const int64_t *vals, int64_t **out, int64_t n, int bits,
+                       Workspace &ws);
+int radix_sort_vals_ws(uint32_t **keys, const int64_t *vals, int64_t **out, int64_t n, int bits,
+                       Workspace &ws);
 
 // In place: hist[d * nblocks + b] (per block b the count of digit d, 256
 // digits) becomes the position of block b's first key of digit d in the
