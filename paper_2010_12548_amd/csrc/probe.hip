@@ -669,7 +669,7 @@ __global__ void k_lookup(const int64_t *ij, int64_t n, GridView g, HilbView hv, 
 
 // ---------------------------------------------------------------- host
 
-static int cu_count()
+int cu_count()
 {
     static int cached[64] = {0};
     int dev = 0;

@@ -467,6 +467,9 @@ inline unsigned grid_for(int64_t n, int block = 256)
     return (unsigned)g;
 }
 
+// compute units of the current device (probe.hip)
+int cu_count();
+
 // Probe entry points (probe.hip).
 int probe_launch(const int32_t *xy, const int64_t *values, int64_t n, const sba_handle *h,
                  int32_t search, uint64_t *counts, int64_t *sums, hipStream_t st);
