@@ -31,6 +31,12 @@
 #define PROBE_BLOCK 256
 #define PROBE_UNROLL 4
 #define LDS_MAX_POLYS 4096
+// Calls of up to this many points look their cells up in memory, a pair a lane:
+// staging a directory in LDS (up to 128 KB a workgroup) and a trip through the
+// pipeline take 8 to 13 us whatever the points.  2e4 points over 260 polygons at
+// 10 m: 13.0 us staged, 4.8 this way; 131,072: 13.5 and 8.9; 262,144: 14.8 and
+// 14.4; 524,288: 18 and 26.
+#define SMALL_POINTS (1 << 17)
 
 struct GridView {
     int64_t ox, oy;        // coordinate of the stored box's first cell
@@ -571,8 +577,8 @@ __device__ __forceinline__ void flush_bins(const uint32_t *lcnt, const unsigned 
 }
 
 // LDS-privatised histograms, added to the outputs once per workgroup (grids
-// whose directory does not fit LDS)
-template <bool VALS>
+// whose directory does not fit LDS, and calls of few points, UNROLL 1)
+template <bool VALS, int UNROLL>
 __global__ __launch_bounds__(PROBE_BLOCK) void k_probe_lds(const int4 *__restrict__ xy4,
                                                            const longlong2 *__restrict__ v2,
                                                            const int32_t *__restrict__ xy,
@@ -592,31 +598,31 @@ __global__ __launch_bounds__(PROBE_BLOCK) void k_probe_lds(const int4 *__restric
     __syncthreads();
     const int64_t npairs = n >> 1;
     const int64_t stride = (int64_t)gridDim.x * PROBE_BLOCK;
-    // PROBE_UNROLL pairs per lane per trip: the stream loads of the trip are
-    // issued together, then the cell lookups of all 2*PROBE_UNROLL points
+    // UNROLL pairs per lane per trip: the stream loads of the trip are
+    // issued together, then the cell lookups of all 2 * UNROLL points
     // (batched, see grid_codes); latency is hidden by the other waves
     for (int64_t t0 = (int64_t)blockIdx.x * PROBE_BLOCK + threadIdx.x; t0 < npairs;
-         t0 += stride * PROBE_UNROLL) {
-        int4 q[PROBE_UNROLL];
-        longlong2 vv[PROBE_UNROLL];
+         t0 += stride * UNROLL) {
+        int4 q[UNROLL];
+        longlong2 vv[UNROLL];
 #pragma unroll
-        for (int u = 0; u < PROBE_UNROLL; u++) {
+        for (int u = 0; u < UNROLL; u++) {
             int64_t t = t0 + (int64_t)u * stride;
             q[u] = t < npairs ? xy4[t] : make_int4(INT32_MIN, INT32_MIN, INT32_MIN, INT32_MIN);
             vv[u] = (VALS && t < npairs) ? v2[t] : make_longlong2(0, 0);
         }
-        int32_t xs[2 * PROBE_UNROLL], ys[2 * PROBE_UNROLL];
+        int32_t xs[2 * UNROLL], ys[2 * UNROLL];
 #pragma unroll
-        for (int u = 0; u < PROBE_UNROLL; u++) {
+        for (int u = 0; u < UNROLL; u++) {
             xs[2 * u] = q[u].x;
             ys[2 * u] = q[u].y;
             xs[2 * u + 1] = q[u].z;
             ys[2 * u + 1] = q[u].w;
         }
-        uint32_t c[2 * PROBE_UNROLL];
-        grid_codes<2 * PROBE_UNROLL>(g, xs, ys, c);
+        uint32_t c[2 * UNROLL];
+        grid_codes<2 * UNROLL>(g, xs, ys, c);
 #pragma unroll
-        for (int u = 0; u < PROBE_UNROLL; u++) {
+        for (int u = 0; u < UNROLL; u++) {
             add_lds<VALS>(c[2 * u], vv[u].x, A, lcnt, lsum);
             add_lds<VALS>(c[2 * u + 1], vv[u].y, A, lcnt, lsum);
         }
@@ -759,13 +765,12 @@ static int launch_lds(const int32_t *xy, const int64_t *values, int64_t n, const
     const longlong2 *v2 = (const longlong2 *)values;
     hipLaunchKernelGGL(k_zero_out, dim3(grid_for(np)), dim3(256), 0, st, counts,
                        vals ? sums : nullptr, np);
-    size_t lds = (size_t)np * 12;
-    if (vals)
-        hipLaunchKernelGGL(k_probe_lds<true>, dim3((unsigned)nb), dim3(PROBE_BLOCK), lds, st, xy4,
-                           v2, xy, values, n, g, A, np, counts, sums);
-    else
-        hipLaunchKernelGGL(k_probe_lds<false>, dim3((unsigned)nb), dim3(PROBE_BLOCK), lds, st, xy4,
-                           v2, xy, values, n, g, A, np, counts, sums);
+    const size_t lds = (size_t)np * 12;
+    const auto kern = n <= SMALL_POINTS
+                          ? (vals ? k_probe_lds<true, 1> : k_probe_lds<false, 1>)
+                          : (vals ? k_probe_lds<true, PROBE_UNROLL> : k_probe_lds<false, PROBE_UNROLL>);
+    hipLaunchKernelGGL(kern, dim3((unsigned)nb), dim3(PROBE_BLOCK), lds, st, xy4, v2, xy, values, n,
+                       g, A, np, counts, sums);
     HIP_OK(hipGetLastError());
     return 0;
 }
@@ -1607,7 +1612,8 @@ int probe_launch(const int32_t *xy, const int64_t *values, int64_t n, const sba_
         return 0;
     }
     if (h->kind == SBA_KIND_GRID) {
-        if (grid16_fits(h)) return launch_grid16(xy, values, n, h, counts, sums, st);
+        const bool few = n <= SMALL_POINTS && h->n_polys <= LDS_MAX_POLYS;
+        if (!few && grid16_fits(h)) return launch_grid16(xy, values, n, h, counts, sums, st);
         if (h->n_polys <= LDS_MAX_POLYS) return launch_lds(xy, values, n, h, counts, sums, st);
         return launch_items(xy, values, n, h, 0, 1, counts, sums, st);
     }
