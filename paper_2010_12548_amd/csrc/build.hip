@@ -566,7 +566,7 @@ __global__ void k_square_classify(const int64_t *seg_beg, const int64_t *seg_end
                                   int64_t gh, const int64_t *mt, int tl, int sl, int64_t tw,
                                   int64_t n_sq, uint32_t *code, int64_t *mixed)
 {
-    int64_t u = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / G;
+    int64_t u = ((int64_t)xcd_block() * blockDim.x + threadIdx.x) / G;
     int lane = threadIdx.x & (G - 1);
     if (u >= n_sq) return;  // whole groups leave together (G divides the block)
     const int side_log2 = mt ? sl : tl;
@@ -607,6 +607,172 @@ __global__ void k_square_classify(const int64_t *seg_beg, const int64_t *seg_end
     }
 }
 
+// The same for big tiles (2^tl >= 64 cells): a workgroup takes regions of 2^tl
+// rows and Q squares side by side -- the sub-tiles of a mixed tile (mt), or 16
+// tiles of a tile row -- 256 rows at a time.  Each row is searched once for the
+// region's first cell, a lane a row, its next SQ_WIN segments go to LDS, and
+// the squares find theirs there (rows with more segments in the region fall
+// back to a search in memory).  What bounds it is those searches' and windows'
+// lines from beyond the L2, so neighbouring regions go to one XCD.  49,000 tiles
+// of 256 x 256 cells and 1.95M sub-tiles of 16 x 16 over 56,590 rows: 245 and 295
+// us with a search in memory for every row of every square; 114 and 132 with one
+// a row and region; 79 and 109 with regions in order on each XCD (windows of 8:
+// 78 and 151).
+#define SQ_WIN 4
+#define SQ_MAX 2048   // squares of a workgroup
+#define SQ_Q 16       // tiles side by side of one region
+
+struct SquareGeo {
+    const int64_t *seg_beg, *seg_end;
+    const int32_t *seg_x0, *seg_x1;
+    const uint32_t *seg_code;
+    int64_t gw, gh, tw, th;
+    const int64_t *mt;
+    int tl, sl;
+    int qlog;        // log2 of the squares side by side in a region
+    int64_t regions; // mixed tiles, or tile rows times groups of tiles
+};
+
+__global__ __launch_bounds__(256) void k_squares(SquareGeo G, uint32_t *code, int64_t *mixed)
+{
+    __shared__ int32_t wx0[256][SQ_WIN + 1], wx1[256][SQ_WIN + 1];
+    __shared__ uint32_t wcode[256][SQ_WIN + 1];
+    __shared__ int64_t sfirst[256], send[256];
+    extern __shared__ uint32_t sq_lds[];
+    const uint32_t block = xcd_block();
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int rows = 1 << G.tl, side = G.mt ? G.sl : G.tl;
+    const int Q = 1 << G.qlog, strips = rows >> side;
+    const int rpb = rows < 256 ? 256 >> G.tl : 1;       // regions of a workgroup
+    const int nsq = rpb * strips << G.qlog;
+    const uint32_t groups = (uint32_t)((G.tw + SQ_Q - 1) / SQ_Q);
+    uint32_t *lo_s = sq_lds, *hi_s = sq_lds + nsq;
+    for (int k = tid; k < nsq; k += 256) {
+        lo_s[k] = 0xffffffffu;
+        hi_s[k] = 0;
+    }
+    // first cell and row of region g of the workgroup
+    // (tiles and regions are fewer than 2^31, rows and columns at most 2^21)
+    auto origin = [&](int g, int32_t *x0, int32_t *r0) {
+        const uint32_t k = block * (uint32_t)rpb + (uint32_t)g;
+        if (k >= (uint32_t)G.regions) {
+            *x0 = (int32_t)G.gw;
+            *r0 = (int32_t)G.gh;
+            return false;
+        }
+        const uint32_t t = G.mt ? (uint32_t)G.mt[k] : k, m = G.mt ? (uint32_t)G.tw : groups;
+        const uint32_t ty = t / m, tx = t - ty * m;
+        *x0 = (int32_t)((G.mt ? tx : tx * SQ_Q) << G.tl);
+        *r0 = (int32_t)(ty << G.tl);
+        return true;
+    };
+    for (int c0 = 0; c0 < (rows < 256 ? 256 : rows); c0 += 256) {
+        __syncthreads();
+        {   // each lane a row: its last segment at or before the region's first cell
+            const int g = rows < 256 ? tid >> G.tl : 0;
+            int32_t X, R;
+            origin(g, &X, &R);
+            const int32_t r = R + (rows < 256 ? tid & (rows - 1) : c0 + tid);
+            int64_t a = 0, e = 0;
+            if (r < G.gh && X < G.gw) {
+                a = G.seg_beg[r];
+                e = G.seg_end[r];
+                int64_t lo = a, hi = e;
+                while (lo < hi) {
+                    const int64_t mid = (lo + hi) >> 1;
+                    if (G.seg_x0[mid] <= X) lo = mid + 1; else hi = mid;
+                }
+                a = lo > a ? lo - 1 : a;
+            }
+            sfirst[tid] = a;
+            send[tid] = e;
+        }
+        __syncthreads();
+        for (int k = tid; k < 256 * SQ_WIN; k += 256) {
+            const int row = k / SQ_WIN, u = k % SQ_WIN;
+            const int64_t t = sfirst[row] + u;
+            const bool in = t < send[row];
+            wx0[row][u] = in ? G.seg_x0[t] : INT32_MAX;
+            wx1[row][u] = in ? G.seg_x1[t] : 0;
+            wcode[row][u] = in ? G.seg_code[t] : 0u;
+        }
+        __syncthreads();
+        // a wavefront takes 64 rows, 64 / Q a pass, a lane a square
+        const int q = lane & (Q - 1), rw = 64 >> G.qlog;
+        const int g = rows < 256 ? (w * 64) >> G.tl : 0;
+        int32_t X, R;
+        origin(g, &X, &R);
+        const int32_t gw = (int32_t)G.gw, gh = (int32_t)G.gh;
+        const int32_t cx0 = X + (q << side), cx1 = min(cx0 + (1 << side), gw);
+        const int rin = (rows < 256 ? (w * 64) & (rows - 1) : c0 + w * 64);  // in the region
+        uint32_t lo_c = 0xffffffffu, hi_c = 0;
+        for (int p = 0; p < 64; p += rw) {
+            const int y = p + (lane >> G.qlog), row = w * 64 + y;
+            if (R + rin + y < gh && cx0 < gw) {
+                // segments of the window that start at or before the square
+                int n = 0;
+#pragma unroll
+                for (int b = SQ_WIN / 2; b > 0; b >>= 1)
+                    if (wx0[row][n + b - 1] <= cx0) n += b;
+                if (wx0[row][n] <= cx0) n++;
+                uint32_t c;
+                if (n == SQ_WIN && sfirst[row] + SQ_WIN < send[row]) {
+                    const int64_t e = send[row];
+                    int64_t lo = sfirst[row] + SQ_WIN, hi = e;
+                    while (lo < hi) {
+                        const int64_t mid = (lo + hi) >> 1;
+                        if (G.seg_x0[mid] <= cx0) lo = mid + 1; else hi = mid;
+                    }
+                    if (cx0 < G.seg_x1[lo - 1])
+                        c = G.seg_x1[lo - 1] >= cx1 ? G.seg_code[lo - 1] : 0xffffffffu;
+                    else
+                        c = (lo >= e || G.seg_x0[lo] >= cx1) ? 0u : 0xffffffffu;
+                } else if (n > 0 && cx0 < wx1[row][n - 1]) {
+                    c = wx1[row][n - 1] >= cx1 ? wcode[row][n - 1] : 0xffffffffu;
+                } else {
+                    c = (n == SQ_WIN || wx0[row][n] >= cx1) ? 0u : 0xffffffffu;
+                }
+                lo_c = min(lo_c, c);
+                hi_c = max(hi_c, c);
+            }
+            if (((rin + p + rw) & ((1 << side) - 1)) == 0 || p + rw == 64) {  // the strip ends
+                for (int o = 32; o >= Q; o >>= 1) {
+                    lo_c = min(lo_c, (uint32_t)__shfl_xor((int)lo_c, o, 64));
+                    hi_c = max(hi_c, (uint32_t)__shfl_xor((int)hi_c, o, 64));
+                }
+                if (lane < Q) {
+                    const int k = ((g * strips + ((rin + p) >> side)) << G.qlog) + q;
+                    atomicMin(&lo_s[k], lo_c);
+                    atomicMax(&hi_s[k], hi_c);
+                }
+                lo_c = 0xffffffffu;
+                hi_c = 0;
+            }
+        }
+    }
+    __syncthreads();
+    for (int k = tid; k < nsq; k += 256) {
+        const int q = k & (Q - 1), strip = (k >> G.qlog) & (strips - 1);
+        const int g = k >> (G.qlog + G.tl - side);
+        int32_t X, R;
+        if (!origin(g, &X, &R)) continue;
+        const int32_t x0 = X + (q << side), r0 = R + (strip << side);
+        int64_t u;
+        if (G.mt) {
+            u = (((int64_t)block * rpb + g) << (2 * G.qlog)) +
+                (k & ((strips << G.qlog) - 1));
+        } else {
+            if ((x0 >> G.tl) >= G.tw) continue;  // past the row's last tile
+            u = (int64_t)(r0 >> G.tl) * G.tw + (x0 >> G.tl);
+        }
+        uint32_t lo_c = lo_s[k], hi_c = hi_s[k];
+        if (x0 >= G.gw || r0 >= G.gh) lo_c = hi_c = 0;  // wholly outside the stored box
+        const bool uni = lo_c == hi_c && hi_c != 0xffffffffu;
+        code[u] = uni ? hi_c : 0xffffffffu;
+        mixed[u] = uni ? 0 : 1;
+    }
+}
+
 // list[pos[u]] = u for every flagged u (pos = exclusive scan of the flags)
 __global__ void k_flag_list(const int64_t *pos, int64_t n, int64_t total, int64_t *list)
 {
@@ -630,7 +796,7 @@ __global__ __launch_bounds__(256) void k_block_fill(const int64_t *seg_beg, cons
     const int side = 1 << side_log2;
     const int runs = side > 16 ? side >> 4 : 1;
     const int rlen = side > 16 ? 16 : side;
-    int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    int64_t t = (int64_t)xcd_block() * 256 + threadIdx.x;
     if (t >= nblk * side * runs) return;
     int64_t k = t / ((int64_t)side * runs);
     int rem = (int)(t - k * side * runs);
@@ -1145,7 +1311,7 @@ template <int G>
 static void launch_classify(const BuildState &B, const sba_handle *h, const int64_t *mt, int tl,
                             int sl, int64_t n_sq, uint32_t *code, int64_t *mixed, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_square_classify<G>, dim3(grid_for(n_sq * G)), dim3(256), 0, st,
+    hipLaunchKernelGGL(k_square_classify<G>, dim3(xcd_grid(grid_for(n_sq * G))), dim3(256), 0, st,
                        B.seg_beg, B.seg_end, B.seg_x0, B.seg_x1, B.seg_code, h->gw, h->gh, mt, tl, sl,
                        h->tw, n_sq, code, mixed);
 }
@@ -1154,6 +1320,18 @@ static void classify(const BuildState &B, const sba_handle *h, const int64_t *mt
                      int64_t n_sq, uint32_t *code, int64_t *mixed, hipStream_t st)
 {
     int side_log2 = mt ? sl : tl;
+    const int qlog = mt ? tl - sl : 4;
+    const int64_t nsq = (int64_t)(tl < 8 ? 256 >> tl : 1) << (mt ? 2 * qlog : qlog);
+    if (tl >= 6 && qlog >= 2 && qlog <= 5 && nsq <= SQ_MAX) {
+        const int64_t regions = mt ? n_sq >> (2 * qlog)
+                                   : ((h->tw + SQ_Q - 1) / SQ_Q) * h->th;
+        const SquareGeo G{B.seg_beg, B.seg_end, B.seg_x0, B.seg_x1, B.seg_code, h->gw, h->gh,
+                          h->tw, h->th, mt, tl, sl, qlog, regions};
+        const int rpb = tl < 8 ? 256 >> tl : 1;
+        hipLaunchKernelGGL(k_squares, dim3(xcd_grid((unsigned)((regions + rpb - 1) / rpb))), dim3(256),
+                           (size_t)nsq * 8, st, G, code, mixed);
+        return;
+    }
     if (side_log2 >= 6) launch_classify<64>(B, h, mt, tl, sl, n_sq, code, mixed, st);
     else if (side_log2 == 5) launch_classify<32>(B, h, mt, tl, sl, n_sq, code, mixed, st);
     else if (side_log2 == 4) launch_classify<16>(B, h, mt, tl, sl, n_sq, code, mixed, st);
@@ -1303,13 +1481,13 @@ int build_grid(sba_handle *h, BuildState &B, int tile_log2, int sub_log2, hipStr
     if (compact) {
         RC(handle_alloc(h, &h->blocks16, std::max<int64_t>(cells, 1)));
         if (nfine)
-            hipLaunchKernelGGL(k_block_fill<uint16_t>, dim3(grid_for(threads)), dim3(256), 0, st,
+            hipLaunchKernelGGL(k_block_fill<uint16_t>, dim3(xcd_grid(grid_for(threads))), dim3(256), 0, st,
                                B.seg_beg, B.seg_end, B.seg_x0, B.seg_x1, B.seg_code, h->gw, h->gh, fine_sq,
                                nfine, fine_mt, tl, sl, h->tw, fine_log2, np, h->blocks16);
     } else {
         RC(handle_alloc(h, &h->blocks, std::max<int64_t>(cells, 1)));
         if (nfine)
-            hipLaunchKernelGGL(k_block_fill<uint32_t>, dim3(grid_for(threads)), dim3(256), 0, st,
+            hipLaunchKernelGGL(k_block_fill<uint32_t>, dim3(xcd_grid(grid_for(threads))), dim3(256), 0, st,
                                B.seg_beg, B.seg_end, B.seg_x0, B.seg_x1, B.seg_code, h->gw, h->gh, fine_sq,
                                nfine, fine_mt, tl, sl, h->tw, fine_log2, np, h->blocks);
     }

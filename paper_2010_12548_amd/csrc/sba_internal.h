@@ -470,6 +470,15 @@ inline unsigned grid_for(int64_t n, int block = 256)
 // compute units of the current device (probe.hip)
 int cu_count();
 
+// Workgroup b of a grid of 8 k is dispatched to XCD b mod 8: numbered like
+// this, each XCD takes a contiguous eighth of the work, and workgroups that
+// share lines share an L2.
+__device__ __forceinline__ uint32_t xcd_block()
+{
+    return (blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+}
+inline unsigned xcd_grid(unsigned blocks) { return (blocks + 7u) & ~7u; }
+
 // Probe entry points (probe.hip).
 int probe_launch(const int32_t *xy, const int64_t *values, int64_t n, const sba_handle *h,
                  int32_t search, uint64_t *counts, int64_t *sums, hipStream_t st);
