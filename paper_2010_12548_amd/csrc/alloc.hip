@@ -42,7 +42,8 @@ DevCache g_cache[MAX_DEV];
 constexpr size_t PINNED_BYTES = 4096;
 // the staged values sit below FLAG_OFF; the flag word (a number unique to
 // each sync) above it
-constexpr size_t FLAG_OFF = PINNED_BYTES - 64;
+constexpr size_t FLAG_OFF = WS_FLAG_OFF;
+static_assert(WS_FLAG_OFF == PINNED_BYTES - 64, "the flag has the last line");
 // how long the host polls the flag before it blocks on the stream
 constexpr double POLL_US = 300.0;
 std::atomic<uint32_t> g_read_seq{0};
@@ -189,36 +190,9 @@ void Workspace::put(void *p)
     }
 }
 
-// Copies the queued reads into the staging buffer (one workgroup; sizes and
-// offsets in bytes, 8-byte words where both ends allow), then makes them
-// visible to the host before it writes `seq` to the flag word.
-struct ReadSet {
-    const unsigned char *src[WS_MAX_READS];
-    uint32_t off[WS_MAX_READS], bytes[WS_MAX_READS];
-    int n;
-    unsigned char *dst;  // device address of the staging buffer
-    uint32_t seq;
-};
-
 __global__ __launch_bounds__(64) void k_readback(ReadSet R)
 {
-    for (int r = 0; r < R.n; r++) {
-        const unsigned char *src = R.src[r];
-        unsigned char *dst = R.dst + R.off[r];
-        const uint32_t nb = R.bytes[r];
-        if ((((uintptr_t)src | (uintptr_t)dst | nb) & 7) == 0) {
-            for (uint32_t k = threadIdx.x; k < nb / 8; k += 64)
-                ((uint64_t *)dst)[k] = ((const uint64_t *)src)[k];
-        } else {
-            for (uint32_t k = threadIdx.x; k < nb; k += 64) dst[k] = src[k];
-        }
-    }
-    __threadfence_system();
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        __threadfence_system();
-        *(volatile uint32_t *)(R.dst + FLAG_OFF) = R.seq;
-    }
+    read_back(R);
 }
 
 int Workspace::read(void *host, const void *dev, size_t bytes)
@@ -255,12 +229,8 @@ int Workspace::read(void *host, const void *dev, size_t bytes)
     return 0;
 }
 
-int Workspace::sync()
+ReadSet Workspace::reads()
 {
-    if (reads_.empty()) {
-        HIP_OK(hipStreamSynchronize(st_));
-        return 0;
-    }
     ReadSet R{};
     for (size_t k = 0; k < reads_.size(); k++) {
         R.src[k] = (const unsigned char *)reads_[k].dev;
@@ -271,9 +241,24 @@ int Workspace::sync()
     R.dst = (unsigned char *)pinned_dev_;
     uint32_t seq = g_read_seq.fetch_add(1) + 1;
     if (seq == 0) seq = g_read_seq.fetch_add(1) + 1;  // 0 marks a fresh buffer
-    R.seq = seq;
-    hipLaunchKernelGGL(k_readback, dim3(1), dim3(64), 0, st_, R);
+    R.seq = seq_ = seq;
+    return R;
+}
+
+int Workspace::sync()
+{
+    if (reads_.empty()) {
+        HIP_OK(hipStreamSynchronize(st_));
+        return 0;
+    }
+    hipLaunchKernelGGL(k_readback, dim3(1), dim3(64), 0, st_, reads());
     HIP_OK(hipGetLastError());
+    return wait();
+}
+
+int Workspace::wait()
+{
+    const uint32_t seq = seq_;
     volatile uint32_t *flag = (volatile uint32_t *)(pinned_ + FLAG_OFF);
     const auto t0 = std::chrono::steady_clock::now();
     while (*flag != seq) {
@@ -303,6 +288,13 @@ int handle_get(sba_handle *h, void **p, size_t bytes)
     h->bytes += (int64_t)bytes;
     *p = b.p;
     return 0;
+}
+
+void handle_put_last(sba_handle *h, size_t bytes)
+{
+    cache_put(h->blocks_owned.back());
+    h->blocks_owned.pop_back();
+    h->bytes -= (int64_t)bytes;
 }
 
 void handle_put_all(sba_handle *h)

@@ -91,74 +91,130 @@ __global__ void k_check_verts(const int64_t *vert_off, int64_t *sizes, int *err)
     }
 }
 
-// one wavefront per polygon: coordinate bounding box, range check (err bit
-// 1), empty polygon (err bit 2); skipped when the offsets were refused
-__global__ void k_poly_bbox(const int32_t *ring_off, const int64_t *vert_off, const int32_t *xy,
-                            int32_t n_polys, int4 *bbox, int *err)
+// k_check_rings and k_check_verts by one workgroup, which zeroes the scalars
+// first: for up to CHECK_POLYS polygons, where a launch each (3.4 us of the
+// host's time) costs more than the checks
+#define CHECK_POLYS 8192
+__global__ __launch_bounds__(1024) void k_check_offsets(const int32_t *ring_off,
+                                                        const int64_t *vert_off, int32_t n_polys,
+                                                        int64_t *sc, int n_sc)
 {
-    int64_t gw = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    int lane = threadIdx.x & 63;
-    if (gw >= n_polys || (*err & 2)) return;
-    int p = (int)gw;
-    int64_t v0 = vert_off[ring_off[p]], v1 = vert_off[ring_off[p + 1]];
-    if (v1 == v0 && lane == 0) atomicOr(err, 2);
-    int xmin = INT32_MAX, ymin = INT32_MAX, xmax = INT32_MIN, ymax = INT32_MIN;
-    bool bad = false;
-    for (int64_t v = v0 + lane; v < v1; v += 64) {
-        int x = xy[2 * v], y = xy[2 * v + 1];
-        bad |= (x <= -(1 << 30)) | (x >= (1 << 30)) | (y <= -(1 << 30)) | (y >= (1 << 30));
-        xmin = min(xmin, x); ymin = min(ymin, y);
-        xmax = max(xmax, x); ymax = max(ymax, y);
+    __shared__ int bad;
+    if (threadIdx.x == 0) bad = ring_off[0] != 0;
+    __syncthreads();
+    const int32_t nr = ring_off[n_polys];
+    bool b = false;
+    for (int32_t p = threadIdx.x; p < n_polys; p += 1024) b |= ring_off[p + 1] < ring_off[p];
+    if (b) atomicOr(&bad, 1);
+    __syncthreads();
+    int64_t nv = 0;
+    if (!bad) {  // the same in every lane: read again only after a barrier
+        nv = vert_off[nr];
+        b = threadIdx.x == 0 && vert_off[0] != 0;
+        for (int64_t r = threadIdx.x; r < nr; r += 1024) b |= vert_off[r + 1] < vert_off[r];
     }
-    for (int o = 32; o > 0; o >>= 1) {
-        xmin = min(xmin, __shfl_xor(xmin, o, 64));
-        ymin = min(ymin, __shfl_xor(ymin, o, 64));
-        xmax = max(xmax, __shfl_xor(xmax, o, 64));
-        ymax = max(ymax, __shfl_xor(ymax, o, 64));
-    }
-    if (bad) atomicOr(err, 1);
-    if (lane == 0) bbox[p] = make_int4(xmin, ymin, xmax, ymax);
+    __syncthreads();
+    if (b) atomicOr(&bad, 1);
+    __syncthreads();
+    for (int k = threadIdx.x; k < n_sc; k += 1024)
+        sc[k] = k == 0 ? (bad ? 2 : 0) : (k == 1 ? nr : (k == 2 ? nv : 0));
 }
 
-// union of the polygons' cell boxes (one workgroup): box = {min over p of
-// ceil(xmin/s) - 1, same for y, max over p of floor(xmax/s), same for y}.
-// ceil and floor are monotone, so the extremes of the coordinates are found
-// first and divided once.
-#define BOX_BLOCK 256
-__global__ __launch_bounds__(BOX_BLOCK) void k_union_box(const int4 *bbox, int32_t n_polys,
-                                                         int64_t s, int64_t *box)
+#define BOX_BLOCK 1024
+#define BOX_GRID 512  // workgroups at most
+
+// the extremes over a workgroup, in thread 0
+__device__ __forceinline__ int4 box_reduce(int4 v)
 {
-    __shared__ int32_t red[4][BOX_BLOCK / 64];
-    int32_t v[4] = {INT32_MAX, INT32_MAX, INT32_MIN, INT32_MIN};
-    for (int p = threadIdx.x; p < n_polys; p += BOX_BLOCK) {
-        int4 b = bbox[p];
-        v[0] = min(v[0], b.x);
-        v[1] = min(v[1], b.y);
-        v[2] = max(v[2], b.z);
-        v[3] = max(v[3], b.w);
-    }
+    __shared__ int4 red[BOX_BLOCK / 64];
     for (int o = 32; o > 0; o >>= 1) {
-        v[0] = min(v[0], __shfl_xor(v[0], o, 64));
-        v[1] = min(v[1], __shfl_xor(v[1], o, 64));
-        v[2] = max(v[2], __shfl_xor(v[2], o, 64));
-        v[3] = max(v[3], __shfl_xor(v[3], o, 64));
+        v.x = min(v.x, __shfl_xor(v.x, o, 64));
+        v.y = min(v.y, __shfl_xor(v.y, o, 64));
+        v.z = max(v.z, __shfl_xor(v.z, o, 64));
+        v.w = max(v.w, __shfl_xor(v.w, o, 64));
     }
-    const int w = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0)
-        for (int k = 0; k < 4; k++) red[k][w] = v[k];
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    if (threadIdx.x == 0)
+        for (int q = 1; q < BOX_BLOCK / 64; q++)
+            v = make_int4(min(v.x, red[q].x), min(v.y, red[q].y), max(v.z, red[q].z),
+                          max(v.w, red[q].w));
+    return v;
+}
+
+// one wavefront per polygon: coordinate bounding box, range check (err bit
+// 1), empty polygon (err bit 2); skipped when the offsets were refused.  The
+// workgroup that ends last (ticket, zero on entry) forms the union of the cell
+// boxes, {min over p of ceil(xmin/s) - 1, same for y, max over p of
+// floor(xmax/s), same for y} (ceil and floor are monotone, so the extremes of
+// the coordinates are found first and divided once), and copies the host's
+// values.  The workgroups' extremes pass through memory as single words that
+// bypass the caches of their XCD, the ticket after them: a fence a workgroup,
+// which empties its L2, took 80 us for 250 of them.
+__global__ __launch_bounds__(BOX_BLOCK) void k_poly_bbox(const int32_t *ring_off,
+                                                         const int64_t *vert_off, const int32_t *xy,
+                                                         int32_t n_polys, int64_t s, int4 *bbox,
+                                                         int32_t *part, int *err, int64_t *box,
+                                                         unsigned long long *ticket, ReadSet R)
+{
+    const int lane = threadIdx.x & 63;
+    const bool refused = (*err & 2) != 0;
+    int4 u = make_int4(INT32_MAX, INT32_MAX, INT32_MIN, INT32_MIN);
+    for (int64_t p = ((int64_t)blockIdx.x * BOX_BLOCK + threadIdx.x) >> 6; p < n_polys && !refused;
+         p += (int64_t)gridDim.x * (BOX_BLOCK / 64)) {
+        int64_t v0 = vert_off[ring_off[p]], v1 = vert_off[ring_off[p + 1]];
+        if (v1 == v0 && lane == 0) atomicOr(err, 2);
+        int xmin = INT32_MAX, ymin = INT32_MAX, xmax = INT32_MIN, ymax = INT32_MIN;
+        bool bad = false;
+        for (int64_t v = v0 + lane; v < v1; v += 64) {
+            int x = xy[2 * v], y = xy[2 * v + 1];
+            bad |= (x <= -(1 << 30)) | (x >= (1 << 30)) | (y <= -(1 << 30)) | (y >= (1 << 30));
+            xmin = min(xmin, x); ymin = min(ymin, y);
+            xmax = max(xmax, x); ymax = max(ymax, y);
+        }
+        for (int o = 32; o > 0; o >>= 1) {
+            xmin = min(xmin, __shfl_xor(xmin, o, 64));
+            ymin = min(ymin, __shfl_xor(ymin, o, 64));
+            xmax = max(xmax, __shfl_xor(xmax, o, 64));
+            ymax = max(ymax, __shfl_xor(ymax, o, 64));
+        }
+        if (bad) atomicOr(err, 1);
+        if (lane == 0) bbox[p] = make_int4(xmin, ymin, xmax, ymax);
+        u = make_int4(min(u.x, xmin), min(u.y, ymin), max(u.z, xmax), max(u.w, ymax));
+    }
+    u = box_reduce(u);
+    __shared__ bool last;
+    __builtin_amdgcn_s_waitcnt(0);  // the error bits have arrived
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int q = 1; q < BOX_BLOCK / 64; q++) {
-            v[0] = min(v[0], red[0][q]);
-            v[1] = min(v[1], red[1][q]);
-            v[2] = max(v[2], red[2][q]);
-            v[3] = max(v[3], red[3][q]);
-        }
-        box[0] = ceildiv64(v[0], s) - 1;
-        box[1] = ceildiv64(v[1], s) - 1;
-        box[2] = floordiv64(v[2], s);
-        box[3] = floordiv64(v[3], s);
+        int32_t *q = part + 4 * (int64_t)blockIdx.x;
+        __hip_atomic_store(q, u.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(q + 1, u.y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(q + 2, u.z, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(q + 3, u.w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __builtin_amdgcn_s_waitcnt(0);
+        last = atomicAdd(ticket, 1ull) + 1 == gridDim.x;
     }
+    __syncthreads();
+    if (!last) return;
+    u = make_int4(INT32_MAX, INT32_MAX, INT32_MIN, INT32_MIN);
+    for (unsigned k = threadIdx.x; k < gridDim.x; k += BOX_BLOCK) {
+        int32_t *q = part + 4 * (int64_t)k;
+        const int32_t x0 = __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const int32_t y0 = __hip_atomic_load(q + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const int32_t x1 = __hip_atomic_load(q + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const int32_t y1 = __hip_atomic_load(q + 3, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        u = make_int4(min(u.x, x0), min(u.y, y0), max(u.z, x1), max(u.w, y1));
+    }
+    u = box_reduce(u);
+    if (threadIdx.x == 0) {
+        box[0] = ceildiv64(u.x, s) - 1;
+        box[1] = ceildiv64(u.y, s) - 1;
+        box[2] = floordiv64(u.z, s);
+        box[3] = floordiv64(u.w, s);
+    }
+    read_back(R);
 }
 
 // per edge: number of boundary row strips and of row-line crossings inside
@@ -893,6 +949,93 @@ __global__ void k_entries(const uint32_t *code, const int64_t *pos, int64_t n, i
     else out16[u] = (uint16_t)(mixed ? (0x8000u | idx) : short_code(c, np));   // compact dir
 }
 
+// Scan, entries, list and read-back in one launch for up to NUMBER_MAX squares:
+// the mixed squares numbered in order, their total to *tot, list[number] =
+// square, and the entries as k_entries writes them (nothing in mode 2 when the
+// numbers do not fit 16 bits).  Each workgroup takes NUMBER_TILE squares and
+// counts the mixed ones among all by itself (at most 256 KB, read from the L2),
+// so none waits for another, and the first can send the total to the host.
+// (One workgroup for all squares was bound by its instructions: 25 us for
+// 48,000; this way 9.  As five launches, tile sums, their scan, entries, list and read-back,
+// the kernels took 16 us and the gaps between them as much.)
+#define NUMBER_MAX 65536
+#define NUMBER_BLOCK 256
+#define NUMBER_PER 8
+#define NUMBER_TILE (NUMBER_BLOCK * NUMBER_PER)
+__global__ __launch_bounds__(NUMBER_BLOCK) void k_number(const uint32_t *__restrict__ code, int n,
+                                                         int n_pad, uint32_t np, int mode,
+                                                         uint32_t *__restrict__ out32,
+                                                         uint16_t *__restrict__ out16,
+                                                         int64_t *__restrict__ list, int64_t *tot,
+                                                         ReadSet R)
+{
+    constexpr int WAVES = NUMBER_BLOCK / 64;
+    __shared__ uint32_t sb[WAVES], sa[WAVES], sc[WAVES];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int start = (int)blockIdx.x * NUMBER_TILE;
+    uint32_t c[NUMBER_PER], cnt = 0;
+#pragma unroll
+    for (int k = 0; k < NUMBER_PER; k++) {
+        const int u = start + (w * NUMBER_PER + k) * 64 + lane;
+        c[k] = u < n ? code[u] : 0u;
+    }
+    // four codes a load; start is a multiple of four
+    const uint4 *c4 = (const uint4 *)code;
+    auto count = [&](int a, int b) {
+        uint32_t m = 0;
+#pragma unroll 8
+        for (int t = a + (int)threadIdx.x; t < b; t += NUMBER_BLOCK) {
+            const uint4 v = c4[t];
+            m += (v.x == 0xffffffffu) + (v.y == 0xffffffffu) + (v.z == 0xffffffffu) +
+                 (v.w == 0xffffffffu);
+        }
+        return m;
+    };
+    const int s4 = min(start, n) >> 2, n4 = n >> 2;
+    uint32_t before = count(0, s4), after = count(s4, n4);
+    if ((int)threadIdx.x < (n & 3)) {  // the last one to three, not before any start
+        const bool m = code[4 * n4 + threadIdx.x] == 0xffffffffu;
+        if (4 * n4 < start) before += m;
+        else after += m;
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+        before += (uint32_t)__shfl_xor((int)before, o, 64);
+        after += (uint32_t)__shfl_xor((int)after, o, 64);
+    }
+#pragma unroll
+    for (int k = 0; k < NUMBER_PER; k++) cnt += (uint32_t)__popcll(__ballot(c[k] == 0xffffffffu));
+    if (lane == 0) {
+        sb[w] = before;
+        sa[w] = after;
+        sc[w] = cnt;
+    }
+    __syncthreads();
+    uint32_t at = 0, all = 0;
+#pragma unroll
+    for (int k = 0; k < WAVES; k++) {
+        at += sb[k] + (k < w ? sc[k] : 0u);
+        all += sb[k] + sa[k];
+    }
+    const bool entries = mode != 2 || all < 0x8000u;
+#pragma unroll
+    for (int k = 0; k < NUMBER_PER; k++) {
+        const int u = start + (w * NUMBER_PER + k) * 64 + lane;
+        const bool mixed = c[k] == 0xffffffffu;
+        const uint64_t m = __ballot(mixed);
+        const uint32_t idx = at + (uint32_t)__popcll(m & ((1ull << lane) - 1));
+        at += (uint32_t)__popcll(m);
+        if (mixed) list[idx] = u;
+        if (!entries || u >= n_pad) continue;
+        if (mode == 0) out32[u] = mixed ? (TILE_MIXED | idx) : c[k];
+        else if (mode == 1) out32[u] = mixed ? (TILE_MIXED | idx) : short_code(c[k], np);
+        else out16[u] = (uint16_t)(mixed ? (0x8000u | idx) : short_code(c[k], np));
+    }
+    if (blockIdx.x == 0) {
+        if (threadIdx.x == 0) *tot = all;
+        read_back(R);
+    }
+}
+
 // ---------------------------------------------------------------- host side
 
 void magic_for(int64_t s, uint32_t *mag, int32_t *shift)
@@ -904,6 +1047,11 @@ void magic_for(int64_t s, uint32_t *mag, int32_t *shift)
     uint64_t m = (uint64_t)((num + (unsigned __int128)(s - 1)) / (unsigned __int128)s);
     *mag = (uint32_t)m;  // < 2^32 (== 2^31 for s == 1)
     *shift = 31 + l;
+}
+
+static unsigned box_grid(int32_t np)
+{
+    return std::min<unsigned>(grid_for((int64_t)np * 64, BOX_BLOCK), BOX_GRID);
 }
 
 int pool_setup()
@@ -928,7 +1076,7 @@ int pool_setup()
 
 // Hilbert key grid covering the cell boxes of several polygon sets: each
 // set's offsets are checked and its union cell box found by the kernels of
-// the build (k_check_rings, k_check_verts, k_poly_bbox, k_union_box); the
+// the build (k_check_rings, k_check_verts, k_poly_bbox); the
 // grid is anchored at the first cell of the union of the boxes and has the
 // smallest level L >= 1 with 2^L cells covering the union's longer side,
 // the level the Hilbert layout takes for a stored box of that size.
@@ -952,9 +1100,11 @@ int key_grid_launch(const sba_polygons *sets, int32_t n_sets, int64_t eps, hipSt
                            sizes, err);
         hipLaunchKernelGGL(k_check_verts, dim3(1024), dim3(256), 0, st, P.vert_off, sizes, err);
         RC(ws.alloc(&bbox[k], np));
-        hipLaunchKernelGGL(k_poly_bbox, dim3(grid_for((int64_t)np * 64)), dim3(256), 0, st,
-                           P.ring_off, P.vert_off, P.xy, np, bbox[k], err);
-        hipLaunchKernelGGL(k_union_box, dim3(1), dim3(BOX_BLOCK), 0, st, bbox[k], np, s, dbox);
+        int32_t *part = nullptr;
+        RC(ws.alloc(&part, 4 * BOX_GRID));
+        hipLaunchKernelGGL(k_poly_bbox, dim3(box_grid(np)), dim3(BOX_BLOCK), 0, st,
+                           P.ring_off, P.vert_off, P.xy, np, s, bbox[k], part, err, dbox,
+                           (unsigned long long *)(sc + SLOTS * k + 7), ReadSet{});
         HIP_OK(hipGetLastError());
     }
     std::vector<int64_t> hsc((size_t)SLOTS * n_sets);
@@ -1009,7 +1159,6 @@ int build_segments(const sba_polygons *polys, int64_t eps, hipStream_t st, sba_h
     // [0] error bits (int), [1..2] ring and vertex counts, [3..6] union cell
     // box, [8..13] totals of the scans
     RC(B.alloc(&B.sc, SC_SLOTS));
-    HIP_OK(hipMemsetAsync(B.sc, 0, sizeof(int64_t) * SC_SLOTS, st));
     int *err = (int *)B.sc;
     int64_t *sizes = B.sc + 1, *dbox = B.sc + 3, *tot = B.sc + 8;
     int64_t hsc[SC_READ];
@@ -1020,18 +1169,26 @@ int build_segments(const sba_polygons *polys, int64_t eps, hipStream_t st, sba_h
 
     // validate the offsets on the device (each stage reads only what the
     // previous one validated) and read sizes and bounding boxes in one sync
-    hipLaunchKernelGGL(k_check_rings, dim3(grid_for(np + 1)), dim3(256), 0, st, polys->ring_off, np,
-                       sizes, err);
-    hipLaunchKernelGGL(k_check_verts, dim3(1024), dim3(256), 0, st, polys->vert_off, sizes, err);
+    if (np <= CHECK_POLYS) {
+        hipLaunchKernelGGL(k_check_offsets, dim3(1), dim3(1024), 0, st, polys->ring_off,
+                           polys->vert_off, np, B.sc, SC_SLOTS);
+    } else {
+        HIP_OK(hipMemsetAsync(B.sc, 0, sizeof(int64_t) * SC_SLOTS, st));
+        hipLaunchKernelGGL(k_check_rings, dim3(grid_for(np + 1)), dim3(256), 0, st,
+                           polys->ring_off, np, sizes, err);
+        hipLaunchKernelGGL(k_check_verts, dim3(1024), dim3(256), 0, st, polys->vert_off, sizes, err);
+    }
     HIP_OK(hipGetLastError());
     int4 *bbox = nullptr;
+    int32_t *part = nullptr;
     RC(B.alloc(&bbox, np));
-    hipLaunchKernelGGL(k_poly_bbox, dim3(grid_for((int64_t)np * 64)), dim3(256), 0, st,
-                       polys->ring_off, polys->vert_off, polys->xy, np, bbox, err);
+    RC(B.alloc(&part, 4 * BOX_GRID));
+    RC(B.ws.read(hsc, B.sc, sizeof(hsc)));
+    hipLaunchKernelGGL(k_poly_bbox, dim3(box_grid(np)), dim3(BOX_BLOCK), 0, st,
+                       polys->ring_off, polys->vert_off, polys->xy, np, h->s, bbox, part, err, dbox,
+                       (unsigned long long *)(B.sc + SC_TICKET), B.ws.reads());
     HIP_OK(hipGetLastError());
-    hipLaunchKernelGGL(k_union_box, dim3(1), dim3(BOX_BLOCK), 0, st, bbox, np, h->s, dbox);
-    HIP_OK(hipGetLastError());
-    RC(fetch());
+    RC(B.ws.wait());
     int herr = (int)(uint32_t)hsc[0];
     if (herr & 2) return SBA_EINVAL;
     if (herr & 1) return SBA_ERANGE;
@@ -1384,14 +1541,37 @@ int build_grid(sba_handle *h, BuildState &B, int tile_log2, int sub_log2, hipStr
     RC(B.alloc(&tpos, nt + 1));
     classify(B, h, nullptr, tl, sl, nt, tcode, tpos, st);
     HIP_OK(hipGetLastError());
-    RC(scan_exclusive_i64(tpos, tpos, nt, tot, st, &B.ws));
+    // in one launch when the 16-bit directory is sure, or likely, to be taken
+    const bool compact_nt = !g_build_wide && (int64_t)np + h->n_sets < 0x8000 &&
+                            nt <= COMPACT_DIR_TILES_MAX;
+    const int64_t nt16 = (nt + 7) & ~(int64_t)7;  // LDS copies move 16 bytes at a time
+    int64_t *mt = nullptr;  // mixed tiles in order
+    bool numbered = compact_nt && nt16 <= NUMBER_MAX;
     RC(B.ws.read(hsc, B.sc, sizeof(hsc)));
-    RC(B.ws.sync());
+    if (numbered) {
+        RC(B.alloc(&mt, nt));
+        RC(handle_alloc(h, &h->dir16, nt16));
+        hipLaunchKernelGGL(k_number, dim3(grid_for(nt16, NUMBER_TILE)), dim3(NUMBER_BLOCK), 0, st,
+                           tcode, (int)nt, (int)nt16, np, 2, (uint32_t *)nullptr, h->dir16, mt,
+                           tot, B.ws.reads());
+        HIP_OK(hipGetLastError());
+        RC(B.ws.wait());
+        if (hsc[16] >= 0x8000) {  // too many mixed tiles for it after all
+            handle_put_last(h, (size_t)nt16 * sizeof(*h->dir16));
+            h->dir16 = nullptr;
+            B.release(mt);
+            mt = nullptr;
+            numbered = false;
+            RC(scan_exclusive_i64(tpos, tpos, nt, nullptr, st, &B.ws));
+        }
+    } else {
+        RC(scan_exclusive_i64(tpos, tpos, nt, tot, st, &B.ws));
+        RC(B.ws.sync());
+    }
     const int64_t nblk = hsc[16];
     if (nblk >= (int64_t)TILE_MIXED) return SBA_ELIMIT;
     h->n_blocks = nblk;
-    const bool compact = !g_build_wide && (int64_t)np + h->n_sets < 0x8000 && nblk < 0x8000 &&
-                         nt <= COMPACT_DIR_TILES_MAX;
+    const bool compact = compact_nt && nblk < 0x8000;
     h->compact = compact;
     if (sub_log2 == 0 && compact && nblk > 0) {
         // the smallest sub-tile whose 16-bit sub-directory fits the LDS of a
@@ -1410,8 +1590,8 @@ int build_grid(sba_handle *h, BuildState &B, int tile_log2, int sub_log2, hipStr
     }
 
     // directory
-    if (compact) {
-        const int64_t nt16 = (nt + 7) & ~(int64_t)7;  // LDS copies move 16 bytes at a time
+    if (numbered) {
+    } else if (compact) {
         RC(handle_alloc(h, &h->dir16, nt16));
         hipLaunchKernelGGL(k_entries, dim3(grid_for(nt16)), dim3(256), 0, st, tcode, tpos, nt, nt16,
                            np, 2, (uint32_t *)nullptr, h->dir16);
@@ -1437,10 +1617,11 @@ int build_grid(sba_handle *h, BuildState &B, int tile_log2, int sub_log2, hipStr
         }
         return 0;
     }
-    int64_t *mt = nullptr;  // mixed tiles in order
-    RC(B.alloc(&mt, nblk));
-    hipLaunchKernelGGL(k_flag_list, dim3(grid_for(nt)), dim3(256), 0, st, tpos, nt, nblk, mt);
-    HIP_OK(hipGetLastError());
+    if (!numbered) {
+        RC(B.alloc(&mt, nblk));
+        hipLaunchKernelGGL(k_flag_list, dim3(grid_for(nt)), dim3(256), 0, st, tpos, nt, nblk, mt);
+        HIP_OK(hipGetLastError());
+    }
 
     // sub-directories of the mixed tiles
     const int64_t *fine_sq = mt;        // squares stored as fine blocks
@@ -1455,19 +1636,31 @@ int build_grid(sba_handle *h, BuildState &B, int tile_log2, int sub_log2, hipStr
         RC(B.alloc(&spos, nq + 1));
         classify(B, h, mt, tl, sl, nq, scode, spos, st);
         HIP_OK(hipGetLastError());
-        RC(scan_exclusive_i64(spos, spos, nq, tot + 1, st, &B.ws));
         RC(B.ws.read(hsc, B.sc, sizeof(hsc)));
-        RC(B.ws.sync());
+        RC(handle_alloc(h, &h->sub, nq));
+        if (nq <= NUMBER_MAX) {
+            RC(B.alloc(&ms, nq));
+            hipLaunchKernelGGL(k_number, dim3(grid_for(nq, NUMBER_TILE)), dim3(NUMBER_BLOCK), 0, st,
+                               scode, (int)nq, (int)nq, np, compact ? 1 : 0, h->sub,
+                               (uint16_t *)nullptr, ms, tot + 1, B.ws.reads());
+            HIP_OK(hipGetLastError());
+            RC(B.ws.wait());
+        } else {
+            RC(scan_exclusive_i64(spos, spos, nq, tot + 1, st, &B.ws));
+            RC(B.ws.sync());
+        }
         const int64_t nsub = hsc[17];
         if (nsub >= (int64_t)TILE_MIXED) return SBA_ELIMIT;
         h->n_sub = nsub;
-        RC(handle_alloc(h, &h->sub, nq));
-        hipLaunchKernelGGL(k_entries, dim3(grid_for(nq)), dim3(256), 0, st, scode, spos, nq, nq, np,
-                           compact ? 1 : 0, h->sub, (uint16_t *)nullptr);
-        HIP_OK(hipGetLastError());
-        RC(B.alloc(&ms, std::max<int64_t>(nsub, 1)));
-        hipLaunchKernelGGL(k_flag_list, dim3(grid_for(nq)), dim3(256), 0, st, spos, nq, nsub, ms);
-        HIP_OK(hipGetLastError());
+        if (nq > NUMBER_MAX) {
+            hipLaunchKernelGGL(k_entries, dim3(grid_for(nq)), dim3(256), 0, st, scode, spos, nq, nq,
+                               np, compact ? 1 : 0, h->sub, (uint16_t *)nullptr);
+            HIP_OK(hipGetLastError());
+            RC(B.alloc(&ms, std::max<int64_t>(nsub, 1)));
+            hipLaunchKernelGGL(k_flag_list, dim3(grid_for(nq)), dim3(256), 0, st, spos, nq, nsub,
+                               ms);
+            HIP_OK(hipGetLastError());
+        }
         fine_sq = ms;
         fine_mt = mt;
         nfine = nsub;

@@ -11,6 +11,7 @@
 #define SC_READ 20
 // slot of the set table's counter
 #define SC_SET_N 18
+#define SC_TICKET 20  // workgroups of k_poly_bbox that have ended
 
 struct BuildState {
     explicit BuildState(hipStream_t s) : st(s), ws(s) {}

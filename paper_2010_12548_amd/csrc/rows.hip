@@ -250,12 +250,13 @@ __device__ __forceinline__ T wg_scan_incl(T v, T *wsum, T *tot)
 }
 
 // hint[k] = polygon of vertex 64 k (a wavefront per polygon); rowdiff and stat
-// zeroed
+// zeroed, the set table (if any) emptied
 __global__ void k_rows_init(const int32_t *ring_off, const int64_t *vert_off, int32_t np,
                             int32_t *hint, int32_t *rowdiff, int64_t nrow, unsigned long long *stat,
-                            int nstat)
+                            int nstat, uint64_t *tab, int64_t ntab)
 {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    for (int64_t k = t; k < ntab; k += (int64_t)gridDim.x * blockDim.x) tab[k] = ~0ull;
     if (t < nrow) rowdiff[t] = 0;
     if (t < nstat) stat[t] = 0;
     const int64_t p = t >> 6;
@@ -401,6 +402,23 @@ __device__ __forceinline__ int row_class(uint32_t n)
     return n <= 64 ? 0 : (n <= 256 ? 1 : (n <= 1024 ? 2 : (n <= 4096 ? 3 : 4)));
 }
 
+// a place in its class for each lane's row (class c, none if negative): one
+// addition to the workgroup's counters n a class and wavefront
+__device__ __forceinline__ uint32_t class_slot(int c, uint32_t *n)
+{
+    const int lane = threadIdx.x & 63;
+    uint32_t at = 0;
+    for (int q = 0; q < ROW_CLASSES; q++) {
+        const uint64_t b = __ballot(c == q);
+        if (c != q) continue;
+        const uint32_t rank = (uint32_t)__popcll(b & ((1ull << lane) - 1));
+        uint32_t first = 0;
+        if (rank == 0) first = atomicAdd(&n[q], (uint32_t)__popcll(b));
+        at = (uint32_t)__shfl((int)first, __ffsll((long long)b) - 1, 64) + rank;
+    }
+    return at;
+}
+
 // One workgroup: from rowdiff (see k_edge_rows) the rows' pair counts and
 // their exclusive scan rowoff[0..gh] (pairs < 2^31); rowdiff goes back to
 // zero.  out[0]: pairs, out[1]: the most in a row, out[6], out[7]: boundary
@@ -410,16 +428,26 @@ __device__ __forceinline__ int row_class(uint32_t n)
 #define RSCAN 1024
 #define RSCAN_PER 8
 #define RS_PAD(i) ((i) + ((i) >> 3))  // a lane's eight in banks of their own
+// Up to RSCAN_LISTS rows it makes the rows' lists as well (see k_row_lists),
+// and copies the host's values: two launches less.
+#define RSCAN_LISTS (RSCAN * RSCAN_PER)
+struct RowLists {
+    int32_t *list;
+    int64_t *seg_beg, *seg_end;
+    uint32_t *row_stat;
+};
 __global__ __launch_bounds__(RSCAN) void k_row_scan(int32_t *rowdiff, int64_t gh, int64_t *rowoff,
                                                     const unsigned long long *stat,
-                                                    unsigned long long *out)
+                                                    unsigned long long *out, RowLists Q, ReadSet R)
 {
+    __shared__ uint32_t ncls[ROW_CLASSES];
     __shared__ uint32_t wd[RSCAN / 64];
     __shared__ uint32_t chunk[RS_PAD(RSCAN * RSCAN_PER)];
     __shared__ uint32_t smax;
     __shared__ unsigned long long sst[2];
     if (threadIdx.x == 0) smax = 0;
     if (threadIdx.x < 2) sst[threadIdx.x] = 0;
+    if (threadIdx.x < ROW_CLASSES) ncls[threadIdx.x] = 0;
     uint32_t next[RSCAN_PER];
     auto load = [&](int64_t c0) {
 #pragma unroll
@@ -460,6 +488,18 @@ __global__ __launch_bounds__(RSCAN) void k_row_scan(int32_t *rowdiff, int64_t gh
 #pragma unroll
         for (int k = 0; k < RSCAN_PER; k++) {
             chunk[RS_PAD(threadIdx.x * RSCAN_PER + k)] = o;
+            if (Q.list) {
+                const int64_t r = b + k;
+                int c = -1;
+                if (r < gh && d[k] == 0) {
+                    Q.seg_beg[r] = Q.seg_end[r] = 2 * (int64_t)o;
+                    Q.row_stat[r] = Q.row_stat[gh + r] = 0;
+                } else if (r < gh) {
+                    c = row_class(d[k]);
+                }
+                const uint32_t at = class_slot(c, ncls);
+                if (c >= 0 && c < ROW_CLASSES) Q.list[(int64_t)c * gh + at] = (int32_t)r;
+            }
             o += d[k];
         }
         __syncthreads();
@@ -484,6 +524,8 @@ __global__ __launch_bounds__(RSCAN) void k_row_scan(int32_t *rowdiff, int64_t gh
         out[6] = sst[0];
         out[7] = sst[1];
     }
+    if (Q.list && threadIdx.x < ROW_CLASSES) out[2 + threadIdx.x] = ncls[threadIdx.x];
+    read_back(R);
 }
 
 // The rows by class: list[c gh ..] holds class c's, cnt[c] of them (zero on
@@ -509,15 +551,7 @@ __global__ __launch_bounds__(256) void k_row_lists(const int64_t *rowoff, int64_
             c = row_class(d);
         }
     }
-    uint32_t at = 0;
-    for (int q = 0; q < ROW_CLASSES; q++) {
-        const uint64_t b = __ballot(c == q);
-        if (c != q) continue;
-        const uint32_t rank = (uint32_t)__popcll(b & ((1ull << (tid & 63)) - 1));
-        uint32_t first = 0;
-        if (rank == 0) first = atomicAdd(&n[q], (uint32_t)__popcll(b));
-        at = (uint32_t)__shfl((int)first, __ffsll((long long)b) - 1, 64) + rank;
-    }
+    const uint32_t at = class_slot(c, n);
     __syncthreads();
     if (tid < ROW_CLASSES && n[tid]) base[tid] = (uint32_t)atomicAdd(&cnt[tid], (unsigned long long)n[tid]);
     __syncthreads();
@@ -970,15 +1004,18 @@ __global__ __launch_bounds__(BLOCK) void k_row_sweep(const SweepArgs A)
 // out[0..2] += segments, multi-polygon segments and their members of all rows
 // (the rows' own figures, added up once: an addition to a shared counter by
 // every row took 10 ns a row)
-__global__ __launch_bounds__(256) void k_row_totals(const int64_t *seg_beg, const int64_t *seg_end,
-                                                    const uint32_t *row_stat, int64_t gh,
-                                                    unsigned long long *out)
+// (as one workgroup it copies the host's values too)
+template <int BLOCK>
+__global__ __launch_bounds__(BLOCK) void k_row_totals(const int64_t *seg_beg, const int64_t *seg_end,
+                                                      const uint32_t *row_stat, int64_t gh,
+                                                      unsigned long long *out, ReadSet R)
 {
     __shared__ unsigned long long sum[3];
     if (threadIdx.x < 3) sum[threadIdx.x] = 0;
     __syncthreads();
     unsigned long long a = 0, b = 0, c = 0;
-    for (int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x; r < gh; r += (int64_t)gridDim.x * 256) {
+    for (int64_t r = (int64_t)blockIdx.x * BLOCK + threadIdx.x; r < gh;
+         r += (int64_t)gridDim.x * BLOCK) {
         a += (unsigned long long)(seg_end[r] - seg_beg[r]);
         b += row_stat[r];
         c += row_stat[gh + r];
@@ -995,6 +1032,7 @@ __global__ __launch_bounds__(256) void k_row_totals(const int64_t *seg_beg, cons
     }
     __syncthreads();
     if (threadIdx.x < 3 && sum[threadIdx.x]) atomicAdd(&out[threadIdx.x], sum[threadIdx.x]);
+    read_back(R);
 }
 
 // list mode: the multi-polygon segments of all rows, in row order
@@ -1243,9 +1281,13 @@ int rows_coverage(const sba_polygons *polys, const int4 *bbox, int64_t nv,
     RC(B.alloc(&B.seg_beg, gh));
     RC(B.alloc(&B.seg_end, gh));
     unsigned long long *fig = stat + ROW_STATS * ROW_STAT_STEP;
+    bool hash = !(paths_off & 4);
+    SetStage S{};
+    if (hash) RC(sets_table(S, B, np, false));
     hipLaunchKernelGGL(k_rows_init, dim3(grid_for(std::max<int64_t>((int64_t)np * 64, std::max<int64_t>(gh + 1, NST)))),
                        dim3(256), 0, st, polys->ring_off, polys->vert_off, np, hint, rowdiff,
-                       (int64_t)gh + 1, stat, NST);
+                       (int64_t)gh + 1, stat, NST, S.tab.tab,
+                       hash ? (int64_t)1 << S.tab.hb : (int64_t)0);
     // few edges: fewer a workgroup, so that their pairs (each two 64-bit
     // divisions) spread over the chip (512 edges of 55 rows: 80 us with 256 a
     // workgroup)
@@ -1254,14 +1296,21 @@ int rows_coverage(const sba_polygons *polys, const int4 *bbox, int64_t nv,
     const dim3 egrid((unsigned)((nv + epw - 1) / epw));
     hipLaunchKernelGGL(k_edge_rows<false>, egrid, dim3(EB), 0, st, P, G, epw, rowdiff,
                        (const int64_t *)nullptr, (uint4 *)nullptr, stat);
-    hipLaunchKernelGGL(k_row_scan, dim3(1), dim3(RSCAN), 0, st, rowdiff, (int64_t)gh, rowoff, stat,
-                       fig);
-    hipLaunchKernelGGL(k_row_lists, dim3(grid_for(gh)), dim3(256), 0, st, rowoff, (int64_t)gh, list,
-                       B.seg_beg, B.seg_end, row_stat, fig + 2);
-    HIP_OK(hipGetLastError());
+    const bool few_rows = gh < RSCAN_LISTS;  // the scan has gh + 1 entries
     unsigned long long hs[NFIG];
     RC(B.ws.read(hs, fig, sizeof(hs)));
-    RC(B.ws.sync());
+    const RowLists lists{few_rows ? list : nullptr, B.seg_beg, B.seg_end, row_stat};
+    hipLaunchKernelGGL(k_row_scan, dim3(1), dim3(RSCAN), 0, st, rowdiff, (int64_t)gh, rowoff, stat,
+                       fig, lists, few_rows ? B.ws.reads() : ReadSet{});
+    HIP_OK(hipGetLastError());
+    if (few_rows) {
+        RC(B.ws.wait());
+    } else {
+        hipLaunchKernelGGL(k_row_lists, dim3(grid_for(gh)), dim3(256), 0, st, rowoff, (int64_t)gh,
+                           list, B.seg_beg, B.seg_end, row_stat, fig + 2);
+        HIP_OK(hipGetLastError());
+        RC(B.ws.sync());
+    }
     const int64_t items_n = (int64_t)hs[0], max_n = (int64_t)hs[1];
     const int64_t NB = (int64_t)hs[6], NC = (int64_t)hs[7];
     int64_t rows[ROW_CLASSES];
@@ -1274,6 +1323,7 @@ int rows_coverage(const sba_polygons *polys, const int4 *bbox, int64_t nv,
                         (void *)row_stat, (void *)B.seg_beg, (void *)B.seg_end})
             B.release(p);
         B.seg_beg = B.seg_end = nullptr;
+        sets_release(S, B);
         return 0;
     };
     const int pbits = std::max(bits_for((uint64_t)(np - 1)), 1);
@@ -1304,7 +1354,6 @@ int rows_coverage(const sba_polygons *polys, const int4 *bbox, int64_t nv,
     RC(B.alloc(&B.seg_x1, slots));
     RC(B.alloc(&B.seg_code, slots));
     SweepArgs A{};
-    SetStage S{};
     S.fb = fb;
     A.row_stat = row_stat;
     A.list = list;
@@ -1325,7 +1374,6 @@ int rows_coverage(const sba_polygons *polys, const int4 *bbox, int64_t nv,
     A.memloc = S.memloc;
     A.memcnt = fig + 11;
     A.err = (int *)B.sc;
-    bool hash = !(paths_off & 4);
     A.memcap = std::max<int64_t>(1 << 16, items_n);
     RC(B.alloc(&A.mem_ids, A.memcap));
     int64_t NS = 0, NM = 0, NMEM = 0, nset = 0, nids = 0;
@@ -1334,23 +1382,30 @@ int rows_coverage(const sba_polygons *polys, const int4 *bbox, int64_t nv,
             HIP_OK(hipMemsetAsync(fig + 8, 0, 4 * sizeof(unsigned long long), st));
             HIP_OK(hipMemsetAsync(B.sc + SC_SET_N, 0, sizeof(int64_t), st));
         }
-        if (hash) {
-            if (!S.tab.tab) RC(sets_table(S, B, np));
-            else HIP_OK(hipMemsetAsync(S.tab.tab, 0xff, sizeof(uint64_t) << S.tab.hb, st));
-        }
+        if (hash && attempt > 0)
+            HIP_OK(hipMemsetAsync(S.tab.tab, 0xff, sizeof(uint64_t) << S.tab.hb, st));
         A.tab = hash ? S.tab : SetTab{};
         if (!hash && !A.seg_key) RC(B.alloc(&A.seg_key, slots));
         const bool p32 = pbits + xbits <= 32, t32 = xbits + tbits <= 31;
         if (p32 && t32) RC((sweep_launch<uint32_t, uint32_t>(A, rows, st)));
         else if (t32) RC((sweep_launch<uint64_t, uint32_t>(A, rows, st)));
         else RC((sweep_launch<uint64_t, uint64_t>(A, rows, st)));
-        hipLaunchKernelGGL(k_row_totals, dim3((unsigned)std::min<int64_t>((gh + 255) / 256, 64)),
-                           dim3(256), 0, st, B.seg_beg, B.seg_end, row_stat, (int64_t)gh, fig + 8);
-        HIP_OK(hipGetLastError());
         int64_t hsc[SC_READ];
         RC(B.ws.read(hs, fig, sizeof(hs)));
         RC(B.ws.read(hsc, B.sc, sizeof(hsc)));
-        RC(B.ws.sync());
+        if (few_rows) {
+            hipLaunchKernelGGL(k_row_totals<1024>, dim3(1), dim3(1024), 0, st, B.seg_beg, B.seg_end,
+                               row_stat, (int64_t)gh, fig + 8, B.ws.reads());
+            HIP_OK(hipGetLastError());
+            RC(B.ws.wait());
+        } else {
+            hipLaunchKernelGGL(k_row_totals<256>,
+                               dim3((unsigned)std::min<int64_t>((gh + 255) / 256, 64)), dim3(256),
+                               0, st, B.seg_beg, B.seg_end, row_stat, (int64_t)gh, fig + 8,
+                               ReadSet{});
+            HIP_OK(hipGetLastError());
+            RC(B.ws.sync());
+        }
         const int herr = (int)(uint32_t)hsc[0];
         if (herr & ERR_DEPTH) return SBA_ELIMIT;
         if (herr & ~ERR_ROW) return SBA_EDEVICE;

@@ -84,7 +84,7 @@ __device__ __forceinline__ uint32_t set_insert(const SetTab &T, uint64_t key, ui
 }
 
 // an empty table for the sets of np polygons
-int sets_table(SetStage &S, BuildState &B, int32_t np);
+int sets_table(SetStage &S, BuildState &B, int32_t np, bool fill);
 // number the nset distinct sets (nids members) of the table in key order, lay
 // out h's set table (NM multi segments with NMEM members bound its size) and
 // replace the SEG_SLOT codes of B's segments; slots: segment indices

@@ -263,7 +263,7 @@ __global__ void k_set_fill(const uint64_t *key, const uint32_t *val, const int64
 // A partition's distinct sets are its shared sides and corners, a few per
 // polygon: 16 slots a polygon (at least 2^15, at most 2^22), a quarter of them
 // usable, hold those; more (deep overlaps) go through the list.
-int sets_table(SetStage &S, BuildState &B, int32_t np)
+int sets_table(SetStage &S, BuildState &B, int32_t np, bool fill)
 {
     SetTab &T = S.tab;
     T.hb = 15;
@@ -274,7 +274,7 @@ int sets_table(SetStage &S, BuildState &B, int32_t np)
     RC(B.alloc(&T.list, T.cap));
     RC(B.alloc(&T.lslot, T.cap));
     T.cnt = (unsigned long long *)(B.sc + SC_SET_N);
-    HIP_OK(hipMemsetAsync(T.tab, 0xff, sizeof(uint64_t) << T.hb, B.st));
+    if (fill) HIP_OK(hipMemsetAsync(T.tab, 0xff, sizeof(uint64_t) << T.hb, B.st));
     return 0;
 }
 
@@ -333,7 +333,7 @@ int sets_hash_list(SetStage &S, BuildState &B, sba_handle *h, const uint64_t *mk
                    bool *done)
 {
     *done = false;
-    RC(sets_table(S, B, h->n_polys));
+    RC(sets_table(S, B, h->n_polys, true));
     hipLaunchKernelGGL(k_set_insert, dim3(grid_for(NM)), dim3(256), 0, st, mkey, mval, NM, S.fb,
                        S.memloc, S.tab, B.seg_code);
     HIP_OK(hipGetLastError());
