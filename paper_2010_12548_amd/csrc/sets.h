@@ -39,6 +39,7 @@ struct SetStage {
 
 #define SET_EMPTY (~(uint64_t)0)
 #define SET_PROBES 64
+#define SET_ASK 12
 // distinct sets that one workgroup sorts in LDS
 #define SET_CAP 8192
 
@@ -55,12 +56,16 @@ __device__ __forceinline__ uint32_t set_hash(uint64_t k, int hb)
     return (uint32_t)((k * 0x9e3779b97f4a7c15ull) >> (64 - hb));
 }
 
-// the key's slot (d: the size of its set)
+// the key's slot (d: the size of its set).  Whether the table is full is asked
+// only after a run of taken slots, as an overfull table has them: one read of
+// the shared counter by every wavefront of a sweep, about 9 ns each, one after
+// another, made 50,000 rows take 2.8 ms instead of 1.8.
 __device__ __forceinline__ uint32_t set_insert(const SetTab &T, uint64_t key, uint32_t d)
 {
     const uint32_t mask = (1u << T.hb) - 1u;
     uint32_t s = set_hash(key, T.hb);
     for (int probe = 0; probe < SET_PROBES; probe++) {
+        if (probe == SET_ASK && set_full(T)) return 0;
         // a slot that already holds the key is seen without an atomic
         const uint64_t seen = *(const volatile uint64_t *)(T.tab + s);
         if (seen == key) return s;
