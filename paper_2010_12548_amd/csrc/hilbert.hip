@@ -344,7 +344,8 @@ static int write_runs(BuildState &B, sba_handle *h, const K *bk, hipStream_t st)
 #define DIR_LONG 2048   // runs over more blocks are filled by the whole grid
 
 // Run i's entries are the blocks whose first key it holds.  A wavefront shares
-// the entries of its 64 runs; long runs go to a list (cnt, list).
+// the entries of its 64 runs; long runs go to a list (cnt, list).  2^24 entries
+// of 28.9M runs: 159 us (267 while each entry's cell was found level by level).
 __global__ __launch_bounds__(256) void k_dir_fill(const uint64_t *starts, const uint32_t *code,
                                                   int64_t n, uint64_t total, int shift, int dl,
                                                   uint32_t *dir, uint32_t *list,

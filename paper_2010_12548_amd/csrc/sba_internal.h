@@ -340,25 +340,49 @@ __host__ __device__ inline uint32_t block_index(uint32_t ib, uint32_t jb, int dl
     return ((jb >> 2) << (dl + 2)) | ((ib >> 3) << 5) | ((jb & 3u) << 3) | (ib & 7u);
 }
 
-// Inverse of hilbert_index.
+// bits 0, 2, 4, ... of v, packed
+__host__ __device__ inline uint32_t even_bits(uint32_t v)
+{
+    v &= 0x55555555u;
+    v = (v | v >> 1) & 0x33333333u;
+    v = (v | v >> 2) & 0x0f0f0f0fu;
+    v = (v | v >> 4) & 0x00ff00ffu;
+    return (v | v >> 8) & 0xffffu;
+}
+
+// bit k: the exclusive or of v's bits above k
+__host__ __device__ inline uint32_t xor_above(uint32_t v)
+{
+    v >>= 1;
+    v ^= v >> 1;
+    v ^= v >> 2;
+    v ^= v >> 4;
+    v ^= v >> 8;
+    return v ^ v >> 16;
+}
+
+// Inverse of hilbert_index, all levels at once.  A level's two index bits q
+// stand for the quadrant (x, y) = (0,0), (0,1), (1,1), (1,0) in its frame, so x
+// is the upper bit and y the exclusive or of both; a level with y = 0 turns the
+// frame's transposition over for the levels below it, one with y = 0 and x = 1
+// the reflection too.  Neither depends on the frame, so the frames are prefix
+// parities of whole words (level by level, 16 levels took about 200
+// instructions in one chain; these are about 50).
 __host__ __device__ inline void hilbert_cell(int L, uint64_t d, uint32_t *pi, uint32_t *pj)
 {
-    uint32_t i = 0, j = 0, swap = 0, flip = 0;
-    for (int lev = L - 1; lev >= 0; --lev) {
-        uint32_t q = (uint32_t)(d >> (2 * lev)) & 3u;
-        uint32_t x = (q >> 1) & 1u;            // q: 0->(0,0) 1->(0,1) 2->(1,1) 3->(1,0)
-        uint32_t y = (q == 1 || q == 2) ? 1u : 0u;
-        uint32_t fx = x ^ flip, fy = y ^ flip;  // undo the frame
-        uint32_t bi = swap ? fy : fx, bj = swap ? fx : fy;
-        i |= bi << lev;
-        j |= bj << lev;
-        if (y == 0) {
-            if (x == 1) flip ^= 1u;
-            swap ^= 1u;
-        }
+    uint32_t x = even_bits((uint32_t)d >> 1), y = even_bits((uint32_t)d);
+    if (L > 16) {
+        x |= even_bits((uint32_t)(d >> 33)) << 16;
+        y |= even_bits((uint32_t)(d >> 32)) << 16;
     }
-    *pi = i;
-    *pj = j;
+    const uint32_t levels = L >= 32 ? 0xffffffffu : (1u << L) - 1u;
+    x &= levels;
+    y = (y & levels) ^ x;
+    const uint32_t turn = ~y & levels;
+    const uint32_t swap = xor_above(turn), flip = xor_above(turn & x);
+    const uint32_t fx = x ^ flip, fy = y ^ flip;  // undo the frame
+    *pi = ((fy & swap) | (fx & ~swap)) & levels;
+    *pj = ((fx & swap) | (fy & ~swap)) & levels;
 }
 
 // ---------------------------------------------------------------- learned index
