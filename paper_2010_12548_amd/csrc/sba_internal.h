@@ -548,8 +548,8 @@ inline unsigned xcd_grid(unsigned blocks) { return (blocks + 7u) & ~7u; }
 int probe_launch(const int32_t *xy, const int64_t *values, int64_t n, const sba_handle *h,
                  int32_t search, uint64_t *counts, int64_t *sums, hipStream_t st);
 int lookup_launch(const sba_handle *h, const int64_t *ij, int64_t n, int32_t *ref, hipStream_t st);
-// the probe over contiguous items of points with an LDS table of cell codes
-// (any layout; for points in spatial order, or partitioned by region)
+// the probe with LDS lines of bins (any layout), shaped for points partitioned
+// by region
 int items_launch(const int32_t *xy, const int64_t *values, int64_t n, const sba_handle *h,
                  int32_t search, uint64_t *counts, int64_t *sums, hipStream_t st);
 int range_launch(const int32_t *xy, const int64_t *values, int64_t n, const sba_handle *h,
