@@ -1941,11 +1941,16 @@ __device__ __forceinline__ void table_flush(const CodeTable &H, const TaskDev &T
 // table of single codes (2,048 slots a workgroup, four on a unit) overflowed
 // within an item of 4,096 such points and sent each slot out by itself.
 //
-// A bin with values is one 64-bit word, points above bit 44 and their values'
-// sum below it: at most FLUSH_POINTS are added before the bins go out.  The
-// points that need more than one directory entry and one addition (in mixed
-// blocks of the Hilbert layout, 9 in 100 at that size; of polygon sets; with
-// values outside [0, 2^24)) wait in a queue of the wavefront until a lane each can take 64 of
+// A bin with values is one 64-bit word, points above bit 44 and the sum of their
+// values' low 24 bits below it: at most FLUSH_POINTS are added before the bins
+// go out.  What is left of a value outside [0, 2^24), a negative one too, is
+// added modulo 2^64 to the polygon's word of a second line, which takes a place
+// when the first such value comes.  (Values in cents leave them all free; past
+// the bins, as two additions to the outputs each, 2e7 values of both signs over
+// 260 polygons in order took 13.8 ms, now 0.12; cents take 0.12.)
+// The points that need more than one directory entry and one addition (in mixed
+// blocks of the Hilbert layout, 9 in 100 at that size; of polygon sets) wait in
+// a queue of the wavefront until a lane each can take 64 of
 // them: searched in lockstep with the others they made every wavefront step
 // through each search with all of its 512 points.
 //
@@ -1959,6 +1964,7 @@ __device__ __forceinline__ void table_flush(const CodeTable &H, const TaskDev &T
 #define LINE_WAVES (LINE_BLOCK / 64)
 #define LINE_PROBES 4
 #define LINE_EMPTY 0xffffffffu
+#define LINE_HIGH 0x80000000u  // a tag's mark: bins of values' high parts
 #define CHUNK (LINE_WAVES * 64 * 2 * PROBE_UNROLL)  // points a workgroup takes at a time
 #define FLUSH_POINTS (1 << 19)  // below 2^20: a bin's count has 20 bits
 #define VAL_BITS 24
@@ -1970,9 +1976,12 @@ struct LineBins {
     typedef std::conditional_t<VALS, unsigned long long, uint32_t> Word;
     static constexpr int LOG2 = VALS ? 4 : 5;
     Word *bin;         // [lines << LOG2]
-    uint32_t *tag;     // [lines] line number or LINE_EMPTY
-    uint32_t lines;
-    bool direct;       // every line has its own place
+    uint32_t *tag;     // [lines] line number (LINE_HIGH: of values' high parts) or LINE_EMPTY
+    uint32_t lines;    // places in use
+    // the first `own` places are the polygons' lines in order, no tags; lines
+    // of high parts follow in order too (high_own), else by hash; own 0: all by hash
+    uint32_t own;
+    bool high_own;
 };
 
 // Workgroups per compute unit: one with all of its LDS for points in no known
@@ -1984,7 +1993,24 @@ static __host__ __device__ constexpr int line_count(int per_cu)
     return (PROBE_LDS_BYTES / per_cu - HILBERT_TAB * 2 - LINE_WAVES * SLOWQ * 12 - 512) / (128 + 4);
 }
 
-// n points of polygon p < np with values' sum v (each value below 2^VAL_BITS)
+// the place of the line with this tag among the hashed ones, taken now if it has
+// none; LINE_EMPTY: none was free
+template <bool VALS>
+__device__ __forceinline__ uint32_t line_place(const LineBins<VALS> &B, uint32_t tag)
+{
+    const uint32_t n = B.lines - B.own;
+    if (n == 0) return LINE_EMPTY;
+    uint32_t h = B.own + __umulhi(tag * 2654435761u, n);
+    for (int k = 0; k < LINE_PROBES; k++) {
+        uint32_t t = B.tag[h];
+        if (t == LINE_EMPTY) t = atomicCAS(&B.tag[h], LINE_EMPTY, tag);
+        if (t == LINE_EMPTY || t == tag) return h;
+        h = h + 1 == B.lines ? B.own : h + 1;
+    }
+    return LINE_EMPTY;
+}
+
+// n points of polygon p < np with the sum v of their values' low VAL_BITS bits
 template <bool VALS>
 __device__ __forceinline__ void line_add(const LineBins<VALS> &B, uint32_t p, uint32_t n,
                                          unsigned long long v, const TaskDev &T)
@@ -1993,45 +2019,53 @@ __device__ __forceinline__ void line_add(const LineBins<VALS> &B, uint32_t p, ui
     constexpr uint32_t mask = (1u << LineBins<VALS>::LOG2) - 1u;
     const uint32_t line = p >> LineBins<VALS>::LOG2;
     const Word w = VALS ? (Word)(((unsigned long long)n << SUM_BITS) + v) : (Word)n;
-    uint32_t h = line;
-    if (!B.direct) {
-        h = __umulhi(line * 2654435761u, B.lines);
-        bool found = false;
-        for (int k = 0; k < LINE_PROBES; k++) {
-            uint32_t t = B.tag[h];
-            if (t == LINE_EMPTY) t = atomicCAS(&B.tag[h], LINE_EMPTY, line);
-            if (t == LINE_EMPTY || t == line) {
-                found = true;
-                break;
-            }
-            h = h + 1 == B.lines ? 0 : h + 1;
-        }
-        if (!found) {
-            gadd(&T.counts[p], n);
-            if (VALS) gadd(&T.sums[p], v);
-            return;
-        }
+    const uint32_t h = B.own ? line : line_place(B, line);
+    if (h == LINE_EMPTY) {
+        gadd(&T.counts[p], n);
+        if (VALS) gadd(&T.sums[p], v);
+        return;
     }
     atomicAdd(&B.bin[(h << LineBins<VALS>::LOG2) | (p & mask)], w);
 }
 
-// the bins to the outputs and back to zero, the lines' places free again (every
-// place is seen: 130 KB take 16 rounds of 1024 lanes)
+// the sum v of what the values of polygon p < np are without those bits
+__device__ __forceinline__ void line_add_high(const LineBins<true> &B, uint32_t p,
+                                              unsigned long long v, const TaskDev &T)
+{
+    constexpr int LG = LineBins<true>::LOG2;
+    const uint32_t line = p >> LG;
+    const uint32_t h = B.high_own ? B.own + line : line_place(B, LINE_HIGH | line);
+    if (h == LINE_EMPTY) gadd(&T.sums[p], v);
+    else atomicAdd(&B.bin[(h << LG) | (p & ((1u << LG) - 1u))], v);
+}
+
+// the bins to the outputs and back to zero, the hashed lines' places free again
+// (every place is seen: 130 KB take 16 rounds of 1024 lanes)
 template <bool VALS>
 __device__ __forceinline__ void line_flush(const LineBins<VALS> &B, const TaskDev &T)
 {
     constexpr int LG = LineBins<VALS>::LOG2;
     for (uint32_t k = threadIdx.x; k < B.lines << LG; k += LINE_BLOCK) {
         const auto w = B.bin[k];
-        const uint32_t line = B.direct ? k >> LG : B.tag[k >> LG];
-        // the line's last bin frees its place (its 16 or 32 lanes are of one
-        // wavefront and have read the tag)
-        if (!B.direct && (k & ((1u << LG) - 1u)) == (1u << LG) - 1u) B.tag[k >> LG] = LINE_EMPTY;
+        const uint32_t h = k >> LG;
+        uint32_t line;
+        if (h < B.own) {
+            line = h;
+        } else if (B.high_own) {
+            line = LINE_HIGH | (h - B.own);
+        } else {
+            line = B.tag[h];
+            // the line's last bin frees its place (its 16 or 32 lanes are of one
+            // wavefront and have read the tag)
+            if ((k & ((1u << LG) - 1u)) == (1u << LG) - 1u) B.tag[h] = LINE_EMPTY;
+        }
         if (w == 0) continue;
         B.bin[k] = 0;
-        const uint32_t p = (line << LG) | (k & ((1u << LG) - 1u));
+        const uint32_t p = ((line & ~LINE_HIGH) << LG) | (k & ((1u << LG) - 1u));
         if (p >= T.A.np) continue;
-        if (VALS) {
+        if (VALS && (line & LINE_HIGH)) {
+            gadd(&T.sums[p], (unsigned long long)w);
+        } else if (VALS) {
             gadd(&T.counts[p], (unsigned long long)w >> SUM_BITS);
             gadd(&T.sums[p], (unsigned long long)w & ((1ull << SUM_BITS) - 1));
         } else {
@@ -2056,8 +2090,9 @@ __global__ __launch_bounds__(LINE_BLOCK, 4) void k_probe_items(const TaskDev T0,
     B.bin = (Word *)line_lds;
     B.tag = (uint32_t *)(B.bin + ((size_t)NL << LG));
     const uint32_t need = (T.A.np + (1u << LG) - 1u) >> LG;
-    B.direct = need <= (uint32_t)NL;
-    B.lines = B.direct ? need : (uint32_t)NL;
+    B.own = need <= (uint32_t)NL ? need : 0u;
+    B.high_own = VALS && 2 * need <= (uint32_t)NL;
+    B.lines = B.high_own ? 2 * need : (B.own && !VALS ? need : (uint32_t)NL);
     for (uint32_t k = threadIdx.x; k < B.lines << LG; k += LINE_BLOCK) B.bin[k] = 0;
     for (uint32_t k = threadIdx.x; k < B.lines; k += LINE_BLOCK) B.tag[k] = LINE_EMPTY;
     if (LAYOUT) {
@@ -2069,19 +2104,15 @@ __global__ __launch_bounds__(LINE_BLOCK, 4) void k_probe_items(const TaskDev T0,
     uint32_t *qpoint = s_queue[wave][0], *qcode = s_queue[wave][1],
              *qcell = s_queue[wave][LAYOUT ? 2 : 0];
     int queued = 0;  // the same in every lane of the wavefront
-    // n points of polygon code - 1, v their values' sum, each value in range
-    auto add = [&](uint32_t code, uint32_t n, unsigned long long v) {
-        if (code - 1u < T.A.np) line_add<VALS>(B, code - 1u, n, v, T);
+    constexpr unsigned long long LOW = (1ull << VAL_BITS) - 1;
+    // n points of polygon code - 1, the sums of their values' low bits and of the rest
+    auto add = [&](uint32_t code, uint32_t n, unsigned long long lo, unsigned long long hi) {
+        if (code - 1u >= T.A.np) return;
+        line_add<VALS>(B, code - 1u, n, lo, T);
+        if constexpr (VALS)
+            if (hi) line_add_high(B, code - 1u, hi, T);
     };
-    auto one = [&](uint32_t p, long long v) {
-        if (p >= T.A.np) return;
-        if (!VALS || ((unsigned long long)v >> VAL_BITS) == 0) {
-            line_add<VALS>(B, p, 1, (unsigned long long)v, T);
-        } else {
-            gadd(&T.counts[p], 1ull);
-            gadd(&T.sums[p], (unsigned long long)v);
-        }
-    };
+    auto one = [&](uint32_t p, unsigned long long v) { add(p + 1u, 1, v & LOW, v & ~LOW); };
     // the newest (up to 64) queued points, a lane each
     auto drain = [&]() {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -2091,7 +2122,7 @@ __global__ __launch_bounds__(LINE_BLOCK, 4) void k_probe_items(const TaskDev T0,
         queued -= m;
         if (lane < m) {
             const int64_t i = qpoint[queued + lane];
-            const long long v = VALS ? gld(T.vals + i) : 0;
+            const unsigned long long v = VALS ? (unsigned long long)gld(T.vals + i) : 0;
             uint32_t c = qcode[queued + lane];
             if (LAYOUT && (c & TILE_MIXED)) {
                 const uint32_t ij = qcell[queued + lane];
@@ -2169,11 +2200,9 @@ __global__ __launch_bounds__(LINE_BLOCK, 4) void k_probe_items(const TaskDev T0,
             else dir_codes<NP>(T.hv, xs, ys, c, cell);
 #pragma unroll
             for (int k = 0; k < NP; k++) {
-                const long long v = (k & 1) ? vv[k >> 1].y : vv[k >> 1].x;
                 // not one polygon's code (sets lie above them, and mixed
-                // blocks' entries above those), or a large value
-                const bool slow = c[k] >= CODE_SET_BASE ||
-                                  (VALS && c[k] != 0 && ((unsigned long long)v >> VAL_BITS) != 0);
+                // blocks' entries above those)
+                const bool slow = c[k] >= CODE_SET_BASE;
                 const uint64_t b = __ballot(slow);
                 if (b) {
                     if (slow) {
@@ -2191,22 +2220,25 @@ __global__ __launch_bounds__(LINE_BLOCK, 4) void k_probe_items(const TaskDev T0,
             // a lane's points of the trip (pairs 64 apart) often share their
             // code when the input is in spatial order: runs take one add
             uint32_t cur = c[0], run = 1;
-            unsigned long long rs = (unsigned long long)vv[0].x;
+            unsigned long long lo = (unsigned long long)vv[0].x & LOW,
+                               hi = (unsigned long long)vv[0].x & ~LOW;
 #pragma unroll
             for (int k = 1; k < NP; k++) {
                 const unsigned long long v =
                     (unsigned long long)((k & 1) ? vv[k >> 1].y : vv[k >> 1].x);
                 if (c[k] == cur) {
                     run++;
-                    rs += v;
+                    lo += v & LOW;
+                    hi += v & ~LOW;
                 } else {
-                    add(cur, run, rs);
+                    add(cur, run, lo, hi);
                     cur = c[k];
                     run = 1;
-                    rs = v;
+                    lo = v & LOW;
+                    hi = v & ~LOW;
                 }
             }
-            add(cur, run, rs);
+            add(cur, run, lo, hi);
         }
         if (++done == flush_every || ch + nx >= last) {  // the same in the whole workgroup
             done = 0;
