@@ -81,6 +81,14 @@ struct sba_handle;
 int sba_debug_learned_fallbacks(const struct sba_handle *h, const int32_t *xy, int64_t n,
                                 int64_t *fallbacks, int64_t *mismatches, void *stream);
 
+/* The probes' search for a key's run among n ascending starts (1..2^30, the first
+ * at or before every key), as the kernels make it, on the host: run[k] = the
+ * last start at or before key[k], rounds[k] = the rounds of loads that took.
+ * guess: where the learned index's estimate would start it, negative for none.
+ * HOST arrays of n and m entries. */
+int sba_debug_run_search(const uint64_t *starts, int64_t n, const uint64_t *key, int64_t m,
+                         int64_t guess, int64_t *run, int32_t *rounds);
+
 /* Lower bounds in a point index: out[k] = number of indexed points whose cell
  * key is below v[k] (0 <= v[k] <= 4^L), by binary search (search 0) or the
  * RadixSpline (search 1).  v and out are DEVICE arrays of n entries; the host

@@ -231,6 +231,8 @@ def lib():
     L.sba_join_pairs.argtypes = [vp, vp, i64, vp, vp, vp, C.POINTER(i64), vp]
     L.sba_debug_learned_fallbacks.restype = C.c_int
     L.sba_debug_learned_fallbacks.argtypes = [vp, vp, i64, C.POINTER(i64), C.POINTER(i64), vp]
+    L.sba_debug_run_search.restype = C.c_int
+    L.sba_debug_run_search.argtypes = [vp, i64, vp, i64, i64, vp, vp]
     L.sba_debug_pindex_lb.restype = C.c_int
     L.sba_debug_pindex_lb.argtypes = [vp, vp, i64, i32, vp, C.POINTER(i64), vp]
     L.sba_debug_radix_sort.restype = C.c_int
