@@ -1680,7 +1680,7 @@ extern "C" const char *sba_probe_kernel(const sba_handle *h, int with_values)
     if (h->kind == SBA_KIND_GRID && h->n_polys <= LDS_MAX_POLYS)
         snprintf(buf, sizeof(buf), "k_probe_lds<%s>", v);
     else
-        snprintf(buf, sizeof(buf), "k_probe_items<%d, %s, 1>", layout, v);
+        snprintf(buf, sizeof(buf), "k_probe_items<%d, %s, 1, %d>", layout, v, PROBE_UNROLL);
     return buf;
 }
 
@@ -2001,7 +2001,8 @@ __device__ __forceinline__ void table_flush(const CodeTable &H, const TaskDev &T
 #define LINE_PROBES 4
 #define LINE_EMPTY 0xffffffffu
 #define LINE_HIGH 0x80000000u  // a tag's mark: bins of values' high parts
-#define CHUNK (LINE_WAVES * 64 * 2 * PROBE_UNROLL)  // points a workgroup takes at a time
+// points a workgroup takes at a time, `unroll` pairs a lane
+static constexpr int chunk_points(int unroll) { return LINE_WAVES * 64 * 2 * unroll; }
 #define FLUSH_POINTS (1 << 19)  // below 2^20: a bin's count has 20 bits
 #define VAL_BITS 24
 #define SUM_BITS 44
@@ -2110,7 +2111,7 @@ __device__ __forceinline__ void line_flush(const LineBins<VALS> &B, const TaskDe
     }
 }
 
-template <int LAYOUT, bool VALS, int PER_CU>
+template <int LAYOUT, bool VALS, int PER_CU, int UNROLL>
 __global__ __launch_bounds__(LINE_BLOCK, 4) void k_probe_items(const TaskDev T0, int64_t chunks,
                                                                int flush_every)
 {
@@ -2184,8 +2185,8 @@ __global__ __launch_bounds__(LINE_BLOCK, 4) void k_probe_items(const TaskDev T0,
     };
     const int4 *xy4 = (const int4 *)T.xy;
     const longlong2 *v2 = (const longlong2 *)T.vals;
-    constexpr int NP = 2 * PROBE_UNROLL;
-    constexpr int64_t WB = 64 * PROBE_UNROLL;
+    constexpr int NP = 2 * UNROLL;
+    constexpr int64_t WB = 64 * UNROLL;
     const int64_t npairs = T.n >> 1;
     if ((T.n & 1) && blockIdx.x == 0 && threadIdx.x == 0) {
         const int64_t i = T.n - 1;
@@ -2195,14 +2196,14 @@ __global__ __launch_bounds__(LINE_BLOCK, 4) void k_probe_items(const TaskDev T0,
     // each wave takes WB consecutive pairs of a chunk, so the points of one
     // wave's trip are neighbours in the input; lanes past the end take a point
     // no cell holds.  The chunk after next is loaded while one is counted.
-    int4 qn[PROBE_UNROLL];
-    longlong2 vn[PROBE_UNROLL];
+    int4 qn[UNROLL];
+    longlong2 vn[UNROLL];
     const int64_t nx = gridDim.x >> 3, per = (chunks + 7) >> 3;
     const int64_t first = (int64_t)(blockIdx.x & 7) * per + (blockIdx.x >> 3);
     const int64_t last = min((int64_t)(blockIdx.x & 7) * per + per, chunks);
     auto load = [&](int64_t ch) {
 #pragma unroll
-        for (int u = 0; u < PROBE_UNROLL; u++) {
+        for (int u = 0; u < UNROLL; u++) {
             const int64_t t = (ch * LINE_WAVES + wave) * WB + (int64_t)u * 64 + lane;
             const bool in = ch < last && t < npairs;
             qn[u] = in ? gld(xy4 + t) : make_int4(INT32_MIN, INT32_MIN, INT32_MIN, INT32_MIN);
@@ -2214,17 +2215,17 @@ __global__ __launch_bounds__(LINE_BLOCK, 4) void k_probe_items(const TaskDev T0,
     for (int64_t ch = first; ch < last; ch += nx) {
         {
             const int64_t w0 = (ch * LINE_WAVES + wave) * WB;
-            int4 q[PROBE_UNROLL];
-            longlong2 vv[PROBE_UNROLL];
+            int4 q[UNROLL];
+            longlong2 vv[UNROLL];
 #pragma unroll
-            for (int u = 0; u < PROBE_UNROLL; u++) {
+            for (int u = 0; u < UNROLL; u++) {
                 q[u] = qn[u];
                 vv[u] = vn[u];
             }
             load(ch + nx);
             int32_t xs[NP], ys[NP];
 #pragma unroll
-            for (int u = 0; u < PROBE_UNROLL; u++) {
+            for (int u = 0; u < UNROLL; u++) {
                 xs[2 * u] = q[u].x;
                 ys[2 * u] = q[u].y;
                 xs[2 * u + 1] = q[u].z;
@@ -2288,13 +2289,28 @@ __global__ __launch_bounds__(LINE_BLOCK, 4) void k_probe_items(const TaskDev T0,
 
 typedef void (*items_fn)(const TaskDev, int64_t, int);
 
-template <int PER_CU>
+template <int PER_CU, int UNROLL>
 static items_fn items_pick(int layout, bool vals)
 {
-    const items_fn kerns[6] = {k_probe_items<0, false, PER_CU>, k_probe_items<0, true, PER_CU>,
-                               k_probe_items<1, false, PER_CU>, k_probe_items<1, true, PER_CU>,
-                               k_probe_items<2, false, PER_CU>, k_probe_items<2, true, PER_CU>};
+    const items_fn kerns[6] = {
+        k_probe_items<0, false, PER_CU, UNROLL>, k_probe_items<0, true, PER_CU, UNROLL>,
+        k_probe_items<1, false, PER_CU, UNROLL>, k_probe_items<1, true, PER_CU, UNROLL>,
+        k_probe_items<2, false, PER_CU, UNROLL>, k_probe_items<2, true, PER_CU, UNROLL>};
     return kerns[layout * 2 + (vals ? 1 : 0)];
+}
+
+// Pairs a lane takes at a time: fewer where chunks of eight points a lane would
+// leave most compute units without one, and a wavefront to drain its queue of up
+// to 512 points alone.  A pass in us with four pairs, and with this rule, points
+// in no order: 20,000 over 1,200 polygons in six layers (every cell has a set)
+// 43.8, 12.9, over 40,000 at 1 m 34.8, 16.8; 262,144 of these 75.7, 25.1 and
+// 44.7, 33.9; 524,288 (two pairs) 76.1, 42.9 and 52.5, 48.8.  With two pairs 2^20
+// points over 40,000 take 83.6 instead of 76.5: more workgroups send their bins
+// out.
+static int items_unroll(int64_t n, int per_cu)
+{
+    if (per_cu != 1) return PROBE_UNROLL;
+    return n <= (1 << 18) ? 1 : (n <= (1 << 19) ? 2 : PROBE_UNROLL);
 }
 
 static int launch_items(const int32_t *xy, const int64_t *values, int64_t n, const sba_handle *h,
@@ -2314,7 +2330,11 @@ static int launch_items(const int32_t *xy, const int64_t *values, int64_t n, con
     hipLaunchKernelGGL(k_zero_out, dim3(grid_for(h->n_polys)), dim3(256), 0, st, counts,
                        vals ? sums : nullptr, h->n_polys);
     const int lds = line_count(per_cu) * (128 + 4);
-    const items_fn kern = per_cu == 2 ? items_pick<2>(layout, vals) : items_pick<1>(layout, vals);
+    const int unroll = items_unroll(n, per_cu), chunk = chunk_points(unroll);
+    const items_fn kern = per_cu == 2   ? items_pick<2, PROBE_UNROLL>(layout, vals)
+                          : unroll == 1 ? items_pick<1, 1>(layout, vals)
+                          : unroll == 2 ? items_pick<1, 2>(layout, vals)
+                                        : items_pick<1, PROBE_UNROLL>(layout, vals);
     (void)hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     (void)hipGetLastError();
     // queued points are numbered in 32 bits: at most 2^31 of them a launch
@@ -2322,13 +2342,13 @@ static int launch_items(const int32_t *xy, const int64_t *values, int64_t n, con
         T.n = std::min<int64_t>(n - at, (int64_t)1 << 31);
         T.xy = xy + 2 * at;
         if (vals) T.vals = values + at;
-        const int64_t chunks = (T.n + CHUNK - 1) / CHUNK;
+        const int64_t chunks = (T.n + chunk - 1) / chunk;
         int64_t nb = std::min<int64_t>(chunks, (int64_t)cu_count() * per_cu);
         nb = (nb + 7) & ~(int64_t)7;  // whole rounds of the 8 XCDs
         // a workgroup's bins go out after FLUSH_POINTS points at most; over
         // partitioned points every few chunks, before lines of regions left
         // behind fill the places
-        const int flush_every = per_cu == 2 ? 6 : FLUSH_POINTS / CHUNK;
+        const int flush_every = per_cu == 2 ? 6 : FLUSH_POINTS / chunk;
         hipLaunchKernelGGL(kern, dim3((unsigned)nb), dim3(LINE_BLOCK), lds, st, T, chunks,
                            flush_every);
     }
