@@ -331,114 +331,137 @@ static int write_runs(BuildState &B, sba_handle *h, const K *bk, hipStream_t st)
 
 // ---------------------------------------------------------------- block directory
 //
-// One entry per aligned square block of cells (a stretch of consecutive keys):
-// the code of the run that holds the whole block, or TILE_MIXED | the run that
-// holds its first key, from which a search reaches any key of the block.  Most
+// One entry per aligned square block of cells of the stored box (a stretch of
+// consecutive keys): the code of the run that holds the whole block, or
+// TILE_MIXED | the run that holds its first key, from which a search reaches
+// any key of the block.  Most
 // blocks of a partition lie in one run (91 % of the 16 x 16 blocks of 40,000
 // polygons at 1 m), so most lookups are one 4-byte read, at an address that
 // takes no Hilbert key, where a search over the runs takes 6 to 9 cache lines.
-// At least four times as many blocks as runs, at most 2^24 (64 MB, which the
+// Blocks as small as 16 of them a run allow, at most 2^24 (64 MB, which the
 // memory-side cache holds; 2^22 and 2^23 made the probe of 2e7 points in no
-// order 9 and 4 % slower, by their mixed blocks).
-#define DIR_BITS_MAX 24
-#define DIR_LONG 2048   // runs over more blocks are filled by the whole grid
+// order 9 and 4 % slower, by their mixed blocks).  They cover the stored box
+// only, not the whole key grid: on a grid much larger than the polygons (a
+// point index's, or one for several sets) blocks of 4^-12 of it held all runs.
+#define DIR_MAX ((int64_t)1 << 24)
+#define DIR_SQUARE 6    // blocks of a workgroup: a square of 2^6 a side
 
-// Run i's entries are the blocks whose first key it holds.  A wavefront shares
-// the entries of its 64 runs; long runs go to a list (cnt, list).  2^24 entries
-// of 28.9M runs: 159 us (267 while each entry's cell was found level by level).
-__global__ __launch_bounds__(256) void k_dir_fill(const uint64_t *starts, const uint32_t *code,
-                                                  int64_t n, uint64_t total, int shift, int dl,
-                                                  uint32_t *dir, uint32_t *list,
-                                                  unsigned long long *cnt)
+struct DirGeo {
+    int L, r;           // levels of the key grid; blocks of 2^r cells a side
+    int q;              // workgroups' squares of 2^q blocks a side (at most the grid)
+    uint32_t bw, bh;    // blocks of the box
+    uint32_t sw;        // squares a row
+    uint32_t cols;      // tiles of 8 blocks a row (block_index)
+};
+
+// The first run in (lo, hi] that starts at or after v (hi if none does); run lo
+// starts before it.  All 64 lanes of the wavefront search together.
+__device__ __forceinline__ int64_t first_at_least(const uint64_t *starts, int64_t lo, int64_t hi,
+                                                  uint64_t v)
 {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const int lane = threadIdx.x & 63;
-    uint64_t next = 0, b0 = 0, m = 0;
-    uint32_t c = 0;
-    if (i < n) {
-        next = i + 1 < n ? starts[i + 1] : total;
-        const uint64_t r = ((uint64_t)1 << shift) - 1;
-        b0 = (starts[i] + r) >> shift;
-        m = ((next + r) >> shift) - b0;
-        c = code[i];
-        if (m > DIR_LONG) {
-            list[atomicAdd(cnt, 1ull)] = (uint32_t)i;
-            m = 0;
-        }
+    while (hi - lo > 1) {
+        // places lo + 1 .. hi - 1 in 64 steps
+        const int64_t step = (hi - lo + 63) >> 6, at = lo + (lane + 1) * step;
+        const uint64_t below = __ballot(at < hi && starts[at] < v);
+        const int n = __popcll(below);  // starts ascend: the first n lanes
+        const int64_t l = lo + (int64_t)n * step, h = lo + (int64_t)(n + 1) * step;
+        lo = l;
+        hi = h < hi ? h : hi;
     }
-    uint32_t incl = (uint32_t)m;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t u = (uint32_t)__shfl_up((int)incl, o, 64);
-        if (lane >= o) incl += u;
+    return hi;
+}
+
+// A workgroup writes the entries of one square of blocks, a stretch of keys:
+// each of its runs has the blocks whose first key it holds.  A wavefront shares
+// the entries of its 64 runs; where the square has no more than 64, all
+// wavefronts share them.  (One launch over all runs, with a list of those over
+// more than 2,048 blocks that the whole grid then filled one after another: 159
+// + 15 us for 2^24 entries of 28.9M runs, but 800 us for a few hundred large
+// polygons, which are mostly such runs.)
+__global__ __launch_bounds__(256) void k_dir_fill(const uint64_t *__restrict__ starts,
+                                                  const uint32_t *__restrict__ code, int64_t n,
+                                                  DirGeo D, uint32_t *__restrict__ dir)
+{
+    __shared__ int64_t range[2];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, lv = D.L - D.r;
+    const uint32_t sj = blockIdx.x / D.sw, si = blockIdx.x - sj * D.sw;
+    const int kb = 2 * (D.r + D.q);  // bits of a key inside the square
+    const uint64_t k0 = hilbert_index(lv - D.q, si, sj) << kb, k1 = k0 + ((uint64_t)1 << kb);
+    const uint64_t total = (uint64_t)1 << (2 * D.L), part = ((uint64_t)1 << (2 * D.r)) - 1;
+    // the run that holds the first key, and the first past the last one
+    if (w < 2) {
+        const int64_t f = first_at_least(starts, 0, n, w ? k1 : k0 + 1);
+        if (lane == 0) range[w] = w ? f : f - 1;
     }
-    const uint32_t all = (uint32_t)__shfl((int)incl, 63, 64);
-    for (uint32_t t0 = 0; t0 < all; t0 += 64) {
-        const uint32_t t = t0 + lane;
-        // the lane's run: the first whose inclusive count exceeds t
-        int a = 0;
-#pragma unroll
-        for (int step = 32; step > 0; step >>= 1) {
-            const uint32_t u = (uint32_t)__shfl((int)incl, a + step - 1, 64);
-            a += u <= t ? step : 0;
+    __syncthreads();
+    const int64_t r0 = range[0], r1 = range[1];
+    const bool few = r1 - r0 <= 64;
+    for (int64_t base = few ? r0 : r0 + w * 64; base < r1; base += 256) {
+        const int64_t i = base + lane;
+        uint64_t next = 0, b0 = 0;
+        uint32_t c = 0, m = 0;
+        if (i < r1) {
+            const uint64_t at = starts[i] > k0 ? starts[i] : k0;
+            next = i + 1 < n ? starts[i + 1] : total;
+            const uint64_t to = next < k1 ? next : k1;
+            b0 = (at + part) >> (2 * D.r);
+            m = (uint32_t)(((to + part) >> (2 * D.r)) - b0);
+            c = code[i];
         }
-        a = a > 63 ? 63 : a;
-        const uint32_t first = (uint32_t)__shfl((int)(incl - (uint32_t)m), a, 64);
-        const uint64_t bb = __shfl((unsigned long long)b0, a, 64) + (t - first);
-        const uint64_t nx = __shfl((unsigned long long)next, a, 64);
-        const uint32_t cc = (uint32_t)__shfl((int)c, a, 64);
-        if (t < all) {
-            uint32_t ib, jb;
-            hilbert_cell(dl, bb, &ib, &jb);
-            dir[block_index(ib, jb, dl)] =
-                ((bb + 1) << shift) <= nx ? cc : (TILE_MIXED | (uint32_t)(i - lane + a));
+        uint32_t incl = m;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t u = (uint32_t)__shfl_up((int)incl, o, 64);
+            if (lane >= o) incl += u;
+        }
+        const uint32_t all = (uint32_t)__shfl((int)incl, 63, 64);
+        for (uint32_t t0 = few ? w * 64 : 0; t0 < all; t0 += few ? 256 : 64) {
+            const uint32_t t = t0 + lane;
+            // the lane's run: the first whose inclusive count exceeds t
+            int a = 0;
+#pragma unroll
+            for (int step = 32; step > 0; step >>= 1) {
+                const uint32_t u = (uint32_t)__shfl((int)incl, a + step - 1, 64);
+                a += u <= t ? step : 0;
+            }
+            a = a > 63 ? 63 : a;
+            const uint32_t first = (uint32_t)__shfl((int)(incl - m), a, 64);
+            const uint64_t bb = __shfl((unsigned long long)b0, a, 64) + (t - first);
+            const uint64_t nx = __shfl((unsigned long long)next, a, 64);
+            const uint32_t cc = (uint32_t)__shfl((int)c, a, 64);
+            uint32_t ib = 0, jb = 0;
+            if (t < all) hilbert_cell(lv, bb, &ib, &jb);
+            if (t < all && ib < D.bw && jb < D.bh)
+                dir[block_index(ib, jb, D.cols)] =
+                    ((bb + 1) << (2 * D.r)) <= nx ? cc : (TILE_MIXED | (uint32_t)(base + a));
         }
     }
 }
 
-__global__ __launch_bounds__(256) void k_dir_long(const uint64_t *starts, const uint32_t *code,
-                                                  int64_t n, uint64_t total, int shift, int dl,
-                                                  uint32_t *dir, const uint32_t *list,
-                                                  const unsigned long long *cnt)
+static int build_directory(sba_handle *h, hipStream_t st)
 {
-    const int64_t nl = (int64_t)*cnt;
-    const uint64_t r = ((uint64_t)1 << shift) - 1;
-    for (int64_t q = 0; q < nl; q++) {
-        const int64_t i = list[q];
-        const uint64_t next = i + 1 < n ? starts[i + 1] : total;
-        const uint64_t b1 = (next + r) >> shift;
-        const uint32_t c = code[i];
-        for (uint64_t b = ((starts[i] + r) >> shift) + (uint64_t)blockIdx.x * 256 + threadIdx.x;
-             b < b1; b += (uint64_t)gridDim.x * 256) {
-            uint32_t ib, jb;
-            hilbert_cell(dl, b, &ib, &jb);
-            dir[block_index(ib, jb, dl)] =
-                ((b + 1) << shift) <= next ? c : (TILE_MIXED | (uint32_t)i);
-        }
+    DirGeo D{};
+    D.L = h->level;
+    const int64_t most = std::min(
+        DIR_MAX, std::max<int64_t>(1024, (int64_t)16 << bits_for((uint64_t)h->n_runs - 1)));
+    int64_t entries = 0;
+    for (D.r = 0;; D.r++) {
+        D.bw = (uint32_t)(((h->gw - 1) >> D.r) + 1);
+        D.bh = (uint32_t)(((h->gh - 1) >> D.r) + 1);
+        D.cols = (D.bw + 7) >> 3;
+        entries = (int64_t)D.cols * ((D.bh + 3) >> 2) * 32;
+        if (entries <= most || D.r == D.L) break;
     }
-}
-
-static int build_directory(BuildState &B, sba_handle *h, hipStream_t st)
-{
-    const int bits = std::min(DIR_BITS_MAX, bits_for((uint64_t)h->n_runs) + 2);
-    const int dl = std::min(h->level, (bits + 1) / 2);
-    const int64_t blocks = (int64_t)1 << (2 * dl);
-    const int shift = 2 * (h->level - dl);
-    h->dir_level = dl;
-    RC(handle_alloc(h, &h->pdir, blocks));
-    uint32_t *list = nullptr;
-    unsigned long long *cnt = nullptr;
-    RC(B.alloc(&list, blocks / DIR_LONG + 1));
-    RC(B.alloc(&cnt, 1));
-    HIP_OK(hipMemsetAsync(cnt, 0, sizeof(unsigned long long), st));
-    const uint64_t total = (uint64_t)1 << (2 * h->level);
-    hipLaunchKernelGGL(k_dir_fill, dim3(grid_for(h->n_runs)), dim3(256), 0, st, h->starts,
-                       h->run_code, h->n_runs, total, shift, dl, h->pdir, list, cnt);
-    hipLaunchKernelGGL(k_dir_long, dim3(512), dim3(256), 0, st, h->starts, h->run_code, h->n_runs,
-                       total, shift, dl, h->pdir, list, cnt);
+    D.q = std::min(DIR_SQUARE, D.L - D.r);
+    D.sw = ((D.bw - 1) >> D.q) + 1;
+    const uint32_t sh = ((D.bh - 1) >> D.q) + 1;
+    h->dir_r = D.r;
+    h->dir_cols = D.cols;
+    RC(handle_alloc(h, &h->pdir, entries));
+    hipLaunchKernelGGL(k_dir_fill, dim3(D.sw * sh), dim3(256), 0, st, h->starts, h->run_code,
+                       h->n_runs, D, h->pdir);
     HIP_OK(hipGetLastError());
-    B.release(list);
-    B.release(cnt);
     return 0;
 }
 
@@ -601,7 +624,7 @@ int hilbert_finish(BuildState &B, sba_handle *h, const sba_build_opts &o, hipStr
     if (B.bkeys32) RC(write_runs<uint32_t>(B, h, B.bkeys32, st));
     else RC(write_runs<uint64_t>(B, h, B.bkeys, st));
     const int64_t nr = h->n_runs;
-    RC(build_directory(B, h, st));
+    RC(build_directory(h, st));
 
     if (o.search == SBA_SEARCH_LEARNED) {
         if (2 * L > 32) return SBA_ELIMIT;  // leaves store 32-bit key bases

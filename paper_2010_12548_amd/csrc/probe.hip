@@ -69,7 +69,8 @@ struct HilbView {
     // block directory (sba_handle::pdir) and cells in 32-bit arithmetic, as in
     // Grid16: valid when the stored box lies in the int32 coordinates
     const uint32_t *dir;
-    int32_t dl;
+    int32_t dr;            // blocks of 2^dr cells a side
+    uint32_t cols;
     uint32_t pre, post;
     int32_t fits32;
     float a;               // learned root
@@ -440,7 +441,7 @@ __host__ __device__ inline int32_t run_search(const K *keys, K key, int32_t lo, 
 template <bool LEARNED, typename K>
 __device__ __forceinline__ int32_t run_in_block(const HilbView &v, const K *keys, K key, int32_t lo)
 {
-    const int32_t hi = (int32_t)min((int64_t)lo + ((int64_t)1 << min(2 * (v.L - v.dl), 30)), v.n);
+    const int32_t hi = (int32_t)min((int64_t)lo + ((int64_t)1 << min(2 * v.dr, 30)), v.n);
     int32_t guess = -1;
     if (LEARNED) {
         const int4 lf = v.leaves[root_leaf((uint64_t)key, v.a, v.nl)];
@@ -459,7 +460,7 @@ __device__ __forceinline__ void dir_codes(const HilbView &v, const int32_t *xs, 
 {
     bool ok[NP];
     uint32_t b[NP];
-    const int r = v.L - v.dl;
+    const int r = v.dr;
     if (v.fits32) {
         // a point and the box both lie in the int32 coordinates, so the
         // offset modulo 2^32 is below the extent exactly when the point is in
@@ -472,7 +473,7 @@ __device__ __forceinline__ void dir_codes(const HilbView &v, const int32_t *xs, 
             const uint32_t i = __umulhi((ok[k] ? dx : 0u) << v.pre, v.mag) >> v.post;
             const uint32_t j = __umulhi((ok[k] ? dy : 0u) << v.pre, v.mag) >> v.post;
             cell[k] = i | (j << 16);
-            b[k] = block_index(i >> r, j >> r, v.dl);
+            b[k] = block_index(i >> r, j >> r, v.cols);
         }
     } else {
 #pragma unroll
@@ -482,7 +483,7 @@ __device__ __forceinline__ void dir_codes(const HilbView &v, const int32_t *xs, 
             const uint32_t i = divmagic(ok[k] ? (uint32_t)dx : 0u, v.mag, v.shift);
             const uint32_t j = divmagic(ok[k] ? (uint32_t)dy : 0u, v.mag, v.shift);
             cell[k] = i | (j << 16);
-            b[k] = block_index(i >> r, j >> r, v.dl);
+            b[k] = block_index(i >> r, j >> r, v.cols);
         }
     }
 #pragma unroll
@@ -748,7 +749,8 @@ static void views(const sba_handle *h, GridView *g, HilbView *hv)
         hv->k64 = h->starts;
         hv->code = h->run_code;
         hv->dir = h->pdir;
-        hv->dl = h->dir_level;
+        hv->dr = h->dir_r;
+        hv->cols = h->dir_cols;
         hv->pre = h->shift >= 32 ? 0u : 1u;
         hv->post = h->shift >= 32 ? (uint32_t)(h->shift - 32) : 0u;
         const int64_t lim = (int64_t)1 << 31;

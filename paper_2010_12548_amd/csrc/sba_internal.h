@@ -189,11 +189,11 @@ struct sba_handle {
     uint32_t *starts32;  // [n_runs] same keys when 2*level <= 32 (else NULL)
     uint32_t *run_code;  // [n_runs] cell code of each run
     int64_t n_runs;
-    uint32_t *pdir;      // directory of square blocks of 2^(level - dir_level) cells a
-                         // side, 4^dir_level of them at block_index: the code of the run
-                         // that holds the whole block, else TILE_MIXED | the run that
-                         // holds its first key
-    int32_t dir_level;
+    uint32_t *pdir;      // directory of the stored box's square blocks of 2^dir_r cells a
+                         // side, at block_index: the code of the run that holds the
+                         // whole block, else TILE_MIXED | the run that holds its first key
+    int32_t dir_r;
+    uint32_t dir_cols;   // tiles of 8 blocks a row
     // learned index over starts
     int32_t log2_leaves;
     float root_a;        // leaf = floor((float)(key - root_k0) * root_a)
@@ -332,12 +332,11 @@ __host__ __device__ inline uint32_t hilbert_index_tab(int L, uint32_t i, uint32_
     return d;
 }
 
-// Place of block (ib, jb) in a directory of 2^dl x 2^dl blocks: rows of tiles
-// of 8 x 4 blocks, a 128-byte line each.
-__host__ __device__ inline uint32_t block_index(uint32_t ib, uint32_t jb, int dl)
+// Place of block (ib, jb) in a directory of rows of `cols` tiles of 8 x 4 blocks,
+// a 128-byte line each.
+__host__ __device__ inline uint32_t block_index(uint32_t ib, uint32_t jb, uint32_t cols)
 {
-    if (dl < 3) return (jb << dl) | ib;
-    return ((jb >> 2) << (dl + 2)) | ((ib >> 3) << 5) | ((jb & 3u) << 3) | (ib & 7u);
+    return (((jb >> 2) * cols + (ib >> 3)) << 5) | ((jb & 3u) << 3) | (ib & 7u);
 }
 
 // bits 0, 2, 4, ... of v, packed
