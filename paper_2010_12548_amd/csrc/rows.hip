@@ -273,13 +273,21 @@ __global__ void k_rows_init(const int32_t *ring_off, const int64_t *vert_off, in
 // pairs placed so far.  A workgroup whose edges lie within EROWS rows, as
 // neighbouring edges of a polygon do, counts in LDS and touches each row's
 // global word once.  epw edges a workgroup (its lanes share their pairs).
+// Workgroups whose edges have more than EPAIRS_MAX pairs, as edges across
+// thousands of rows make, are left out of the emitting launch: COUNT lists them
+// (big: their numbers; bigfig: how many, the most pairs of one), and another
+// launch gives their pairs to gridDim.y workgroups each, EPAIRS at a time.  (The
+// four edges of a box over 57,143 rows, by one workgroup: 587 us.)
 #define ROW_STATS 64
 #define ROW_STAT_STEP 16  // words between counter pairs: a cache line of their own
+#define EPAIRS_MAX 4096
+#define EPAIRS 1024
 
 template <bool EMIT>
 __global__ __launch_bounds__(EB) void k_edge_rows(PolyView P, RowGeo G, int epw, int32_t *rowdiff,
                                                   const int64_t *rowoff, uint4 *items,
-                                                  unsigned long long *stat)
+                                                  unsigned long long *stat, uint32_t *big,
+                                                  unsigned long long *bigfig)
 {
     __shared__ int32_t hist[EROWS + 1];
     __shared__ uint32_t base[EMIT ? EROWS : 1];
@@ -288,13 +296,13 @@ __global__ __launch_bounds__(EB) void k_edge_rows(PolyView P, RowGeo G, int epw,
     __shared__ int32_t sra[EMIT ? EB : 1], ska[EMIT ? EB : 1], skb[EMIT ? EB : 1];
     __shared__ uint32_t wsum[EB / 64];
     __shared__ int32_t lo_s, hi_s;
-    __shared__ unsigned long long sb[2];
+    __shared__ unsigned long long sb[3];
     const int tid = threadIdx.x;
-    const int64_t v = (int64_t)blockIdx.x * epw + tid;
+    const int64_t v = (int64_t)(EMIT && big ? big[blockIdx.x] : blockIdx.x) * epw + tid;
     if (tid == 0) {
         lo_s = INT32_MAX;
         hi_s = -1;
-        sb[0] = sb[1] = 0;
+        sb[0] = sb[1] = sb[2] = 0;
     }
     for (int k = tid; k <= EROWS; k += EB) hist[k] = 0;
     __syncthreads();
@@ -312,13 +320,16 @@ __global__ __launch_bounds__(EB) void k_edge_rows(PolyView P, RowGeo G, int epw,
     }
     if (!EMIT) {
         unsigned long long tb = nb, tc = nc;
+        uint32_t tn = (uint32_t)n;  // 256 edges of at most 2^21 rows
         for (int o = 32; o > 0; o >>= 1) {
             tb += __shfl_xor(tb, o, 64);
             tc += __shfl_xor(tc, o, 64);
+            tn += (uint32_t)__shfl_xor((int)tn, o, 64);
         }
         if ((tid & 63) == 0 && (tb | tc)) {
             atomicAdd(&sb[0], tb);
             atomicAdd(&sb[1], tc);
+            atomicAdd(&sb[2], (unsigned long long)tn);
         }
     }
     if ((tid & 63) == 0) {
@@ -331,6 +342,10 @@ __global__ __launch_bounds__(EB) void k_edge_rows(PolyView P, RowGeo G, int epw,
         unsigned long long *st = stat + ROW_STAT_STEP * (blockIdx.x & (ROW_STATS - 1));
         atomicAdd(&st[0], sb[0]);
         atomicAdd(&st[1], sb[1]);
+        if (sb[2] > EPAIRS_MAX) {
+            big[atomicAdd(&bigfig[0], 1ull)] = blockIdx.x;
+            atomicMax(&bigfig[1], sb[2]);
+        }
     }
     if (hi_s < 0) return;  // no pair in the whole workgroup
     const bool local = span <= EROWS;
@@ -373,25 +388,35 @@ __global__ __launch_bounds__(EB) void k_edge_rows(PolyView P, RowGeo G, int epw,
     auto row_at = [&](uint32_t t, int e) {
         return sra[e] + (int32_t)(t - (e ? off[e - 1] : 0u));
     };
-    if (local) {
-        for (uint32_t t = tid; t < total; t += EB) {
+    if (!big && total > EPAIRS_MAX) return;  // the other launch's
+    const uint32_t part = big ? EPAIRS : EPAIRS_MAX;
+    for (uint32_t t0 = blockIdx.y * part; t0 < total; t0 += gridDim.y * part) {
+        const uint32_t t1 = min(t0 + part, total);
+        if (local) {
+            for (uint32_t t = t0 + tid; t < t1; t += EB) {
+                const int e = edge_at(t);
+                atomicAdd(&hist[row_at(t, e) - r0], 1);
+            }
+            __syncthreads();
+            for (int k = tid; k < span; k += EB) {
+                const int32_t c = hist[k];
+                base[k] = c ? (uint32_t)atomicAdd(&rowdiff[r0 + k], c) : 0u;
+                hist[k] = 0;
+            }
+            __syncthreads();
+        }
+        for (uint32_t t = t0 + tid; t < t1; t += EB) {
             const int e = edge_at(t);
-            atomicAdd(&hist[row_at(t, e) - r0], 1);
+            const int32_t j = row_at(t, e);
+            const uint32_t at = local ? base[j - r0] + (uint32_t)atomicAdd(&hist[j - r0], 1)
+                                      : (uint32_t)atomicAdd(&rowdiff[j], 1);
+            items[rowoff[j] + at] = edge_row_item(se[e], j, j >= ska[e] && j <= skb[e], G);
         }
-        __syncthreads();
-        for (int k = tid; k < span; k += EB) {
-            const int32_t c = hist[k];
-            base[k] = c ? (uint32_t)atomicAdd(&rowdiff[r0 + k], c) : 0u;
-            hist[k] = 0;
+        if (local && big) {
+            __syncthreads();
+            for (int k = tid; k < span; k += EB) hist[k] = 0;
+            __syncthreads();
         }
-        __syncthreads();
-    }
-    for (uint32_t t = tid; t < total; t += EB) {
-        const int e = edge_at(t);
-        const int32_t j = row_at(t, e);
-        const uint32_t at = local ? base[j - r0] + (uint32_t)atomicAdd(&hist[j - r0], 1)
-                                  : (uint32_t)atomicAdd(&rowdiff[j], 1);
-        items[rowoff[j] + at] = edge_row_item(se[e], j, j >= ska[e] && j <= skb[e], G);
     }
 }
 
@@ -1279,8 +1304,9 @@ int rows_coverage(const sba_polygons *polys, const int4 *bbox, int64_t nv,
     int64_t *rowoff = nullptr;
     unsigned long long *stat = nullptr;
     // the pair counters, then the figures that the host reads: k_row_scan's
-    // and k_row_lists' eight, the sweep's totals (k_row_totals), the members of large sets
-    constexpr int NFIG = 12, NST = ROW_STATS * ROW_STAT_STEP + NFIG;
+    // and k_row_lists' eight, the sweep's totals (k_row_totals), the members of
+    // large sets, k_edge_rows' workgroups of many pairs
+    constexpr int NFIG = 14, NST = ROW_STATS * ROW_STAT_STEP + NFIG;
     RC(B.alloc(&rowdiff, (int64_t)gh + 1));
     RC(B.alloc(&rowoff, (int64_t)gh + 1));
     RC(B.alloc(&stat, NST));
@@ -1304,8 +1330,10 @@ int rows_coverage(const sba_polygons *polys, const int4 *bbox, int64_t nv,
     int epw = EB;
     while (epw > 4 && nv < (int64_t)1024 * epw) epw >>= 1;
     const dim3 egrid((unsigned)((nv + epw - 1) / epw));
+    uint32_t *big = nullptr;
+    RC(B.alloc(&big, egrid.x));
     hipLaunchKernelGGL(k_edge_rows<false>, egrid, dim3(EB), 0, st, P, G, epw, rowdiff,
-                       (const int64_t *)nullptr, (uint4 *)nullptr, stat);
+                       (const int64_t *)nullptr, (uint4 *)nullptr, stat, big, fig + 12);
     const bool few_rows = gh < RSCAN_LISTS;  // the scan has gh + 1 entries
     unsigned long long hs[NFIG];
     RC(B.ws.read(hs, fig, sizeof(hs)));
@@ -1330,7 +1358,7 @@ int rows_coverage(const sba_polygons *polys, const int4 *bbox, int64_t nv,
     if (2 * NB + NC >= ((int64_t)1 << 32)) return SBA_ELIMIT;
     auto leave = [&]() {
         for (void *p : {(void *)rowdiff, (void *)rowoff, (void *)stat, (void *)list, (void *)hint,
-                        (void *)row_stat, (void *)B.seg_beg, (void *)B.seg_end})
+                        (void *)big, (void *)row_stat, (void *)B.seg_beg, (void *)B.seg_end})
             B.release(p);
         B.seg_beg = B.seg_end = nullptr;
         sets_release(S, B);
@@ -1346,12 +1374,24 @@ int rows_coverage(const sba_polygons *polys, const int4 *bbox, int64_t nv,
     RC(B.alloc(&items, items_n));
     if (items_n) {
         hipLaunchKernelGGL(k_edge_rows<true>, egrid, dim3(EB), 0, st, P, G, epw, rowdiff, rowoff,
-                           items, (unsigned long long *)nullptr);
+                           items, (unsigned long long *)nullptr, (uint32_t *)nullptr,
+                           (unsigned long long *)nullptr);
+        const int64_t nbig = (int64_t)hs[12], most = (int64_t)hs[13];
+        if (nbig) {
+            // as many workgroups as have a part, or a few for each compute unit
+            const int64_t parts = std::min<int64_t>((most + EPAIRS - 1) / EPAIRS,
+                                                    std::max<int64_t>(8192 / nbig, 1));
+            hipLaunchKernelGGL(k_edge_rows<true>, dim3((unsigned)nbig, (unsigned)parts), dim3(EB),
+                               0, st, P, G, epw, rowdiff, rowoff, items,
+                               (unsigned long long *)nullptr, big, (unsigned long long *)nullptr);
+        }
         HIP_OK(hipGetLastError());
     }
     B.release(rowdiff);
     B.release(hint);
+    B.release(big);
     rowdiff = hint = nullptr;
+    big = nullptr;
 
     // the sweep; again when the members of large sets outgrew their array,
     // or with set keys instead of the hash table when that overflowed

@@ -156,3 +156,58 @@ def test_more_sets_than_one_workgroup_numbers(sba, orc):
     taken, info = check(sba, orc, polys, 12, n=200_001, step=97)
     assert info["n_sets"] > 8192 and taken & 3 == 3 and not taken & 4
     assert isinstance(polys, Polygons)
+
+
+# a workgroup's edges with more than 4,096 pairs between them go to a launch of
+# their own, 1,024 pairs a workgroup: one edge across all rows (too many to count
+# in LDS), many across 600 of them (counted in LDS part by part), and both beside
+# workgroups that stay in the first launch
+@pytest.mark.parametrize("rows", [1023, 1025, 4095, 4097, 9000])
+@pytest.mark.parametrize("kind", ["grid", "hilbert"])
+def test_edges_across_many_rows(sba, orc, rows, kind):
+    s = orc.cell_side(40)
+    tall = [[[(10, 3), (90 * s, 7), (91 * s, rows * s - 9), (15, rows * s - 4)]]]
+    taken, _ = check(sba, orc, polygons_from_rings(tall), 40, kind=kind, step=7)
+    assert taken & 2
+
+
+@pytest.mark.parametrize("kw,okw", [({}, {}), ({"centre_sampled": True}, {"centre": True}),
+                                    ({"boundary_only": True}, {"boundary_only": True})])
+def test_many_edges_across_many_rows(sba, orc, kw, okw):
+    s, r = orc.cell_side(40), np.random.default_rng(12)
+    rings = []
+    for k in range(24):  # a comb of long teeth each, and small polygons between them
+        x = 40 * s * k
+        teeth = [(x + (q * 37 * s) // 20, (600 + r.integers(0, 9)) * s if q & 1 else r.integers(1, 5))
+                 for q in range(20)]
+        rings.append([teeth + [(x + 38 * s, 700 * s), (x, 701 * s)]])
+        rings += [[[(x + 39 * s, y), (x + 39 * s + 30, y + 2), (x + 39 * s + 9, y + 40)]]
+                  for y in range(50, 600 * s, 61 * s)]
+    taken, _ = check(sba, orc, polygons_from_rings(rings), 40, okw=okw, step=5, **kw)
+    assert taken & 2
+
+
+def test_a_box_around_all_rows_costs_little(sba):
+    """Its four edges' 100,000 pairs, by one workgroup, nearly doubled the build."""
+    import time
+
+    import torch
+
+    from gen import voronoi_partition
+    city = voronoi_partition(60, 4_000_000, (10, 40), seed=98, jitter_seed=99)
+    box = Polygons(np.append(city.ring_off, city.ring_off[-1] + 1).astype(np.int32),
+                   np.append(city.vert_off, city.vert_off[-1] + 4).astype(np.int64),
+                   np.append(city.xy, [0, 0, 4_000_000, 0, 4_000_000, 4_000_000, 0, 4_000_000])
+                   .astype(np.int32))
+
+    def best(polys):
+        t = [torch.from_numpy(a).cuda() for a in (polys.ring_off, polys.vert_off, polys.xy)]
+        ms = []
+        for _ in range(15):
+            t0 = time.perf_counter()
+            A = sba.Approx(*t, 100)
+            ms.append(time.perf_counter() - t0)
+            A.close()
+        return min(ms)
+
+    assert best(box) < 1.5 * best(city)
