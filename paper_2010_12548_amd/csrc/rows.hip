@@ -1111,10 +1111,153 @@ __global__ void k_widen(const uint32_t *a, int64_t n, int64_t *b)
 // search (a lane walking a word's bits against the segments in memory kept a
 // row of 500 cells and 350 segments busy four times as long).  With `border`
 // (clip windows) the cells on the box's border belong to them.
+//
+// That is for rows of more than CELL_PAIRS pairs, or CELLS_FEW cells; of a row
+// of fewer a wavefront sorts the pairs instead, whatever the box's width.  (One
+// ring over 1.5M rows and columns, two pairs a row: the bitmaps alone took 35 ms
+// of a build that now takes 3.2.)
 #define CELL_BITS 65536
 #define CELL_LIST 4096
 #define CELL_SEGS 1536
 #define NO_SEG 0xffffffffu
+#define CELL_PAIRS 64
+#define CELLS_FEW 128
+
+// The rows that get a bitmap: those of the classes above CELL_PAIRS pairs, then
+// with a border the first and the last, then listed ones of many cells.  WRITE
+// gives the rows of more than CELL_LIST cells `parts` workgroups each, before all
+// others: a partition's outer sides are such rows, and by one workgroup those of
+// 260 polygons at 0.5 m, 114,286 cells, made the launch take 1,330 us; 293 now.
+struct CellRows {
+    const int32_t *list;  // by class, see k_row_lists
+    int32_t gh;
+    int32_t n1, n2, n3;   // rows of classes 1 to 3
+    int32_t border;       // 0, or how many of row 0 and row gh - 1 there are
+    int32_t *many, *large;                 // rows listed by COUNT
+    unsigned long long *fig;               // their numbers, the most cells of a row
+    int32_t nlarge, parts;                 // WRITE
+};
+
+// the block's row; -1: a border row, which has a block of its own
+__device__ __forceinline__ int32_t cell_row(const CellRows &C, int *part)
+{
+    int32_t b = (int32_t)blockIdx.x, r;
+    const int64_t gh = C.gh;
+    *part = -1;
+    if (b < C.nlarge * C.parts) {
+        *part = b % C.parts;
+        return C.large[b / C.parts];
+    }
+    b -= C.nlarge * C.parts;
+    if (b < C.n1) {
+        r = C.list[gh + b];
+    } else if ((b -= C.n1) < C.n2) {
+        r = C.list[2 * gh + b];
+    } else if ((b -= C.n2) < C.n3) {
+        r = C.list[3 * gh + b];
+    } else if ((b -= C.n3) < C.border) {
+        return b ? C.gh - 1 : 0;
+    } else {
+        return C.many[b - C.border];
+    }
+    return C.border && (r == 0 || r == C.gh - 1) ? -1 : r;
+}
+
+__device__ __forceinline__ void cells_large(const CellRows &C, int32_t row, int64_t cells)
+{
+    C.large[atomicAdd(&C.fig[1], 1ull)] = row;
+    atomicMax(&C.fig[2], (unsigned long long)cells);
+}
+
+// ascending over a wavefront
+__device__ __forceinline__ void wave_sort(uint64_t (&v)[1])
+{
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int k = 2; k <= 64; k <<= 1) {
+        const bool up = k == 64 || (lane & k) == 0;
+        if (k >= 64) sort_step<32, 1>(v, up);
+        if (k >= 32) sort_step<16, 1>(v, up);
+        if (k >= 16) sort_step<8, 1>(v, up);
+        if (k >= 8) sort_step<4, 1>(v, up);
+        if (k >= 4) sort_step<2, 1>(v, up);
+        sort_step<1, 1>(v, up);
+    }
+}
+
+// A row of at most CELL_PAIRS pairs by a wavefront: its intervals in order of
+// their first cells, each less what the ones before it reach.  COUNT lists the
+// rows of more than CELLS_FEW cells, which WRITE leaves to a bitmap.
+template <bool WRITE, typename K>
+__device__ __forceinline__ void row_cells_few(int32_t row, const uint4 *items,
+                                              const int64_t *rowoff, int32_t gw, int32_t gh,
+                                              int border, int64_t *rowcell, const int64_t *seg_beg,
+                                              const int64_t *seg_end, const int32_t *seg_x0,
+                                              const int32_t *seg_x1, int L, K *keys, uint32_t *bseg,
+                                              const CellRows &C)
+{
+    const int lane = threadIdx.x & 63;
+    if (row >= gh || (border && (row == 0 || row == gh - 1))) return;
+    const int64_t i0 = rowoff[row];
+    const int n = (int)(rowoff[row + 1] - i0);
+    if (n > CELL_PAIRS) return;
+    const int64_t done = WRITE ? rowcell[row] : 0;
+    if (WRITE && (rowcell[row + 1] == done || rowcell[row + 1] - done > CELLS_FEW)) return;
+    uint64_t v[1] = {~(uint64_t)0};
+    if (lane < n) {
+        const uint4 it = items[i0 + lane];
+        const uint32_t end = min(it.z, (uint32_t)gw);
+        if (it.y < end) v[0] = ((uint64_t)it.y << 32) | end;
+    }
+    wave_sort(v);
+    const bool in = v[0] != ~(uint64_t)0;
+    const uint32_t a = in ? (uint32_t)(v[0] >> 32) : 0xffffffffu, b = in ? (uint32_t)v[0] : 0u;
+    const uint32_t reach = wave_scan<OpMax>(b);  // of the intervals up to this one
+    // (every lane takes part: a lane that does not reads as 0)
+    const uint32_t up = (uint32_t)__shfl_up((int)reach, 1, 64), before = lane ? up : 0u;
+    const uint32_t from = max(a, before), len = in && b > from ? b - from : 0u;
+    const uint32_t incl = wave_scan<OpAdd>(len);
+    const uint32_t cells = (uint32_t)__shfl((int)incl, 63, 64);
+    // the border's cells, where no interval holds them
+    const uint32_t lowest = (uint32_t)__shfl((int)a, 0, 64);
+    const uint32_t highest = (uint32_t)__shfl((int)reach, 63, 64);
+    const uint32_t first = border && lowest != 0 ? 1u : 0u;
+    const uint32_t last = border && highest != (uint32_t)gw && gw > 1 ? 1u : 0u;
+    const uint32_t all = cells + first + last;
+    if (!WRITE) {
+        if (lane == 0) {
+            rowcell[row] = all;
+            if (all > CELL_LIST) cells_large(C, row, all);
+            else if (all > CELLS_FEW) C.many[atomicAdd(&C.fig[0], 1ull)] = row;
+        }
+        return;
+    }
+    const int64_t sb = seg_beg[row];
+    const int ns = (int)(seg_end[row] - sb);
+    for (uint32_t t0 = 0; t0 < all; t0 += 64) {
+        const uint32_t t = t0 + lane;
+        // the interval of cell t: the first whose inclusive count exceeds it
+        int i = 0;
+#pragma unroll
+        for (int step = 32; step > 0; step >>= 1) {
+            const uint32_t u = (uint32_t)__shfl((int)incl, i + step - 1, 64);
+            i += u <= t ? step : 0;
+        }
+        i = i > 63 ? 63 : i;
+        uint32_t x = (uint32_t)__shfl((int)from, i, 64) +
+                     (t - (uint32_t)__shfl((int)(incl - len), i, 64));
+        if (t >= cells) x = t == cells && first ? 0u : (uint32_t)gw - 1;
+        if (t >= all) continue;
+        int lo = 0, hi = ns;  // segments that start at or before x
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (seg_x0[sb + mid] <= (int32_t)x) lo = mid + 1; else hi = mid;
+        }
+        const bool held = lo > 0 && (int32_t)x < seg_x1[sb + lo - 1];
+        keys[done + t] = (K)hilbert_index(L, x, (uint32_t)row);
+        bseg[done + t] = held ? (uint32_t)(sb + lo - 1) : NO_SEG;
+    }
+}
 
 template <bool WRITE, typename K>
 __global__ __launch_bounds__(256) void k_row_cells(const uint4 *items, const int64_t *rowoff,
@@ -1122,18 +1265,31 @@ __global__ __launch_bounds__(256) void k_row_cells(const uint4 *items, const int
                                                    int64_t *rowcell, const int64_t *seg_beg,
                                                    const int64_t *seg_end, const int32_t *seg_x0,
                                                    const int32_t *seg_x1, int L, K *keys,
-                                                   uint32_t *bseg)
+                                                   uint32_t *bseg, CellRows C, int bitmaps)
 {
+    // the first workgroups a row's bitmap each, the others four rows of few pairs
+    if ((int)blockIdx.x >= bitmaps) {
+        row_cells_few<WRITE, K>(
+            (int32_t)((blockIdx.x - (unsigned)bitmaps) * 4 + (threadIdx.x >> 6)), items, rowoff, gw,
+            gh, border, rowcell, seg_beg, seg_end, seg_x0, seg_x1, L, keys, bseg, C);
+        return;
+    }
     __shared__ uint32_t bits[CELL_BITS / 32];
     __shared__ uint16_t cells[WRITE ? CELL_LIST : 1];
     __shared__ int32_t sx[WRITE ? CELL_SEGS : 1];
     __shared__ uint16_t htab[WRITE ? HILBERT_TAB : 1];
     __shared__ uint32_t wsum[4];
-    const int row = blockIdx.x, tid = threadIdx.x;
+    __shared__ uint32_t taken;  // chunks of CELL_BITS columns that hold a cell
+    static_assert(MAX_GRID_SIDE <= 32 * CELL_BITS, "a bit a chunk");
+    int part;
+    const int row = cell_row(C, &part), tid = threadIdx.x;
+    if (row < 0) return;
     const int64_t i0 = rowoff[row];
     const int n = (int)(rowoff[row + 1] - i0);
     int64_t done = WRITE ? rowcell[row] : 0;
     if (WRITE && rowcell[row + 1] == done) return;
+    if (WRITE && part < 0 && rowcell[row + 1] - done > CELL_LIST) return;  // in parts
+    int batch = 0;  // of CELL_LIST cells
     const int64_t sb = WRITE ? seg_beg[row] : 0;
     const int ns = WRITE ? (int)(seg_end[row] - sb) : 0;
     const bool staged = ns <= CELL_SEGS;
@@ -1142,10 +1298,25 @@ __global__ __launch_bounds__(256) void k_row_cells(const uint4 *items, const int
             for (int k = tid; k < ns; k += 256) sx[k] = seg_x0[sb + k];
         for (int e = tid; e < HILBERT_TAB; e += 256) htab[e] = hilbert_tab_entry((uint32_t)e);
     }
+    const bool all = border && (row == 0 || row == gh - 1);
+    if (gw > CELL_BITS && !all) {
+        if (tid == 0) taken = border ? 1u | 1u << ((gw - 1) / CELL_BITS) : 0u;
+        __syncthreads();
+        uint32_t m = 0;
+        for (int i = tid; i < n; i += 256) {
+            const uint4 it = items[i0 + i];
+            const int32_t b = min((int32_t)it.z, gw);
+            if ((int32_t)it.y >= b) continue;
+            const int ca = (int32_t)it.y / CELL_BITS, cb = (b - 1) / CELL_BITS;
+            m |= (0xffffffffu << ca) & (0xffffffffu >> (31 - cb));
+        }
+        if (m) atomicOr(&taken, m);
+        __syncthreads();
+    }
     for (int32_t w0 = 0; w0 < gw; w0 += CELL_BITS) {
+        if (gw > CELL_BITS && !all && !(taken >> (w0 / CELL_BITS) & 1u)) continue;
         const int32_t wn = min(CELL_BITS, gw - w0);
         const int words = (wn + 31) >> 5;
-        const bool all = border && (row == 0 || row == gh - 1);
         for (int k = tid; k < words; k += 256) {
             uint32_t v = 0;
             if (all) v = (k + 1) * 32 <= wn ? 0xffffffffu : (1u << (wn & 31)) - 1u;
@@ -1175,6 +1346,7 @@ __global__ __launch_bounds__(256) void k_row_cells(const uint4 *items, const int
         const uint32_t first = wg_scan_incl<256>(c, wsum, &tot) - c;
         if (WRITE) {
             for (uint32_t base = 0; base < tot; base += CELL_LIST) {
+                if (part >= 0 && batch++ % C.parts != part) continue;
                 uint32_t o = first;
                 for (int k = k0; k < k1 && o < base + CELL_LIST; k++) {
                     for (uint32_t v = bits[k]; v; v &= v - 1, o++)
@@ -1210,19 +1382,24 @@ __global__ __launch_bounds__(256) void k_row_cells(const uint4 *items, const int
         done += tot;
         __syncthreads();
     }
-    if (!WRITE && tid == 0) rowcell[row] = done;
+    if (!WRITE && tid == 0) {
+        rowcell[row] = done;
+        if (done > CELL_LIST) cells_large(C, row, done);
+    }
 }
 
 template <typename K>
 static int row_cells_write(BuildState &B, const sba_handle *h, const uint4 *items,
-                           const int64_t *rowoff, int64_t *rowcell, int64_t nc, K **keys,
-                           hipStream_t st)
+                           const int64_t *rowoff, int64_t *rowcell, int64_t nc, const CellRows &C,
+                           unsigned rows, K **keys, hipStream_t st)
 {
     RC(B.alloc(keys, nc));
     RC(B.alloc(&B.bseg, nc));
-    hipLaunchKernelGGL((k_row_cells<true, K>), dim3((unsigned)h->gh), dim3(256), 0, st, items,
-                       rowoff, (int32_t)h->gw, (int32_t)h->gh, B.window ? 1 : 0, rowcell, B.seg_beg,
-                       B.seg_end, B.seg_x0, B.seg_x1, h->level, *keys, B.bseg);
+    const int32_t gw = (int32_t)h->gw, gh = (int32_t)h->gh;
+    const int border = B.window ? 1 : 0;
+    hipLaunchKernelGGL((k_row_cells<true, K>), dim3(rows + grid_for(gh, 4)), dim3(256), 0, st,
+                       items, rowoff, gw, gh, border, rowcell, B.seg_beg, B.seg_end, B.seg_x0,
+                       B.seg_x1, h->level, *keys, B.bseg, C, (int)rows);
     HIP_OK(hipGetLastError());
     return 0;
 }
@@ -1305,8 +1482,8 @@ int rows_coverage(const sba_polygons *polys, const int4 *bbox, int64_t nv,
     unsigned long long *stat = nullptr;
     // the pair counters, then the figures that the host reads: k_row_scan's
     // and k_row_lists' eight, the sweep's totals (k_row_totals), the members of
-    // large sets, k_edge_rows' workgroups of many pairs
-    constexpr int NFIG = 14, NST = ROW_STATS * ROW_STAT_STEP + NFIG;
+    // large sets, k_edge_rows' workgroups of many pairs, k_row_cells' listed rows
+    constexpr int NFIG = 17, NST = ROW_STATS * ROW_STAT_STEP + NFIG;
     RC(B.alloc(&rowdiff, (int64_t)gh + 1));
     RC(B.alloc(&rowoff, (int64_t)gh + 1));
     RC(B.alloc(&stat, NST));
@@ -1519,7 +1696,6 @@ int rows_coverage(const sba_polygons *polys, const int4 *bbox, int64_t nv,
     *one_wg = S.one_workgroup;
     B.release(A.seg_key);
     B.release(row_stat);
-    B.release(list);
     B.release(A.mem_ids);
     sets_release(S, B);
 
@@ -1528,28 +1704,46 @@ int rows_coverage(const sba_polygons *polys, const int4 *bbox, int64_t nv,
         RC(hilbert_level(B, h));
         int64_t *rowcell = nullptr;
         RC(B.alloc(&rowcell, (int64_t)gh + 1));
-        hipLaunchKernelGGL((k_row_cells<false, uint64_t>), dim3((unsigned)gh), dim3(256), 0, st,
-                           items, rowoff, (int32_t)h->gw, gh, B.window ? 1 : 0, rowcell,
+        const int border = B.window ? 1 : 0;
+        CellRows C{list, gh, (int32_t)rows[1], (int32_t)rows[2], (int32_t)rows[3],
+                   border ? std::min(gh, 2) : 0, nullptr, nullptr, fig + 14, 0, 1};
+        RC(B.alloc(&C.many, gh));
+        RC(B.alloc(&C.large, gh));
+        const unsigned bitmaps = (unsigned)(rows[1] + rows[2] + rows[3] + C.border);
+        hipLaunchKernelGGL((k_row_cells<false, uint64_t>), dim3(bitmaps + grid_for(gh, 4)),
+                           dim3(256), 0, st, items, rowoff, (int32_t)h->gw, gh, border, rowcell,
                            (const int64_t *)nullptr, (const int64_t *)nullptr,
                            (const int32_t *)nullptr, (const int32_t *)nullptr, 0,
-                           (uint64_t *)nullptr, (uint32_t *)nullptr);
+                           (uint64_t *)nullptr, (uint32_t *)nullptr, C, (int)bitmaps);
         HIP_OK(hipGetLastError());
         RC(scan_exclusive_i64(rowcell, rowcell, gh, rowcell + gh, st, &B.ws));
         int64_t nc = 0;
+        unsigned long long hc[3] = {0, 0, 0};
         RC(B.ws.read(&nc, rowcell + gh, sizeof(int64_t)));
+        RC(B.ws.read(hc, C.fig, sizeof(hc)));
         RC(B.ws.sync());
         B.nbkeys = nc;
         if (nc > 0) {
+            C.nlarge = (int32_t)hc[1];
+            if (C.nlarge)
+                C.parts = (int32_t)std::min<int64_t>(((int64_t)hc[2] + CELL_LIST - 1) / CELL_LIST,
+                                                     std::max<int64_t>(4096 / C.nlarge, 1));
+            const unsigned all = (unsigned)(C.nlarge * C.parts) + bitmaps + (unsigned)hc[0];
             if (2 * h->level <= 32) {
-                RC(row_cells_write<uint32_t>(B, h, items, rowoff, rowcell, nc, &B.bkeys32, st));
+                RC(row_cells_write<uint32_t>(B, h, items, rowoff, rowcell, nc, C, all, &B.bkeys32,
+                                             st));
                 RC(radix_sort_u32_ws(&B.bkeys32, &B.bseg, nc, 2 * h->level, B.ws));
             } else {
-                RC(row_cells_write<uint64_t>(B, h, items, rowoff, rowcell, nc, &B.bkeys, st));
+                RC(row_cells_write<uint64_t>(B, h, items, rowoff, rowcell, nc, C, all, &B.bkeys,
+                                             st));
                 RC(radix_sort_u64_ws(&B.bkeys, &B.bseg, nc, 2 * h->level, B.ws));
             }
         }
+        B.release(C.many);
+        B.release(C.large);
         B.release(rowcell);
     }
+    B.release(list);
     B.release(items);
     B.release(rowoff);
     B.release(stat);
