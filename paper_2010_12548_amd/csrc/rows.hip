@@ -274,10 +274,10 @@ __global__ void k_rows_init(const int32_t *ring_off, const int64_t *vert_off, in
 // neighbouring edges of a polygon do, counts in LDS and touches each row's
 // global word once.  epw edges a workgroup (its lanes share their pairs).
 // Workgroups whose edges have more than EPAIRS_MAX pairs, as edges across
-// thousands of rows make, are left out of the emitting launch: COUNT lists them
-// (big: their numbers; bigfig: how many, the most pairs of one), and another
-// launch gives their pairs to gridDim.y workgroups each, EPAIRS at a time.  (The
-// four edges of a box over 57,143 rows, by one workgroup: 587 us.)
+// thousands of rows make, leave them to others when they emit: COUNT lists them
+// (big: their numbers; bigfig: how many, the most pairs of one), and the first
+// nbig * parts workgroups share their pairs, EPAIRS at a time.  (The four edges of
+// a box over 57,143 rows, by one workgroup: 587 us.)
 #define ROW_STATS 64
 #define ROW_STAT_STEP 16  // words between counter pairs: a cache line of their own
 #define EPAIRS_MAX 4096
@@ -287,7 +287,7 @@ template <bool EMIT>
 __global__ __launch_bounds__(EB) void k_edge_rows(PolyView P, RowGeo G, int epw, int32_t *rowdiff,
                                                   const int64_t *rowoff, uint4 *items,
                                                   unsigned long long *stat, uint32_t *big,
-                                                  unsigned long long *bigfig)
+                                                  unsigned long long *bigfig, int nbig, int parts)
 {
     __shared__ int32_t hist[EROWS + 1];
     __shared__ uint32_t base[EMIT ? EROWS : 1];
@@ -296,9 +296,13 @@ __global__ __launch_bounds__(EB) void k_edge_rows(PolyView P, RowGeo G, int epw,
     __shared__ int32_t sra[EMIT ? EB : 1], ska[EMIT ? EB : 1], skb[EMIT ? EB : 1];
     __shared__ uint32_t wsum[EB / 64];
     __shared__ int32_t lo_s, hi_s;
-    __shared__ unsigned long long sb[3];
+    __shared__ uint32_t sb[3];  // of 256 edges, each over at most 2^21 rows
     const int tid = threadIdx.x;
-    const int64_t v = (int64_t)(EMIT && big ? big[blockIdx.x] : blockIdx.x) * epw + tid;
+    const uint32_t shared = EMIT ? (uint32_t)(nbig * parts) : 0u;
+    const bool sharing = EMIT && blockIdx.x < shared;
+    const uint32_t part = sharing ? blockIdx.x % (uint32_t)parts : 0u;
+    const int64_t v =
+        (int64_t)(sharing ? big[blockIdx.x / (uint32_t)parts] : blockIdx.x - shared) * epw + tid;
     if (tid == 0) {
         lo_s = INT32_MAX;
         hi_s = -1;
@@ -319,17 +323,12 @@ __global__ __launch_bounds__(EB) void k_edge_rows(PolyView P, RowGeo G, int epw,
         hi = max(hi, __shfl_xor(hi, o, 64));
     }
     if (!EMIT) {
-        unsigned long long tb = nb, tc = nc;
-        uint32_t tn = (uint32_t)n;  // 256 edges of at most 2^21 rows
-        for (int o = 32; o > 0; o >>= 1) {
-            tb += __shfl_xor(tb, o, 64);
-            tc += __shfl_xor(tc, o, 64);
-            tn += (uint32_t)__shfl_xor((int)tn, o, 64);
-        }
-        if ((tid & 63) == 0 && (tb | tc)) {
+        const uint32_t tb = wave_scan<OpAdd>(nb), tc = wave_scan<OpAdd>(nc),
+                       tn = wave_scan<OpAdd>((uint32_t)n);
+        if ((tid & 63) == 63 && (tb | tc)) {
             atomicAdd(&sb[0], tb);
             atomicAdd(&sb[1], tc);
-            atomicAdd(&sb[2], (unsigned long long)tn);
+            atomicAdd(&sb[2], tn);
         }
     }
     if ((tid & 63) == 0) {
@@ -340,11 +339,11 @@ __global__ __launch_bounds__(EB) void k_edge_rows(PolyView P, RowGeo G, int epw,
     const int32_t r0 = lo_s, span = hi_s - lo_s + 1;
     if (!EMIT && tid == 0 && (sb[0] | sb[1])) {
         unsigned long long *st = stat + ROW_STAT_STEP * (blockIdx.x & (ROW_STATS - 1));
-        atomicAdd(&st[0], sb[0]);
-        atomicAdd(&st[1], sb[1]);
+        atomicAdd(&st[0], (unsigned long long)sb[0]);
+        atomicAdd(&st[1], (unsigned long long)sb[1]);
         if (sb[2] > EPAIRS_MAX) {
             big[atomicAdd(&bigfig[0], 1ull)] = blockIdx.x;
-            atomicMax(&bigfig[1], sb[2]);
+            atomicMax(&bigfig[1], (unsigned long long)sb[2]);
         }
     }
     if (hi_s < 0) return;  // no pair in the whole workgroup
@@ -388,10 +387,10 @@ __global__ __launch_bounds__(EB) void k_edge_rows(PolyView P, RowGeo G, int epw,
     auto row_at = [&](uint32_t t, int e) {
         return sra[e] + (int32_t)(t - (e ? off[e - 1] : 0u));
     };
-    if (!big && total > EPAIRS_MAX) return;  // the other launch's
-    const uint32_t part = big ? EPAIRS : EPAIRS_MAX;
-    for (uint32_t t0 = blockIdx.y * part; t0 < total; t0 += gridDim.y * part) {
-        const uint32_t t1 = min(t0 + part, total);
+    if (!sharing && total > EPAIRS_MAX) return;
+    const uint32_t step = sharing ? (uint32_t)parts * EPAIRS : EPAIRS_MAX;
+    for (uint32_t t0 = part * EPAIRS; t0 < total; t0 += step) {
+        const uint32_t t1 = sharing ? min(t0 + EPAIRS, total) : total;
         if (local) {
             for (uint32_t t = t0 + tid; t < t1; t += EB) {
                 const int e = edge_at(t);
@@ -412,7 +411,7 @@ __global__ __launch_bounds__(EB) void k_edge_rows(PolyView P, RowGeo G, int epw,
                                       : (uint32_t)atomicAdd(&rowdiff[j], 1);
             items[rowoff[j] + at] = edge_row_item(se[e], j, j >= ska[e] && j <= skb[e], G);
         }
-        if (local && big) {
+        if (local && sharing) {
             __syncthreads();
             for (int k = tid; k < span; k += EB) hist[k] = 0;
             __syncthreads();
@@ -1539,7 +1538,7 @@ int rows_coverage(const sba_polygons *polys, const int4 *bbox, int64_t nv,
     uint32_t *big = nullptr;
     RC(B.alloc(&big, egrid.x));
     hipLaunchKernelGGL(k_edge_rows<false>, egrid, dim3(EB), 0, st, P, G, epw, rowdiff,
-                       (const int64_t *)nullptr, (uint4 *)nullptr, stat, big, fig + 12);
+                       (const int64_t *)nullptr, (uint4 *)nullptr, stat, big, fig + 12, 0, 1);
     const bool few_rows = gh < RSCAN_LISTS;  // the scan has gh + 1 entries
     unsigned long long hs[NFIG];
     RC(B.ws.read(hs, fig, sizeof(hs)));
@@ -1579,18 +1578,14 @@ int rows_coverage(const sba_polygons *polys, const int4 *bbox, int64_t nv,
     uint4 *items = nullptr;
     RC(B.alloc(&items, items_n));
     if (items_n) {
-        hipLaunchKernelGGL(k_edge_rows<true>, egrid, dim3(EB), 0, st, P, G, epw, rowdiff, rowoff,
-                           items, (unsigned long long *)nullptr, (uint32_t *)nullptr,
-                           (unsigned long long *)nullptr);
         const int64_t nbig = (int64_t)hs[12], most = (int64_t)hs[13];
-        if (nbig) {
-            // as many workgroups as have a part, or a few for each compute unit
-            const int64_t parts = std::min<int64_t>((most + EPAIRS - 1) / EPAIRS,
-                                                    std::max<int64_t>(8192 / nbig, 1));
-            hipLaunchKernelGGL(k_edge_rows<true>, dim3((unsigned)nbig, (unsigned)parts), dim3(EB),
-                               0, st, P, G, epw, rowdiff, rowoff, items,
-                               (unsigned long long *)nullptr, big, (unsigned long long *)nullptr);
-        }
+        // as many workgroups as have a part, or a few for each compute unit
+        const int64_t parts = nbig ? std::min<int64_t>((most + EPAIRS - 1) / EPAIRS,
+                                                       std::max<int64_t>(8192 / nbig, 1))
+                                   : 1;
+        hipLaunchKernelGGL(k_edge_rows<true>, dim3(egrid.x + (unsigned)(nbig * parts)), dim3(EB), 0,
+                           st, P, G, epw, rowdiff, rowoff, items, (unsigned long long *)nullptr, big,
+                           (unsigned long long *)nullptr, (int)nbig, (int)parts);
         HIP_OK(hipGetLastError());
     }
     B.release(rowdiff);
