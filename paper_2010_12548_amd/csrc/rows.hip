@@ -249,15 +249,16 @@ __device__ __forceinline__ T wg_scan_incl(T v, T *wsum, T *tot)
     }
 }
 
-// hint[k] = polygon of vertex 64 k (a wavefront per polygon); rowdiff and stat
-// zeroed, the set table (if any) emptied
+// hint[k] = polygon of vertex 64 k (a wavefront per polygon); rowdiff, stat and
+// the rows' figures of large sets zeroed, the set table (if any) emptied
 __global__ void k_rows_init(const int32_t *ring_off, const int64_t *vert_off, int32_t np,
                             int32_t *hint, int32_t *rowdiff, int64_t nrow, unsigned long long *stat,
-                            int nstat, uint64_t *tab, int64_t ntab)
+                            int nstat, uint32_t *row_large, uint64_t *tab, int64_t ntab)
 {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     for (int64_t k = t; k < ntab; k += (int64_t)gridDim.x * blockDim.x) tab[k] = ~0ull;
     if (t < nrow) rowdiff[t] = 0;
+    if (t < nrow - 1) row_large[t] = row_large[t + nrow - 1] = 0;
     if (t < nstat) stat[t] = 0;
     const int64_t p = t >> 6;
     if (p >= np) return;
@@ -455,6 +456,9 @@ __device__ __forceinline__ uint32_t class_slot(int c, uint32_t *n)
 // Up to RSCAN_LISTS rows it makes the rows' lists as well (see k_row_lists),
 // and copies the host's values: two launches less.
 #define RSCAN_LISTS (RSCAN * RSCAN_PER)
+// a row's figures, [gh] each: multi-polygon segments and their members, then
+// those of more than three polygons and theirs
+#define ROW_FIGS 4
 struct RowLists {
     int32_t *list;
     int64_t *seg_beg, *seg_end;
@@ -665,7 +669,7 @@ struct SweepArgs {
     int32_t *seg_x0, *seg_x1;
     uint32_t *seg_code;
     uint64_t *seg_key;       // set keys of multi-polygon segments (list mode), or NULL
-    uint32_t *row_stat;      // [gh] multi-polygon segments, [gh] members of each row
+    uint32_t *row_stat;      // the rows' figures (ROW_FIGS)
     uint64_t *memloc;        // members of the sets of more than three polygons
     int32_t *mem_ids;
     unsigned long long *memcnt;
@@ -942,8 +946,8 @@ __global__ __launch_bounds__(BLOCK) void k_row_sweep(const SweepArgs A)
     // each piece's first one in psum, and how many it has in pmin
     const bool large = s_large != 0;
     bool fits = false;  // all of them, in mem_ids
+    uint32_t places = 0;
     if (large) {
-        uint32_t places = 0;
         for (int b = 0; b < nd; b += BLOCK) {
             const int k = b + tid, d = k < nd ? L.D[k] : 0;
             const uint32_t need = d > 3 && d <= MAX_DEPTH ? (uint32_t)d : 0u;
@@ -1011,14 +1015,19 @@ __global__ __launch_bounds__(BLOCK) void k_row_sweep(const SweepArgs A)
         }
     }
     // segments: the pieces that hold a polygon
-    uint32_t nseg = 0, nm = 0, nmem = 0;
+    uint32_t nseg = 0, nm = 0, nmem = 0, nlarge = 0;
     const bool hash = A.tab.tab != nullptr;
     for (int b = 0; b < nd; b += BLOCK) {
         const int k = b + tid;
         const int d = k < nd ? L.D[k] : 0;
+        // segments, and above bit 16 those of more than three polygons (at most
+        // 1024 a step)
         uint32_t tot;
-        const uint32_t o = nseg + wg_scan_incl<BLOCK>(d ? 1u : 0u, wsum, &tot) - 1;
-        nseg += tot;
+        const uint32_t at_once = wg_scan_incl<BLOCK>((d ? 1u : 0u) | (d > 3 ? 1u << 16 : 0u), wsum,
+                                                     &tot);
+        const uint32_t o = nseg + (at_once & 0xffffu) - 1, g = nlarge + (at_once >> 16) - 1;
+        nseg += tot & 0xffffu;
+        nlarge += tot >> 16;
         if (!d) continue;
         const int64_t at = sbase + o;
         A.seg_x0[at] = (int32_t)L.E[k];
@@ -1044,7 +1053,14 @@ __global__ __launch_bounds__(BLOCK) void k_row_sweep(const SweepArgs A)
             A.memloc[at] = ((uint64_t)(s_mem + L.psum[k]) << 6) | (uint64_t)d;
             key = (1ull << (3 * A.fb)) + (uint64_t)at;
         }
-        if (hash) {
+        if (hash && d > 3) {
+            // not shared, so no place in the table (which they filled, so that
+            // the sweep was made again for keys to be sorted: 64 stars in layers
+            // 192 us of sweeps, now 62)
+            A.seg_code[at] = SEG_SLOT | SEG_LARGE | g;
+            const uint64_t of = (s_mem + L.psum[k]) >> 2;  // a set has at least four members
+            if (of < LARGE_FEW) A.tab.large[of] = key;
+        } else if (hash) {
             A.seg_code[at] = SEG_SLOT | set_insert(A.tab, key, (uint32_t)d);
         } else {
             A.seg_key[at] = key;
@@ -1061,40 +1077,50 @@ __global__ __launch_bounds__(BLOCK) void k_row_sweep(const SweepArgs A)
         A.seg_end[row] = sbase + nseg;
         A.row_stat[row] = s_stat[0];
         A.row_stat[A.gh + row] = s_stat[1];
+        if (large) {
+            A.row_stat[2 * (int64_t)A.gh + row] = nlarge;
+            A.row_stat[3 * (int64_t)A.gh + row] = places;
+        }
     }
 }
 
-// out[0..2] += segments, multi-polygon segments and their members of all rows
+// out[0..2] += segments, multi-polygon segments and their members of all rows,
+// *large += those of more than three polygons
 // (the rows' own figures, added up once: an addition to a shared counter by
 // every row took 10 ns a row)
 // (as one workgroup it copies the host's values too)
 template <int BLOCK>
 __global__ __launch_bounds__(BLOCK) void k_row_totals(const int64_t *seg_beg, const int64_t *seg_end,
                                                       const uint32_t *row_stat, int64_t gh,
-                                                      unsigned long long *out, ReadSet R)
+                                                      unsigned long long *out,
+                                                      unsigned long long *large, ReadSet R)
 {
-    __shared__ unsigned long long sum[3];
-    if (threadIdx.x < 3) sum[threadIdx.x] = 0;
+    __shared__ unsigned long long sum[4];
+    if (threadIdx.x < 4) sum[threadIdx.x] = 0;
     __syncthreads();
-    unsigned long long a = 0, b = 0, c = 0;
+    unsigned long long a = 0, b = 0, c = 0, d = 0;
     for (int64_t r = (int64_t)blockIdx.x * BLOCK + threadIdx.x; r < gh;
          r += (int64_t)gridDim.x * BLOCK) {
         a += (unsigned long long)(seg_end[r] - seg_beg[r]);
         b += row_stat[r];
         c += row_stat[gh + r];
+        d += row_stat[2 * gh + r];
     }
     for (int o = 32; o > 0; o >>= 1) {
         a += __shfl_xor(a, o, 64);
         b += __shfl_xor(b, o, 64);
         c += __shfl_xor(c, o, 64);
+        d += __shfl_xor(d, o, 64);
     }
     if ((threadIdx.x & 63) == 0) {
         atomicAdd(&sum[0], a);
         atomicAdd(&sum[1], b);
         atomicAdd(&sum[2], c);
+        atomicAdd(&sum[3], d);
     }
     __syncthreads();
-    if (threadIdx.x < 3 && sum[threadIdx.x]) atomicAdd(&out[threadIdx.x], sum[threadIdx.x]);
+    if (threadIdx.x < 4 && sum[threadIdx.x])
+        atomicAdd(threadIdx.x < 3 ? &out[threadIdx.x] : large, sum[threadIdx.x]);
     read_back(R);
 }
 
@@ -1511,14 +1537,15 @@ int rows_coverage(const sba_polygons *polys, const int4 *bbox, int64_t nv,
     // the pair counters, then the figures that the host reads: k_row_scan's
     // and k_row_lists' eight, the sweep's totals (k_row_totals), the members of
     // large sets, k_edge_rows' workgroups of many pairs, k_row_cells' listed rows
-    constexpr int NFIG = 17, NST = ROW_STATS * ROW_STAT_STEP + NFIG;
+    // (three), the number of large sets
+    constexpr int NFIG = 18, NST = ROW_STATS * ROW_STAT_STEP + NFIG;
     RC(B.alloc(&rowdiff, (int64_t)gh + 1));
     RC(B.alloc(&rowoff, (int64_t)gh + 1));
     RC(B.alloc(&stat, NST));
     int32_t *list = nullptr;
     uint32_t *row_stat = nullptr;
     RC(B.alloc(&list, (int64_t)gh * ROW_CLASSES));
-    RC(B.alloc(&row_stat, (int64_t)gh * 2));
+    RC(B.alloc(&row_stat, (int64_t)gh * ROW_FIGS));
     RC(B.alloc(&B.seg_beg, gh));
     RC(B.alloc(&B.seg_end, gh));
     unsigned long long *fig = stat + ROW_STATS * ROW_STAT_STEP;
@@ -1527,8 +1554,8 @@ int rows_coverage(const sba_polygons *polys, const int4 *bbox, int64_t nv,
     if (hash) RC(sets_table(S, B, np, false));
     hipLaunchKernelGGL(k_rows_init, dim3(grid_for(std::max<int64_t>((int64_t)np * 64, std::max<int64_t>(gh + 1, NST)))),
                        dim3(256), 0, st, polys->ring_off, polys->vert_off, np, hint, rowdiff,
-                       (int64_t)gh + 1, stat, NST, S.tab.tab,
-                       hash ? (int64_t)1 << S.tab.hb : (int64_t)0);
+                       (int64_t)gh + 1, stat, NST, row_stat + 2 * (int64_t)gh, S.tab.tab,
+                       hash ? set_tab_words(S.tab) : (int64_t)0);
     // few edges: fewer a workgroup, so that their pairs (each two 64-bit
     // divisions) spread over the chip (512 edges of 55 rows: 80 us with 256 a
     // workgroup)
@@ -1631,10 +1658,11 @@ int rows_coverage(const sba_polygons *polys, const int4 *bbox, int64_t nv,
     for (int attempt = 0;; attempt++) {
         if (attempt > 0) {
             HIP_OK(hipMemsetAsync(fig + 8, 0, 4 * sizeof(unsigned long long), st));
+            HIP_OK(hipMemsetAsync(fig + 17, 0, sizeof(unsigned long long), st));
             HIP_OK(hipMemsetAsync(B.sc + SC_SET_N, 0, sizeof(int64_t), st));
         }
         if (hash && attempt > 0)
-            HIP_OK(hipMemsetAsync(S.tab.tab, 0xff, sizeof(uint64_t) << S.tab.hb, st));
+            HIP_OK(hipMemsetAsync(S.tab.tab, 0xff, sizeof(uint64_t) * set_tab_words(S.tab), st));
         A.tab = hash ? S.tab : SetTab{};
         if (!hash && !A.seg_key) RC(B.alloc(&A.seg_key, slots));
         const bool p32 = pbits + xbits <= 32, t32 = xbits + tbits <= 31;
@@ -1646,14 +1674,14 @@ int rows_coverage(const sba_polygons *polys, const int4 *bbox, int64_t nv,
         RC(B.ws.read(hsc, B.sc, sizeof(hsc)));
         if (few_rows) {
             hipLaunchKernelGGL(k_row_totals<1024>, dim3(1), dim3(1024), 0, st, B.seg_beg, B.seg_end,
-                               row_stat, (int64_t)gh, fig + 8, B.ws.reads());
+                               row_stat, (int64_t)gh, fig + 8, fig + 17, B.ws.reads());
             HIP_OK(hipGetLastError());
             RC(B.ws.wait());
         } else {
             hipLaunchKernelGGL(k_row_totals<256>,
                                dim3((unsigned)std::min<int64_t>((gh + 255) / 256, 64)), dim3(256),
                                0, st, B.seg_beg, B.seg_end, row_stat, (int64_t)gh, fig + 8,
-                               ReadSet{});
+                               fig + 17, ReadSet{});
             HIP_OK(hipGetLastError());
             RC(B.ws.sync());
         }
@@ -1698,7 +1726,8 @@ int rows_coverage(const sba_polygons *polys, const int4 *bbox, int64_t nv,
     // polygon sets
     if (NM > 0) {
         if (hash) {
-            RC(sets_from_table(S, B, h, NM, NMEM, nset, nids, slots, st));
+            RC(sets_from_table(S, B, h, NM, NMEM, nset, nids, slots, (int64_t)hs[17],
+                               (int64_t)hs[11], row_stat + 2 * (int64_t)gh, st));
         } else {
             uint64_t *mkey = nullptr;
             uint32_t *mval = nullptr;

@@ -8,6 +8,9 @@
 // A multi-polygon segment's code until the sets are numbered: SEG_SLOT | the
 // hash slot of its set key.
 #define SEG_SLOT 0x80000000u
+// From the row sweep, a larger set's (of more than three polygons, which is not
+// shared): SEG_SLOT | SEG_LARGE | its number among its row's larger sets.
+#define SEG_LARGE 0x40000000u
 
 // The key of a set of two or three polygons holds its ids + 1, ascending, in
 // fields of fb bits; a larger set is not shared and has the key 2^(3 fb) + the
@@ -25,8 +28,24 @@ struct SetTab {
     uint64_t *list = nullptr;
     uint32_t *lslot = nullptr;
     unsigned long long *cnt = nullptr;
+    uint64_t *large = nullptr;  // [LARGE_FEW] behind tab: keys of the row sweep's larger
+                                // sets, at a quarter of their first member's place
     int hb = 0;
     uint32_t cap = 0;
+};
+
+// The row sweep's larger sets, numbered after the others in order of their
+// segments, where they are too many for one workgroup (which then numbers all):
+// of each row how many, and their members, which lie together in
+// mem_ids in that order (memloc: of the first one's and the others' segments).
+struct LargeSets {
+    const int64_t *sets = nullptr, *ids = nullptr;  // [gh] numbers before each row
+    const uint32_t *row_ids = nullptr;              // [gh]
+    const uint64_t *memloc = nullptr;
+    const int32_t *mem_ids = nullptr;
+    int64_t *set_off = nullptr;                     // the handle's table
+    int32_t *set_ids = nullptr;
+    int64_t first = 0, first_id = 0;                // sets and members before all of them
 };
 
 struct SetStage {
@@ -42,6 +61,12 @@ struct SetStage {
 #define SET_ASK 12
 // distinct sets that one workgroup sorts in LDS
 #define SET_CAP 8192
+// quarters of the row sweep's larger sets' members up to which these are listed
+// for it too
+#define LARGE_FEW 4096
+
+// words to empty (SET_EMPTY): the slots and the list of larger sets
+inline int64_t set_tab_words(const SetTab &T) { return ((int64_t)1 << T.hb) + LARGE_FEW; }
 
 __host__ __device__ inline int64_t set_count(int64_t cnt) { return (int64_t)((uint64_t)cnt >> 32); }
 __host__ __device__ inline int64_t set_ids_count(int64_t cnt) { return cnt & 0xffffffffll; }
@@ -92,9 +117,12 @@ __device__ __forceinline__ uint32_t set_insert(const SetTab &T, uint64_t key, ui
 int sets_table(SetStage &S, BuildState &B, int32_t np, bool fill);
 // number the nset distinct sets (nids members) of the table in key order, lay
 // out h's set table (NM multi segments with NMEM members bound its size) and
-// replace the SEG_SLOT codes of B's segments; slots: segment indices
+// replace the SEG_SLOT codes of B's segments; slots: segment indices.  The row
+// sweep's larger sets: nlarge with nlargeids members, and per row ([gh] each, at
+// row_large) how many of both.
 int sets_from_table(SetStage &S, BuildState &B, sba_handle *h, int64_t NM, int64_t NMEM,
-                    int64_t nset, int64_t nids, int64_t slots, hipStream_t st);
+                    int64_t nset, int64_t nids, int64_t slots, int64_t nlarge, int64_t nlargeids,
+                    const uint32_t *row_large, hipStream_t st);
 // the same from the list of multi segments (key, segment), sorted as a whole;
 // mkey and mval come from B.ws and go back to it
 int sets_from_list(SetStage &S, BuildState &B, sba_handle *h, uint64_t *mkey, uint32_t *mval,

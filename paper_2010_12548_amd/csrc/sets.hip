@@ -143,14 +143,16 @@ __device__ __forceinline__ uint32_t set_find(const SetTab &T, uint64_t k)
     return s;
 }
 
-// One workgroup, n <= SET_CAP distinct keys: sorts them in LDS, numbers the
-// sets in key order, lays out and fills the set table and leaves each key's
-// number in rank.  Dynamic LDS: two buffers of `cap` keys (n rounded up) and
+// One workgroup, n <= SET_CAP distinct keys, the table's and the listed ones of
+// larger sets (among nlist places): sorts them in LDS, numbers the sets in key
+// order, lays out and fills the set table and leaves each key's number in rank,
+// a larger set's as its segment's code.  Dynamic LDS: two buffers of `cap` keys (n rounded up) and
 // the digit counters.
-__global__ __launch_bounds__(SEG_BLOCK) void k_set_table(SetTab T, int n, int cap, int kbits, int fb,
+__global__ __launch_bounds__(SEG_BLOCK) void k_set_table(SetTab T, int ntab, int n, int nlist,
+                                                         int cap, int kbits, int fb,
                                                          const uint64_t *memloc,
                                                          const int32_t *mem_ids, int64_t *set_off,
-                                                         int32_t *set_ids)
+                                                         int32_t *set_ids, uint32_t *seg_code)
 {
     extern __shared__ __align__(16) uint64_t set_lds[];
     uint64_t *src = set_lds, *dst = set_lds + cap;
@@ -158,7 +160,16 @@ __global__ __launch_bounds__(SEG_BLOCK) void k_set_table(SetTab T, int n, int ca
     __shared__ uint32_t doff[SEG_RADIX];
     __shared__ uint32_t wtot[SEG_RADIX / 64];
     __shared__ uint32_t wsum[SEG_WAVES];
-    for (int i = threadIdx.x; i < n; i += SEG_BLOCK) src[i] = T.list[i];
+    __shared__ int at;
+    if (threadIdx.x == 0) at = ntab;
+    for (int i = threadIdx.x; i < ntab; i += SEG_BLOCK) src[i] = T.list[i];
+    __syncthreads();
+    for (int i = threadIdx.x; i < nlist; i += SEG_BLOCK) {
+        const uint64_t k = T.large[i];
+        if (k == SET_EMPTY) continue;
+        const int to = atomicAdd(&at, 1);
+        if (to < n) src[to] = k;
+    }
     __syncthreads();
     lds_radix(src, dst, n, kbits, wcnt, doff, wtot);
     // set r = src[r]: sizes, offsets (each lane `per` consecutive sets)
@@ -173,7 +184,8 @@ __global__ __launch_bounds__(SEG_BLOCK) void k_set_table(SetTab T, int n, int ca
         const int c = set_members(k, fb, memloc, &loc);
         set_off[i] = off;
         set_write(k, fb, c, loc, mem_ids, set_ids + off);
-        T.rank[set_find(T, k)] = (uint32_t)i;
+        if (nlist && loc >= 0) seg_code[k - (1ull << (3 * fb))] = CODE_SET_BASE + (uint32_t)i;
+        else T.rank[set_find(T, k)] = (uint32_t)i;
         off += (uint32_t)c;
     }
     if (threadIdx.x == SEG_BLOCK - 1) set_off[n] = off;
@@ -200,18 +212,44 @@ __global__ void k_set_ids(const uint64_t *key, int64_t n, int fb, const uint64_t
     set_write(key[t], fb, c, loc, mem_ids, set_ids + set_off[t]);
 }
 
-// SEG_SLOT codes of the segments to set codes, a wavefront per row
+// SEG_SLOT codes of the segments to set codes, a wavefront per row, which also
+// lays out the row's larger sets
 __global__ __launch_bounds__(256) void k_set_codes(const int64_t *seg_beg, const int64_t *seg_end,
                                                    int64_t gh, const uint32_t *rank,
-                                                   uint32_t *seg_code)
+                                                   uint32_t *seg_code, LargeSets G)
 {
     const int lane = threadIdx.x & 63;
     const int64_t r = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
     if (r >= gh) return;
-    for (int64_t q = seg_beg[r] + lane, e = seg_end[r]; q < e; q += 64) {
-        const uint32_t c = seg_code[q];
-        if (c & SEG_SLOT) seg_code[q] = CODE_SET_BASE + rank[c & ~SEG_SLOT];
+    const uint32_t ids = G.sets ? G.row_ids[r] : 0u;
+    const int64_t first = ids ? G.first + G.sets[r] : 0, to = ids ? G.first_id + G.ids[r] : 0;
+    int64_t from = -1;  // of the row's members in mem_ids
+    for (int64_t q0 = seg_beg[r], e = seg_end[r]; q0 < e; q0 += 64) {
+        const int64_t q = q0 + lane;
+        const uint32_t c = q < e ? seg_code[q] : 0u;
+        const bool large = ids && (c & SEG_SLOT) && (c & SEG_LARGE);
+        const uint64_t any = __ballot(large);
+        const int64_t loc = large ? (int64_t)(G.memloc[q] >> 6) : 0;
+        if (any) {
+            const int64_t least = __shfl((long long)loc, __ffsll((unsigned long long)any) - 1, 64);
+            if (from < 0) from = least;
+        }
+        if (large) {
+            const int64_t k = first + (c & (SEG_LARGE - 1));
+            G.set_off[k] = to + (loc - from);
+            seg_code[q] = CODE_SET_BASE + (uint32_t)k;
+        } else if (c & SEG_SLOT) {
+            seg_code[q] = CODE_SET_BASE + rank[c & ~SEG_SLOT];
+        }
     }
+    for (uint32_t t = lane; t < ids; t += 64) G.set_ids[to + t] = G.mem_ids[from + t];
+}
+
+__global__ void k_set_widen(const uint32_t *a, int64_t n, int64_t *b, int64_t *end, int64_t total)
+{
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t < n) b[t] = a[t];
+    if (t == 0) *end = total;
 }
 
 // the multi segments' keys through the table; neighbouring multi segments
@@ -269,12 +307,13 @@ int sets_table(SetStage &S, BuildState &B, int32_t np, bool fill)
     T.hb = 15;
     while (T.hb < 22 && ((int64_t)1 << T.hb) < (int64_t)16 * np) T.hb++;
     T.cap = 1u << (T.hb - 2);
-    RC(B.alloc(&T.tab, (int64_t)1 << T.hb));
+    RC(B.alloc(&T.tab, set_tab_words(T)));
+    T.large = T.tab + ((int64_t)1 << T.hb);
     RC(B.alloc(&T.rank, (int64_t)1 << T.hb));
     RC(B.alloc(&T.list, T.cap));
     RC(B.alloc(&T.lslot, T.cap));
     T.cnt = (unsigned long long *)(B.sc + SC_SET_N);
-    if (fill) HIP_OK(hipMemsetAsync(T.tab, 0xff, sizeof(uint64_t) << T.hb, B.st));
+    if (fill) HIP_OK(hipMemsetAsync(T.tab, 0xff, sizeof(uint64_t) * set_tab_words(T), B.st));
     return 0;
 }
 
@@ -293,21 +332,27 @@ static int key_bits(const SetStage &S, int64_t slots)
 }
 
 int sets_from_table(SetStage &S, BuildState &B, sba_handle *h, int64_t NM, int64_t NMEM,
-                    int64_t nset, int64_t nids, int64_t slots, hipStream_t st)
+                    int64_t nset, int64_t nids, int64_t slots, int64_t nlarge, int64_t nlargeids,
+                    const uint32_t *row_large, hipStream_t st)
 {
     SetTab &T = S.tab;
     const int kbits = key_bits(S, slots);
     RC(handle_alloc(h, &h->set_off, NM + 1));
     RC(handle_alloc(h, &h->set_ids, NMEM));
-    if (nset <= SET_CAP) {
-        const int cap = (int)((nset + 63) & ~(int64_t)63);
+    S.one_workgroup = nset + nlarge <= SET_CAP;
+    // all by one workgroup, or the larger sets row by row (three more launches)
+    const bool listed = nlarge && S.one_workgroup && nlargeids <= 4 * LARGE_FEW;
+    if (nset + (listed ? nlarge : 0) == 0) {
+    } else if (nset <= SET_CAP) {
+        const int64_t n = nset + (listed ? nlarge : 0);
+        const int cap = (int)((n + 63) & ~(int64_t)63);
         constexpr int wc = SEG_WAVES * SEG_RADIX * (int)sizeof(uint32_t);
         (void)hipFuncSetAttribute((const void *)k_set_table,
                                   hipFuncAttributeMaxDynamicSharedMemorySize, 16 * SET_CAP + wc);
         (void)hipGetLastError();
         hipLaunchKernelGGL(k_set_table, dim3(1), dim3(SEG_BLOCK), 16 * cap + wc, st, T, (int)nset,
-                           cap, kbits, S.fb, S.memloc, S.mem_ids, h->set_off, h->set_ids);
-        S.one_workgroup = true;
+                           (int)n, listed ? (int)((nlargeids + 3) / 4) : 0, cap, kbits, S.fb,
+                           S.memloc, S.mem_ids, h->set_off, h->set_ids, B.seg_code);
     } else {
         int64_t *sz = nullptr;
         RC(B.alloc(&sz, nset));
@@ -320,11 +365,26 @@ int sets_from_table(SetStage &S, BuildState &B, sba_handle *h, int64_t NM, int64
                            S.memloc, S.mem_ids, h->set_off, h->set_ids);
         B.release(sz);
     }
+    LargeSets G{};
+    int64_t *before = nullptr;
+    if (nlarge && !listed) {
+        const int64_t gh = h->gh;
+        RC(B.alloc(&before, 2 * gh));
+        hipLaunchKernelGGL(k_set_widen, dim3(grid_for(2 * gh)), dim3(256), 0, st, row_large, 2 * gh,
+                           before, h->set_off + nset + nlarge, nids + nlargeids);
+        HIP_OK(hipGetLastError());
+        const int64_t *in[2] = {before, before + gh}, n[2] = {gh, gh};
+        int64_t *out[2] = {before, before + gh}, *sum[2] = {nullptr, nullptr};
+        RC(scan_exclusive_i64_multi(2, in, out, n, sum, st, &B.ws));
+        G = LargeSets{before, before + gh, row_large + gh, S.memloc, S.mem_ids, h->set_off,
+                      h->set_ids, nset, nids};
+    }
     hipLaunchKernelGGL(k_set_codes, dim3(grid_for(h->gh * 64)), dim3(256), 0, st, B.seg_beg,
-                       B.seg_end, h->gh, T.rank, B.seg_code);
+                       B.seg_end, h->gh, T.rank, B.seg_code, G);
     HIP_OK(hipGetLastError());
-    h->n_sets = nset;
-    h->n_set_ids = nids;
+    B.release(before);
+    h->n_sets = nset + nlarge;
+    h->n_set_ids = nids + nlargeids;
     return 0;
 }
 
@@ -342,7 +402,8 @@ int sets_hash_list(SetStage &S, BuildState &B, sba_handle *h, const uint64_t *mk
     RC(B.ws.sync());
     const int64_t nset = set_count(hsc[SC_SET_N]);
     if (nset > (int64_t)S.tab.cap) return 0;
-    RC(sets_from_table(S, B, h, NM, NMEM, nset, set_ids_count(hsc[SC_SET_N]), slots, st));
+    RC(sets_from_table(S, B, h, NM, NMEM, nset, set_ids_count(hsc[SC_SET_N]), slots, 0, 0, nullptr,
+                       st));
     *done = true;
     return 0;
 }
