@@ -298,8 +298,11 @@ int scan_exclusive_i64_multi(int m, const int64_t *const *in, int64_t *const *ou
 #define RS_WAVES (RS_BLOCK / 64)
 // Below RS_SMALL keys a block sorts 4 x 256 of them, so that a sort of a few
 // hundred thousand keys still spreads over every compute unit; larger sorts
-// take the tiles of RB_TILE keys further down.
-#define RS_SMALL (4 << 20)
+// take the tiles of RB_TILE keys further down.  Sorts of 8-byte keys with 4-byte
+// values in us, small tiles and large: 800,000 keys of 24 bits 118 and 134, of 64
+// bits 223 and 256; 1,400,000 147 and 144, 295 and 274; 4,000,000 289 and 172,
+// 634 and 321.
+#define RS_SMALL (5 << 18)
 #define RS_ROUNDS 4
 #define RS_TILE (RS_BLOCK * RS_ROUNDS)
 #define RS_RADIX 256       // digits of an 8-bit pass (the partition pass uses these offsets)
