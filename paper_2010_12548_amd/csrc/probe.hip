@@ -35,7 +35,13 @@
 // staging a directory in LDS (up to 128 KB a workgroup) and a trip through the
 // pipeline take 8 to 13 us whatever the points.  2e4 points over 260 polygons at
 // 10 m: 13.0 us staged, 4.8 this way; 131,072: 13.5 and 8.9; 262,144: 14.8 and
-// 14.4; 524,288: 18 and 26.
+// 14.4; 524,288: 18 and 26.  Half as many where the staged probe reads the
+// directory and one fine block a point, no sets in LDS and no sub-directory: there
+// it takes less, and thousands of polygons' bins sent out by a workgroup each 512
+// points more (passes queued, 4,000 polygons at 100 m: 65,536 points 12.1 staged,
+// 11.8 this way; 98,304 12.6 and 15.6; 131,072 14.0 and 19.4).  Three quarters for
+// other handles of more than 2,048 polygons (3,000 at 100 m: 98,304 points 15.8 and
+// 13.5, 131,072 16.5 and 17.6; 2,000: 14.2 and 13.9, 13.7 and 13.1).
 #define SMALL_POINTS (1 << 17)
 
 struct GridView {
@@ -1624,6 +1630,16 @@ extern "C" const char *sba_range_kernel(const sba_handle *h, const sba_handle *h
     return buf;
 }
 
+// the most points of a call on a grid handle that the staged probe leaves alone
+static int64_t small_points(const sba_handle *h)
+{
+    if (h->n_polys > LDS_MAX_POLYS) return 0;
+    if (!h->compact) return SMALL_POINTS;
+    const Grid16Plan pl = grid16_plan(h);
+    if (pl.lev == 0 && pl.sets == SETS_GLOBAL) return SMALL_POINTS / 2;
+    return h->n_polys > LDS_MAX_POLYS / 2 ? SMALL_POINTS / 4 * 3 : SMALL_POINTS;
+}
+
 int probe_launch(const int32_t *xy, const int64_t *values, int64_t n, const sba_handle *h,
                  int32_t search, uint64_t *counts, int64_t *sums, hipStream_t st)
 {
@@ -1635,8 +1651,8 @@ int probe_launch(const int32_t *xy, const int64_t *values, int64_t n, const sba_
         return 0;
     }
     if (h->kind == SBA_KIND_GRID) {
-        const bool few = n <= SMALL_POINTS && h->n_polys <= LDS_MAX_POLYS;
-        if (!few && grid16_fits(h)) return launch_grid16(xy, values, n, h, counts, sums, st);
+        if (n > small_points(h) && grid16_fits(h))
+            return launch_grid16(xy, values, n, h, counts, sums, st);
         if (h->n_polys <= LDS_MAX_POLYS) return launch_lds(xy, values, n, h, counts, sums, st);
         return launch_items(xy, values, n, h, 0, 1, counts, sums, st);
     }
