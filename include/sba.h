@@ -358,7 +358,8 @@ int sba_get_runs(const sba_handle *h, uint64_t *starts, int32_t *ids, void *stre
 /* Handle metadata (host struct). */
 int sba_info(const sba_handle *h, sba_info_t *info);
 
-/* Name of the probe kernel that sba_aggregate launches for h, with values
+/* Name of the probe kernel that sba_aggregate launches for h and more than
+ * 524,288 points (fewer may take variants for few points), with values
  * (with_values != 0) or counts only, as profilers list it (template
  * arguments, no parameters).  Static per-thread storage, valid until the
  * next call on the same thread; "" for a null handle or one without

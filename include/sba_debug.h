@@ -28,8 +28,9 @@ uint64_t sba_debug_hilbert_tab(int L, uint32_t i, uint32_t j);
 
 void sba_debug_hilbert_cell(int L, uint64_t d, uint32_t *i, uint32_t *j);
 
-/* Workgroups per compute unit of the streaming probes (default 8, 1..64).
- * Process-wide; for launch-shape sweeps. */
+/* Workgroups per compute unit of the streaming probe over grids whose directory
+ * stays in memory (default 8, 1..64); the probes over Hilbert handles and over more
+ * than 4,096 polygons have one shape.  Process-wide; for launch-shape sweeps. */
 int sba_debug_set_blocks_per_cu(int k);
 
 /* Cap on workgroups per compute unit of the grid probe with the LDS-staged

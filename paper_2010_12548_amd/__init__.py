@@ -439,7 +439,8 @@ class Approx:
             pass
 
     def probe_kernel(self, with_values: bool = True) -> str:
-        """Name of the kernel aggregate() launches (as profilers list it)."""
+        """Name of the kernel aggregate() launches over many points (more than
+        524,288; fewer may take variants), as profilers list it."""
         return lib().sba_probe_kernel(self._h, 1 if with_values else 0).decode()
 
     def info(self) -> dict:

@@ -664,7 +664,7 @@ __global__ __launch_bounds__(PROBE_BLOCK) void k_probe_lds(const int4 *__restric
     flush_bins<VALS>(lcnt, lsum, np, PROBE_BLOCK, counts, sums);
 }
 
-// one block per polygon: sum the workgroup histograms, overwrite the outputs
+// the outputs to zero, which the probes add to
 __global__ void k_zero_out(uint64_t *counts, int64_t *sums, int32_t np)
 {
     int p = blockIdx.x * blockDim.x + threadIdx.x;
@@ -1680,8 +1680,8 @@ int lookup_launch(const sba_handle *h, const int64_t *ij, int64_t n, int32_t *re
     return 0;
 }
 
-// Name of the kernel an aggregate call on h launches (as profilers print it,
-// without arguments).
+// Name of the kernel an aggregate call of many points on h launches (as profilers
+// print it, without arguments).
 extern "C" const char *sba_probe_kernel(const sba_handle *h, int with_values)
 {
     static thread_local char buf[96];
@@ -1696,7 +1696,7 @@ extern "C" const char *sba_probe_kernel(const sba_handle *h, int with_values)
     }
     int layout = h->kind == SBA_KIND_GRID ? 0 : (h->search == SBA_SEARCH_LEARNED ? 2 : 1);
     if (h->kind == SBA_KIND_GRID && h->n_polys <= LDS_MAX_POLYS)
-        snprintf(buf, sizeof(buf), "k_probe_lds<%s>", v);
+        snprintf(buf, sizeof(buf), "k_probe_lds<%s, %d>", v, PROBE_UNROLL);
     else
         snprintf(buf, sizeof(buf), "k_probe_items<%d, %s, 1, %d>", layout, v, PROBE_UNROLL);
     return buf;
