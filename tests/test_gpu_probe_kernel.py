@@ -20,10 +20,11 @@ def test_names(sba):
         for kw, layout in ((dict(kind="hilbert"), 1), (dict(kind="hilbert", search="learned"), 2)):
             A = sba.Approx.from_polygons(polys, 5, **kw)
             assert A.probe_kernel(v) == "k_probe_items<%d, %s, 1, 4>" % (layout, t)
-        assert sba.Approx.from_polygons(many, 100).probe_kernel(v) == "k_probe_items<0, %s, 1, 4>" % t
         sba.lib().sba_debug_force_wide_grid(1)
         try:
             A = sba.Approx.from_polygons(polys, 5)
+            M = sba.Approx.from_polygons(many, 100)
         finally:
             sba.lib().sba_debug_force_wide_grid(0)
         assert A.probe_kernel(v) == "k_probe_lds<%s, 4>" % t
+        assert M.probe_kernel(v) == "k_probe_items<0, %s, 1, 4>" % t
