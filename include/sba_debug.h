@@ -72,12 +72,12 @@ int sba_debug_last_build_paths(void);
  * (comparison runs); 0: default.  Process-wide, read at build time. */
 int sba_debug_force_wide_grid(int on);
 
-/* The learned run search of a Hilbert handle (built with the learned
- * index) over the cells of n points (DEVICE xy, x,y interleaved): the host
- * *fallbacks receives how many searches failed their bracket check and took
- * the full binary search (an exact leaf error bound makes that 0), and
- * *mismatches how many answers differ from the binary search's (must be 0).
- * Points outside the key grid are skipped.  Synchronous.  Test support. */
+/* The probes' learned lookup of a Hilbert handle (built with the learned index)
+ * for the cells of n points (DEVICE xy, x,y interleaved), against a binary search
+ * over all runs: the host *fallbacks receives how many points' runs are further
+ * from the model's position than their leaf's stored error (0 when that bounds
+ * every key), *mismatches how many lookups end elsewhere (must be 0).  Points
+ * outside the stored box are skipped.  Synchronous.  Test support. */
 struct sba_handle;
 int sba_debug_learned_fallbacks(const struct sba_handle *h, const int32_t *xy, int64_t n,
                                 int64_t *fallbacks, int64_t *mismatches, void *stream);

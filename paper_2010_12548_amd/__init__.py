@@ -481,8 +481,9 @@ class Approx:
                 _first(sums, own_s, self.n_polys) if values is not None else None)
 
     def learned_fallbacks(self, xy, stream=None):
-        """Test support: (fallbacks, mismatches) of the learned run search over
-        the cells of the points xy (int32 GPU tensor [2n])."""
+        """Test support: of the cells of the points xy (int32 GPU tensor [2n]),
+        how many lie further from the learned model's position than its leaf's
+        stored error, and how many the probes' lookup gets wrong."""
         fb, mm = C.c_int64(0), C.c_int64(0)
         _check(lib().sba_debug_learned_fallbacks(self._h, xy.data_ptr(), xy.numel() // 2,
                                                  C.byref(fb), C.byref(mm), _stream_ptr(stream)),

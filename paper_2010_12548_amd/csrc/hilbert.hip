@@ -494,8 +494,9 @@ static int build_directory(sba_handle *h, hipStream_t st)
 // answer| over EVERY key of [K_l, K_{l+1}), not only the stored ones: the
 // answer is a step function of the key and the prediction is monotone, so the
 // largest gap sits at an end of a step, and the fit evaluates exactly those
-// keys.  The probe still verifies the bracket and falls back to a full binary
-// search if it ever fails.
+// keys.  A probe starts its search inside a mixed block of the directory at
+// the model's position (clamped to the block) and goes on until two runs bracket
+// the key, so it needs no bound; the stored errors are reported and tested.
 
 // smallest key whose leaf is >= l (keys in [0, total])
 __device__ uint64_t leaf_first_key(uint32_t l, float a, uint32_t nl, uint64_t total)

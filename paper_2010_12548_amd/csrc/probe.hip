@@ -82,7 +82,6 @@ struct HilbView {
     float a;               // learned root
     uint32_t nl;
     const int4 *leaves;
-    const int32_t *leaf_lo;
     const uint16_t *tab;   // Hilbert table in LDS (set by the kernel) or NULL
 };
 
@@ -252,129 +251,6 @@ __device__ __forceinline__ void grid_codes(const GridView &g, const int32_t *xs,
     }
 #pragma unroll
     for (int k = 0; k < NP; k++) c[k] = mix[k] ? (cpt ? full_code(f[k], g.np) : f[k]) : v[k];
-}
-
-// NP predecessor searches in lockstep over keys[lo[k] .. lo[k]+len): the
-// step count depends only on len, so every step issues NP loads at once.
-template <typename K, int NP>
-__device__ __forceinline__ void pred_search_n(const K *keys, int64_t *lo, int64_t len, const K *key)
-{
-    while (len > 1) {
-        const int64_t half = len >> 1;
-        K v[NP];
-#pragma unroll
-        for (int k = 0; k < NP; k++) v[k] = keys[lo[k] + half];
-#pragma unroll
-        for (int k = 0; k < NP; k++) lo[k] = (v[k] <= key[k]) ? lo[k] + half : lo[k];
-        len -= half;
-    }
-}
-
-// 4-ary predecessor search with a window per point: each step issues three
-// independent loads at the window's quarter points and keeps one quarter, so
-// a window of W keys costs about log4(W) dependent round trips instead of
-// log2(W) (the lookups are bound by such round trips); windows shorter than
-// four take binary steps.  Lanes whose windows are done re-read their
-// current key, which changes nothing.
-template <int NP>
-__device__ __forceinline__ void pred_search_var4(const uint32_t *keys, int32_t *lo, int32_t *len,
-                                                 const uint32_t *key)
-{
-    while (true) {
-        bool more = false;
-#pragma unroll
-        for (int k = 0; k < NP; k++) more |= len[k] > 1;
-        if (!__any(more)) break;
-        int32_t c1[NP], c2[NP], c3[NP];
-#pragma unroll
-        for (int k = 0; k < NP; k++) {
-            const int32_t L = len[k];
-            if (L >= 4) {
-                c1[k] = lo[k] + (L >> 2);
-                c2[k] = lo[k] + (L >> 1);
-                c3[k] = lo[k] + (int32_t)(((int64_t)3 * L) >> 2);
-            } else {
-                c1[k] = c2[k] = c3[k] = lo[k] + (L > 1 ? (L >> 1) : 0);
-            }
-        }
-        uint32_t v1[NP], v2[NP], v3[NP];
-#pragma unroll
-        for (int k = 0; k < NP; k++) {
-            v1[k] = keys[c1[k]];
-            v2[k] = keys[c2[k]];
-            v3[k] = keys[c3[k]];
-        }
-#pragma unroll
-        for (int k = 0; k < NP; k++) {
-            if (len[k] <= 1) continue;
-            int32_t end = lo[k] + len[k];
-            if (v3[k] <= key[k]) {
-                lo[k] = c3[k];
-            } else if (v2[k] <= key[k]) {
-                lo[k] = c2[k];
-                end = c3[k];
-            } else if (v1[k] <= key[k]) {
-                lo[k] = c1[k];
-                end = c2[k];
-            } else {
-                end = c1[k];
-            }
-            len[k] = end - lo[k];
-        }
-    }
-}
-
-// NP learned-index lookups in lockstep.  The leaf's model predicts p (clamped
-// into the leaf's run range); the answer lies within the leaf's stored error
-// of p, and a bounded 4-ary predecessor search over that window finds it.
-// The bracket is verified; a full binary search is the fallback (never taken
-// for an exact error bound).
-template <int NP>
-__device__ __forceinline__ void learned_search_n(const HilbView &v, const uint32_t *kk,
-                                                 const uint64_t *key, int64_t *q,
-                                                 unsigned long long *fallbacks = nullptr)
-{
-    const uint32_t *keys = v.k32;
-    int4 lf[NP];
-    int64_t llo[NP], lhi[NP];
-    int32_t lo32[NP], len[NP];  // positions fit 31 bits (runs < 2^31)
-#pragma unroll
-    for (int k = 0; k < NP; k++) {
-        uint32_t l = root_leaf(key[k], v.a, v.nl);
-        lf[k] = v.leaves[l];
-        llo[k] = v.leaf_lo[l];
-        lhi[k] = v.leaf_lo[l + 1];
-    }
-#pragma unroll
-    for (int k = 0; k < NP; k++) {
-        int64_t ra, rb;
-        leaf_range(llo[k], lhi[k], &ra, &rb);
-        int64_t p = predict_in_leaf(lf[k], llo[k], lhi[k], key[k]);
-        int64_t a = p - lf[k].w < ra ? ra : p - lf[k].w;
-        int64_t e = p + lf[k].w > rb ? rb : p + lf[k].w;
-        lo32[k] = (int32_t)a;
-        len[k] = (int32_t)(e - a + 1);
-    }
-    uint32_t first[NP];
-#pragma unroll
-    for (int k = 0; k < NP; k++) first[k] = keys[lo32[k]];
-    pred_search_var4<NP>(keys, lo32, len, kk);
-#pragma unroll
-    for (int k = 0; k < NP; k++) q[k] = lo32[k];
-    uint32_t nxt[NP];
-#pragma unroll
-    for (int k = 0; k < NP; k++) nxt[k] = q[k] + 1 < v.n ? keys[q[k] + 1] : 0xffffffffu;
-#pragma unroll
-    for (int k = 0; k < NP; k++) {
-        bool good = first[k] <= kk[k] && (q[k] + 1 == v.n || nxt[k] > kk[k]);
-        if (!good) {  // bracket missed (never for an exact error bound): full search
-            if (fallbacks) atomicAdd(fallbacks, 1ull);
-            int64_t lo1[1] = {0};
-            uint32_t k1[1] = {kk[k]};
-            pred_search_n<uint32_t, 1>(keys, lo1, v.n, k1);
-            q[k] = lo1[0];
-        }
-    }
 }
 
 // The last place in [lo, hi) at or before the key (place lo is), from place
@@ -765,7 +641,6 @@ static void views(const sba_handle *h, GridView *g, HilbView *hv)
         hv->a = h->root_a;
         hv->nl = 1u << h->log2_leaves;
         hv->leaves = h->leaves;
-        hv->leaf_lo = h->leaf_lo;
     }
 }
 
@@ -991,7 +866,6 @@ __global__ __launch_bounds__(BLOCK) void k_probe_grid16(const int4 *__restrict__
     const int64_t npairs = n >> 1;
     const int64_t stride = (int64_t)gridDim.x * BLOCK;
     const int64_t trip = stride * PROBE_UNROLL;
-    const int64_t tlast = npairs - 1;
     const uint32_t ox = (uint32_t)g.ox, oy = (uint32_t)g.oy;
     // Three-stage software pipeline.  Trip r covers pairs [r trip, (r + 1) trip)
     // of the whole grid, PROBE_UNROLL pairs per lane, and pass r of the loop
@@ -1702,10 +1576,12 @@ extern "C" const char *sba_probe_kernel(const sba_handle *h, int with_values)
     return buf;
 }
 
-// Learned run search over the cells of n points, counted: fb[0] = searches
-// whose bracket check failed (full binary search taken), fb[1] = points whose
-// learned answer differs from the binary search's.
-__global__ void k_debug_learned(HilbView v, const int32_t *xy, int64_t n, unsigned long long *fb)
+// The probes' learned lookup of n points' cells, counted against a binary search
+// over all runs: fb[0] = points whose run is further from the model's position in
+// its leaf than the leaf's stored error, fb[1] = points whose mixed block's search
+// ends at another run, or whose uniform block's entry is not their run's code.
+__global__ void k_debug_learned(HilbView v, const int32_t *leaf_lo, const int32_t *xy, int64_t n,
+                                unsigned long long *fb)
 {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= n) return;
@@ -1713,12 +1589,17 @@ __global__ void k_debug_learned(HilbView v, const int32_t *xy, int64_t n, unsign
     if ((uint64_t)dx >= v.extx || (uint64_t)dy >= v.exty) return;
     const uint32_t i = divmagic((uint32_t)dx, v.mag, v.shift);
     const uint32_t j = divmagic((uint32_t)dy, v.mag, v.shift);
-    const uint64_t key[1] = {hilbert_index(v.L, i, j)};
-    const uint32_t k32[1] = {(uint32_t)key[0]};
-    int64_t q[1], qb[1] = {0};
-    learned_search_n<1>(v, k32, key, q, fb);
-    pred_search_n<uint32_t, 1>(v.k32, qb, v.n, k32);
-    if (q[0] != qb[0]) atomicAdd(&fb[1], 1ull);
+    const uint64_t key = hilbert_index(v.L, i, j);
+    const int64_t want = pred_search<uint32_t>(v.k32, 0, v.n, (uint32_t)key);
+    const uint32_t l = root_leaf(key, v.a, v.nl);
+    const int64_t p = predict_in_leaf(v.leaves[l], leaf_lo[l], leaf_lo[l + 1], key);
+    if (want < p - v.leaves[l].w || want > p + v.leaves[l].w) atomicAdd(&fb[0], 1ull);
+    const uint32_t e = v.dir[block_index(i >> v.dr, j >> v.dr, v.cols)];
+    const bool same =
+        (e & TILE_MIXED)
+            ? run_in_block<true, uint32_t>(v, v.k32, (uint32_t)key, (int32_t)(e & ~TILE_MIXED)) == want
+            : e == v.code[want];
+    if (!same) atomicAdd(&fb[1], 1ull);
 }
 
 extern "C" int sba_debug_learned_fallbacks(const sba_handle *h, const int32_t *xy, int64_t n,
@@ -1736,7 +1617,8 @@ extern "C" int sba_debug_learned_fallbacks(const sba_handle *h, const int32_t *x
     unsigned long long *fb = nullptr;
     RC(ws.alloc(&fb, 2));
     HIP_OK(hipMemsetAsync(fb, 0, 2 * sizeof(unsigned long long), st));
-    hipLaunchKernelGGL(k_debug_learned, dim3(grid_for(n)), dim3(256), 0, st, hv, xy, n, fb);
+    hipLaunchKernelGGL(k_debug_learned, dim3(grid_for(n)), dim3(256), 0, st, hv, h->leaf_lo, xy,
+                       n, fb);
     HIP_OK(hipGetLastError());
     unsigned long long hfb[2];
     RC(ws.read(hfb, fb, sizeof(hfb)));

@@ -199,7 +199,7 @@ struct sba_handle {
     float root_a;        // leaf = floor((float)(key - root_k0) * root_a)
     uint64_t root_k0;
     int4 *leaves;        // [2^log2_leaves] {key base (u32 bits), slope (f32 bits), icpt (f32 bits), err}
-    int32_t *leaf_lo;    // [2^log2_leaves + 1] first run position of each leaf's key range
+    int32_t *leaf_lo;    // [2^log2_leaves + 1] first run position of each leaf's key range (tests)
     int64_t max_leaf_err;
     double mean_leaf_err;
     // bookkeeping
