@@ -396,9 +396,28 @@ __device__ __forceinline__ void hilbert_codes(const HilbView &v, const int32_t *
     }
     uint32_t cell[NP];
     dir_codes<NP>(v, xs, ys, c, cell);
+    // each lane searches for its own next point in a mixed block: as many searches
+    // in lockstep as the lane with the most of them has, not one for every place k
+    // at which some lane has one (a batch over 40,000 polygons at 1 m, 2e7 points in
+    // order 3.57 -> 2.71 ms, in none 3.96 -> 3.11; over 260 at 10 m 0.96 -> 0.77)
+    uint32_t left = 0;
 #pragma unroll
-    for (int k = 0; k < NP; k++)
-        if (c[k] & TILE_MIXED) c[k] = mixed_code<LEARNED>(v, xs[k], ys[k], c[k]);
+    for (int k = 0; k < NP; k++) left |= (c[k] & TILE_MIXED) ? 1u << k : 0u;
+    while (left) {
+        const int at = __builtin_ctz(left);
+        left &= left - 1;
+        int32_t x = xs[0], y = ys[0];
+        uint32_t e = c[0];
+#pragma unroll
+        for (int k = 1; k < NP; k++) {
+            x = at == k ? xs[k] : x;
+            y = at == k ? ys[k] : y;
+            e = at == k ? c[k] : e;
+        }
+        e = mixed_code<LEARNED>(v, x, y, e);
+#pragma unroll
+        for (int k = 0; k < NP; k++) c[k] = at == k ? e : c[k];
+    }
 }
 
 struct Agg {
