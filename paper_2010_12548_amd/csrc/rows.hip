@@ -444,7 +444,7 @@ __device__ __forceinline__ uint32_t class_slot(int c, uint32_t *n)
     return at;
 }
 
-// One workgroup: from rowdiff (see k_edge_rows) the rows' pair counts and
+// One workgroup, or many (PARTS): from rowdiff (see k_edge_rows) the rows' pair counts and
 // their exclusive scan rowoff[0..gh] (pairs < 2^31); rowdiff goes back to
 // zero.  out[0]: pairs, out[1]: the most in a row, out[6], out[7]: boundary
 // strips and crossings (the sums over stat).  The rows come and go by threads
@@ -456,6 +456,10 @@ __device__ __forceinline__ uint32_t class_slot(int c, uint32_t *n)
 // Up to RSCAN_LISTS rows it makes the rows' lists as well (see k_row_lists),
 // and copies the host's values: two launches less.
 #define RSCAN_LISTS (RSCAN * RSCAN_PER)
+// From RSCAN_PARTS times as many rows on, a workgroup for each RSCAN_LISTS of them
+// (one workgroup takes 3 us for so many: 1,048,577 rows 393 us, now 10 and
+// less than 5 for the parts' sums).
+#define RSCAN_PARTS 4
 // a row's figures, [gh] each: multi-polygon segments and their members, then
 // those of more than three polygons and theirs
 #define ROW_FIGS 4
@@ -464,9 +468,33 @@ struct RowLists {
     int64_t *seg_beg, *seg_end;
     uint32_t *row_stat;
 };
+
+// Of each RSCAN_LISTS rows (a workgroup): the sum of their differences, and of
+// their pairs had no row before them any.
+__global__ __launch_bounds__(RSCAN) void k_row_parts(const int32_t *rowdiff, int64_t gh, uint2 *parts)
+{
+    __shared__ uint32_t wsum[RSCAN / 64];
+    const int64_t c0 = (int64_t)blockIdx.x * RSCAN_LISTS;
+    const int64_t c1 = min(c0 + RSCAN_LISTS, gh);
+    uint32_t d = 0, sum = 0;
+    for (int64_t r = c0 + threadIdx.x; r < c1; r += RSCAN) {
+        const uint32_t v = (uint32_t)rowdiff[r];
+        d += v;
+        sum += v * (uint32_t)(c1 - r);
+    }
+    uint32_t td, ts;
+    wg_scan_incl<RSCAN>(d, wsum, &td);
+    wg_scan_incl<RSCAN>(sum, wsum, &ts);
+    if (threadIdx.x == 0) parts[blockIdx.x] = make_uint2(td, ts);
+}
+
+// PARTS (of k_row_parts; no lists): workgroup c scans the c-th RSCAN_LISTS rows,
+// after the sums of the parts before it.
+template <bool PARTS>
 __global__ __launch_bounds__(RSCAN) void k_row_scan(int32_t *rowdiff, int64_t gh, int64_t *rowoff,
                                                     const unsigned long long *stat,
-                                                    unsigned long long *out, RowLists Q, ReadSet R)
+                                                    unsigned long long *out, const uint2 *parts,
+                                                    RowLists Q, ReadSet R)
 {
     __shared__ uint32_t ncls[ROW_CLASSES];
     __shared__ uint32_t wd[RSCAN / 64];
@@ -484,13 +512,21 @@ __global__ __launch_bounds__(RSCAN) void k_row_scan(int32_t *rowdiff, int64_t gh
             next[k] = r <= gh ? (uint32_t)rowdiff[r] : 0u;
         }
     };
-    load(0);
+    const int64_t beg = PARTS ? (int64_t)blockIdx.x * RSCAN_LISTS : 0;
+    const int64_t end = PARTS ? min(beg + RSCAN_LISTS - 1, gh) : gh;
+    load(beg);
     __syncthreads();
     if (threadIdx.x < 2 * ROW_STATS)
         atomicAdd(&sst[threadIdx.x & 1],
                   stat[ROW_STAT_STEP * (threadIdx.x >> 1) + (threadIdx.x & 1)]);
     uint32_t cd = 0, cs = 0, m = 0;
-    for (int64_t c0 = 0; c0 <= gh; c0 += RSCAN * RSCAN_PER) {
+    if constexpr (PARTS) {  // at most RSCAN of them: MAX_GRID_SIDE rows
+        static_assert(MAX_GRID_SIDE / RSCAN_LISTS < RSCAN, "a part a thread");
+        const uint2 p = threadIdx.x < blockIdx.x ? parts[threadIdx.x] : make_uint2(0, 0);
+        const uint32_t before = wg_scan_incl<RSCAN>(p.x, wd, &cd) - p.x;
+        wg_scan_incl<RSCAN>(threadIdx.x < blockIdx.x ? p.y + before * RSCAN_LISTS : 0u, wd, &cs);
+    }
+    for (int64_t c0 = beg; c0 <= end; c0 += RSCAN * RSCAN_PER) {
         const int64_t b = c0 + (int64_t)threadIdx.x * RSCAN_PER;
 #pragma unroll
         for (int k = 0; k < RSCAN_PER; k++) chunk[RS_PAD(k * RSCAN + threadIdx.x)] = next[k];
@@ -501,7 +537,7 @@ __global__ __launch_bounds__(RSCAN) void k_row_scan(int32_t *rowdiff, int64_t gh
             run += chunk[RS_PAD(threadIdx.x * RSCAN_PER + k)];  // modulo 2^32
             d[k] = run;
         }
-        load(c0 + RSCAN * RSCAN_PER);
+        if (!PARTS) load(c0 + RSCAN * RSCAN_PER);
         uint32_t totd;
         const uint32_t before = cd + wg_scan_incl<RSCAN>(run, wd, &totd) - run;
         uint32_t sum = 0;
@@ -516,7 +552,7 @@ __global__ __launch_bounds__(RSCAN) void k_row_scan(int32_t *rowdiff, int64_t gh
 #pragma unroll
         for (int k = 0; k < RSCAN_PER; k++) {
             chunk[RS_PAD(threadIdx.x * RSCAN_PER + k)] = o;
-            if (Q.list) {
+            if (!PARTS && Q.list) {
                 const int64_t r = b + k;
                 int c = -1;
                 if (r < gh && d[k] == 0) {
@@ -547,12 +583,13 @@ __global__ __launch_bounds__(RSCAN) void k_row_scan(int32_t *rowdiff, int64_t gh
     if ((threadIdx.x & 63) == 0) atomicMax(&smax, m);
     __syncthreads();
     if (threadIdx.x == 0) {
-        out[0] = cs;
-        out[1] = smax;
+        if (end == gh) out[0] = cs;
+        if (PARTS) atomicMax(&out[1], (unsigned long long)smax);
+        else out[1] = smax;
         out[6] = sst[0];
         out[7] = sst[1];
     }
-    if (Q.list && threadIdx.x < ROW_CLASSES) out[2 + threadIdx.x] = ncls[threadIdx.x];
+    if (!PARTS && Q.list && threadIdx.x < ROW_CLASSES) out[2 + threadIdx.x] = ncls[threadIdx.x];
     read_back(R);
 }
 
@@ -1176,6 +1213,14 @@ __global__ void k_widen(const uint32_t *a, int64_t n, int64_t *b)
 #define NO_SEG 0xffffffffu
 #define CELL_PAIRS 64
 #define CELLS_FEW 128
+// Many rows of few pairs each, a ring's over a large box, take a lane each: rows of
+// up to TINY_PAIRS pairs and TINY_CELLS cells, where there are TINY_ROWS rows or
+// more and no more than TINY_PAIRS pairs a row on average (a ring of 64 edges over
+// 1,048,577 rows: COUNT 296 us with a wavefront a row, 80 so, WRITE 908 and 243;
+// over fewer rows than wavefronts in flight, 8 a SIMD, a wavefront each is better).
+#define TINY_PAIRS 4
+#define TINY_CELLS 16
+#define TINY_ROWS (1 << 17)
 
 // The rows that get a bitmap: those of the classes above CELL_PAIRS pairs, then
 // with a border the first and the last, then listed ones of many cells.  WRITE
@@ -1313,19 +1358,97 @@ __device__ __forceinline__ void row_cells_few(int32_t row, const uint4 *items,
     }
 }
 
+// A row of at most TINY_PAIRS pairs and TINY_CELLS cells by one lane; false: not
+// such a row (or, WRITE, none of a wavefront's).
+template <bool WRITE, typename K>
+__device__ __forceinline__ bool row_cells_tiny(int32_t row, const uint4 *items,
+                                               const int64_t *rowoff, int32_t gw, int32_t gh,
+                                               int border, int64_t *rowcell, const int64_t *seg_beg,
+                                               const int64_t *seg_end, const int32_t *seg_x0,
+                                               const int32_t *seg_x1, int L, K *keys, uint32_t *bseg)
+{
+    if (row >= gh || (border && (row == 0 || row == gh - 1))) return true;  // none, or a bitmap's
+    const int64_t i0 = rowoff[row];
+    const int n = (int)(rowoff[row + 1] - i0);
+    if (n > TINY_PAIRS) return false;
+    const int64_t done = WRITE ? rowcell[row] : 0;
+    const int64_t total = WRITE ? rowcell[row + 1] - done : 0;
+    if (WRITE && total > TINY_CELLS) return false;
+    if (WRITE && total == 0) return true;
+    uint64_t v[TINY_PAIRS];
+#pragma unroll
+    for (int k = 0; k < TINY_PAIRS; k++) {
+        v[k] = ~(uint64_t)0;
+        if (k >= n) continue;
+        const uint4 it = items[i0 + k];
+        const uint32_t end = min(it.z, (uint32_t)gw);
+        if (it.y < end) v[k] = ((uint64_t)it.y << 32) | end;
+    }
+#pragma unroll
+    for (int i = 0; i < TINY_PAIRS; i++)
+#pragma unroll
+        for (int k = 0; k + 1 < TINY_PAIRS - i; k++) {
+            const uint64_t a = min(v[k], v[k + 1]), b = max(v[k], v[k + 1]);
+            v[k] = a;
+            v[k + 1] = b;
+        }
+    uint32_t reach = 0, cells = 0;
+    const uint32_t lowest = (uint32_t)(v[0] >> 32);
+    const int64_t sb = WRITE ? seg_beg[row] : 0;
+    const int ns = WRITE ? (int)(seg_end[row] - sb) : 0;
+    int lo = 0;  // segments that start at or before the cell
+    auto put = [&](uint32_t x) {
+        while (lo < ns && seg_x0[sb + lo] <= (int32_t)x) lo++;
+        const bool held = lo > 0 && (int32_t)x < seg_x1[sb + lo - 1];
+        keys[done + cells] = (K)hilbert_index(L, x, (uint32_t)row);
+        bseg[done + cells] = held ? (uint32_t)(sb + lo - 1) : NO_SEG;
+    };
+    const uint32_t first = border && lowest != 0 ? 1u : 0u;
+    if (WRITE && first) put(0);
+    cells += first;
+#pragma unroll
+    for (int k = 0; k < TINY_PAIRS; k++) {
+        if (v[k] == ~(uint64_t)0) continue;
+        const uint32_t b = (uint32_t)v[k], a = max((uint32_t)(v[k] >> 32), reach);
+        if (b <= a) continue;
+        reach = b;
+        if (WRITE)
+            for (uint32_t x = a; x < b; x++, cells++) put(x);
+        else
+            cells += b - a;
+    }
+    const uint32_t last = border && reach != (uint32_t)gw && gw > 1 ? 1u : 0u;
+    if (WRITE && last) put((uint32_t)gw - 1);
+    cells += last;
+    if (!WRITE) {
+        if (cells > TINY_CELLS) return false;
+        rowcell[row] = cells;
+    }
+    return true;
+}
+
 template <bool WRITE, typename K>
 __global__ __launch_bounds__(256) void k_row_cells(const uint4 *items, const int64_t *rowoff,
                                                    int32_t gw, int32_t gh, int border,
                                                    int64_t *rowcell, const int64_t *seg_beg,
                                                    const int64_t *seg_end, const int32_t *seg_x0,
                                                    const int32_t *seg_x1, int L, K *keys,
-                                                   uint32_t *bseg, CellRows C, int bitmaps)
+                                                   uint32_t *bseg, CellRows C, int bitmaps,
+                                                   int tiny)
 {
-    // the first workgroups a row's bitmap each, the others four rows of few pairs
+    // the first workgroups a row's bitmap each, the others rows of few pairs: a
+    // wavefront one, or (tiny) a lane one and the wavefront those left
     if ((int)blockIdx.x >= bitmaps) {
-        row_cells_few<WRITE, K>(
-            (int32_t)((blockIdx.x - (unsigned)bitmaps) * 4 + (threadIdx.x >> 6)), items, rowoff, gw,
-            gh, border, rowcell, seg_beg, seg_end, seg_x0, seg_x1, L, keys, bseg, C);
+        const unsigned b = blockIdx.x - (unsigned)bitmaps;
+        const int32_t row = (int32_t)(tiny ? b * 256 + threadIdx.x : b * 4 + (threadIdx.x >> 6));
+        const bool rest = !tiny || !row_cells_tiny<WRITE, K>(row, items, rowoff, gw, gh, border,
+                                                             rowcell, seg_beg, seg_end, seg_x0,
+                                                             seg_x1, L, keys, bseg);
+        for (uint64_t m = tiny ? __ballot(rest) : 1ull; m; m &= m - 1) {
+            const int32_t r = tiny ? row - (int32_t)(threadIdx.x & 63) + __ffsll((long long)m) - 1 : row;
+            row_cells_few<WRITE, K>(r, items, rowoff, gw, gh, border, rowcell, seg_beg, seg_end,
+                                    seg_x0, seg_x1, L, keys, bseg, C);
+        }
         return;
     }
     __shared__ uint32_t bits[CELL_BITS / 32];
@@ -1445,15 +1568,15 @@ __global__ __launch_bounds__(256) void k_row_cells(const uint4 *items, const int
 template <typename K>
 static int row_cells_write(BuildState &B, const sba_handle *h, const uint4 *items,
                            const int64_t *rowoff, int64_t *rowcell, int64_t nc, const CellRows &C,
-                           unsigned rows, K **keys, hipStream_t st)
+                           unsigned rows, int tiny, K **keys, hipStream_t st)
 {
     RC(B.alloc(keys, nc));
     RC(B.alloc(&B.bseg, nc));
     const int32_t gw = (int32_t)h->gw, gh = (int32_t)h->gh;
     const int border = B.window ? 1 : 0;
-    hipLaunchKernelGGL((k_row_cells<true, K>), dim3(rows + grid_for(gh, 4)), dim3(256), 0, st,
-                       items, rowoff, gw, gh, border, rowcell, B.seg_beg, B.seg_end, B.seg_x0,
-                       B.seg_x1, h->level, *keys, B.bseg, C, (int)rows);
+    hipLaunchKernelGGL((k_row_cells<true, K>), dim3(rows + grid_for(gh, tiny ? 256 : 4)), dim3(256),
+                       0, st, items, rowoff, gw, gh, border, rowcell, B.seg_beg, B.seg_end, B.seg_x0,
+                       B.seg_x1, h->level, *keys, B.bseg, C, (int)rows, tiny);
     HIP_OK(hipGetLastError());
     return 0;
 }
@@ -1570,8 +1693,16 @@ int rows_coverage(const sba_polygons *polys, const int4 *bbox, int64_t nv,
     unsigned long long hs[NFIG];
     RC(B.ws.read(hs, fig, sizeof(hs)));
     const RowLists lists{few_rows ? list : nullptr, B.seg_beg, B.seg_end, row_stat};
-    hipLaunchKernelGGL(k_row_scan, dim3(1), dim3(RSCAN), 0, st, rowdiff, (int64_t)gh, rowoff, stat,
-                       fig, lists, few_rows ? B.ws.reads() : ReadSet{});
+    uint2 *parts = nullptr;
+    const unsigned nparts = (unsigned)(gh / RSCAN_LISTS + 1);
+    if (nparts >= RSCAN_PARTS) {
+        RC(B.alloc(&parts, nparts));
+        hipLaunchKernelGGL(k_row_parts, dim3(nparts), dim3(RSCAN), 0, st, rowdiff, (int64_t)gh,
+                           parts);
+    }
+    hipLaunchKernelGGL(parts ? k_row_scan<true> : k_row_scan<false>, dim3(parts ? nparts : 1),
+                       dim3(RSCAN), 0, st, rowdiff, (int64_t)gh, rowoff, stat, fig, parts, lists,
+                       few_rows ? B.ws.reads() : ReadSet{});
     HIP_OK(hipGetLastError());
     if (few_rows) {
         RC(B.ws.wait());
@@ -1590,7 +1721,7 @@ int rows_coverage(const sba_polygons *polys, const int4 *bbox, int64_t nv,
     if (2 * NB + NC >= ((int64_t)1 << 32)) return SBA_ELIMIT;
     auto leave = [&]() {
         for (void *p : {(void *)rowdiff, (void *)rowoff, (void *)stat, (void *)list, (void *)hint,
-                        (void *)big, (void *)row_stat, (void *)B.seg_beg, (void *)B.seg_end})
+                        (void *)parts, (void *)big, (void *)row_stat, (void *)B.seg_beg, (void *)B.seg_end})
             B.release(p);
         B.seg_beg = B.seg_end = nullptr;
         sets_release(S, B);
@@ -1618,8 +1749,10 @@ int rows_coverage(const sba_polygons *polys, const int4 *bbox, int64_t nv,
     B.release(rowdiff);
     B.release(hint);
     B.release(big);
+    B.release(parts);
     rowdiff = hint = nullptr;
     big = nullptr;
+    parts = nullptr;
 
     // the sweep; again when the members of large sets outgrew their array,
     // or with set keys instead of the hash table when that overflowed
@@ -1763,11 +1896,12 @@ int rows_coverage(const sba_polygons *polys, const int4 *bbox, int64_t nv,
         RC(B.alloc(&C.many, gh));
         RC(B.alloc(&C.large, gh));
         const unsigned bitmaps = (unsigned)(rows[1] + rows[2] + rows[3] + C.border);
-        hipLaunchKernelGGL((k_row_cells<false, uint64_t>), dim3(bitmaps + grid_for(gh, 4)),
-                           dim3(256), 0, st, items, rowoff, (int32_t)h->gw, gh, border, rowcell,
+        const int tiny = gh >= TINY_ROWS && items_n <= (int64_t)TINY_PAIRS * gh ? 1 : 0;
+        hipLaunchKernelGGL((k_row_cells<false, uint64_t>),
+                           dim3(bitmaps + grid_for(gh, tiny ? 256 : 4)), dim3(256), 0, st, items, rowoff, (int32_t)h->gw, gh, border, rowcell,
                            (const int64_t *)nullptr, (const int64_t *)nullptr,
                            (const int32_t *)nullptr, (const int32_t *)nullptr, 0,
-                           (uint64_t *)nullptr, (uint32_t *)nullptr, C, (int)bitmaps);
+                           (uint64_t *)nullptr, (uint32_t *)nullptr, C, (int)bitmaps, tiny);
         HIP_OK(hipGetLastError());
         RC(scan_exclusive_i64(rowcell, rowcell, gh, rowcell + gh, st, &B.ws));
         int64_t nc = 0;
@@ -1783,12 +1917,12 @@ int rows_coverage(const sba_polygons *polys, const int4 *bbox, int64_t nv,
                                                      std::max<int64_t>(4096 / C.nlarge, 1));
             const unsigned all = (unsigned)(C.nlarge * C.parts) + bitmaps + (unsigned)hc[0];
             if (2 * h->level <= 32) {
-                RC(row_cells_write<uint32_t>(B, h, items, rowoff, rowcell, nc, C, all, &B.bkeys32,
-                                             st));
+                RC(row_cells_write<uint32_t>(B, h, items, rowoff, rowcell, nc, C, all, tiny,
+                                             &B.bkeys32, st));
                 RC(radix_sort_u32_ws(&B.bkeys32, &B.bseg, nc, 2 * h->level, B.ws));
             } else {
-                RC(row_cells_write<uint64_t>(B, h, items, rowoff, rowcell, nc, C, all, &B.bkeys,
-                                             st));
+                RC(row_cells_write<uint64_t>(B, h, items, rowoff, rowcell, nc, C, all, tiny,
+                                             &B.bkeys, st));
                 RC(radix_sort_u64_ws(&B.bkeys, &B.bseg, nc, 2 * h->level, B.ws));
             }
         }
