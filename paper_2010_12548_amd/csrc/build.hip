@@ -111,7 +111,18 @@ __global__ __launch_bounds__(1024) void k_check_offsets(const int32_t *ring_off,
     if (!bad) {  // the same in every lane: read again only after a barrier
         nv = vert_off[nr];
         b = threadIdx.x == 0 && vert_off[0] != 0;
-        for (int64_t r = threadIdx.x; r < nr; r += 1024) b |= vert_off[r + 1] < vert_off[r];
+        int64_t r = threadIdx.x;
+        for (; r + 7 * 1024 < nr; r += 8 * 1024) {  // 3.2M rings: 1456 us one by one
+            int64_t v[8], w[8];  // and 531 with eight rings' loads together
+#pragma unroll
+            for (int k = 0; k < 8; k++) {
+                v[k] = vert_off[r + k * 1024];
+                w[k] = vert_off[r + k * 1024 + 1];
+            }
+#pragma unroll
+            for (int k = 0; k < 8; k++) b |= w[k] < v[k];
+        }
+        for (; r < nr; r += 1024) b |= vert_off[r + 1] < vert_off[r];
     }
     __syncthreads();
     if (b) atomicOr(&bad, 1);
