@@ -338,9 +338,12 @@ static int write_runs(BuildState &B, sba_handle *h, const K *bk, hipStream_t st)
 // blocks of a partition lie in one run (91 % of the 16 x 16 blocks of 40,000
 // polygons at 1 m), so most lookups are one 4-byte read, at an address that
 // takes no Hilbert key, where a search over the runs takes 6 to 9 cache lines.
-// Blocks as small as 16 of them a run allow, at most 2^24 (64 MB, which the
-// memory-side cache holds; 2^22 and 2^23 made the probe of 2e7 points in no
-// order 9 and 4 % slower, by their mixed blocks).  They cover the stored box
+// Blocks as small as 4 to 8 of them a run allow, and at most 2^24.  Four times as
+// many leave fewer mixed blocks but more lines: 2e7 points over 260 polygons at
+// 10 m (230,000 runs) in no order, counts only, 141 us with up to 32 a run, 122 so,
+// with values 183 and 173; in order 93 and 107.  (2^24 are 64 MB, which the
+// memory-side cache holds; 2^22 and 2^23 made the probe of 2e7 points over 40,000
+// polygons at 1 m in no order 9 and 4 % slower, by their mixed blocks.)  They cover the stored box
 // only, not the whole key grid: on a grid much larger than the polygons (a
 // point index's, or one for several sets) blocks of 4^-12 of it held all runs.
 #define DIR_MAX ((int64_t)1 << 24)
@@ -461,7 +464,7 @@ static int build_directory(sba_handle *h, hipStream_t st)
     DirGeo D{};
     D.L = h->level;
     const int64_t most = std::min(
-        DIR_MAX, std::max<int64_t>(1024, (int64_t)16 << bits_for((uint64_t)h->n_runs - 1)));
+        DIR_MAX, std::max<int64_t>(1024, (int64_t)4 << bits_for((uint64_t)h->n_runs - 1)));
     int64_t entries = 0;
     for (D.r = 0;; D.r++) {
         D.bw = (uint32_t)(((h->gw - 1) >> D.r) + 1);
