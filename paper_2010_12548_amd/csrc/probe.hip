@@ -39,9 +39,11 @@
 // directory and one fine block a point, no sets in LDS and no sub-directory: there
 // it takes less, and thousands of polygons' bins sent out by a workgroup each 512
 // points more (passes queued, 4,000 polygons at 100 m: 65,536 points 12.1 staged,
-// 11.8 this way; 98,304 12.6 and 15.6; 131,072 14.0 and 19.4).  Three quarters for
-// other handles of more than 2,048 polygons (3,000 at 100 m: 98,304 points 15.8 and
-// 13.5, 131,072 16.5 and 17.6; 2,000: 14.2 and 13.9, 13.7 and 13.1).
+// 11.8 this way; 98,304 12.6 and 15.6; 131,072 14.0 and 19.4; counts only, three
+// quarters: 98,304 10.8 and 10.3, 131,072 11.2 and 12.1).  Three quarters for
+// other handles of more than 2,048 polygons, with values (3,000 at 100 m: 98,304
+// points 15.8 and 13.5, 131,072 16.5 and 17.6, counts only 14.6 and 12.3; 2,000
+// polygons: 14.2 and 13.9, 13.7 and 13.1).
 #define SMALL_POINTS (1 << 17)
 
 struct GridView {
@@ -1524,13 +1526,15 @@ extern "C" const char *sba_range_kernel(const sba_handle *h, const sba_handle *h
 }
 
 // the most points of a call on a grid handle that the staged probe leaves alone
-static int64_t small_points(const sba_handle *h)
+static int64_t small_points(const sba_handle *h, bool vals)
 {
     if (h->n_polys > LDS_MAX_POLYS) return 0;
     if (!h->compact) return SMALL_POINTS;
     const Grid16Plan pl = grid16_plan(h);
-    if (pl.lev == 0 && pl.sets == SETS_GLOBAL) return SMALL_POINTS / 2;
-    return h->n_polys > LDS_MAX_POLYS / 2 ? SMALL_POINTS / 4 * 3 : SMALL_POINTS;
+    const int quarters = pl.lev == 0 && pl.sets == SETS_GLOBAL
+                             ? (vals ? 2 : 3)
+                             : (vals && h->n_polys > LDS_MAX_POLYS / 2 ? 3 : 4);
+    return SMALL_POINTS / 4 * quarters;
 }
 
 int probe_launch(const int32_t *xy, const int64_t *values, int64_t n, const sba_handle *h,
@@ -1544,7 +1548,7 @@ int probe_launch(const int32_t *xy, const int64_t *values, int64_t n, const sba_
         return 0;
     }
     if (h->kind == SBA_KIND_GRID) {
-        if (n > small_points(h) && grid16_fits(h))
+        if (n > small_points(h, values && sums) && grid16_fits(h))
             return launch_grid16(xy, values, n, h, counts, sums, st);
         if (h->n_polys <= LDS_MAX_POLYS) return launch_lds(xy, values, n, h, counts, sums, st);
         return launch_items(xy, values, n, h, 0, 1, counts, sums, st);
