@@ -1944,9 +1944,12 @@ struct LineBins {
     bool high_own;
 };
 
-// Workgroups per compute unit: one with all of its LDS for points in no known
-// order, two for partitioned points (a region meets few lines, and twice the
-// wavefronts hide twice the latency).
+// Workgroups per compute unit that the grid is sized for: one with all of its LDS
+// for points in no known order, two with half of it each for partitioned points,
+// where a region meets few lines.  (With 85 registers a lane and more one of the two
+// runs at a time.  One with all of the LDS instead, 2e7 partitioned points: 40,000
+// polygons at 1 m 606 us and 606, with values of both signs 648 and 606, 4,000 at
+// 3 m 454 and 461; 200,000 points 154 and 156.)
 static __host__ __device__ constexpr int line_count(int per_cu)
 {
     // LDS less the Hilbert table, the queues and a little more
@@ -2270,7 +2273,8 @@ static int launch_items(const int32_t *xy, const int64_t *values, int64_t n, con
         nb = (nb + 7) & ~(int64_t)7;  // whole rounds of the 8 XCDs
         // a workgroup's bins go out after FLUSH_POINTS points at most; over
         // partitioned points every few chunks, before lines of regions left
-        // behind fill the places
+        // behind fill the places (12 of them instead of 6, with all of the LDS:
+        // 2e7 points of 40,000 polygons 609 us instead of 602, of 4,000 463 and 461)
         const int flush_every = per_cu == 2 ? 6 : FLUSH_POINTS / chunk;
         hipLaunchKernelGGL(kern, dim3((unsigned)nb), dim3(LINE_BLOCK), lds, st, T, chunks,
                            flush_every);

