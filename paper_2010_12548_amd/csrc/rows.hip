@@ -1005,6 +1005,10 @@ __global__ __launch_bounds__(BLOCK) void k_row_sweep(const SweepArgs A)
     // the pieces it spans, a lane an interval, or a wavefront those of more than 64
     // pieces; up to three ids come back from their smallest, largest and sum
     const int ni = nt >> 1;
+    // small classes: a wavefront looks through the row's intervals, at most four
+    // steps of 64, for each large set (its members, written to memory, read again
+    // and sorted took a row of 64 pairs 2.5 us more)
+    constexpr bool SCAN = BLOCK <= 256;
     auto join = [&](int k, uint32_t p) {
         const int d = L.D[k];
         if (d == 1) {
@@ -1013,7 +1017,7 @@ __global__ __launch_bounds__(BLOCK) void k_row_sweep(const SweepArgs A)
             atomicMin(&L.pmin[k], p);
             atomicMax(&L.pmax[k], p);
             atomicAdd(&L.psum[k], p);
-        } else if (fits && d <= MAX_DEPTH) {
+        } else if (!SCAN && fits && d <= MAX_DEPTH) {
             mem[L.psum[k] + atomicAdd(&L.pmin[k], 1u)] = (int32_t)p;
         }
     };
@@ -1037,7 +1041,28 @@ __global__ __launch_bounds__(BLOCK) void k_row_sweep(const SweepArgs A)
     // its place by the members below it).  (A wavefront that looked through all
     // of the row's intervals for each set: the two sweeps of 300,000 rectangles in
     // layers 23.3 ms, 17.9 this way.)
-    if (large && fits) {
+    if (SCAN && large && fits) {
+        for (int b = 0; b < nd; b += BLOCK) {
+            const int k = b + tid, d = k < nd ? L.D[k] : 0;
+            uint64_t sets = __ballot(d > 3 && d <= MAX_DEPTH);
+            while (sets) {
+                const int l = __ffsll((unsigned long long)sets) - 1;
+                sets &= sets - 1;
+                const int kk = __shfl(k, l), dd = __shfl(d, l);
+                int32_t *const set = mem + L.psum[kk];
+                // intervals are in polygon order: the ids come out ascending
+                for (int m0 = 0, q = 0; m0 < ni && q < dd; m0 += 64) {
+                    const int m = m0 + lane;
+                    const bool in = m < ni && (int)L.rank[2 * m] <= kk &&
+                                    kk < (int)L.rank[2 * m + 1];
+                    const uint64_t who = __ballot(in);
+                    const int at = q + __popcll(who & ((1ull << lane) - 1));
+                    if (in && at < dd) set[at] = (int32_t)L.tpoly[2 * m];
+                    q += __popcll(who);
+                }
+            }
+        }
+    } else if (large && fits) {
         static_assert(MAX_DEPTH == 32, "half a wavefront");
         for (int k0 = (tid >> 6) * 2; k0 < nd; k0 += BLOCK / 32) {
             const int k = k0 + (lane >> 5), d = k < nd ? L.D[k] : 0, q = lane & 31;
@@ -1046,7 +1071,8 @@ __global__ __launch_bounds__(BLOCK) void k_row_sweep(const SweepArgs A)
             int32_t *const set = mem + (in ? L.psum[k] : 0u);
             const int32_t v = in ? set[q] : INT32_MAX;
             int below = 0;
-#pragma unroll
+            // (all 32 at once took 80 registers, and a wavefront a SIMD)
+#pragma unroll 4
             for (int j = 0; j < 32; j++) below += __shfl(v, (lane & 32) | j) < v ? 1 : 0;
             if (in) set[below] = v;
         }
@@ -1132,32 +1158,51 @@ __global__ __launch_bounds__(BLOCK) void k_row_totals(const int64_t *seg_beg, co
                                                       unsigned long long *out,
                                                       unsigned long long *large, ReadSet R)
 {
-    __shared__ unsigned long long sum[4];
-    if (threadIdx.x < 4) sum[threadIdx.x] = 0;
+    __shared__ unsigned long long sum[3];
+    if (threadIdx.x < 3) sum[threadIdx.x] = 0;
     __syncthreads();
-    unsigned long long a = 0, b = 0, c = 0, d = 0;
-    for (int64_t r = (int64_t)blockIdx.x * BLOCK + threadIdx.x; r < gh;
-         r += (int64_t)gridDim.x * BLOCK) {
-        a += (unsigned long long)(seg_end[r] - seg_beg[r]);
-        b += row_stat[r];
-        c += row_stat[gh + r];
-        d += row_stat[2 * gh + r];
+    // (b: multi-polygon segments, and above bit 32 those of more than three
+    // polygons: below 2^32 each, as two segments a pair are)
+    unsigned long long a = 0, b = 0, c = 0;
+    // four rows' loads together: the chain of them is what one workgroup takes
+    const int64_t step = (int64_t)gridDim.x * BLOCK;
+    for (int64_t r0 = (int64_t)blockIdx.x * BLOCK + threadIdx.x; r0 < gh; r0 += 4 * step) {
+        int64_t e[4], s[4];
+        uint32_t m[4], f[4], l[4];
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            const int64_t r = r0 + k * step;
+            const bool in = r < gh;
+            const int64_t q = in ? r : r0;
+            e[k] = seg_end[q];
+            s[k] = in ? seg_beg[q] : e[k];
+            m[k] = in ? row_stat[q] : 0u;
+            f[k] = in ? row_stat[gh + q] : 0u;
+            l[k] = in ? row_stat[2 * gh + q] : 0u;
+        }
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            a += (unsigned long long)(e[k] - s[k]);
+            b += m[k] + ((unsigned long long)l[k] << 32);
+            c += f[k];
+        }
     }
     for (int o = 32; o > 0; o >>= 1) {
         a += __shfl_xor(a, o, 64);
         b += __shfl_xor(b, o, 64);
         c += __shfl_xor(c, o, 64);
-        d += __shfl_xor(d, o, 64);
     }
     if ((threadIdx.x & 63) == 0) {
         atomicAdd(&sum[0], a);
         atomicAdd(&sum[1], b);
         atomicAdd(&sum[2], c);
-        atomicAdd(&sum[3], d);
     }
     __syncthreads();
-    if (threadIdx.x < 4 && sum[threadIdx.x])
-        atomicAdd(threadIdx.x < 3 ? &out[threadIdx.x] : large, sum[threadIdx.x]);
+    if (threadIdx.x < 4) {
+        const unsigned long long v = threadIdx.x == 3 ? sum[1] >> 32
+                                     : threadIdx.x == 1 ? (uint32_t)sum[1] : sum[threadIdx.x];
+        if (v) atomicAdd(threadIdx.x < 3 ? &out[threadIdx.x] : large, v);
+    }
     read_back(R);
 }
 
