@@ -347,7 +347,13 @@ static int write_runs(BuildState &B, sba_handle *h, const K *bk, hipStream_t st)
 // only, not the whole key grid: on a grid much larger than the polygons (a
 // point index's, or one for several sets) blocks of 4^-12 of it held all runs.
 #define DIR_MAX ((int64_t)1 << 24)
-#define DIR_SQUARE 6    // blocks of a workgroup: a square of 2^6 a side
+// blocks of a workgroup: a square of 2^6 a side, or of down to 2^4 where that leaves
+// fewer than DIR_WGS workgroups (500,000 blocks of 260 polygons at 10 m: 144 squares
+// 22 us, 2,025 of 2^4 8.8, 7,921 of 2^3 20.4; 4.2M blocks under one large ring: 1,089
+// squares 138, 4,225 80)
+#define DIR_SQUARE 6
+#define DIR_SQUARE_MIN 4
+#define DIR_WGS 2048
 
 struct DirGeo {
     int L, r;           // levels of the key grid; blocks of 2^r cells a side
@@ -378,9 +384,9 @@ __device__ __forceinline__ int64_t first_at_least(const uint64_t *starts, int64_
 // A workgroup writes the entries of one square of blocks, a stretch of keys:
 // each of its runs has the blocks whose first key it holds.  It takes 256 runs
 // at a time, the next ones loaded meanwhile, and its lanes share their entries.
-// (A wavefront for 64 runs and their entries: 41 us instead of 19 for 230,000 runs
-// of 260 polygons, some of hundreds of blocks; 182 and 140 for 2^24 entries of
-// 28.9M runs.  One launch over all runs, with a
+// (A wavefront for 64 runs and their entries: 182 us instead of 140 for 2^24
+// entries of 28.9M runs, and 2.2 times as long for 230,000 runs of 260 polygons, some of
+// hundreds of blocks.  One launch over all runs, with a
 // list of those over more than 2,048 blocks that the whole grid then filled one
 // after another: 800 us for a few hundred large polygons, which are mostly such
 // runs.)
@@ -473,9 +479,13 @@ static int build_directory(sba_handle *h, hipStream_t st)
         entries = (int64_t)D.cols * ((D.bh + 3) >> 2) * 32;
         if (entries <= most || D.r == D.L) break;
     }
-    D.q = std::min(DIR_SQUARE, D.L - D.r);
-    D.sw = ((D.bw - 1) >> D.q) + 1;
-    const uint32_t sh = ((D.bh - 1) >> D.q) + 1;
+    // smaller squares where there would be too few for the chip
+    uint32_t sh = 0;
+    for (D.q = std::min(DIR_SQUARE, D.L - D.r);; D.q--) {
+        D.sw = ((D.bw - 1) >> D.q) + 1;
+        sh = ((D.bh - 1) >> D.q) + 1;
+        if (D.q <= DIR_SQUARE_MIN || D.sw * sh >= DIR_WGS) break;
+    }
     h->dir_r = D.r;
     h->dir_cols = D.cols;
     RC(handle_alloc(h, &h->pdir, entries));

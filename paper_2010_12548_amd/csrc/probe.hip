@@ -1906,7 +1906,7 @@ __device__ __forceinline__ void table_flush(const CodeTable &H, const TaskDev &T
 // added modulo 2^64 to the polygon's word of a second line, which takes a place
 // when the first such value comes.  (Values in cents leave them all free; past
 // the bins, as two additions to the outputs each, 2e7 values of both signs over
-// 260 polygons in order took 13.8 ms, now 0.12; cents take 0.12.)
+// 260 polygons in order took 13.8 ms, now 0.11, as cents do.)
 // The points that need more than one directory entry and one addition (in mixed
 // blocks of the Hilbert layout, 9 in 100 at that size; of polygon sets) wait in
 // a queue of the wavefront until a lane each can take 64 of

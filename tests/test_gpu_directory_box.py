@@ -67,3 +67,17 @@ def test_a_far_key_grid_takes_as_long(sba):
         return min(ms)
 
     assert best((21, -2, -2)) < 2 * best((13, -2, -2))
+
+
+@pytest.mark.parametrize("n", [20, 300, 3_000, 30_000])
+def test_squares_of_every_size(sba, orc, n):
+    """Directories whose squares of blocks have 16, 32 and 64 a side."""
+    polys = voronoi_partition(n, 3_000_000, (1, 2), seed=n, jitter_seed=n + 1)
+    eps = 3_000 if n < 3_000 else 800
+    A = sba.Approx.from_polygons(polys, eps, kind="hilbert")
+    xy = uniform_points(100_001, -5_000, 3_005_000, n)
+    vals = np.random.default_rng(n).integers(-1000, 1000, 100_001).astype(np.int64)
+    want = orc.Approx(polys, eps).aggregate(xy, vals)
+    c, s = run_agg(A, xy, vals)
+    np.testing.assert_array_equal(c, want[0])
+    np.testing.assert_array_equal(s, want[1])
