@@ -20,6 +20,9 @@ def test_names(sba):
         for kw, layout in ((dict(kind="hilbert"), 1), (dict(kind="hilbert", search="learned"), 2)):
             A = sba.Approx.from_polygons(polys, 5, **kw)
             assert A.probe_kernel(v) == "k_probe_items<%d, %s, 1, 4>" % (layout, t)
+        # a key grid above level 16: 64-bit keys
+        A = sba.Approx.from_polygons(polys, 5, kind="hilbert", key_grid=(18, -100, -100))
+        assert A.probe_kernel(v) == "k_probe_items<3, %s, 1, 4>" % t
         sba.lib().sba_debug_force_wide_grid(1)
         try:
             A = sba.Approx.from_polygons(polys, 5)
